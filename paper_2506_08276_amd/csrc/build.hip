@@ -3,9 +3,10 @@
 // Nodes enter in id order, in batches: the nodes of a batch search the graph as it was before the batch (Algorithm 1
 // with exact similarities from the stored embeddings), pick their neighbours with the RNG rule, then the forward and
 // reverse edges of the batch are committed and every node that received edges is brought back under the degree cap M.
-// With batch = 1 this is the sequential listing; larger batches are what fills the device (one wavefront per
+// With batch = 1 this is the sequential listing; larger batches are what fills the device (one block per
 // inserted node).  Batch k holds min(batch, max(1, inserted / ramp)) nodes, so the first nodes still go in one by one.
 #include "common.h"
+#include "wave.h"
 
 #include <algorithm>
 
@@ -15,6 +16,7 @@ constexpr int EFC_MAX = 256;    // construction queue length
 constexpr int M_MAX = 64;       // degree cap
 constexpr int BATCH_MAX = 1024;  // nodes per batch
 constexpr int LIST_MAX = M_MAX + BATCH_MAX;
+constexpr int64_t BITMAP_NODES = 262144;  // visited marks of a search as a bitmap in LDS up to here (32 KB: four blocks per CU)
 
 struct BuildState {
     const float *emb;   // [n][d]
@@ -23,7 +25,7 @@ struct BuildState {
     int32_t *deg;       // [n] current list length
     int32_t *deg0;      // [n] list length when the batch started
     int stride;         // M + batch
-    uint16_t *stamp;    // [batch][n] visited marks of the searches: seen iff == epoch
+    uint16_t *stamp;    // [batch][n] visited marks of the searches where a bitmap in LDS is too large: seen iff == epoch
     int64_t n;
     int32_t *fwd;       // [batch][M] neighbours chosen by the nodes of the batch
     int32_t *fwd_n;     // [batch]
@@ -33,161 +35,237 @@ struct BuildState {
     int M, m, efC;
 };
 
-__device__ inline bool better_i(float sa, int32_t ia, float sb, int32_t ib) { return sa > sb || (sa == sb && ia < ib); }
+// One anchor row against other rows, fp32.  NV = 4-byte pieces per lane (lane l owns elements l, l + 64, ...), 0: rows
+// longer than 1024, read from memory each time.  Every lane gets the result; its bits do not depend on how many rows are
+// taken at once.
+template <int NV>
+struct RowDots {
+    float a[NV > 0 ? NV : 1];
+    const float *row;
+    int d, lane;
 
-__device__ inline void wave_best_i(float &s, int32_t &id, int &pos)
-{
+    __device__ static inline float piece(__amdgpu_buffer_rsrc_t r, int lane, int j)  // 0 beyond the row's end
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (j * 64 + lane) * 4, 0, 0));
+    }
+    __device__ inline __amdgpu_buffer_rsrc_t rsrc(const float *p) const
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, d * (int)sizeof(float), 0x00020000);
+    }
+    __device__ inline void load(const float *p, int d_, int lane_)
+    {
+        row = p;
+        d = d_;
+        lane = lane_;
+        if constexpr (NV > 0) {
+            const auto r = rsrc(p);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float s2 = __shfl_xor(s, o, 64);
-        const int32_t id2 = __shfl_xor(id, o, 64);
-        const int p2 = __shfl_xor(pos, o, 64);
-        if (p2 >= 0 && (pos < 0 || better_i(s2, id2, s, id))) {
-            s = s2;
-            id = id2;
-            pos = p2;
+            for (int j = 0; j < NV; ++j) a[j] = piece(r, lane, j);
         }
     }
-}
-
-// <emb[a], emb[b]> by one wavefront; every lane gets the result.  Lane l sums elements l, l + 64, ...
-__device__ inline float wave_dot(const float *__restrict__ ea, const float *__restrict__ eb, int d, int lane)
-{
-    float acc = 0.f;
-    for (int i = lane; i < d; i += 64) acc += ea[i] * eb[i];
+    // out[k] = <anchor, emb row id_at(k)> for k < c <= 4.  The rows' loads are all issued before the first sum: a row comes
+    // from beyond L2 as a rule, and four in flight per wavefront cost little more time than one.
+    template <class IdAt>
+    __device__ inline void four(const float *emb, IdAt id_at, int c, float (&out)[4]) const
+    {
+        if constexpr (NV > 0) {
+            float r[4][NV];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    return acc;
-}
-
-// RNG selection among cand[0..cnt) (similarities sim[] to the anchor) into out[], at most cap: walk by (similarity
-// desc, id asc); keep x unless a kept y is closer to x than the anchor is.  taken[] is scratch.  One wavefront; all
-// arrays in LDS.  Returns the number kept (uniform).
-__device__ inline int wave_shrink(const BuildState &s, const int32_t *cand, const float *sim, unsigned char *taken, int cnt,
-                                  int cap, int32_t *out, int lane)
-{
-    for (int i = lane; i < cnt; i += 64) taken[i] = 0;
-    __builtin_amdgcn_wave_barrier();
-    int kept = 0;
-    for (int step = 0; step < cnt && kept < cap; ++step) {
-        float bs = -INFINITY;
-        int32_t bid = 0x7fffffff;
-        int bpos = -1;
-        for (int i = lane; i < cnt; i += 64)
-            if (!taken[i] && (bpos < 0 || better_i(sim[i], cand[i], bs, bid))) {
-                bs = sim[i];
-                bid = cand[i];
-                bpos = i;
+            for (int k = 0; k < 4; ++k)
+                if (k < c) {
+                    const int id = __builtin_amdgcn_readfirstlane(id_at(k));
+                    const auto rs = rsrc(emb + (size_t)id * d);
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) r[k][j] = piece(rs, lane, j);
+                }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < c) {
+                    float acc = 0.f;
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) acc = fmaf(a[j], r[k][j], acc);
+                    out[k] = wave_sum(acc);
+                }
+        } else {
+            for (int k = 0; k < c; ++k) {
+                const float *e = emb + (size_t)__builtin_amdgcn_readfirstlane(id_at(k)) * d;
+                float acc = 0.f;
+                for (int i = lane; i < d; i += 64) acc = fmaf(row[i], e[i], acc);
+                out[k] = wave_sum(acc);
             }
-        wave_best_i(bs, bid, bpos);
-        if (lane == 0) taken[bpos] = 1;
-        const float *ex = s.emb + (size_t)bid * s.d;
-        bool ok = true;
-        for (int j = 0; j < kept && ok; ++j)
-            if (wave_dot(ex, s.emb + (size_t)out[j] * s.d, s.d, lane) > bs) ok = false;
-        if (ok) {
-            if (lane == 0) out[kept] = bid;
+        }
+    }
+};
+
+// RNG selection among cnt candidates (keys of similarity to the anchor and id, best first, LDS) into out[] (LDS), at most
+// cap: walk them in order; keep x unless a kept y is closer to x than the anchor is.  The whole block works on it: a group
+// of as many candidates as there are wavefronts is checked at once, each wavefront its candidate against everything kept
+// so far and, if it survives, against the earlier candidates of the group; which of those count is settled afterwards, in
+// order.  Returns the number kept (uniform).
+constexpr int WAVES_MAX = 16;
+
+template <int NV>
+__device__ inline int block_shrink(const BuildState &s, const uint64_t *key, int cnt, int cap, int32_t *out, uint32_t *flags)
+{
+    constexpr uint32_t DROPPED = 1u << 31;
+    const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int kept = 0;
+    for (int base = 0; base < cnt && kept < cap; base += nw) {
+        uint32_t res = DROPPED;
+        if (base + wave < cnt) {
+            const uint64_t kx = key[base + wave];
+            const int x = __builtin_amdgcn_readfirstlane((int)key_id(kx));
+            const float bs = key_score(kx);
+            RowDots<NV> dots;
+            dots.load(s.emb + (size_t)x * s.d, s.d, lane);
+            float dv[4];
+            bool ok = true;
+            for (int j = 0; j < kept && ok; j += 4) {
+                const int c = min(4, kept - j);
+                dots.four(s.emb, [&](int k) { return out[j + k]; }, c, dv);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k < c && dv[k] > bs) ok = false;
+            }
+            if (ok) {
+                res = 0;
+                for (int j = 0; j < wave; j += 4) {
+                    const int c = min(4, wave - j);
+                    dots.four(s.emb, [&](int k) { return (int)key_id(key[base + j + k]); }, c, dv);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (k < c && dv[k] > bs) res |= 1u << (j + k);
+                }
+            }
+        }
+        if (lane == 0) flags[wave] = res;
+        __syncthreads();
+        uint32_t group = 0;  // candidates of this group that are kept
+        for (int b = 0; b < nw && kept < cap; ++b) {
+            const uint32_t f = flags[b];
+            if (f == DROPPED || (f & group)) continue;
+            if (tid == 0) out[kept] = (int32_t)key_id(key[base + b]);
+            group |= 1u << b;
             ++kept;
         }
-        __builtin_amdgcn_wave_barrier();
+        __syncthreads();
     }
     return kept;
 }
 
-// One wavefront per node of the batch: Search(v, efC) on the graph of the first `inserted` nodes, then Shrink(W, M0).
-__global__ __launch_bounds__(64) void build_search_select_kernel(BuildState s, int64_t inserted, int epoch)
+// One block per node of the batch: Search(v, efC) on the graph of the first `inserted` nodes, then Shrink(W, M0).
+// Latency bounds it: a hop is a chain of reads (list, vectors) and the next hop depends on its similarities.  So all the
+// wavefronts of a block share a hop: the neighbours' similarities are taken side by side, and the queue W is kept sorted
+// (two copies, the hop's newcomers are merged from one into the other by counting), which makes "closest not expanded" one
+// ballot and dropping the worst a bound.  Measured at n = 8192, d = 768, efC = 128, batches of up to 1024: 219 us per
+// batch on average, one wavefront per node with an unsorted queue took 2632.  words > 0: the visited marks are a bitmap of that many words in LDS (the caller
+// has made sure that it fits), else 16-bit stamps in memory.
+template <int NV>
+__global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(BuildState s, int64_t inserted, int epoch, int words)
 {
-    __shared__ float w_sim[EFC_MAX];
-    __shared__ int32_t w_id[EFC_MAX];
-    __shared__ unsigned char w_vis[EFC_MAX];
-    __shared__ unsigned char taken[EFC_MAX];
-    __shared__ int32_t kept_ids[M_MAX];
-    const int slot = blockIdx.x, lane = threadIdx.x;
+    extern __shared__ uint32_t seen[];
+    __shared__ uint64_t w_key[2][EFC_MAX];
+    __shared__ __attribute__((aligned(4))) uint8_t w_vis[2][EFC_MAX];  // 1: expanded, or no entry there
+    __shared__ uint64_t new_key[64];
+    __shared__ int32_t new_id[64], kept_ids[M_MAX];
+    __shared__ uint32_t flags[WAVES_MAX];
+    __shared__ int n_new_s;
+    const int slot = blockIdx.x, tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t v = inserted + slot;
+    if (slot == 0 && tid == 0) *s.n_touched = 0;  // counted by the commit kernel, which runs next
     if (inserted == 0) {  // the first node has nothing to link to
-        if (lane == 0) s.fwd_n[slot] = 0;
+        if (tid == 0) s.fwd_n[slot] = 0;
         return;
     }
-    const float *ev = s.emb + (size_t)v * s.d;
     uint16_t *stamp = s.stamp + (size_t)slot * s.n;
-    int n_w = 1;
-    {
-        const float s0 = wave_dot(ev, s.emb, s.d, lane);
+    RowDots<NV> dots;
+    dots.load(s.emb + (size_t)v * s.d, s.d, lane);
+    for (int i = tid; i < words; i += blockDim.x) seen[i] = i == 0;  // node 0 is the entry point: seen from the start
+    for (int i = tid; i < 2 * EFC_MAX; i += blockDim.x) (&w_vis[0][0])[i] = 1;
+    __syncthreads();
+    float dv[4];
+    if (wave == 0) {
+        dots.four(s.emb, [](int) { return 0; }, 1, dv);
         if (lane == 0) {
-            w_sim[0] = s0;
-            w_id[0] = 0;
-            w_vis[0] = 0;
+            w_key[0][0] = queue_key(dv[0], 0);
+            w_vis[0][0] = 0;
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    __syncthreads();
+    int n_w = 1, cur = 0;
     for (;;) {
-        float bs = -INFINITY;
-        int32_t bid = 0x7fffffff;
-        int bpos = -1;
-        for (int i = lane; i < n_w; i += 64)
-            if (!w_vis[i] && (bpos < 0 || better_i(w_sim[i], w_id[i], bs, bid))) {
-                bs = w_sim[i];
-                bid = w_id[i];
-                bpos = i;
+        // the best entry that has not been expanded: lane l looks at positions 4l .. 4l + 3
+        static_assert(EFC_MAX == 256, "one 32-bit word of marks per lane");
+        const uint32_t z = ~reinterpret_cast<const uint32_t *>(w_vis[cur])[lane] & 0x01010101u;
+        const unsigned long long open = __ballot(z != 0);
+        if (!open) break;
+        const int l = __ffsll((long long)open) - 1;
+        const int pos = l * 4 + (__ffs(__builtin_amdgcn_readlane((int)z, l)) - 1) / 8;
+        if (wave == 0) {
+            const int u = __builtin_amdgcn_readfirstlane((int)key_id(w_key[cur][pos]));
+            const int32_t *nb = s.adj + (size_t)u * s.stride;
+            int32_t x = lane < s.stride ? nb[lane] : -1;
+            if (lane >= s.deg[u]) x = -1;  // deg <= M: lists are under the cap between batches
+            if (words > 0) {
+                if (x >= 0 && (atomicOr(&seen[x >> 5], 1u << (x & 31)) >> (x & 31) & 1u)) x = -1;
+            } else if (x >= 0) {
+                if (x == 0 || stamp[x] == (uint16_t)epoch) x = -1;
+                else stamp[x] = (uint16_t)epoch;
             }
-        wave_best_i(bs, bid, bpos);
-        if (bpos < 0) break;
-        if (lane == 0) w_vis[bpos] = 1;
-        const int du = s.deg[bid];  // <= M: lists are under the cap between batches
-        const int32_t *nb = s.adj + (size_t)bid * s.stride;
-        int32_t x = -1;
-        if (lane < du) {
-            x = nb[lane];
-            if (x == 0 || stamp[x] == (uint16_t)epoch) x = -1;  // node 0 is the entry point: seen from the start
-            else stamp[x] = (uint16_t)epoch;
+            const unsigned long long fresh = __ballot(x >= 0);
+            if (x >= 0) new_id[__popcll(fresh & ((1ull << lane) - 1ull))] = x;
+            if (lane == 0) n_new_s = __popcll(fresh);
         }
-        unsigned long long todo = __ballot(x >= 0);
-        while (todo) {
-            const int src = __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            const int32_t xi = __shfl(x, src, 64);
-            const float sx = wave_dot(ev, s.emb + (size_t)xi * s.d, s.d, lane);
-            if (n_w < s.efC) {
-                if (lane == 0) {
-                    w_sim[n_w] = sx;
-                    w_id[n_w] = xi;
-                    w_vis[n_w] = 0;
-                }
-                ++n_w;
-            } else {  // replace the worst entry when the newcomer is better
-                float ws = INFINITY;
-                int32_t wid = -1;
-                int wpos = -1;
-                for (int i = lane; i < n_w; i += 64)
-                    if (wpos < 0 || better_i(ws, wid, w_sim[i], w_id[i])) {
-                        ws = w_sim[i];
-                        wid = w_id[i];
-                        wpos = i;
-                    }
+        __syncthreads();
+        const int n_new = n_new_s;
+        if (n_new == 0) {
+            if (tid == 0) w_vis[cur][pos] = 1;
+            __syncthreads();
+            continue;
+        }
+        for (int i0 = wave; i0 < n_new; i0 += 4 * nw) {
+            const int c = min(4, (n_new - i0 + nw - 1) / nw);
+            dots.four(s.emb, [&](int k) { return new_id[i0 + k * nw]; }, c, dv);
 #pragma unroll
-                for (int o = 32; o > 0; o >>= 1) {
-                    const float s2 = __shfl_xor(ws, o, 64);
-                    const int32_t id2 = __shfl_xor(wid, o, 64);
-                    const int p2 = __shfl_xor(wpos, o, 64);
-                    if (p2 >= 0 && (wpos < 0 || better_i(ws, wid, s2, id2))) {
-                        ws = s2;
-                        wid = id2;
-                        wpos = p2;
-                    }
-                }
-                if (better_i(sx, xi, ws, wid) && lane == 0) {
-                    w_sim[wpos] = sx;
-                    w_id[wpos] = xi;
-                    w_vis[wpos] = 0;
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
+            for (int k = 0; k < 4; ++k)
+                if (k < c && lane == 0) new_key[i0 + k * nw] = queue_key(dv[k], (uint32_t)new_id[i0 + k * nw]);
         }
+        __syncthreads();
+        // merge: an entry moves down by the number of better newcomers, a newcomer lands behind everything better
+        const int nxt = cur ^ 1;
+        const uint64_t fresh_key = lane < n_new ? new_key[lane] : 0;
+        for (int i = tid; i < n_w; i += blockDim.x) {
+            const uint64_t k = w_key[cur][i];
+            int p = i;
+            for (int j = 0; j < n_new; ++j) p += new_key[j] > k;
+            if (p < s.efC) {
+                w_key[nxt][p] = k;
+                w_vis[nxt][p] = w_vis[cur][i] | (uint8_t)(i == pos);
+            }
+        }
+        uint64_t own[EFC_MAX / 64];
+#pragma unroll
+        for (int j = 0; j < EFC_MAX / 64; ++j) own[j] = j * 64 + lane < n_w ? w_key[cur][j * 64 + lane] : 0;
+        for (int i = wave; i < n_new; i += nw) {
+            const uint64_t k = new_key[i];
+            int p = __popcll(__ballot(fresh_key > k));
+#pragma unroll
+            for (int j = 0; j < EFC_MAX / 64; ++j) p += __popcll(__ballot(own[j] > k));
+            if (p < s.efC && lane == 0) {
+                w_key[nxt][p] = k;
+                w_vis[nxt][p] = 0;
+            }
+        }
+        n_w = min(n_w + n_new, s.efC);
+        cur = nxt;
+        __syncthreads();
     }
     const int cap = (!s.is_hub || s.is_hub[v]) ? s.M : s.m;
-    const int kept = wave_shrink(s, w_id, w_sim, taken, n_w, cap, kept_ids, lane);
-    if (lane < kept) s.fwd[(size_t)slot * s.M + lane] = kept_ids[lane];
-    if (lane == 0) s.fwd_n[slot] = kept;
+    const int kept = block_shrink<NV>(s, w_key[cur], n_w, cap, kept_ids, flags);
+    if (tid < kept) s.fwd[(size_t)slot * s.M + tid] = kept_ids[tid];
+    if (tid == 0) s.fwd_n[slot] = kept;
 }
 
 // Forward lists of the batch's nodes, reverse edges appended to their targets (order fixed later), targets noted.
@@ -209,54 +287,61 @@ __global__ __launch_bounds__(64) void build_commit_kernel(BuildState s, int64_t 
     }
 }
 
-// One wavefront per node that received reverse edges: put the new edges in id order (the order of insertion), and if
-// the list exceeds M shrink it with the RNG rule anchored at the node.
-__global__ __launch_bounds__(64) void build_reverse_kernel(BuildState s)
+// One block per node that received reverse edges: put the new edges in id order (the order of insertion), and if the
+// list exceeds M shrink it with the RNG rule anchored at the node (up to M * cnt / 2 similarities, shared by the block's
+// wavefronts: 22 us per batch at the sizes above, 347 with one wavefront).
+template <int NV>
+__global__ __launch_bounds__(64 * WAVES_MAX) void build_reverse_kernel(BuildState s)
 {
     __shared__ int32_t list[LIST_MAX];
-    __shared__ int32_t sorted[BATCH_MAX];
-    __shared__ float sim[LIST_MAX];
-    __shared__ unsigned char taken[LIST_MAX];
+    __shared__ uint64_t key[LIST_MAX], sorted[LIST_MAX];
     __shared__ int32_t kept_ids[M_MAX];
-    const int lane = threadIdx.x;
+    __shared__ uint32_t flags[WAVES_MAX];
+    const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= *s.n_touched) return;
-    const int32_t r = s.touched[blockIdx.x];
+    const int r = __builtin_amdgcn_readfirstlane(s.touched[blockIdx.x]);
     const int cnt = s.deg[r], old = s.deg0[r];
     int32_t *row = s.adj + (size_t)r * s.stride;
-    for (int i = lane; i < cnt; i += 64) list[i] = row[i];
-    __builtin_amdgcn_wave_barrier();
-    // rank sort of the appended ids (all different)
-    const int na = cnt - old;
-    for (int i = lane; i < na; i += 64) {
-        const int32_t x = list[old + i];
-        int rank = 0;
-        for (int j = 0; j < na; ++j) rank += list[old + j] < x;
-        sorted[rank] = x;
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int i = lane; i < na; i += 64) list[old + i] = sorted[i];
-    __builtin_amdgcn_wave_barrier();
-    if (cnt <= s.M) {
-        for (int i = lane; i < na; i += 64) row[old + i] = list[old + i];
+    if (cnt <= s.M) {  // at most 64 entries: a lane's appended id goes behind the smaller ones (all are different)
+        if (wave > 0) return;
+        const int32_t x = lane >= old && lane < cnt ? row[lane] : 0x7fffffff;
+        int rank = old;
+        for (int j = old; j < cnt; ++j) rank += __builtin_amdgcn_readlane(x, j) < x;
+        if (lane >= old && lane < cnt) row[rank] = x;
         if (lane == 0) s.deg0[r] = cnt;
         return;
     }
-    const float *er = s.emb + (size_t)r * s.d;
-    for (int i = 0; i < cnt; ++i) {
-        const float v = wave_dot(er, s.emb + (size_t)list[i] * s.d, s.d, lane);
-        if (lane == 0) sim[i] = v;
+    for (int i = tid; i < cnt; i += blockDim.x) list[i] = row[i];
+    __syncthreads();
+    RowDots<NV> dots;
+    dots.load(s.emb + (size_t)r * s.d, s.d, lane);
+    for (int i0 = wave; i0 < cnt; i0 += 4 * nw) {
+        const int c = min(4, (cnt - i0 + nw - 1) / nw);
+        float dv[4];
+        dots.four(s.emb, [&](int k) { return list[i0 + k * nw]; }, c, dv);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < c && lane == 0) key[i0 + k * nw] = queue_key(dv[k], (uint32_t)list[i0 + k * nw]);
     }
-    __builtin_amdgcn_wave_barrier();
-    const int kept = wave_shrink(s, list, sim, taken, cnt, s.M, kept_ids, lane);
-    if (lane < kept) row[lane] = kept_ids[lane];
-    if (lane == 0) {
+    __syncthreads();
+    for (int i = tid; i < cnt; i += blockDim.x) {
+        const uint64_t k = key[i];
+        int rank = 0;
+        for (int j = 0; j < cnt; ++j) rank += key[j] > k;
+        sorted[rank] = k;
+    }
+    __syncthreads();
+    const int kept = block_shrink<NV>(s, sorted, cnt, s.M, kept_ids, flags);
+    if (tid < kept) row[tid] = kept_ids[tid];
+    if (tid == 0) {
         s.deg[r] = kept;
         s.deg0[r] = kept;
     }
 }
 
-// CSR out of the fixed-stride lists: one block; row_ptr by a chunked scan, then the copy.
-__global__ __launch_bounds__(1024) void build_csr_kernel(BuildState s, uint64_t *__restrict__ row_ptr, uint32_t *__restrict__ col_idx)
+// CSR out of the fixed-stride lists: row_ptr by a chunked scan in one block, then a wavefront per node copies its list.
+__global__ __launch_bounds__(1024) void build_row_ptr_kernel(BuildState s, uint64_t *__restrict__ row_ptr)
 {
     __shared__ unsigned long long part[1024];
     const int tid = threadIdx.x;
@@ -275,11 +360,17 @@ __global__ __launch_bounds__(1024) void build_csr_kernel(BuildState s, uint64_t 
     unsigned long long run = tid ? part[tid - 1] : 0;
     for (int64_t v = beg; v < end; ++v) {
         row_ptr[v] = run;
-        const int dv = s.deg[v];
-        for (int j = 0; j < dv; ++j) col_idx[run + j] = (uint32_t)s.adj[(size_t)v * s.stride + j];
-        run += dv;
+        run += (unsigned long long)s.deg[v];
     }
     if (tid == 1023) row_ptr[s.n] = part[1023];
+}
+
+__global__ __launch_bounds__(256) void build_col_idx_kernel(BuildState s, const uint64_t *__restrict__ row_ptr,
+                                                            uint32_t *__restrict__ col_idx)
+{
+    const int lane = threadIdx.x & 63;
+    for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < s.n; v += (int64_t)gridDim.x * 4)
+        if (lane < s.deg[v]) col_idx[row_ptr[v] + lane] = (uint32_t)s.adj[(size_t)v * s.stride + lane];  // deg <= M <= 64
 }
 
 // Flags of the ceil(beta * n) nodes of largest out-degree, ties to the lower id.  One block: histogram of the degrees,
@@ -338,6 +429,23 @@ __global__ __launch_bounds__(1024) void top_degree_kernel(const uint64_t *__rest
     }
 }
 
+// The construction kernels for rows of d elements.
+struct BuildKernels {
+    void (*search_select)(BuildState, int64_t, int, int);
+    void (*reverse)(BuildState);
+};
+
+BuildKernels build_kernels(int d)
+{
+    if (d <= 128) return {build_search_select_kernel<2>, build_reverse_kernel<2>};
+    if (d <= 256) return {build_search_select_kernel<4>, build_reverse_kernel<4>};
+    if (d <= 384) return {build_search_select_kernel<6>, build_reverse_kernel<6>};
+    if (d <= 512) return {build_search_select_kernel<8>, build_reverse_kernel<8>};
+    if (d <= 768) return {build_search_select_kernel<12>, build_reverse_kernel<12>};
+    if (d <= 1024) return {build_search_select_kernel<16>, build_reverse_kernel<16>};
+    return {build_search_select_kernel<0>, build_reverse_kernel<0>};
+}
+
 }  // namespace
 
 int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, const uint8_t *is_hub_dev, int32_t efC,
@@ -369,7 +477,8 @@ int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d
     };
     if ((rc = adj.reserve((size_t)n * stride * sizeof(int32_t))) != LEANN_OK) return done(rc);
     if ((rc = deg.reserve((size_t)n * 2 * sizeof(int32_t))) != LEANN_OK) return done(rc);
-    if ((rc = stamp.reserve((size_t)batch * n * sizeof(uint16_t))) != LEANN_OK) return done(rc);
+    const int words = n <= BITMAP_NODES ? (int)((n + 31) / 32) : 0;
+    if (words == 0 && (rc = stamp.reserve((size_t)batch * n * sizeof(uint16_t))) != LEANN_OK) return done(rc);
     const size_t fwd_bytes = (size_t)batch * M * sizeof(int32_t);
     if ((rc = misc.reserve(fwd_bytes + (size_t)batch * sizeof(int32_t) + (size_t)batch * M * sizeof(int32_t) + 256)) != LEANN_OK)
         return done(rc);
@@ -391,25 +500,32 @@ int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d
     s.m = m;
     s.efC = efC;
     hipError_t e = hipMemsetAsync(deg.p, 0, (size_t)n * 2 * sizeof(int32_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(stamp.p, 0, (size_t)batch * n * sizeof(uint16_t), st);
+    if (e == hipSuccess && words == 0) e = hipMemsetAsync(stamp.p, 0, (size_t)batch * n * sizeof(uint16_t), st);
+    const BuildKernels kernels = build_kernels(d);
     int epoch = 0;
     for (int64_t ins = 0; ins < n && e == hipSuccess;) {
         int64_t b = std::max<int64_t>(1, ins / ramp);
         b = std::min<int64_t>(std::min<int64_t>(b, batch), n - ins);
-        if (++epoch == 65536) {  // the 16-bit marks wrap: start over with clean ones
+        if (words == 0 && ++epoch == 65536) {  // the 16-bit marks wrap: start over with clean ones
             e = hipMemsetAsync(stamp.p, 0, (size_t)batch * n * sizeof(uint16_t), st);
             epoch = 1;
             if (e != hipSuccess) break;
         }
-        e = hipMemsetAsync(s.n_touched, 0, sizeof(int32_t), st);
-        if (e != hipSuccess) break;
-        hipLaunchKernelGGL(build_search_select_kernel, dim3((unsigned)b), dim3(64), 0, st, s, ins, epoch);
+        // wavefronts per node: as many as the chip holds (16 per CU with 128 registers each), so that small batches, which
+        // are bound by one node's chain of hops, spread each hop widest
+        const int threads = 64 * (b <= ctx->num_cus ? 16 : b <= 2 * ctx->num_cus ? 8 : 4);
+        hipLaunchKernelGGL(kernels.search_select, dim3((unsigned)b), dim3(threads), words * sizeof(uint32_t), st, s, ins,
+                           epoch, words);
         hipLaunchKernelGGL(build_commit_kernel, dim3((unsigned)b), dim3(64), 0, st, s, ins);
-        hipLaunchKernelGGL(build_reverse_kernel, dim3((unsigned)(b * M)), dim3(64), 0, st, s);
+        // a node receives edges at most once per batch into the list of touched ones, and only inserted nodes do
+        if (ins > 0)
+            hipLaunchKernelGGL(kernels.reverse, dim3((unsigned)std::min<int64_t>(b * M, ins)), dim3(512), 0, st, s);
         ins += b;
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(build_csr_kernel, dim3(1), dim3(1024), 0, st, s, row_ptr_dev, col_idx_dev);
+        hipLaunchKernelGGL(build_row_ptr_kernel, dim3(1), dim3(1024), 0, st, s, row_ptr_dev);
+        hipLaunchKernelGGL(build_col_idx_kernel, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 8192)), dim3(256), 0, st, s,
+                           row_ptr_dev, col_idx_dev);
         e = hipGetLastError();
     }
     unsigned long long edges = 0;

@@ -49,6 +49,22 @@ def test_construction_identical_on_exact_arithmetic(L, orc, ctx, n, batch, ramp,
     assert len(ci) == st["edges"]
 
 
+@pytest.mark.parametrize("n,d,efC,M,m,batch", [(600, 130, 256, 64, 64, 1024), (400, 300, 100, 40, 16, 512),
+                                               (400, 512, 64, 16, 4, 128), (400, 700, 64, 16, 4, 1), (300, 1000, 64, 16, 16, 7),
+                                               (300, 1030, 64, 16, 4, 64), (262_400, 5, 6, 4, 4, 1024)])
+def test_construction_identical_at_other_widths_and_lists(L, orc, ctx, n, d, efC, M, m, batch):
+    """Row widths of every kernel variant (in registers up to 1024 elements, from memory beyond), lists longer than the
+    block has wavefronts, and more nodes than the visited bitmap in LDS covers.  Integer-valued, so all sums are exact."""
+    rng = np.random.default_rng(n + d)
+    emb = rng.integers(-9, 10, size=(n, d)).astype(np.float32)
+    is_hub = (rng.random(n) < 0.1).astype(np.uint8) if m < M else None
+    say(f"build n={n} d={d} efC={efC} M={M} batch={batch}")
+    rp, ci = gpu_csr(*L.leann_build_graph(ctx, to_dev(emb), efC, M, m, None if is_hub is None else to_dev(is_hub), batch, 1))
+    want_rp, want_ci, _ = orc.build_graph(emb, efC, M, m, is_hub, batch, 1)
+    np.testing.assert_array_equal(rp, want_rp)
+    np.testing.assert_array_equal(ci, want_ci)
+
+
 def test_top_degree_matches_oracle(L, orc, ctx):
     rng = np.random.default_rng(0)
     emb = rng.integers(-5, 6, size=(500, 8)).astype(np.float32)
