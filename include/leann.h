@@ -241,13 +241,13 @@ int leann_search_updates(leann_ctx *ctx, const float *queries_dev, int64_t nq, c
  * directions, and a neighbour whose list exceeds M is shrunk to M with the same rule.
  * Total order (similarity descending, id ascending).
  * batch > 1: the nodes of a batch search the graph as it was before the batch (one
- * wavefront each), then their edges are committed in id order and every node that
+ * block each), then their edges are committed in id order and every node that
  * received edges is shrunk once; batch k holds min(batch, max(1, inserted / ramp)) nodes.
  * batch = 1 is the sequential listing.
  *   emb_dev fp32[n][d] (device); is_hub_dev uint8[n] or NULL (device);
  *   row_ptr_dev uint64[n + 1], col_idx_dev uint32 with room for n * M entries (device,
  *   caller-owned); n_edges_host receives the edge count.  Scratch is allocated and freed
- *   inside the call (n * (M + batch) * 4 + batch * n * 2 bytes).  Synchronises the stream.
+ *   inside the call (n * (M + batch) * 4 bytes, and batch * n * 2 when n > 262144).  Synchronises the stream.
  * Errors: efC outside 1..256, M outside 1..64, m outside 1..M, batch outside 1..1024,
  * ramp < 1, n >= 2^31 -> LEANN_EINVAL.
  */

@@ -124,6 +124,53 @@ def test_build_pq_invariants_and_error(L, orc, ctx, n, d, m_sub, iters):
     assert close > 0.5
 
 
+@pytest.mark.parametrize("n,d,m_sub,offset", [(5, 16, 2, 0), (300, 32, 1, 0), (1000, 51, 3, 0), (777, 20, 20, 0), (640, 40, 2, 0),
+                                              (3000, 768, 32, 0), (4097, 48, 2, 4000), (70001, 24, 1, 0)])
+def test_build_pq_exact_on_integer_rows(L, ctx, n, d, m_sub, offset):
+    """Integer-valued rows: squared distances and sums are exact in fp32, so the nearest centroid (lowest index among
+    equals; there are many) and the means have one right value.  Sub-vector lengths 1 to 32, aligned and not, fewer rows
+    than centroids, rows far from the origin, non-finite rows, and more rows than are trained on."""
+    say(f"build_pq integer rows n={n} d={d} m_sub={m_sub} offset={offset}")
+    rng = np.random.default_rng(n + d)
+    x = (rng.integers(-6, 7, size=(n, d)) + offset).astype(np.float32)
+    dsub = d // m_sub
+
+    def nearest(rows, cb):
+        out = np.empty((len(rows), m_sub), np.int64)
+        for s in range(0, len(rows), 1000):
+            sub = rows[s:s + 1000].reshape(-1, m_sub, 1, dsub).astype(np.float64)
+            dist = np.stack([((sub[:, m] - cb[m][None].astype(np.float64)) ** 2).sum(-1) for m in range(m_sub)], 1)
+            out[s:s + 1000] = np.where(np.isnan(dist), np.inf, dist).argmin(2)
+        return out
+
+    def build(rows, iters):
+        pq = L.leann_build_pq(ctx, to_dev(rows), m_sub, iters, 7)
+        got = L.leann_pq_export(ctx, pq)
+        L.leann_pq_free(pq)
+        return got
+
+    cb0, codes0 = build(x, 0)  # the first centroids are rows
+    want0 = nearest(x, cb0)
+    np.testing.assert_array_equal(codes0, want0)
+    if n <= 65536:  # every row is trained on
+        cb1, _ = build(x, 1)
+        sub = x.reshape(n, m_sub, dsub)
+        for m in range(m_sub):
+            want = cb0[m].copy()
+            for c in np.unique(want0[:, m]):
+                own = sub[want0[:, m] == c, m]
+                want[c] = own.sum(0, dtype=np.float64).astype(np.float32) / np.float32(len(own))
+            np.testing.assert_array_equal(cb1[m], want)
+    if n > 256:
+        bad = x.copy()
+        bad[::97, 0], bad[1::89, d - 1], bad[5, 0] = np.nan, np.inf, -3e38
+        cbb, codesb = build(bad, 0)
+        with np.errstate(invalid="ignore", over="ignore"):
+            want = nearest(bad, cbb)
+        rows = np.arange(n) != 5  # 3e38 squared is infinite in fp32 only
+        np.testing.assert_array_equal(codesb[rows], want[rows])
+
+
 def test_build_pq_rejects_bad_shapes(L, ctx):
     say("build_pq bad shapes")
     x = to_dev(np.zeros((10, 130), np.float32))
