@@ -340,7 +340,7 @@ int leann_embed(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     LEANN_TRY(ctx->meta.reserve(256));
     int *err = (int *)ctx->meta.p;
     LEANN_HIP(hipMemsetAsync(err, 0, sizeof(int), ctx->stream));
-    LEANN_TRY(enc_forward(ctx, chunks, ids_dev, 0, n_ids, out_emb_dev, err, nullptr));
+    LEANN_TRY(enc_forward(ctx, chunks, ids_dev, 0, n_ids, out_emb_dev, err, nullptr, 0));
     int herr = 0;
     LEANN_HIP(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     LEANN_HIP(hipStreamSynchronize(ctx->stream));

@@ -61,7 +61,7 @@ struct leann_ctx {
     int64_t max_tokens = 1048576;  // padded tokens per encoder pass (workspaces: about 17 KB per token at BERT-base width)
     int32_t aq_capacity = 0;  // 0 = derive from ef and graph
     int32_t gemm_large_tile = 256;   // 256: 256x256 block tiles for large passes; 128: never (leann_set_gemm_tiles)
-    int32_t gemm_small_rows = 2048;  // passes of at most this many padded rows use 64x64 tiles
+    int32_t gemm_small_rows = 2048;  // passes of at most this many rows may use tiles of 64x64 and smaller
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
     // search workspace
@@ -103,9 +103,10 @@ int search_init_device();
 
 // ---- encoder.hip
 // Embeds the chunks named by ids_dev[0..n) (NULL: first_id .. first_id+n) into out[n][d] (fp32), in passes of at
-// most ctx->max_tokens padded tokens.  err_dev: device int, set non-zero on invalid tokens / lengths / ids.
+// most ctx->max_tokens padded tokens.  err_dev: device int, set non-zero on invalid tokens / lengths / ids.  tokens: the
+// chunks' valid tokens in all if the caller knows them, else 0 (for the choice of GEMM tiles only).
 int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_dev, int64_t first_id, int64_t n,
-                float *out_dev, int *err_dev, int64_t *tok_count_dev);
+                float *out_dev, int *err_dev, int64_t *tok_count_dev, int64_t tokens);
 
 // ---- pq.hip
 int pq_build_lut(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_pq *pq, float *lut_dev);

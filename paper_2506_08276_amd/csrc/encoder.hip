@@ -5,6 +5,9 @@
 // Tokens of all chunks of a pass are packed back to back (no padding rows): chunk i owns rows
 // cu[i] .. cu[i+1] of every activation matrix.  The number of valid rows T is only known on the device,
 // so grids are sized for the worst case and blocks beyond T leave at once.
+#include <limits.h>
+#include <math.h>
+
 #include <algorithm>
 
 #include "common.h"
@@ -513,6 +516,100 @@ int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W,
     return LEANN_OK;
 }
 
+// How gemm_small_kernel's grid covers the 8 XCDs: xr of them side by side over the rows, the rest over the columns.  First
+// the arrangement with the fewest rounds of blocks on the fullest XCD, among those the one that reads least (an XCD
+// reads its share of the rows of A and of W once).
+struct SmallPlan {
+    int xr, rounds, blocks;
+};
+
+SmallPlan plan_small(const leann_ctx *ctx, int tmb, int tnb, int rows, int N)
+{
+    SmallPlan best = {1, INT_MAX, 0};
+    double best_bytes = 0;
+    const int rt = (rows + 32 * tmb - 1) / (32 * tmb), ct = N / (32 * tnb);
+    const int cus = std::max(1, ctx->num_cus / 8);
+    for (int xr = 1; xr <= 8; xr *= 2) {
+        const int xc = 8 / xr;
+        const int per_xcd = ((ct + xc - 1) / xc) * ((rt + xr - 1) / xr);
+        const int rounds = (per_xcd + cus - 1) / cus;
+        const double bytes = (double)rows * xc + (double)N * xr;
+        if (rounds < best.rounds || (rounds == best.rounds && bytes < best_bytes)) {
+            best = {xr, rounds, 8 * per_xcd};
+            best_bytes = bytes;
+        }
+    }
+    return best;
+}
+
+template <int TMB, int TNB, int EPI>
+int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
+                      const int32_t *T_dev, int max_rows, int N, int K, int xr)
+{
+    typedef SmallCfg<TMB, TNB> Cfg;
+    const int rt = (max_rows + 32 * TMB - 1) / (32 * TMB), ct = N / (32 * TNB), xc = 8 / xr;
+    ProfScope prof(ctx, prof_kind);
+    hipLaunchKernelGGL((gemm_small_kernel<TMB, TNB, EPI>), dim3(8 * ((ct + xc - 1) / xc) * ((rt + xr - 1) / xr)), dim3(Cfg::THREADS),
+                       Cfg::SMEM, ctx->stream, A, W, bias, out, T_dev, N, K, xr);
+    LEANN_HIP(hipGetLastError());
+    return LEANN_OK;
+}
+
+// Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
+// Measured per launch, twelve layers' weights in turn, in microseconds (rows x N x K):
+//                       32x32   64x32   64x64 (small)   64x64   128x128   256x256
+//    80 x  768 x  768     4.2     4.7       5.8           6.2      8.5
+//    80 x  768 x 3072     8.0     9.9      14.9          18.0     26.0
+//   244 x 2304 x  768     9.9     8.5       6.4           6.7      9.0
+//  1040 x  768 x 3072    26.8    18.8      16.0          19.3     31.6
+//  1040 x 3072 x  768    35.8    25.8      20.7          15.9     11.9
+//  3000 x  768 x  768                                    11.6     10.2      18.2
+//  4000 x 3072 x  768                                    46.5     29.9      22.7
+//  8000 x  768 x 3072                                    82.9     50.6      56.4
+// 32000 x  768 x  768                                    86.3     50.8      42.6
+// What decides is how many tiles the busiest CU gets: with c = ceil(tiles / CUs) the larger three take about 2.5 + 3.7 c,
+// 2.5 + 8 c and 21 c - 2 (K = 768; the ratios are the same at K = 3072).  The small-pass kernel is the fastest while its
+// blocks fit the chip at once, its smallest tile first.
+template <int EPI>
+int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
+         const int32_t *T_dev, int max_rows, int rows, int N, int K)
+{
+    const int cus = ctx->num_cus;
+    const bool fine = rows <= ctx->gemm_small_rows && N % 64 == 0;
+    if (fine && K % SMALL_BK == 0) {
+#define LEANN_SMALL(TMB, TNB)                                                                                       \
+    {                                                                                                               \
+        const SmallPlan p = plan_small(ctx, TMB, TNB, rows, N);                                                     \
+        if (p.rounds == 1)                                                                                          \
+            return launch_gemm_small<TMB, TNB, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K, p.xr);  \
+    }
+        LEANN_SMALL(1, 1)
+        LEANN_SMALL(2, 1)
+        LEANN_SMALL(2, 2)
+#undef LEANN_SMALL
+    }
+    auto busiest = [&](int tile) {  // tiles of the busiest CU
+        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * (N / tile);
+        return (double)((tiles + cus - 1) / cus);
+    };
+    const double cost128 = N % 128 == 0 ? 2.5 + 8.0 * busiest(128) : INFINITY;
+    const double cost64 = fine ? 2.5 + 3.7 * busiest(64) : INFINITY;
+    const bool wide = ctx->gemm_large_tile == 256 && N % 256 == 0 && K >= 8 * GEMM_BK;
+    const double cost256 = wide ? 21.0 * busiest(256) - 2.0 : INFINITY;
+    if (cost256 <= cost128 && cost256 <= cost64)
+        return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
+    if (cost64 < cost128) return launch_gemm<64, 64, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
+    return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
+}
+
+template <int TMB, int TNB, int EPI>
+int gemm_small_allow_lds()
+{
+    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_small_kernel<TMB, TNB, EPI>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, SmallCfg<TMB, TNB>::SMEM));
+    return LEANN_OK;
+}
+
 template <int BM, int BN, int EPI>
 int gemm_allow_lds()
 {
@@ -541,13 +638,19 @@ int enc_init_device()
     LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS_GELU>()));
     LEANN_TRY((gemm_allow_lds<64, 64, EPI_BIAS>()));
     LEANN_TRY((gemm_allow_lds<64, 64, EPI_BIAS_GELU>()));
+    LEANN_TRY((gemm_small_allow_lds<1, 1, EPI_BIAS>()));
+    LEANN_TRY((gemm_small_allow_lds<1, 1, EPI_BIAS_GELU>()));
+    LEANN_TRY((gemm_small_allow_lds<2, 1, EPI_BIAS>()));
+    LEANN_TRY((gemm_small_allow_lds<2, 1, EPI_BIAS_GELU>()));
+    LEANN_TRY((gemm_small_allow_lds<2, 2, EPI_BIAS>()));
+    LEANN_TRY((gemm_small_allow_lds<2, 2, EPI_BIAS_GELU>()));
     LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(attention_kernel<8>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, AttCfg<8>::SMEM));
     return LEANN_OK;
 }
 
 int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_dev, int64_t first_id, int64_t n,
-                float *out_dev, int *err_dev, int64_t *tok_count_dev)
+                float *out_dev, int *err_dev, int64_t *tok_count_dev, int64_t tokens)
 {
     const leann_encoder_desc &e = ctx->desc;
     const int d = e.hidden, F = e.ffn, H = e.heads, seq = chunks->seq;
@@ -572,21 +675,11 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     int32_t *cu = (int32_t *)ctx->cu.p;
     int64_t *chunk_of = (int64_t *)ctx->enc_ids.p;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)(d / H));
-    // 256x256 block tiles for large passes and output widths that are multiples of 256 (LDS traffic per flop
-    // halves); leann_set_gemm_tiles can force the small tile and move the row limit of the 64x64 tile.
-    const bool wide = ctx->gemm_large_tile == 256;
-    const int small_rows = ctx->gemm_small_rows;
-
     for (int64_t s = 0; s < n; s += per_pass) {
         const int m = (int)((n - s < per_pass) ? n - s : per_pass);
         const int max_rows = m * seq;
-        // a pass of a few thousand tokens has too few 256x256 tiles for the CUs: the 128x128 tile (four times the blocks,
-        // two per CU) is faster there (measured: +15 % at 32 chunks of up to 256 tokens, -6 % at 64).  Both tiles add
-        // the K-slabs in the same order, so a row's result does not depend on the choice.
-        const bool big = wide && max_rows > 8192;  // and, per GEMM, an output width that is a multiple of 256
-        // a pass of one query's flush (a dozen chunks) does not even fill the CUs with 128x128 tiles: 64x64 tiles
-        // (measured: faster up to 2048 padded rows, slower from 3072 on; leann_set_gemm_tiles moves the limit)
-        const bool tiny = !big && max_rows <= small_rows && d % 64 == 0 && F % 64 == 0;
+        // how many of the rows hold tokens decides the tiles; unless the caller knows, chunks are taken to be five eighths full
+        const int rows = (int)std::min<int64_t>(max_rows, tokens > 0 ? (tokens * m + n - 1) / n : ((int64_t)max_rows * 5 + 7) / 8);
         const int32_t *T_dev = cu + m;
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
@@ -609,12 +702,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         };
         for (int l = 0; l < e.layers; ++l) {
             const LayerWeights &w = ctx->layers[l];
-#define LEANN_GEMM(EPI, KIND, A_, W_, B_, O_, N_, K_)                                                               \
-    LEANN_TRY((big && (N_) % 256 == 0 && (K_) >= 256                                                                \
-                   ? launch_gemm<256, 256, EPI>(ctx, KIND, A_, W_, B_, O_, T_dev, max_rows, N_, K_)                   \
-               : tiny ? launch_gemm<64, 64, EPI>(ctx, KIND, A_, W_, B_, O_, T_dev, max_rows, N_, K_)                   \
-                      : launch_gemm<128, 128, EPI>(ctx, KIND, A_, W_, B_, O_, T_dev, max_rows, N_, K_)))
-            LEANN_GEMM(EPI_BIAS, LEANN_PROF_GEMM_QKV, x, w.wqkv, w.bqkv, qkv, 3 * d, d);
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_QKV, x, w.wqkv, w.bqkv, qkv, T_dev, max_rows, rows, 3 * d, d));
             {
                 ProfScope prof(ctx, LEANN_PROF_ATTENTION);
                 if (seq <= 128)
@@ -624,11 +712,10 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
                     hipLaunchKernelGGL(attention_kernel<8>, dim3((unsigned)m * H), dim3(256), AttCfg<8>::SMEM, ctx->stream, qkv, cu,
                                        att, d, scale_log2e);
             }
-            LEANN_GEMM(EPI_BIAS, LEANN_PROF_GEMM_O, att, w.wo, w.bo, delta, d, d);
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, w.wo, w.bo, delta, T_dev, max_rows, rows, d, d));
             layer_norm(w.g1, w.be1);
-            LEANN_GEMM(EPI_BIAS_GELU, LEANN_PROF_GEMM_FFN1, x, w.w1, w.b1, hid, F, d);
-            LEANN_GEMM(EPI_BIAS, LEANN_PROF_GEMM_FFN2, hid, w.w2, w.b2, delta, d, F);
-#undef LEANN_GEMM
+            LEANN_TRY(gemm<EPI_BIAS_GELU>(ctx, LEANN_PROF_GEMM_FFN1, x, w.w1, w.b1, hid, T_dev, max_rows, rows, F, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_FFN2, hid, w.w2, w.b2, delta, T_dev, max_rows, rows, d, F));
             layer_norm(w.g2, w.be2);
         }
         {

@@ -654,7 +654,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             const int64_t n_enc = h_ctr[CTR_NENC];
             if (n_enc > 0) {
                 rc = enc_forward(ctx, chunks, s.enc_ids, 0, n_enc, (float *)ctx->s_emb.p, enc_err,
-                                 (int64_t *)&counters[CTR_TOKENS]);
+                                 (int64_t *)&counters[CTR_TOKENS], 0);
                 if (rc != LEANN_OK) break;
                 encoded += n_enc;
                 if (memo_cap > 0 && memo_n < memo_cap) {

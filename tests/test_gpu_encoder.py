@@ -181,3 +181,31 @@ def test_width_256_all_three_gemm_tiles(L, orc):
     assert np.abs(got[ids] - want_bf).max() <= TOL_BF16_MODE
     print("width-256 sample max-abs vs fp32 oracle %.3e, vs bf16-mode oracle %.3e" %
           (np.abs(got[ids] - want).max(), np.abs(got[ids] - want_bf).max()))
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 512), (256, 4, 1024), (384, 6, 1536), (768, 12, 3072)])
+def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
+    """Passes from a handful of tokens to tens of thousands go through every GEMM tile (32 x 32 up to 256 x 256, one to 24
+    K-slabs, row counts that are no multiple of any tile): each chunk's embedding equals the one that the 128 x 128 tile
+    alone gives."""
+    import torch
+    cfg = dict(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=128, ln_eps=1e-12)
+    say(f"all GEMM tiles, hidden {hidden}")
+    w = li.encoder_weights(cfg, li.config_seed(2) + hidden, bf16_exact=True)
+    n = 420
+    tokens, lengths = li.uniform_chunks(n, 128, 1, cfg["vocab"], 16, 128, li.config_seed(2) + 30)
+    lengths[:3] = [1, 33, 127]
+    ctx = L.leann_create(cfg, to_dev(w).to(torch.bfloat16))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        L.leann_set_gemm_tiles(ctx, 128, 0)
+        want = L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy()
+        L.leann_set_gemm_tiles(ctx, 256, 2048)
+        assert np.isfinite(want).all()
+        for m in (1, 2, 3, 5, 9, 14, 25, 40, 80, 200, n):
+            got = L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden).cpu().numpy()
+            assert np.array_equal(got, want[:m]), m
+        L.leann_set_gemm_tiles(ctx, 0, 1 << 20)  # the 64 x 64 tile as far as it goes
+        assert np.array_equal(L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy(), want)
+    finally:
+        L.leann_destroy(ctx)
