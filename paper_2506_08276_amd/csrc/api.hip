@@ -224,6 +224,7 @@ void leann_destroy(leann_ctx *ctx)
                       &ctx->s_misc, &ctx->s_owner, &ctx->s_buf, &ctx->s_memo_slot, &ctx->s_memo_emb};
     for (DevBuf *b : bufs) b->release();
     ctx->prof_tokens.release();
+    if (ctx->host_counters) (void)hipHostFree(ctx->host_counters);
     for (auto &sp : ctx->prof_spans) {
         (void)hipEventDestroy(sp.a);
         (void)hipEventDestroy(sp.b);

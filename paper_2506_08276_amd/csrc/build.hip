@@ -35,67 +35,7 @@ struct BuildState {
     int M, m, efC;
 };
 
-// One anchor row against other rows, fp32.  NV = 4-byte pieces per lane (lane l owns elements l, l + 64, ...), 0: rows
-// longer than 1024, read from memory each time.  Every lane gets the result; its bits do not depend on how many rows are
-// taken at once.
-template <int NV>
-struct RowDots {
-    float a[NV > 0 ? NV : 1];
-    const float *row;
-    int d, lane;
-
-    __device__ static inline float piece(__amdgpu_buffer_rsrc_t r, int lane, int j)  // 0 beyond the row's end
-    {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (j * 64 + lane) * 4, 0, 0));
-    }
-    __device__ inline __amdgpu_buffer_rsrc_t rsrc(const float *p) const
-    {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, d * (int)sizeof(float), 0x00020000);
-    }
-    __device__ inline void load(const float *p, int d_, int lane_)
-    {
-        row = p;
-        d = d_;
-        lane = lane_;
-        if constexpr (NV > 0) {
-            const auto r = rsrc(p);
-#pragma unroll
-            for (int j = 0; j < NV; ++j) a[j] = piece(r, lane, j);
-        }
-    }
-    // out[k] = <anchor, emb row id_at(k)> for k < c <= 4.  The rows' loads are all issued before the first sum: a row comes
-    // from beyond L2 as a rule, and four in flight per wavefront cost little more time than one.
-    template <class IdAt>
-    __device__ inline void four(const float *emb, IdAt id_at, int c, float (&out)[4]) const
-    {
-        if constexpr (NV > 0) {
-            float r[4][NV];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < c) {
-                    const int id = __builtin_amdgcn_readfirstlane(id_at(k));
-                    const auto rs = rsrc(emb + (size_t)id * d);
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) r[k][j] = piece(rs, lane, j);
-                }
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < c) {
-                    float acc = 0.f;
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) acc = fmaf(a[j], r[k][j], acc);
-                    out[k] = wave_sum(acc);
-                }
-        } else {
-            for (int k = 0; k < c; ++k) {
-                const float *e = emb + (size_t)__builtin_amdgcn_readfirstlane(id_at(k)) * d;
-                float acc = 0.f;
-                for (int i = lane; i < d; i += 64) acc = fmaf(row[i], e[i], acc);
-                out[k] = wave_sum(acc);
-            }
-        }
-    }
-};
+__device__ inline const float *row_of(const BuildState &s, int id) { return s.emb + (size_t)id * s.d; }
 
 // RNG selection among cnt candidates (keys of similarity to the anchor and id, best first, LDS) into out[] (LDS), at most
 // cap: walk them in order; keep x unless a kept y is closer to x than the anchor is.  The whole block works on it: a group
@@ -123,7 +63,7 @@ __device__ inline int block_shrink(const BuildState &s, const uint64_t *key, int
             bool ok = true;
             for (int j = 0; j < kept && ok; j += 4) {
                 const int c = min(4, kept - j);
-                dots.four(s.emb, [&](int k) { return out[j + k]; }, c, dv);
+                dots.four([&](int k) { return row_of(s, out[j + k]); }, c, dv);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
                     if (k < c && dv[k] > bs) ok = false;
@@ -132,7 +72,7 @@ __device__ inline int block_shrink(const BuildState &s, const uint64_t *key, int
                 res = 0;
                 for (int j = 0; j < wave; j += 4) {
                     const int c = min(4, wave - j);
-                    dots.four(s.emb, [&](int k) { return (int)key_id(key[base + j + k]); }, c, dv);
+                    dots.four([&](int k) { return row_of(s, (int)key_id(key[base + j + k])); }, c, dv);
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
                         if (k < c && dv[k] > bs) res |= 1u << (j + k);
@@ -187,7 +127,7 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(Bui
     __syncthreads();
     float dv[4];
     if (wave == 0) {
-        dots.four(s.emb, [](int) { return 0; }, 1, dv);
+        dots.four([&](int) { return s.emb; }, 1, dv);
         if (lane == 0) {
             w_key[0][0] = queue_key(dv[0], 0);
             w_vis[0][0] = 0;
@@ -227,7 +167,7 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(Bui
         }
         for (int i0 = wave; i0 < n_new; i0 += 4 * nw) {
             const int c = min(4, (n_new - i0 + nw - 1) / nw);
-            dots.four(s.emb, [&](int k) { return new_id[i0 + k * nw]; }, c, dv);
+            dots.four([&](int k) { return row_of(s, new_id[i0 + k * nw]); }, c, dv);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (k < c && lane == 0) new_key[i0 + k * nw] = queue_key(dv[k], (uint32_t)new_id[i0 + k * nw]);
@@ -319,7 +259,7 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_reverse_kernel(BuildStat
     for (int i0 = wave; i0 < cnt; i0 += 4 * nw) {
         const int c = min(4, (cnt - i0 + nw - 1) / nw);
         float dv[4];
-        dots.four(s.emb, [&](int k) { return list[i0 + k * nw]; }, c, dv);
+        dots.four([&](int k) { return row_of(s, list[i0 + k * nw]); }, c, dv);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (k < c && lane == 0) key[i0 + k * nw] = queue_key(dv[k], (uint32_t)list[i0 + k * nw]);

@@ -1,48 +1,54 @@
 // Two-level search with dynamic batching (LEANN Algorithm 2, Sec. 4.1-4.2), every stage on the device.
 //
-// All queries of a call advance in rounds.  In a round each active query runs hops on its own wavefront
-// (traverse_kernel: read the best unvisited node of the exact queue EQ, gather its CSR neighbours, ADC-score
-// the new ones out of an LDS-resident lookup table, push them into the approximate queue AQ, move the
-// top re-rank fraction to the pending list P) until |P| >= batch or EQ has no unvisited node.  The pending
-// lists of all queries are then packed into one list, re-embedded by the encoder in large cross-query
-// batches, scored against their own query and try-inserted into EQ (score_insert_kernel).  Per query this
-// is exactly the sequential algorithm; batching across queries changes no value because the encoder's
-// output for a chunk does not depend on the rest of the batch.
+// All queries of a call advance in rounds.  In a round each active query runs hops on its own block (advance_kernel:
+// take the best unvisited node of the exact queue EQ, gather its CSR neighbours, ADC-score the new ones out of an
+// LDS-resident lookup table, push them into the approximate queue AQ, move the top re-rank fraction to the pending
+// list P) until |P| >= batch or EQ has no unvisited node.  The pending lists of all queries are then packed into one
+// list (collect_kernel) and re-embedded by the encoder in large cross-query batches; the next advance_kernel scores them
+// against their own query and try-inserts them into EQ.  Per query this is exactly the sequential algorithm; batching
+// across queries changes no value because the encoder's output for a chunk does not depend on the rest of the batch.
 #include <algorithm>
 #include <vector>
 
 #include "common.h"
+#include "wave.h"
 
 namespace {
 
 constexpr int KSUB = 256;
 
 struct SearchState {
-    float *eq_score;      // [G][ef]
-    uint32_t *eq_id;      // [G][ef]
+    uint64_t *eq_key;     // [G][ef] exact queue, best first (queue_key)
     uint8_t *eq_vis;      // [G][ef]
     int32_t *eq_n;        // [G]
-    float *aq_score;      // [G][aqcap]
-    uint32_t *aq_id;      // [G][aqcap]
-    int32_t *aq_n;        // [G]
+    uint64_t *aq_key;     // [G][aqcap] approximate queue, 0 where an entry has been taken out
+    uint64_t *aq_max;     // [G][aq_groups] best entry of each run of aq_run entries
+    int32_t *aq_tail;     // [G] end of the used part
+    int32_t *aq_live;     // [G] entries in it
     uint32_t *seen;       // [G][words]
     uint32_t *pend;       // [G][pcap]
     int32_t *n_pend;      // [G]
-    int32_t *src;         // [G][pcap]  >= 0: row of the encoder output; -1 .. -2^30: -(cache row + 1); below: -(2^30 + memo row + 1)
-    int32_t *owner;       // [N] smallest pending entry (q * pcap + j) that asked for the chunk this round, else INT_MAX
+    int32_t *src;         // [G][pcap] row of the encoder output, for entries that own their chunk
+    int32_t *own;         // [G][pcap] the entry that owns this entry's chunk
+    unsigned long long *owner;  // [N] (~round << 32 | entry) of the chunk's smallest entry in the newest round that asked for it
     int32_t *memo_slot;   // [N] row of the call's embedding memo that holds the chunk, -1: none; NULL: memo off
     const float *memo_emb;  // [memo rows][d]
     int32_t *done;        // [G]
-    int32_t *enc_off;     // [G + 1]
     int64_t *enc_ids;     // [G * pcap]
     long long *counters;  // see CTR_*
+    long long *host_counters;  // the same in host memory, written at the end of every round
     const float *lut;     // [G][m_sub][256]
+    const int32_t *slot_of;     // stored-embedding table, NULL: none
+    const float *cache_emb;
+    int64_t cache_rows;
     int64_t words;
     int32_t ef, aqcap, pcap;
+    int32_t aq_run, aq_groups;  // run length (a multiple of 64), number of runs
+    int32_t aq_lds;             // entries of AQ that a running block keeps in LDS (a multiple of 64)
 };
 
-enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_PENDING, CTR_NENC, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_COUNT };
-constexpr int MEMO_SRC_BASE = 1 << 30;
+// CTR_PENDING .. CTR_TICKET belong to one round
+enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET, CTR_COUNT };
 enum { ERR_BAD_NEIGHBOUR = 1, ERR_AQ_OVERFLOW = 2, ERR_P_OVERFLOW = 4, ERR_BAD_SLOT = 8 };
 
 __device__ inline bool better(float sa, uint32_t ia, float sb, uint32_t ib) { return sa > sb || (sa == sb && ia < ib); }
@@ -63,28 +69,14 @@ __device__ inline void wave_best(float &s, uint32_t &id, int &pos)
     }
 }
 
-// wave-wide arg-worst under the same order.
-__device__ inline void wave_worst(float &s, uint32_t &id, int &pos)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        float s2 = __shfl_xor(s, o, 64);
-        uint32_t id2 = __shfl_xor(id, o, 64);
-        int p2 = __shfl_xor(pos, o, 64);
-        if (p2 >= 0 && (pos < 0 || better(s, id, s2, id2))) {
-            s = s2;
-            id = id2;
-            pos = p2;
-        }
-    }
-}
-
 __global__ void maxdeg_kernel(const uint64_t *__restrict__ row_ptr, int64_t n, long long *__restrict__ counters)
 {
     long long best = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         best = max(best, (long long)(row_ptr[i + 1] - row_ptr[i]));
-    atomicMax(&counters[CTR_MAXDEG], best);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) best = max(best, (long long)__shfl_xor(best, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&counters[CTR_MAXDEG], best);
 }
 
 __global__ void init_kernel(SearchState s, int g, uint32_t entry)
@@ -92,326 +84,440 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= g) return;
     s.eq_n[q] = 0;
-    s.aq_n[q] = 0;
+    s.aq_tail[q] = 0;
+    s.aq_live[q] = 0;
     s.done[q] = 0;
     s.n_pend[q] = 1;  // the entry point's exact score is the first flush
     s.pend[(size_t)q * s.pcap] = entry;
     s.seen[(size_t)q * s.words + (entry >> 5)] = 1u << (entry & 31);
 }
 
-// One wavefront per query.  Dynamic LDS: lookup table [m_sub][256] fp32, then EQ score/id/visited copies.
-__global__ __launch_bounds__(64) void traverse_kernel(SearchState s, const uint64_t *__restrict__ row_ptr,
-                                                      const uint32_t *__restrict__ col_idx, int64_t n,
-                                                      const uint8_t *__restrict__ codes, int m_sub, float alpha, int batch)
+// Score, expand, score again: one block per query takes its query as far as it goes without the encoder.
+//
+// A launch starts with the exact scores of the pending chunks that the encoder (or a stored table) has supplied since the
+// last one, then runs hops until a flush is due.  A flush whose chunks all come from the stored-embedding table is scored on
+// the spot and the hops go on; otherwise the block claims its chunks (see claim below) and leaves.  So a search over
+// stored embeddings is one launch, and with recomputation a round is this kernel, collect_kernel and the encoder.
+//
+// Latency bounds it: a hop is a chain of dependent reads, so the chain is kept short.
+//  - EQ is sorted (keys of score and id, LDS).  It does not change between flushes, so the next hops are known: their CSR
+//    rows are fetched two hops ahead, the PQ codes of all neighbours (seen or not) one hop ahead, and the visited marks one
+//    hop ahead where it is certain that the next hop will be run.
+//  - AQ is unsorted in runs of aq_run entries, the best entry of every run on the side: taking out the best of some
+//    thousand entries reads the runs' best and one run.  A taken entry leaves a hole; holes are squeezed out when the
+//    end reaches the capacity, so AQ overflows when more than aqcap entries are alive, not earlier.
+//  - a flush's exact scores are taken side by side (four wavefronts, four rows in flight each), and merged into EQ by
+//    counting.  "Insert if there is room or better than the worst" entry by entry leaves the ef best of both, which is
+//    what the merge keeps.
+// Measured with every embedding stored (500 queries, ef 200, N = 12288, d = 768): a search of 239 hops, 37 flushes and 248
+// exact scores per query takes 0.9 ms; one wavefront per query with scans over both queues and a host round per flush
+// took 13.8 ms (78 rounds of 77 us hops, 44 us scores and 24 us packing).
+constexpr int ADV_THREADS = 256;
+constexpr int EQ_MAX = 1024;
+constexpr int AQ_LDS_MAX = 2048, AQ_GROUPS_MAX = 512;
+
+__device__ inline uint64_t readlane64(uint64_t v, int l)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+
+template <int NV>  // 4-byte pieces of an embedding row per lane
+__global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, const uint64_t *__restrict__ row_ptr,
+                                                              const uint32_t *__restrict__ col_idx, int64_t n,
+                                                              const uint8_t *__restrict__ codes, int m_sub, float alpha, int batch,
+                                                              const float *__restrict__ queries, int d,
+                                                              const float *__restrict__ enc_emb, bool have_results, uint32_t round)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    float *tab = reinterpret_cast<float *>(smem);
-    float *eqs = tab + m_sub * KSUB;
-    uint32_t *eqi = reinterpret_cast<uint32_t *>(eqs + s.ef);
-    uint8_t *eqv = reinterpret_cast<uint8_t *>(eqi + s.ef);
-    const int q = blockIdx.x, lane = threadIdx.x;
+    float *tab = reinterpret_cast<float *>(smem);                        // [m_sub][256]
+    uint64_t *eqk = reinterpret_cast<uint64_t *>(tab + m_sub * KSUB);    // [ef]
+    uint64_t *aqm = eqk + s.ef;                                          // [aq_groups]
+    uint64_t *aql = aqm + s.aq_groups;                                   // [aq_lds]
+    uint8_t *eqv = reinterpret_cast<uint8_t *>(aql + s.aq_lds);          // [ef]
+    __shared__ uint64_t new_key[64];
+    __shared__ const float *new_row[64];
+    __shared__ uint32_t new_id[64];
+    __shared__ int list[64];
+    __shared__ int sh_pend, sh_tail;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (q == 0 && tid == 0)  // the round's counters: collect_kernel, which runs next, adds to them
+        for (int i = CTR_PENDING; i <= CTR_TICKET; ++i) s.counters[i] = 0;
     if (s.done[q]) return;
-    const int n_eq = s.eq_n[q];
-    int n_aq = s.aq_n[q], n_pend = s.n_pend[q];
-    int any = 0;
-    for (int i = lane; i < n_eq; i += 64) {
-        eqs[i] = s.eq_score[(size_t)q * s.ef + i];
-        eqi[i] = s.eq_id[(size_t)q * s.ef + i];
-        uint8_t v = s.eq_vis[(size_t)q * s.ef + i];
-        eqv[i] = v;
-        any |= !v;
-    }
-    if (__ballot(any) == 0ull) {  // nothing to expand: wait for the flush, or finished
-        if (lane == 0 && n_pend == 0) s.done[q] = 1;
-        return;
-    }
-    {
-        const float4 *src = reinterpret_cast<const float4 *>(s.lut + (size_t)q * m_sub * KSUB);
-        for (int i = lane; i < m_sub * KSUB / 4; i += 64) reinterpret_cast<float4 *>(tab)[i] = src[i];
-    }
-    __syncthreads();
-    float *aqs = s.aq_score + (size_t)q * s.aqcap;
-    uint32_t *aqi = s.aq_id + (size_t)q * s.aqcap;
-    uint32_t *seen = s.seen + (size_t)q * s.words;
     uint32_t *pend = s.pend + (size_t)q * s.pcap;
-    int hops = 0, adc = 0, err = 0;
-    while (n_pend < batch) {
-        // Alg. 2: u = the best node of EQ that has not been expanded yet; it is marked visited
-        float bs = -INFINITY;
-        uint32_t bid = 0xffffffffu;
-        int bpos = -1;
-        for (int i = lane; i < n_eq; i += 64)
-            if (!eqv[i] && (bpos < 0 || better(eqs[i], eqi[i], bs, bid))) {
-                bs = eqs[i];
-                bid = eqi[i];
-                bpos = i;
-            }
-        wave_best(bs, bid, bpos);
-        if (bpos < 0) break;
-        if (lane == 0) eqv[bpos] = 1;
-        ++hops;
-        const uint64_t beg = row_ptr[bid], end = row_ptr[bid + 1];
-        int n_new = 0;
-        for (uint64_t base = beg; base < end; base += 64) {
-            const uint64_t e = base + lane;
-            bool is_new = false;
-            uint32_t v = 0;
-            if (e < end) {
-                v = col_idx[e];
-                if (v >= n) {
-                    err |= ERR_BAD_NEIGHBOUR;
-                } else {
-                    const uint32_t bit = 1u << (v & 31);
-                    is_new = !(atomicOr(&seen[v >> 5], bit) & bit);
-                }
-            }
-            float sc = 0.f;
-            if (is_new) {  // ADC: table entries summed in subspace order
-                const uint8_t *code = codes + (size_t)v * m_sub;
-                if ((m_sub & 15) == 0) {
-                    for (int m0 = 0; m0 < m_sub; m0 += 16) {
-                        const uint4 w = *reinterpret_cast<const uint4 *>(code + m0);
-                        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) sc += tab[(m0 + i) * KSUB + ((ww[i >> 2] >> (8 * (i & 3))) & 255u)];
-                    }
-                } else {
-                    for (int m = 0; m < m_sub; ++m) sc += tab[m * KSUB + code[m]];
-                }
-            }
-            const unsigned long long mask = __ballot(is_new);
-            const int pos = n_aq + __popcll(mask & ((1ull << lane) - 1ull));
-            if (is_new) {
-                if (pos < s.aqcap) {
-                    aqs[pos] = sc;
-                    aqi[pos] = v;
-                } else {
-                    err |= ERR_AQ_OVERFLOW;
-                }
-            }
-            const int cnt = __popcll(mask);
-            n_aq = min(n_aq + cnt, s.aqcap);
-            n_new += cnt;
-        }
-        adc += n_new;
-        __syncthreads();  // single-wave block: orders this wave's AQ stores before the scans below
-        // move the r best entries of AQ to the pending list
-        const int r = (int)ceilf(alpha * (float)n_new);
-        for (int t = 0; t < r && n_aq > 0; ++t) {
-            float ps = -INFINITY;
-            uint32_t pid = 0xffffffffu;
-            int ppos = -1;
-            for (int i = lane; i < n_aq; i += 64) {
-                const float x = aqs[i];
-                const uint32_t id = aqi[i];
-                if (ppos < 0 || better(x, id, ps, pid)) {
-                    ps = x;
-                    pid = id;
-                    ppos = i;
-                }
-            }
-            wave_best(ps, pid, ppos);
-            if (lane == 0) {
-                if (n_pend < s.pcap) pend[n_pend] = pid;
-                aqs[ppos] = aqs[n_aq - 1];
-                aqi[ppos] = aqi[n_aq - 1];
-            }
-            if (n_pend >= s.pcap) err |= ERR_P_OVERFLOW;
-            n_pend = min(n_pend + 1, s.pcap);
-            --n_aq;
-            __syncthreads();
-        }
-    }
-    for (int i = lane; i < n_eq; i += 64) s.eq_vis[(size_t)q * s.ef + i] = eqv[i];
-    const unsigned long long anyerr = __ballot(err != 0);
-    if (anyerr) {
-        int e = err;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) e |= __shfl_xor(e, o, 64);
-        if (lane == 0) atomicOr((unsigned long long *)&s.counters[CTR_ERR], (unsigned long long)e);
-    }
-    if (lane == 0) {
-        s.aq_n[q] = n_aq;
-        s.n_pend[q] = n_pend;
-        if (n_pend == 0) s.done[q] = 1;  // left the loop with no unvisited node and nothing pending
-        atomicAdd((unsigned long long *)&s.counters[CTR_HOPS], (unsigned long long)hops);
-        atomicAdd((unsigned long long *)&s.counters[CTR_ADC], (unsigned long long)adc);
-    }
-}
-
-// Chunks that several queries ask for in the same round are encoded once: the pending entry with the smallest
-// index (q * pcap + j) owns the chunk, the others read the owner's row.  The encoder's output for a chunk does
-// not depend on its batch, so every query still sees exactly the scores it would compute alone.
-constexpr int NO_OWNER = 0x7f7f7f7f;  // the fill byte 0x7f makes hipMemsetAsync usable
-
-// slot_of entries >= cache_rows would send score_insert_kernel outside the stored table: they are reported
-// (ERR_BAD_SLOT) and the host ends the search before anything reads through them.
-__global__ __launch_bounds__(64) void claim_kernel(SearchState s, const int32_t *__restrict__ slot_of, int64_t cache_rows)
-{
-    const int q = blockIdx.x;
-    const int np = s.n_pend[q];
-    int hits = 0, memo_hits = 0;
-    bool bad = false;
-    for (int j = threadIdx.x; j < np; j += 64) {
-        const uint32_t c = s.pend[(size_t)q * s.pcap + j];
-        if (slot_of && slot_of[c] >= 0) {
-            bad |= slot_of[c] >= cache_rows;
-            ++hits;
-            continue;
-        }
-        if (s.memo_slot && s.memo_slot[c] >= 0) {  // encoded earlier in this call
-            ++memo_hits;
-            continue;
-        }
-        atomicMin(&s.owner[c], q * s.pcap + j);
-    }
-    if (bad) atomicOr((unsigned long long *)&s.counters[CTR_ERR], (unsigned long long)ERR_BAD_SLOT);
-    if (s.memo_slot) {
-        for (int o = 32; o; o >>= 1) memo_hits += __shfl_xor(memo_hits, o);
-        if (threadIdx.x == 0 && memo_hits)
-            atomicAdd((unsigned long long *)&s.counters[CTR_MEMO_HITS], (unsigned long long)memo_hits);
-    }
-    if (slot_of) {
-        for (int o = 32; o; o >>= 1) hits += __shfl_xor(hits, o);
-        if (threadIdx.x == 0 && hits) atomicAdd((unsigned long long *)&s.counters[CTR_HITS], (unsigned long long)hits);
-    }
-}
-
-// Pack the round: encoder input list (one entry per owned chunk, in entry order), source rows of the owners and
-// of the entries served by the stored-embedding table, and the round's totals.  One block of 1024 threads.
-__global__ __launch_bounds__(1024) void collect_kernel(SearchState s, int g, const int32_t *__restrict__ slot_of)
-{
-    __shared__ int part[1024];
-    const int tid = threadIdx.x;
-    const int per = (g + 1023) / 1024;
-    const int beg = tid * per, end = min(g, beg + per);
-    int need = 0, pending = 0;
-    for (int q = beg; q < end; ++q) {
-        const int np = s.n_pend[q];
-        pending += np;
-        for (int j = 0; j < np; ++j) need += s.owner[s.pend[(size_t)q * s.pcap + j]] == q * s.pcap + j;
-    }
-    part[tid] = need;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        int v = tid >= o ? part[tid - o] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    int run = tid ? part[tid - 1] : 0;
-    for (int q = beg; q < end; ++q) {
-        s.enc_off[q] = run;
-        const int np = s.n_pend[q];
-        for (int j = 0; j < np; ++j) {
-            const int e = q * s.pcap + j;
-            const uint32_t c = s.pend[e];
-            const int slot = slot_of ? slot_of[c] : -1;
-            const int mslot = (slot < 0 && s.memo_slot) ? s.memo_slot[c] : -1;
-            if (slot >= 0) {
-                s.src[e] = -(slot + 1);
-            } else if (mslot >= 0) {
-                s.src[e] = -(MEMO_SRC_BASE + mslot + 1);
-            } else if (s.owner[c] == e) {
-                s.enc_ids[run] = c;
-                s.src[e] = run++;
-            }
-        }
-    }
-    if (tid == 1023) {
-        s.enc_off[g] = part[1023];
-        s.counters[CTR_NENC] = part[1023];
-    }
-    if (pending) atomicAdd((unsigned long long *)&s.counters[CTR_PENDING], (unsigned long long)pending);
-}
-
-// Entries that do not own their chunk take the owner's row.
-__global__ __launch_bounds__(64) void resolve_kernel(SearchState s, const int32_t *__restrict__ slot_of)
-{
-    const int q = blockIdx.x;
-    const int np = s.n_pend[q];
-    for (int j = threadIdx.x; j < np; j += 64) {
-        const int e = q * s.pcap + j;
-        const uint32_t c = s.pend[e];
-        if (slot_of && slot_of[c] >= 0) continue;
-        if (s.memo_slot && s.memo_slot[c] >= 0) continue;
-        const int o = s.owner[c];
-        if (o != e) s.src[e] = s.src[o];
-    }
-}
-
-// Exact scores of the pending chunks and try-insert into EQ, in pending order.  One wavefront per query.
-__global__ __launch_bounds__(64) void score_insert_kernel(SearchState s, const float *__restrict__ queries, int d,
-                                                          const float *__restrict__ enc_emb,
-                                                          const float *__restrict__ cache_emb)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    float *eqs = reinterpret_cast<float *>(smem);
-    uint32_t *eqi = reinterpret_cast<uint32_t *>(eqs + s.ef);
-    uint8_t *eqv = reinterpret_cast<uint8_t *>(eqi + s.ef);
-    const int q = blockIdx.x, lane = threadIdx.x;
-    const int np = s.n_pend[q];
-    if (np == 0) return;
-    int n_eq = s.eq_n[q];
-    for (int i = lane; i < n_eq; i += 64) {
-        eqs[i] = s.eq_score[(size_t)q * s.ef + i];
-        eqi[i] = s.eq_id[(size_t)q * s.ef + i];
+    uint64_t *aqg = s.aq_key + (size_t)q * s.aqcap;
+    uint32_t *seen = s.seen + (size_t)q * s.words;
+    int n_pend = s.n_pend[q], n_eq = s.eq_n[q], tail = s.aq_tail[q], live = s.aq_live[q];
+    int hops = 0, adc = 0, err = 0, recomp = 0, flushes = 0, hits = 0;
+    for (int i = tid; i < n_eq; i += ADV_THREADS) {
+        eqk[i] = s.eq_key[(size_t)q * s.ef + i];
         eqv[i] = s.eq_vis[(size_t)q * s.ef + i];
     }
-    float qv[16];
-    const int per = (d + 63) >> 6;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) qv[j] = (j < per && j * 64 + lane < d) ? queries[(size_t)q * d + j * 64 + lane] : 0.f;
+    for (int i = tid; i < s.aq_groups; i += ADV_THREADS) aqm[i] = i * s.aq_run < tail ? s.aq_max[(size_t)q * s.aq_groups + i] : 0;
+    for (int i = tid; i < min(tail, s.aq_lds); i += ADV_THREADS) aql[i] = aqg[i];
+    {
+        const float4 *src = reinterpret_cast<const float4 *>(s.lut + (size_t)q * m_sub * KSUB);
+        for (int i = tid; i < m_sub * KSUB / 4; i += ADV_THREADS) reinterpret_cast<float4 *>(tab)[i] = src[i];
+    }
+    RowDots<NV> dots;
+    dots.load(queries + (size_t)q * d, d, lane);
+    if (tid == 0) sh_tail = tail;
     __syncthreads();
-    for (int c = 0; c < np; ++c) {
-        const int src = s.src[(size_t)q * s.pcap + c];
-        const uint32_t id = s.pend[(size_t)q * s.pcap + c];
-        const float *e = src >= 0                ? enc_emb + (size_t)src * d
-                         : src >= -MEMO_SRC_BASE ? cache_emb + (size_t)(-src - 1) * d
-                                                 : s.memo_emb + (size_t)(-(src + MEMO_SRC_BASE) - 1) * d;
-        float acc = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (j < per && j * 64 + lane < d) acc += qv[j] * e[j * 64 + lane];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-        if (n_eq < s.ef) {
-            if (lane == 0) {
-                eqs[n_eq] = acc;
-                eqi[n_eq] = id;
-                eqv[n_eq] = 0;
+
+    bool ready = have_results;  // the pending chunks' embeddings are there
+    bool finished = false;
+    for (;;) {
+        if (!ready) {  // all of them in the stored table?
+            int missing = 0, bad = 0;
+            for (int j = tid; j < n_pend; j += ADV_THREADS) {
+                const int slot = s.slot_of ? s.slot_of[pend[j]] : -1;
+                missing |= slot < 0;
+                bad |= slot >= 0 && slot >= s.cache_rows;
             }
-            ++n_eq;
-        } else {  // EQ full: the candidate must beat the tail
-            float ws = 0.f;
-            uint32_t wid = 0;
-            int wpos = -1;
-            for (int i = lane; i < n_eq; i += 64)
-                if (wpos < 0 || better(ws, wid, eqs[i], eqi[i])) {
-                    ws = eqs[i];
-                    wid = eqi[i];
-                    wpos = i;
+            if (__syncthreads_or(bad)) {  // reported; the host ends the search before anything reads through the slot
+                err |= ERR_BAD_SLOT;
+                break;
+            }
+            if (__syncthreads_or(missing)) break;
+            hits += n_pend;
+        }
+        // exact scores, 64 entries at a time, and their merge into EQ
+        for (int j0 = 0; j0 < n_pend; j0 += 64) {
+            const int cnt = min(64, n_pend - j0);
+            if (tid < cnt) {
+                const uint32_t id = pend[j0 + tid];
+                const int slot = s.slot_of ? s.slot_of[id] : -1;
+                const int mslot = slot < 0 && s.memo_slot ? s.memo_slot[id] : -1;
+                new_id[tid] = id;
+                new_row[tid] = slot >= 0    ? s.cache_emb + (size_t)slot * d
+                               : mslot >= 0 ? s.memo_emb + (size_t)mslot * d
+                                            : enc_emb + (size_t)s.src[s.own[(size_t)q * s.pcap + j0 + tid]] * d;
+            }
+            __syncthreads();
+            for (int i0 = wave; i0 < cnt; i0 += ADV_THREADS / 16) {
+                const int c = min(4, (cnt - i0 + 3) / 4);
+                float dv[4];
+                dots.four([&](int k) { return new_row[i0 + 4 * k]; }, c, dv);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k < c && lane == 0) new_key[i0 + 4 * k] = queue_key(dv[k], new_id[i0 + 4 * k]);
+            }
+            __syncthreads();
+            int to = s.ef;  // where newcomer tid goes: behind everything better, old or new
+            uint64_t mine = 0;
+            if (tid < cnt) {
+                mine = new_key[tid];
+                int lo = 0, hi = n_eq;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (eqk[mid] > mine) lo = mid + 1;
+                    else hi = mid;
                 }
-            wave_worst(ws, wid, wpos);
-            if (lane == 0 && better(acc, id, ws, wid)) {
-                eqs[wpos] = acc;
-                eqi[wpos] = id;
-                eqv[wpos] = 0;
+                to = lo;
+                for (int j = 0; j < cnt; ++j) to += new_key[j] > mine;
+            }
+            __syncthreads();
+            for (int base = (n_eq - 1) / ADV_THREADS * ADV_THREADS; base >= 0; base -= ADV_THREADS) {  // from the back: entries only move down
+                const int i = base + tid;
+                uint64_t k = 0;
+                uint8_t v = 0;
+                int p = s.ef;
+                if (i < n_eq) {
+                    k = eqk[i];
+                    v = eqv[i];
+                    p = i;
+                    for (int j = 0; j < cnt; ++j) p += new_key[j] > k;
+                }
+                __syncthreads();
+                if (p < s.ef) {
+                    eqk[p] = k;
+                    eqv[p] = v;
+                }
+                __syncthreads();
+            }
+            if (to < s.ef) {
+                eqk[to] = mine;
+                eqv[to] = 0;
+            }
+            n_eq = min(s.ef, n_eq + cnt);
+            __syncthreads();
+        }
+        if (n_pend > 0) {
+            recomp += n_pend;
+            ++flushes;
+        }
+        n_pend = 0;
+        ready = false;
+
+        if (wave == 0) {
+            const int runs64 = s.aq_run >> 6;
+            auto aq_get = [&](int p) -> uint64_t { return p < s.aq_lds ? aql[p] : aqg[p]; };
+            auto aq_put = [&](int p, uint64_t k) {
+                if (p < s.aq_lds) aql[p] = k;
+                else aqg[p] = k;
+            };
+            const int n16 = (m_sub & 15) == 0 && m_sub <= 64 ? m_sub >> 4 : 0;  // 16-byte pieces of a code row that are fetched ahead
+            auto fetch_codes = [&](uint32_t v, bool on, u32x4 (&c)[4]) {
+                if (!on) return;
+                const uint8_t *row = codes + (size_t)v * m_sub;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i < n16) c[i] = *reinterpret_cast<const u32x4 *>(row + 16 * i);
+            };
+            auto mark = [&](uint32_t v, bool on) -> bool {  // first time this query meets v?
+                if (!on) return false;
+                const uint32_t bit = 1u << (v & 31);
+                return !(atomicOr(&seen[v >> 5], bit) & bit);
+            };
+            // the neighbours that are new go to AQ with their approximate scores; returns how many there are
+            auto take = [&](uint32_t v, bool is_new, const u32x4 (&c)[4]) -> int {
+                float sc = 0.f;
+                if (is_new) {  // table entries summed in subspace order
+                    if (n16 > 0) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (i < n16) {
+#pragma unroll
+                                for (int m = 0; m < 16; ++m) sc += tab[(16 * i + m) * KSUB + ((c[i][m >> 2] >> (8 * (m & 3))) & 255u)];
+                            }
+                    } else {
+                        const uint8_t *row = codes + (size_t)v * m_sub;
+                        for (int m = 0; m < m_sub; ++m) sc += tab[m * KSUB + row[m]];
+                    }
+                }
+                const unsigned long long mask = __ballot(is_new);
+                const int cnt = __popcll(mask);
+                if (tail + cnt > s.aqcap && live + cnt <= s.aqcap) {  // squeeze the holes out
+                    __threadfence_block();
+                    int out = 0;
+                    for (int b = 0; b < tail; b += 64) {
+                        const uint64_t k = b + lane < tail ? aq_get(b + lane) : 0;
+                        const unsigned long long full = __ballot(k != 0);
+                        if (k) aq_put(out + __popcll(full & ((1ull << lane) - 1ull)), k);
+                        out += __popcll(full);
+                    }
+                    tail = out;
+                    __threadfence_block();
+                    for (int g = 0; g < s.aq_groups; ++g) {
+                        uint64_t best = 0;
+                        for (int b = g * s.aq_run + lane; b < min(tail, (g + 1) * s.aq_run); b += 64) best = max(best, aq_get(b));
+                        best = wave_max_key(best);
+                        if (lane == 0) aqm[g] = best;
+                    }
+                }
+                const int pos = tail + __popcll(mask & ((1ull << lane) - 1ull));
+                if (is_new) {
+                    if (pos < s.aqcap) {
+                        const uint64_t k = queue_key(sc, v);
+                        aq_put(pos, k);
+                        atomicMax(reinterpret_cast<unsigned long long *>(&aqm[pos / s.aq_run]), (unsigned long long)k);
+                    } else {
+                        err |= ERR_AQ_OVERFLOW;
+                    }
+                }
+                const int fit = min(cnt, s.aqcap - tail);
+                tail += fit;
+                live += fit;
+                return cnt;
+            };
+            bool more = true;
+            while (more && n_pend < batch) {
+                // the next hops: the best 64 entries of EQ that have not been expanded
+                int m = 0;
+                for (int b = 0; b < n_eq && m < 64; b += 64) {
+                    const bool open = b + lane < n_eq && !eqv[b + lane];
+                    const unsigned long long mask = __ballot(open);
+                    const int at = m + __popcll(mask & ((1ull << lane) - 1ull));
+                    if (open && at < 64) list[at] = b + lane;
+                    m = min(64, m + __popcll(mask));
+                }
+                if (m == 0) break;
+                more = m == 64;
+                __builtin_amdgcn_wave_barrier();
+                const int at = lane < m ? list[lane] : 0;
+                const uint32_t u = lane < m ? key_id(eqk[at]) : 0;
+                uint64_t beg = 0;
+                int deg = 0;
+                if (lane < m) {
+                    beg = row_ptr[u];
+                    deg = (int)(row_ptr[u + 1] - beg);
+                }
+                auto fetch_row = [&](int h) -> uint32_t {  // the first 64 neighbours of hop h
+                    uint32_t v = 0;
+                    if (h < m && lane < __builtin_amdgcn_readlane(deg, h)) v = col_idx[readlane64(beg, h) + lane];
+                    return v;
+                };
+                uint32_t v0 = fetch_row(0), v1 = fetch_row(1);
+                u32x4 c0[4], c1[4];
+                bool on0 = lane < __builtin_amdgcn_readlane(deg, 0) && v0 < n;
+                fetch_codes(v0, on0, c0);
+                bool marked = false, fresh = false;  // hop h's marks have been set a hop ahead; what that said
+                int h = 0;
+                for (; h < m && n_pend < batch; ++h) {
+                    const int dh = __builtin_amdgcn_readlane(deg, h);
+                    const uint64_t bh = readlane64(beg, h);
+                    if (lane == 0) eqv[__builtin_amdgcn_readlane(at, h)] = 1;
+                    ++hops;
+                    if (lane < dh && v0 >= n) err |= ERR_BAD_NEIGHBOUR;
+                    if (!marked) fresh = mark(v0, on0);
+                    // the next hop's codes, the row of the one after it
+                    const int dn = h + 1 < m ? __builtin_amdgcn_readlane(deg, h + 1) : 0;
+                    const bool on1 = lane < dn && v1 < n;
+                    fetch_codes(v1, on1, c1);
+                    const uint32_t v2 = fetch_row(h + 2);
+                    bool fresh1 = false;
+                    const bool certain = h + 1 < m && dh <= 64 && n_pend + (int)ceilf(alpha * (float)dh) < batch;
+                    if (certain) fresh1 = mark(v1, on1);
+                    int n_new = take(v0, fresh, c0);
+                    for (int b = 64; b < dh; b += 64) {  // rows longer than a wavefront
+                        uint32_t v = 0;
+                        const bool in = b + lane < dh;
+                        if (in) v = col_idx[bh + b + lane];
+                        if (in && v >= n) err |= ERR_BAD_NEIGHBOUR;
+                        u32x4 c[4];
+                        const bool is_new = mark(v, in && v < n);
+                        fetch_codes(v, is_new, c);
+                        n_new += take(v, is_new, c);
+                    }
+                    adc += n_new;
+                    if (tail > s.aq_lds) __threadfence_block();  // orders this wave's AQ stores before the reads below
+                    // move the r best entries of AQ to the pending list
+                    const int r = (int)ceilf(alpha * (float)n_new);
+                    const int groups = (tail + s.aq_run - 1) / s.aq_run;
+                    for (int t = 0; t < r && live > 0; ++t) {
+                        uint64_t best = 0;
+                        int from = 0;
+                        for (int g = lane; g < groups; g += 64)
+                            if (aqm[g] > best) {
+                                best = aqm[g];
+                                from = g;
+                            }
+                        const uint64_t top = wave_max_key(best);
+                        const int g = __builtin_amdgcn_readlane(from, __ffsll((long long)__ballot(best == top)) - 1);
+                        uint64_t rest = 0;
+                        for (int i = 0; i < runs64; ++i) {
+                            const int p = g * s.aq_run + i * 64 + lane;
+                            const uint64_t k = p < tail ? aq_get(p) : 0;
+                            if (k == top) aq_put(p, 0);
+                            else rest = max(rest, k);
+                        }
+                        rest = wave_max_key(rest);
+                        if (lane == 0) {
+                            aqm[g] = rest;
+                            if (n_pend < s.pcap) pend[n_pend] = key_id(top);
+                        }
+                        if (tail > s.aq_lds) __threadfence_block();
+                        if (n_pend >= s.pcap) err |= ERR_P_OVERFLOW;
+                        n_pend = min(n_pend + 1, s.pcap);
+                        --live;
+                    }
+                    v0 = v1;
+                    on0 = on1;
+                    v1 = v2;
+                    marked = certain;
+                    fresh = fresh1;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) c0[i] = c1[i];
+                }
+            }
+            if (lane == 0) {
+                sh_pend = n_pend;
+                sh_tail = tail;
             }
         }
         __syncthreads();
+        n_pend = sh_pend;
+        if (n_pend == 0) {  // no unvisited node and nothing pending
+            finished = true;
+            break;
+        }
     }
-    for (int i = lane; i < n_eq; i += 64) {
-        s.eq_score[(size_t)q * s.ef + i] = eqs[i];
-        s.eq_id[(size_t)q * s.ef + i] = eqi[i];
+
+    for (int i = tid; i < n_eq; i += ADV_THREADS) {
+        s.eq_key[(size_t)q * s.ef + i] = eqk[i];
         s.eq_vis[(size_t)q * s.ef + i] = eqv[i];
     }
-    for (int j = lane; j < np; j += 64) s.owner[s.pend[(size_t)q * s.pcap + j]] = NO_OWNER;  // free for the next round
-    if (lane == 0) {
+    int mine = 0, memo_hits = 0;  // of the pending entries: served by the stored table, by the memo
+    if (!finished) {
+        const int end = sh_tail;
+        for (int i = tid; i < min(end, s.aq_lds); i += ADV_THREADS) aqg[i] = aql[i];
+        for (int i = tid; i < s.aq_groups; i += ADV_THREADS) s.aq_max[(size_t)q * s.aq_groups + i] = aqm[i];
+        // Claim.  Chunks that several queries ask for in the same round are encoded once: the pending entry with the
+        // smallest number (q * pcap + j) owns the chunk.  The encoder's output for a chunk does not depend on its batch, so
+        // every query still sees exactly the scores it would compute alone.  Newer rounds have smaller values: nothing has
+        // to be taken back.
+        for (int j = tid; j < n_pend; j += ADV_THREADS) {
+            const uint32_t c = pend[j];
+            if (s.slot_of && s.slot_of[c] >= 0) ++mine;
+            else if (s.memo_slot && s.memo_slot[c] >= 0) ++memo_hits;  // encoded earlier in this call
+            else atomicMin(&s.owner[c], (unsigned long long)~round << 32 | (uint32_t)(q * s.pcap + j));
+        }
+    }
+    if (mine) atomicAdd((unsigned long long *)&s.counters[CTR_HITS], (unsigned long long)mine);
+    if (memo_hits) atomicAdd((unsigned long long *)&s.counters[CTR_MEMO_HITS], (unsigned long long)memo_hits);
+    if (err) atomicOr((unsigned long long *)&s.counters[CTR_ERR], (unsigned long long)err);
+    if (tid == 0) {  // wavefront 0 has counted the hops
         s.eq_n[q] = n_eq;
-        s.n_pend[q] = 0;
-        atomicAdd((unsigned long long *)&s.counters[CTR_RECOMP], (unsigned long long)np);
-        atomicAdd((unsigned long long *)&s.counters[CTR_FLUSH], 1ull);
+        s.aq_tail[q] = tail;
+        s.aq_live[q] = live;
+        s.n_pend[q] = n_pend;
+        if (finished) s.done[q] = 1;
+        atomicAdd((unsigned long long *)&s.counters[CTR_HOPS], (unsigned long long)hops);
+        atomicAdd((unsigned long long *)&s.counters[CTR_ADC], (unsigned long long)adc);
+        atomicAdd((unsigned long long *)&s.counters[CTR_RECOMP], (unsigned long long)recomp);
+        atomicAdd((unsigned long long *)&s.counters[CTR_FLUSH], (unsigned long long)flushes);
+        atomicAdd((unsigned long long *)&s.counters[CTR_HITS], (unsigned long long)hits);
+    }
+}
+
+// Pack the round: encoder input list (one entry per owned chunk; the order does not matter), owners' rows, the round's
+// totals.  One wavefront per query; the last block hands the counters to the host.
+__global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_t *__restrict__ lengths, int seq)
+{
+    const int q = blockIdx.x, lane = threadIdx.x;
+    const int np = s.done[q] ? 0 : s.n_pend[q];
+    int tokens = 0;
+    for (int j0 = 0; j0 < np; j0 += 64) {
+        const int j = j0 + lane, e = q * s.pcap + j;
+        bool mine = false;
+        uint32_t c = 0;
+        if (j < np) {
+            c = s.pend[e];
+            if (!(s.slot_of && s.slot_of[c] >= 0) && !(s.memo_slot && s.memo_slot[c] >= 0)) {
+                const int o = (int)(uint32_t)s.owner[c];
+                s.own[e] = o;
+                mine = o == e;
+            }
+        }
+        const unsigned long long mask = __ballot(mine);
+        if (!mask) continue;
+        int at = 0;
+        if (lane == 0) at = (int)atomicAdd((unsigned long long *)&s.counters[CTR_NENC], (unsigned long long)__popcll(mask));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((1ull << lane) - 1ull));
+        if (mine) {
+            s.enc_ids[at] = c;
+            s.src[e] = at;
+            const int len = lengths[c];
+            if (len >= 1 && len <= seq) tokens += len;  // others are reported by the encoder
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tokens += __shfl_xor(tokens, o, 64);
+    int last = 0;
+    if (lane == 0) {
+        if (np) {
+            atomicAdd((unsigned long long *)&s.counters[CTR_PENDING], (unsigned long long)np);
+            atomicAdd((unsigned long long *)&s.counters[CTR_ROUND_TOKENS], (unsigned long long)tokens);
+        }
+        __threadfence();
+        last = atomicAdd((unsigned long long *)&s.counters[CTR_TICKET], 1ull) == gridDim.x - 1;
+    }
+    if (__builtin_amdgcn_readfirstlane(last)) {
+        __threadfence();
+        if (lane < CTR_COUNT)
+            __hip_atomic_store(&s.host_counters[lane], __hip_atomic_load(&s.counters[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __threadfence_system();
     }
 }
 
@@ -454,8 +560,7 @@ __global__ __launch_bounds__(64) void finalize_kernel(SearchState s, int k, cons
 {
     const int q = blockIdx.x, lane = threadIdx.x;
     const int n_eq = s.eq_n[q];
-    const float *eqs = s.eq_score + (size_t)q * s.ef;
-    const uint32_t *eqi = s.eq_id + (size_t)q * s.ef;
+    const uint64_t *eqk = s.eq_key + (size_t)q * s.ef;
     const float *bsc = buf_scores + (size_t)q * nb;
     float last_s = INFINITY;
     uint32_t last_id = 0;
@@ -469,8 +574,8 @@ __global__ __launch_bounds__(64) void finalize_kernel(SearchState s, int k, cons
                 float x;
                 uint32_t id;
                 if (i < n_eq) {
-                    x = eqs[i];
-                    id = eqi[i];
+                    x = key_score(eqk[i]);
+                    id = key_id(eqk[i]);
                     if (deleted_bits && (deleted_bits[id >> 5] >> (id & 31) & 1u)) continue;
                 } else {
                     x = bsc[i - n_eq];
@@ -499,10 +604,23 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
+namespace {
+
+constexpr int LDS_LIMIT = 158 * 1024;  // dynamic LDS of advance_kernel, beside its few fixed arrays
+
+// advance_kernel for rows of d elements (the encoder's widths end at 1024)
+auto advance_for(int d) -> decltype(&advance_kernel<2>)
+{
+    return d <= 128 ? advance_kernel<2> : d <= 384 ? advance_kernel<6> : d <= 768 ? advance_kernel<12> : advance_kernel<16>;
+}
+
+}  // namespace
+
 int search_init_device()
 {
-    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(traverse_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
+    for (int d : {128, 384, 768, 1024})
+        LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(advance_for(d)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      LDS_LIMIT));
     return LEANN_OK;
 }
 
@@ -520,8 +638,10 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     int *enc_err = (int *)ctx->meta.p;
     LEANN_HIP(hipMemsetAsync(enc_err, 0, sizeof(int), st));
     hipLaunchKernelGGL(maxdeg_kernel, dim3(256), dim3(256), 0, st, graph->row_ptr, n, counters);
-    long long h_ctr[CTR_COUNT];
-    LEANN_HIP(hipMemcpyAsync(h_ctr, counters, sizeof(h_ctr), hipMemcpyDeviceToHost, st));
+    if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, CTR_COUNT * sizeof(long long), hipHostMallocDefault));
+    long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after a synchronisation only
+    const size_t ctr_bytes = CTR_COUNT * sizeof(long long);
+    LEANN_HIP(hipMemcpyAsync(h_ctr, counters, ctr_bytes, hipMemcpyDeviceToHost, st));
     LEANN_HIP(hipStreamSynchronize(st));
     const long long maxdeg = h_ctr[CTR_MAXDEG];
 
@@ -545,19 +665,21 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         off = align_up(off + bytes, 256);
         return o;
     };
-    const size_t o_eqs = carve((size_t)G * ef * 4), o_eqi = carve((size_t)G * ef * 4), o_eqv = carve((size_t)G * ef);
-    const size_t o_eqn = carve((size_t)G * 4), o_aqs = carve((size_t)G * aqcap * 4), o_aqi = carve((size_t)G * aqcap * 4);
-    const size_t o_aqn = carve((size_t)G * 4), o_pend = carve((size_t)G * pcap * 4), o_np = carve((size_t)G * 4);
-    const size_t o_src = carve((size_t)G * pcap * 4), o_done = carve((size_t)G * 4), o_eoff = carve((size_t)(G + 1) * 4);
-    const size_t o_eids = carve((size_t)G * pcap * 8);
+    const int32_t aq_run = (int32_t)(((int64_t)aqcap + AQ_GROUPS_MAX * 64 - 1) / (AQ_GROUPS_MAX * 64) * 64);
+    const int32_t aq_groups = (int32_t)(((int64_t)aqcap + aq_run - 1) / aq_run);
+    const size_t o_eqk = carve((size_t)G * ef * 8), o_eqv = carve((size_t)G * ef), o_eqn = carve((size_t)G * 4);
+    const size_t o_aqk = carve((size_t)G * aqcap * 8), o_aqm = carve((size_t)G * aq_groups * 8);
+    const size_t o_aqt = carve((size_t)G * 4), o_aql = carve((size_t)G * 4), o_pend = carve((size_t)G * pcap * 4);
+    const size_t o_np = carve((size_t)G * 4), o_src = carve((size_t)G * pcap * 4), o_own = carve((size_t)G * pcap * 4);
+    const size_t o_done = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
     LEANN_TRY(ctx->s_state.reserve(off));
     LEANN_TRY(ctx->s_seen.reserve((size_t)G * words * 4));
     LEANN_TRY(ctx->s_lut.reserve((size_t)G * m_sub * KSUB * sizeof(float)));
     LEANN_TRY(ctx->s_emb.reserve((size_t)G * pcap * d * sizeof(float)));
-    LEANN_TRY(ctx->s_owner.reserve((size_t)n * sizeof(int32_t)));
-    LEANN_HIP(hipMemsetAsync(ctx->s_owner.p, 0x7f, (size_t)n * sizeof(int32_t), st));
+    LEANN_TRY(ctx->s_owner.reserve((size_t)n * sizeof(unsigned long long)));
+    LEANN_HIP(hipMemsetAsync(ctx->s_owner.p, 0xff, (size_t)n * sizeof(unsigned long long), st));
     // per-call embedding memo (leann_set_call_memo): empty at the start of every call
-    const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, MEMO_SRC_BASE - 1);
+    const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, (1 << 30) - 1);
     int64_t memo_n = 0;
     if (memo_cap > 0) {
         LEANN_TRY(ctx->s_memo_slot.reserve((size_t)n * sizeof(int32_t)));
@@ -566,22 +688,22 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     }
     char *base = (char *)ctx->s_state.p;
     SearchState s;
-    s.eq_score = (float *)(base + o_eqs);
-    s.eq_id = (uint32_t *)(base + o_eqi);
+    s.eq_key = (uint64_t *)(base + o_eqk);
     s.eq_vis = (uint8_t *)(base + o_eqv);
     s.eq_n = (int32_t *)(base + o_eqn);
-    s.aq_score = (float *)(base + o_aqs);
-    s.aq_id = (uint32_t *)(base + o_aqi);
-    s.aq_n = (int32_t *)(base + o_aqn);
+    s.aq_key = (uint64_t *)(base + o_aqk);
+    s.aq_max = (uint64_t *)(base + o_aqm);
+    s.aq_tail = (int32_t *)(base + o_aqt);
+    s.aq_live = (int32_t *)(base + o_aql);
     s.seen = (uint32_t *)ctx->s_seen.p;
     s.pend = (uint32_t *)(base + o_pend);
     s.n_pend = (int32_t *)(base + o_np);
     s.src = (int32_t *)(base + o_src);
+    s.own = (int32_t *)(base + o_own);
     s.done = (int32_t *)(base + o_done);
-    s.owner = (int32_t *)ctx->s_owner.p;
+    s.owner = (unsigned long long *)ctx->s_owner.p;
     s.memo_slot = memo_cap > 0 ? (int32_t *)ctx->s_memo_slot.p : nullptr;
     s.memo_emb = memo_cap > 0 ? (const float *)ctx->s_memo_emb.p : nullptr;
-    s.enc_off = (int32_t *)(base + o_eoff);
     s.enc_ids = (int64_t *)(base + o_eids);
     s.counters = counters;
     s.lut = (const float *)ctx->s_lut.p;
@@ -589,13 +711,24 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     s.ef = ef;
     s.aqcap = aqcap;
     s.pcap = pcap;
+    s.aq_run = aq_run;
+    s.aq_groups = aq_groups;
+    s.host_counters = h_ctr;
+    s.slot_of = cache ? cache->slot_of : nullptr;
+    s.cache_emb = cache ? cache->emb : nullptr;
+    s.cache_rows = cache ? cache->rows : 0;
 
-    const int trav_smem = m_sub * KSUB * (int)sizeof(float) + ef * 9 + 16;
-    const int eq_smem = ef * 9 + 16;
-    if (trav_smem > 150 * 1024) {
-        leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", trav_smem);
+    const int table_smem = m_sub * KSUB * (int)sizeof(float) + ef * 9 + 16;
+    if (table_smem > 150 * 1024) {
+        leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", table_smem);
         return LEANN_ESHAPE;
     }
+    // what is left holds the head of AQ
+    const int aq_room = (LDS_LIMIT - table_smem - aq_groups * 8) / (64 * 8) * 64;
+    s.aq_lds = std::min(AQ_LDS_MAX, aq_room);
+    const int adv_smem = table_smem + aq_groups * 8 + s.aq_lds * 8;
+    const auto advance = advance_for(d);
+    uint32_t launches = 0;
 
     struct Events : std::vector<hipEvent_t> {  // destroyed on every way out of this function
         ~Events()
@@ -619,22 +752,17 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         LEANN_HIP(hipMemsetAsync(s.seen, 0, (size_t)g * words * 4, st));
         hipLaunchKernelGGL(init_kernel, dim3((g + 255) / 256), dim3(256), 0, st, s, g, graph->entry);
         LEANN_TRY(pq_build_lut(ctx, qg, g, pq, (float *)ctx->s_lut.p));
-        for (;;) {
+        for (bool have_results = false;; have_results = true) {
             LEANN_TRY(mark());
             {
                 ProfScope prof(ctx, LEANN_PROF_TRAVERSE);
-                hipLaunchKernelGGL(traverse_kernel, dim3(g), dim3(64), trav_smem, st, s, graph->row_ptr, graph->col_idx,
-                                   n, pq->codes, m_sub, alpha, batch);
+                hipLaunchKernelGGL(advance, dim3(g), dim3(ADV_THREADS), adv_smem, st, s, graph->row_ptr, graph->col_idx, n,
+                                   pq->codes, m_sub, alpha, batch, qg, d, (const float *)ctx->s_emb.p, have_results, ++launches);
             }
-            LEANN_HIP(hipMemsetAsync(&counters[CTR_PENDING], 0, 2 * sizeof(long long), st));
             {
                 ProfScope prof(ctx, LEANN_PROF_COLLECT);
-                const int32_t *slot_of = cache ? cache->slot_of : nullptr;
-                hipLaunchKernelGGL(claim_kernel, dim3(g), dim3(64), 0, st, s, slot_of, cache ? cache->rows : 0);
-                hipLaunchKernelGGL(collect_kernel, dim3(1), dim3(1024), 0, st, s, g, slot_of);
-                hipLaunchKernelGGL(resolve_kernel, dim3(g), dim3(64), 0, st, s, slot_of);
+                hipLaunchKernelGGL(collect_kernel, dim3(g), dim3(64), 0, st, s, chunks->lengths, chunks->seq);
             }
-            LEANN_HIP(hipMemcpyAsync(h_ctr, counters, sizeof(h_ctr), hipMemcpyDeviceToHost, st));
             LEANN_TRY(mark());
             LEANN_HIP(hipStreamSynchronize(st));
             if (h_ctr[CTR_ERR]) {
@@ -654,7 +782,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             const int64_t n_enc = h_ctr[CTR_NENC];
             if (n_enc > 0) {
                 rc = enc_forward(ctx, chunks, s.enc_ids, 0, n_enc, (float *)ctx->s_emb.p, enc_err,
-                                 (int64_t *)&counters[CTR_TOKENS], 0);
+                                 (int64_t *)&counters[CTR_TOKENS], h_ctr[CTR_ROUND_TOKENS]);
                 if (rc != LEANN_OK) break;
                 encoded += n_enc;
                 if (memo_cap > 0 && memo_n < memo_cap) {
@@ -663,11 +791,6 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                                        (float *)ctx->s_memo_emb.p, s.memo_slot);
                     memo_n = std::min<int64_t>(memo_cap, memo_n + n_enc);
                 }
-            }
-            {
-                ProfScope prof(ctx, LEANN_PROF_SCORE_INSERT);
-                hipLaunchKernelGGL(score_insert_kernel, dim3(g), dim3(64), eq_smem, st, s, qg, d,
-                                   (const float *)ctx->s_emb.p, cache ? cache->emb : nullptr);
             }
             ++rounds;
         }
@@ -692,7 +815,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     if (rc == LEANN_OK) rc = mark();
     int h_enc_err = 0;
     if (rc == LEANN_OK) {
-        LEANN_HIP(hipMemcpyAsync(h_ctr, counters, sizeof(h_ctr), hipMemcpyDeviceToHost, st));
+        LEANN_HIP(hipMemcpyAsync(h_ctr, counters, ctr_bytes, hipMemcpyDeviceToHost, st));
         LEANN_HIP(hipMemcpyAsync(&h_enc_err, enc_err, sizeof(int), hipMemcpyDeviceToHost, st));
     }
     hipError_t sync_rc = hipStreamSynchronize(st);

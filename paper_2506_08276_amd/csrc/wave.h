@@ -1,4 +1,4 @@
-// Wave-wide (64 lanes) sums and ordered keys of the queue kernels.
+// Wave-wide (64 lanes) sums, inner products and ordered keys of the queue kernels.
 #pragma once
 #include "common.h"
 
@@ -76,5 +76,72 @@ __device__ inline uint64_t wave_max_key(uint64_t k)
     const uint32_t low = wave_max(hi == top ? (uint32_t)k : 0u);
     return ((uint64_t)top << 32) | low;
 }
+
+// One anchor row against other rows, fp32.  NV = 4-byte pieces per lane (lane l owns elements l, l + 64, ...), 0: rows
+// longer than 1024, read from memory each time.  Every lane gets the result; its bits do not depend on how many rows are
+// taken at once.
+template <int NV>
+struct RowDots {
+    float a[NV > 0 ? NV : 1];
+    const float *row;
+    int d, lane;
+
+    __device__ static inline float piece(__amdgpu_buffer_rsrc_t r, int lane, int j)  // 0 beyond the row's end
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (j * 64 + lane) * 4, 0, 0));
+    }
+    __device__ inline __amdgpu_buffer_rsrc_t rsrc(const float *p) const
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, d * (int)sizeof(float), 0x00020000);
+    }
+    __device__ inline void load(const float *p, int d_, int lane_)
+    {
+        row = p;
+        d = d_;
+        lane = lane_;
+        if constexpr (NV > 0) {
+            const auto r = rsrc(p);
+#pragma unroll
+            for (int j = 0; j < NV; ++j) a[j] = piece(r, lane, j);
+        }
+    }
+    __device__ static inline const float *uniform(const float *p)  // the same in all lanes: scalar registers
+    {
+        const uint64_t u = (uint64_t)p;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+        return (const float *)((uint64_t)hi << 32 | lo);
+    }
+    // out[k] = <anchor, row_at(k)> for k < c <= 4.  The rows' loads are all issued before the first sum: a row comes
+    // from beyond L2 as a rule, and four in flight per wavefront cost little more time than one.
+    template <class RowAt>
+    __device__ inline void four(RowAt row_at, int c, float (&out)[4]) const
+    {
+        if constexpr (NV > 0) {
+            float r[4][NV];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < c) {
+                    const auto rs = rsrc(uniform(row_at(k)));
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) r[k][j] = piece(rs, lane, j);
+                }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < c) {
+                    float acc = 0.f;
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) acc = fmaf(a[j], r[k][j], acc);
+                    out[k] = wave_sum(acc);
+                }
+        } else {
+            for (int k = 0; k < c; ++k) {
+                const float *e = uniform(row_at(k));
+                float acc = 0.f;
+                for (int i = lane; i < d; i += 64) acc = fmaf(row[i], e[i], acc);
+                out[k] = wave_sum(acc);
+            }
+        }
+    }
+};
 
 }  // namespace

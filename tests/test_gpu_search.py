@@ -176,6 +176,65 @@ def test_queue_capacity_overflow_is_reported(L, world):
     assert torch.equal(ids0, ids1) and torch.equal(sc0, sc1)
 
 
+@pytest.mark.parametrize("m_sub,ef,alpha,batch", [(8, 300, 0.5, 20), (64, 1000, 0.1, 64), (16, 40, 1.0, 200)])
+def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
+    """An approximate queue of thousands of entries, rows longer than a wavefront, empty rows, repeated neighbours, and
+    lookup tables with and without 16-byte code pieces.  Everything is integer-valued, so every score is exact and
+    there are many ties: ids, scores and counts equal the oracle's.  Then the smallest queue capacity that the search gets
+    by with: at it (holes have to be squeezed out) and above it the result is the same, one below it overflows; and a
+    capacity that makes the queue's runs longer than a wavefront."""
+    rng = np.random.default_rng(m_sub)
+    n, d, k, nq = 40_000, 128, 10, 6
+    cfg = li.TINY
+    emb = rng.integers(-4, 5, size=(n, d)).astype(np.float32)
+    queries = rng.integers(-4, 5, size=(nq, d)).astype(np.float32)
+    deg = rng.integers(0, 30, n)
+    deg[0], deg[1::1000] = 150, 90
+    row_ptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.uint64)
+    col_idx = rng.integers(0, n, int(row_ptr[-1])).astype(np.uint32)
+    cb, _ = orc.pq_train(emb[:256], m_sub, 0, 3)
+    codes = orc.pq_encode(emb, cb)
+    say(f"integer world m_sub={m_sub} ef={ef} alpha={alpha} batch={batch}")
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 1)))
+    pq = L.leann_pq_import(ctx, cb, codes)
+    try:
+        args = (to_dev(queries), (to_dev(row_ptr.view(np.int64)), to_dev(col_idx.view(np.int32)), 0), pq,
+                to_dev(np.ones((n, 4), np.int32)), to_dev(np.full(n, 4, np.int32)), ef, k, alpha, batch)
+        cache = (to_dev(np.arange(n, dtype=np.int32)), to_dev(emb))
+
+        def search(capacity):
+            L.leann_set_limits(ctx, 0, capacity)
+            ids, scores, st = L.leann_search(ctx, *args, cache=cache)
+            return ids.cpu().numpy(), scores.cpu().numpy(), st
+
+        ids, scores, st = search(32768)
+        runs = [orc.search_table(q, row_ptr, col_idx, 0, cb, codes, emb, ef, k, alpha, batch) for q in queries]
+        for qi, r in enumerate(runs):
+            assert list(ids[qi]) == list(r["ids"]), qi
+            np.testing.assert_array_equal(scores[qi], r["scores"])
+        for key, okey in (("hops", "hops"), ("adc_candidates", "adc_candidates"), ("recomputed_chunks", "recomputed"),
+                          ("flushes", "flushes")):
+            assert st[key] == sum(r["stats"][okey] for r in runs), key
+        lo, hi = 0, 32768  # lo overflows, hi does not
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                search(mid)
+                hi = mid
+            except L.LeannError as e:
+                assert e.status == -5
+                lo = mid
+        print(f"smallest AQ capacity {hi} for {st['adc_candidates'] // nq} scored neighbours per query")
+        for capacity in (hi, hi + 1, hi + 70, 39_990):
+            got = search(capacity)
+            np.testing.assert_array_equal(got[0], ids)
+            np.testing.assert_array_equal(got[1], scores)
+            assert got[2]["hops"] == st["hops"] and got[2]["adc_candidates"] == st["adc_candidates"]
+    finally:
+        L.leann_pq_free(pq)
+        L.leann_destroy(ctx)
+
+
 def pack_bits(flags):
     """uint8 flags [n] -> int32 words, bit (v & 31) of word (v >> 5)."""
     n = len(flags)
