@@ -225,6 +225,7 @@ void leann_destroy(leann_ctx *ctx)
     for (DevBuf *b : bufs) b->release();
     ctx->prof_tokens.release();
     if (ctx->host_counters) (void)hipHostFree(ctx->host_counters);
+    if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
     for (auto &sp : ctx->prof_spans) {
         (void)hipEventDestroy(sp.a);
         (void)hipEventDestroy(sp.b);

@@ -67,6 +67,7 @@ struct leann_ctx {
     // search workspace
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
+    int *host_flag = nullptr;            // pinned host memory: leann_adc's bad-id flag
     int64_t memo_rows = 0;  // rows of the per-call embedding memo (leann_set_call_memo), 0 = off
     // optional per-kernel timing (leann_profile_begin / leann_profile_end)
     bool prof_on = false;

@@ -334,22 +334,104 @@ __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ x
     if (tid < dsub) codebook[((size_t)m * KSUB + c) * dsub + tid] = part[tid] / (float)cnt;
 }
 
-// lut[q][m][c] = -|q_m - codebook[m][c]|^2 (PQ's asymmetric distance, negated so that larger is closer),
-// sub-vector summed in index order.  grid (nq, m_sub), 256 threads.
-__global__ __launch_bounds__(256) void lut_kernel(const float *__restrict__ queries, int d, int m_sub,
+// -|q_m - c|^2 (PQ's asymmetric distance, negated so that larger is closer), elements in index order.
+__device__ inline float neg_dist(const float *__restrict__ q, const float *__restrict__ c, int dsub, bool vec)
+{
+    float s = 0.f;
+    if (vec) {
+        for (int j = 0; j < dsub; j += 4) {
+            const f32x4 cv = *reinterpret_cast<const f32x4 *>(c + j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float t = q[j + i] - cv[i];
+                s = fmaf(t, t, s);
+            }
+        }
+    } else {
+        for (int j = 0; j < dsub; ++j) {
+            const float t = q[j] - c[j];
+            s = fmaf(t, t, s);
+        }
+    }
+    return -s;
+}
+
+// lut[q][m][c] = -|q_m - codebook[m][c]|^2.  grid (ceil(nq / LUT_QUERIES), m_sub), 256 threads; a thread keeps its
+// centroid in registers for all of the block's queries (a block per query read the codebook out of L2 once for each of
+// them: 53 us for 1024 queries of 768 elements).
+constexpr int LUT_QUERIES = 8;
+
+__global__ __launch_bounds__(256) void lut_kernel(const float *__restrict__ queries, int64_t nq, int d, int m_sub,
                                                   const float *__restrict__ codebook, float *__restrict__ lut)
 {
-    __shared__ float qs[MAX_DSUB];
-    const int q = blockIdx.x, m = blockIdx.y, dsub = d / m_sub, c = threadIdx.x;
-    if (c < dsub) qs[c] = queries[(size_t)q * d + m * dsub + c];
-    __syncthreads();
+    __shared__ float qs[LUT_QUERIES][MAX_DSUB];
+    const int m = blockIdx.y, dsub = d / m_sub, c = threadIdx.x;
+    const int64_t q0 = (int64_t)blockIdx.x * LUT_QUERIES;
+    const int nb = (int)min((int64_t)LUT_QUERIES, nq - q0);
+    const int ql = threadIdx.x >> 5, j0 = threadIdx.x & 31;
+    static_assert(LUT_QUERIES * MAX_DSUB == 256, "one element per thread");
+    qs[ql][j0] = ql < nb && j0 < dsub ? queries[(size_t)(q0 + ql) * d + m * dsub + j0] : 0.f;
+    float cv[MAX_DSUB];
     const float *cb = codebook + ((size_t)m * KSUB + c) * dsub;
-    float s = 0.f;
-    for (int j = 0; j < dsub; ++j) {
-        const float t = qs[j] - cb[j];
-        s += t * t;
+    if ((dsub & 3) == 0) {  // the codebook is an allocation of its own: its rows start at 16 bytes then
+#pragma unroll
+        for (int j = 0; j < MAX_DSUB; j += 4)
+            if (j < dsub) *reinterpret_cast<f32x4 *>(cv + j) = *reinterpret_cast<const f32x4 *>(cb + j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < MAX_DSUB; ++j)
+            if (j < dsub) cv[j] = cb[j];
     }
-    lut[((size_t)q * m_sub + m) * KSUB + c] = -s;
+    __syncthreads();
+    for (int i = 0; i < nb; ++i) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < MAX_DSUB; ++j)
+            if (j < dsub) {
+                const float t = qs[i][j] - cv[j];
+                s = fmaf(t, t, s);
+            }
+        lut[((size_t)(q0 + i) * m_sub + m) * KSUB + c] = -s;
+    }
+}
+
+void launch_lut(hipStream_t st, const float *queries, int64_t nq, const leann_pq *pq, float *lut)
+{
+    hipLaunchKernelGGL(lut_kernel, dim3((unsigned)((nq + LUT_QUERIES - 1) / LUT_QUERIES), pq->m_sub), dim3(256), 0, st, queries, nq,
+                       pq->d, pq->m_sub, pq->codebook, lut);
+}
+
+// The scores without a table, for calls with few candidates: the table entries that they name are computed one by one (the
+// same operations: the same bits) and added in subspace order.  grid (nq, ceil(nc / DIRECT_CAND)), 256 threads.
+constexpr int DIRECT_CAND = 16;
+
+__global__ __launch_bounds__(256) void adc_direct_kernel(const float *__restrict__ queries, int d, int m_sub,
+                                                         const float *__restrict__ codebook, const uint8_t *__restrict__ codes,
+                                                         int64_t n, const uint32_t *__restrict__ cand, int nc,
+                                                         float *__restrict__ out, int *__restrict__ err)
+{
+    extern __shared__ float part[];  // [DIRECT_CAND][m_sub | 1]
+    const int q = blockIdx.x, j0 = blockIdx.y * DIRECT_CAND, here = min(DIRECT_CAND, nc - j0);
+    const int dsub = d / m_sub, pitch = m_sub | 1;
+    const float *qv = queries + (size_t)q * d;
+    const uint32_t *cq = cand + (size_t)q * nc + j0;
+    for (int i = threadIdx.x; i < here * m_sub; i += 256) {
+        const int c = i / m_sub, m = i - c * m_sub;
+        const uint32_t id = cq[c];
+        float v = -INFINITY;
+        if (id < n) v = neg_dist(qv + m * dsub, codebook + ((size_t)m * KSUB + codes[(size_t)id * m_sub + m]) * dsub, dsub, (dsub & 3) == 0);
+        part[c * pitch + m] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < here) {
+        float s = 0.f;
+        for (int m = 0; m < m_sub; ++m) s += part[threadIdx.x * pitch + m];
+        if (cq[threadIdx.x] >= n) {
+            s = -INFINITY;
+            *err = 1;
+        }
+        out[(size_t)q * nc + j0 + threadIdx.x] = s;
+    }
 }
 
 // out[q][j] = sum_m lut[q][m][codes[cand[q][j]][m]], m ascending.  grid (nq, parts), 256 threads; the query's table
@@ -357,6 +439,7 @@ __global__ __launch_bounds__(256) void lut_kernel(const float *__restrict__ quer
 // load is paid once per block, not once per 2048 candidates.  A thread owns 8 candidates per round: all their ids,
 // then all their code rows are requested before the first lookup, so that the random row gathers overlap instead of
 // queueing up; the ids of the next round are fetched while the current round's lookups run.
+constexpr int64_t ADC_DIRECT_MAX = 16384;  // candidates of a call that are scored without a table at most
 constexpr int ADC_PER_ROUND = 2048, ADC_PER_THREAD = ADC_PER_ROUND / 256;
 
 __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut, const uint8_t *__restrict__ codes,
@@ -411,7 +494,7 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
                 oq[j] = s;
             }
         }
-        if (bad) atomicOr(err, 1);
+        if (bad) *err = 1;
         return;
     }
     __syncthreads();
@@ -440,7 +523,7 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
             oq[j] = s;
         }
     }
-    if (bad) atomicOr(err, 1);
+    if (bad) *err = 1;
 }
 
 // A few blocks per CU, each with a multiple of what its wavefronts take at once.
@@ -551,8 +634,7 @@ int pq_build_lut(leann_ctx *ctx, const float *queries_dev, int64_t nq, const lea
 {
     if (nq <= 0) return LEANN_OK;
     ProfScope prof(ctx, LEANN_PROF_LUT);
-    hipLaunchKernelGGL(lut_kernel, dim3((unsigned)nq, pq->m_sub), dim3(256), 0, ctx->stream, queries_dev, pq->d,
-                       pq->m_sub, pq->codebook, lut_dev);
+    launch_lut(ctx->stream, queries_dev, nq, pq, lut_dev);
     LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
@@ -713,30 +795,38 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
     }
     if (nq == 0 || nc == 0) return LEANN_OK;
     LEANN_HIP(hipSetDevice(ctx->device));
-    const size_t lut_bytes = (size_t)nq * pq->m_sub * KSUB * sizeof(float);
-    LEANN_TRY(ctx->s_lut.reserve(lut_bytes));
-    LEANN_TRY(ctx->meta.reserve(256));
-    int *err = (int *)ctx->meta.p;
-    LEANN_HIP(hipMemsetAsync(err, 0, sizeof(int), ctx->stream));
-    LEANN_TRY(pq_build_lut(ctx, queries_dev, nq, pq, (float *)ctx->s_lut.p));
     const int smem = pq->m_sub * KSUB * (int)sizeof(float);
     if (smem > 96 * 1024) {
         leann_set_error("lookup table of %d bytes does not fit the ADC kernel's LDS budget", smem);
         return LEANN_ESHAPE;
     }
-    {
+    // the flag lies in pinned host memory: a kernel that meets a bad id writes it there, nothing is cleared or copied on
+    // the device.  Calls on a context wait for their kernels, so nobody else holds it now.
+    if (!ctx->host_flag) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flag, sizeof(int), hipHostMallocDefault));
+    volatile int *flag = ctx->host_flag;
+    *flag = 0;
+    // A lookup table holds 256 entries per subspace: for fewer candidates than that, and few enough of them in all that
+    // launches and not work are what counts, computing the entries that are used is less of both (d = 768, 32 subspaces,
+    // whole call: one query, 64 candidates 18 us, with a table 23; 64 x 64 20 and 31 us; 128 x 128 29 us, 256 x 128
+    // with a table 34).
+    if (nc <= KSUB && nq * nc <= ADC_DIRECT_MAX) {
+        ProfScope prof(ctx, LEANN_PROF_ADC);
+        hipLaunchKernelGGL(adc_direct_kernel, dim3((unsigned)nq, (nc + DIRECT_CAND - 1) / DIRECT_CAND), dim3(256),
+                           DIRECT_CAND * (pq->m_sub | 1) * sizeof(float), ctx->stream, queries_dev, pq->d, pq->m_sub, pq->codebook,
+                           pq->codes, pq->n, cand_ids_dev, nc, out_dev, ctx->host_flag);
+    } else {
+        LEANN_TRY(ctx->s_lut.reserve((size_t)nq * pq->m_sub * KSUB * sizeof(float)));
+        LEANN_TRY(pq_build_lut(ctx, queries_dev, nq, pq, (float *)ctx->s_lut.p));
         ProfScope prof(ctx, LEANN_PROF_ADC);
         int parts = 1, per_block = ADC_PER_ROUND;
         adc_launch_shape(nq, nc, &parts, &per_block);
         hipLaunchKernelGGL(adc_kernel, dim3((unsigned)nq, parts), dim3(256), smem, ctx->stream,
                            (const float *)ctx->s_lut.p, pq->codes, pq->n, pq->m_sub, cand_ids_dev, nc, per_block, out_dev,
-                           err);
+                           ctx->host_flag);
     }
     LEANN_HIP(hipGetLastError());
-    int herr = 0;
-    LEANN_HIP(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     LEANN_HIP(hipStreamSynchronize(ctx->stream));
-    if (herr) {
+    if (*flag) {
         leann_set_error("leann_adc: candidate id outside [0, n)");
         return LEANN_EINVAL;
     }
@@ -769,8 +859,7 @@ int leann_adc_noalloc(leann_ctx *ctx, const float *queries_dev, int64_t nq, cons
     // the array keeps the last call's contents: the flag starts at zero (a kernel, not a memset, so that the call
     // can be recorded into a graph); the tables are overwritten for exactly the queries that are read
     hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, ctx->stream, flag);
-    hipLaunchKernelGGL(lut_kernel, dim3((unsigned)nq, pq->m_sub), dim3(256), 0, ctx->stream, queries_dev, pq->d,
-                       pq->m_sub, pq->codebook, lut);
+    launch_lut(ctx->stream, queries_dev, nq, pq, lut);
     int parts = 1, per_block = ADC_PER_ROUND;
     adc_launch_shape(nq, nc, &parts, &per_block);
     hipLaunchKernelGGL(adc_kernel, dim3((unsigned)nq, parts), dim3(256), smem, ctx->stream, (const float *)lut, pq->codes,

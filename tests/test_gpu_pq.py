@@ -96,6 +96,30 @@ def test_adc_many_queries_several_rounds_per_block(L, orc, ctx, m_sub, d):
     L.leann_pq_free(pq)
 
 
+@pytest.mark.parametrize("m_sub,d", [(32, 768), (3, 51), (20, 20), (96, 768)])
+def test_adc_with_and_without_table_give_the_same_bits(L, ctx, m_sub, d):
+    """Calls of at most 256 candidates per query compute the table entries they need, longer ones look them up: the same
+    candidates as part of a longer list score bit for bit the same.  A bad id is an error on both ways."""
+    import torch
+    n, nq = 1000, 5
+    say(f"adc direct and by table m_sub={m_sub} d={d}")
+    rng = np.random.default_rng(m_sub)
+    codes = rng.integers(0, 256, size=(n, m_sub)).astype(np.uint8)
+    pq = L.leann_pq_import(ctx, (0.1 * rng.standard_normal((m_sub, 256, d // m_sub))).astype(np.float32), codes)
+    q = to_dev(unit_rows(nq, d, 2))
+    cand = to_dev(rng.integers(0, n, size=(nq, 300)).astype(np.int32))
+    want = L.leann_adc(ctx, q, pq, cand)
+    for nc in (1, 15, 16, 17, 64, 256):
+        assert torch.equal(L.leann_adc(ctx, q, pq, cand[:, :nc].contiguous()), want[:, :nc]), nc
+    for nc in (40, 300):
+        bad = cand[:, :nc].clone()
+        bad[nq - 1, nc - 1] = n
+        with pytest.raises(L.LeannError):
+            L.leann_adc(ctx, q, pq, bad)
+        assert torch.equal(L.leann_adc(ctx, q, pq, cand[:, :nc].contiguous()), want[:, :nc])
+    L.leann_pq_free(pq)
+
+
 @pytest.mark.parametrize("n,d,m_sub,iters", [(2000, 128, 16, 10), (70000, 48, 2, 3)])
 def test_build_pq_invariants_and_error(L, orc, ctx, n, d, m_sub, iters):
     say(f"build_pq n={n} d={d} m_sub={m_sub} iters={iters}")
