@@ -40,6 +40,14 @@ void DevBuf::release()
     bytes = 0;
 }
 
+int clear_host_flags(leann_ctx *ctx)
+{
+    if (!ctx->host_flags) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flags, FLAG_COUNT * sizeof(int), hipHostMallocDefault));
+    volatile int *f = ctx->host_flags;
+    for (int i = 0; i < FLAG_COUNT; ++i) f[i] = 0;
+    return LEANN_OK;
+}
+
 ProfScope::ProfScope(leann_ctx *c, int kind) : ctx(c)
 {
     if (!c->prof_on) return;
@@ -225,7 +233,7 @@ void leann_destroy(leann_ctx *ctx)
     for (DevBuf *b : bufs) b->release();
     ctx->prof_tokens.release();
     if (ctx->host_counters) (void)hipHostFree(ctx->host_counters);
-    if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
+    if (ctx->host_flags) (void)hipHostFree(ctx->host_flags);
     for (auto &sp : ctx->prof_spans) {
         (void)hipEventDestroy(sp.a);
         (void)hipEventDestroy(sp.b);
@@ -339,16 +347,13 @@ int leann_embed(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     }
     if (n_ids == 0) return LEANN_OK;
     LEANN_HIP(hipSetDevice(ctx->device));
-    LEANN_TRY(ctx->meta.reserve(256));
-    int *err = (int *)ctx->meta.p;
-    LEANN_HIP(hipMemsetAsync(err, 0, sizeof(int), ctx->stream));
-    LEANN_TRY(enc_forward(ctx, chunks, ids_dev, 0, n_ids, out_emb_dev, err, nullptr, 0));
-    int herr = 0;
-    LEANN_HIP(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    LEANN_TRY(clear_host_flags(ctx));
+    LEANN_TRY(enc_forward(ctx, chunks, ids_dev, 0, n_ids, out_emb_dev, nullptr, 0));
     LEANN_HIP(hipStreamSynchronize(ctx->stream));
-    if (herr) {
-        leann_set_error("leann_embed: %s%s%s", (herr & 1) ? "chunk id outside the store; " : "",
-                        (herr & 2) ? "length outside [1, seq]; " : "", (herr & 4) ? "token id outside [0, vocab)" : "");
+    const volatile int *bad = ctx->host_flags;
+    if (bad[FLAG_CHUNK_ID] || bad[FLAG_LENGTH] || bad[FLAG_TOKEN]) {
+        leann_set_error("leann_embed: %s%s%s", bad[FLAG_CHUNK_ID] ? "chunk id outside the store; " : "",
+                        bad[FLAG_LENGTH] ? "length outside [1, seq]; " : "", bad[FLAG_TOKEN] ? "token id outside [0, vocab)" : "");
         return LEANN_EINVAL;
     }
     return LEANN_OK;

@@ -67,7 +67,7 @@ struct leann_ctx {
     // search workspace
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
-    int *host_flag = nullptr;            // pinned host memory: leann_adc's bad-id flag
+    int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags
     int64_t memo_rows = 0;  // rows of the per-call embedding memo (leann_set_call_memo), 0 = off
     // optional per-kernel timing (leann_profile_begin / leann_profile_end)
     bool prof_on = false;
@@ -79,6 +79,12 @@ struct leann_ctx {
     std::vector<ProfSpan> prof_spans;
     std::vector<hipEvent_t> prof_pool;
 };
+
+// Error flags of a call, in pinned host memory: kernels store 1 to what they find wrong, the host reads them after it has
+// waited for the stream.  Nothing has to be cleared or copied on the device.  Calls on a context wait for their kernels, so
+// nothing of an earlier call is still to be written.
+enum { FLAG_CHUNK_ID = 0, FLAG_LENGTH, FLAG_TOKEN, FLAG_CANDIDATE, FLAG_COUNT };
+int clear_host_flags(leann_ctx *ctx);
 
 // Brackets one kernel launch with HIP events on the context's stream when profiling is on.
 struct ProfScope {
@@ -105,10 +111,10 @@ int search_init_device();
 
 // ---- encoder.hip
 // Embeds the chunks named by ids_dev[0..n) (NULL: first_id .. first_id+n) into out[n][d] (fp32), in passes of at
-// most ctx->max_tokens padded tokens.  err_dev: device int, set non-zero on invalid tokens / lengths / ids.  tokens: the
+// most ctx->max_tokens padded tokens.  Invalid tokens / lengths / ids: see ctx->host_flags.  tokens: the
 // chunks' valid tokens in all if the caller knows them, else 0 (for the choice of GEMM tiles only).
 int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_dev, int64_t first_id, int64_t n,
-                float *out_dev, int *err_dev, int64_t *tok_count_dev, int64_t tokens);
+                float *out_dev, int64_t *tok_count_dev, int64_t tokens);
 
 // ---- pq.hip
 int pq_build_lut(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_pq *pq, float *lut_dev);

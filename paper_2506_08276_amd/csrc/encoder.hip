@@ -12,15 +12,9 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "wave.h"
 
 namespace {
-
-__device__ inline float wave_sum(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // ------------------------------------------------------------------ pass set-up
 // lengths of the requested chunks -> exclusive prefix sum cu[0..n], cu[n] = T.  One block of 1024 threads.
@@ -39,12 +33,12 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ 
         int64_t id = ids ? ids[i] : first_id + i;
         int len = 0;
         if (id < 0 || id >= n_store) {
-            atomicOr(err, 1);
+            err[FLAG_CHUNK_ID] = 1;
             id = 0;
         } else {
             len = lengths[id];
             if (len < 1 || len > seq) {
-                atomicOr(err, 2);
+                err[FLAG_LENGTH] = 1;
                 len = 0;
             }
         }
@@ -90,7 +84,7 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
     if (t >= len) return;
     int tok = tokens[chunk_of[i] * seq + t];
     if (tok < 0 || tok >= vocab) {
-        if (lane == 0) atomicOr(err, 4);
+        if (lane == 0) err[FLAG_TOKEN] = 1;
         tok = 0;
     }
     // a lane owns 16-byte pieces (8 elements) j*64 + lane of the row, as in the residual LayerNorm below
@@ -150,11 +144,9 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
                                                  const int32_t *__restrict__ T_dev, int d, float eps)
 {
     const int lane = threadIdx.x & 63;
-    const int T = *T_dev;
     const int pieces = d >> 3;
     const int nwaves = gridDim.x * 4;
     int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= T) return;
     // a wave goes through rows row, row + nwaves, ...: the scale and shift of its pieces stay in registers, and the
     // next row's loads are issued before the current row's arithmetic
     f32x4 gg[2][2], bb[2][2];
@@ -170,6 +162,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
             dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + (size_t)row * d + c0));
             xn[j] = *reinterpret_cast<const bf16x8 *>(x + (size_t)row * d + c0);
         }
+    const int T = *T_dev;  // the loads above do not wait for it: the buffers reach past the last block's rows
     for (; row < T; row += nwaves) {
         bf16_t *xr = x + (size_t)row * d;
         float v[2][8];
@@ -431,6 +424,8 @@ __global__ __launch_bounds__(256, NKT == 4 ? 3 : 2) void attention_kernel(const 
 // One block per chunk.  Wave w sums rows w, w + 4, ... with 16-byte loads (a lane owns pieces j*64 + lane of a row, as
 // in the LayerNorm kernels); the four partial sums of a column are added in wave order, so the result does not depend
 // on anything but the chunk.
+constexpr int POOL_AHEAD = 8;
+
 __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x, const int32_t *__restrict__ cu, int d,
                                                    float *__restrict__ out)
 {
@@ -444,14 +439,25 @@ __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x,
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[j][i] = 0.f;
-    for (int t = wave; t < L; t += 4) {
-        const bf16_t *xr = x + (size_t)(t0 + t) * d;
+    for (int t = wave; t < L; t += 4 * POOL_AHEAD) {  // the rows' loads are issued together, their sums keep the order
+        bf16x8 r[POOL_AHEAD][2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (j * 64 + lane < pieces) {
-                const bf16x8 r = *reinterpret_cast<const bf16x8 *>(xr + (j * 64 + lane) * 8);
+        for (int k = 0; k < POOL_AHEAD; ++k)
+            if (t + 4 * k < L) {
+                const bf16_t *xr = x + (size_t)(t0 + t + 4 * k) * d;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) acc[j][i] += (float)r[i];
+                for (int j = 0; j < 2; ++j)
+                    if (j * 64 + lane < pieces) r[k][j] = *reinterpret_cast<const bf16x8 *>(xr + (j * 64 + lane) * 8);
+            }
+#pragma unroll
+        for (int k = 0; k < POOL_AHEAD; ++k)
+            if (t + 4 * k < L) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    if (j * 64 + lane < pieces) {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) acc[j][i] += (float)r[k][j][i];
+                    }
             }
     }
 #pragma unroll
@@ -475,11 +481,8 @@ __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x,
     }
     red[tid] = sq;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) red[tid] += red[tid + o];
-        __syncthreads();
-    }
-    const float nrm = fmaxf(sqrtf(red[0]), 1e-12f);
+    // pairwise over the threads: (t, t + 128), (t, t + 64), then inside the wavefront
+    const float nrm = fmaxf(sqrtf(wave_sum((red[lane] + red[lane + 128]) + (red[lane + 64] + red[lane + 192]))), 1e-12f);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int col = tid + 256 * j;
@@ -650,7 +653,7 @@ int enc_init_device()
 }
 
 int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_dev, int64_t first_id, int64_t n,
-                float *out_dev, int *err_dev, int64_t *tok_count_dev, int64_t tokens)
+                float *out_dev, int64_t *tok_count_dev, int64_t tokens)
 {
     const leann_encoder_desc &e = ctx->desc;
     const int d = e.hidden, F = e.ffn, H = e.heads, seq = chunks->seq;
@@ -684,14 +687,14 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
             hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, ctx->stream, chunks->lengths,
-                               ids_dev ? ids_dev + s : nullptr, first_id + s, m, chunks->n, seq, cu, chunk_of, err_dev,
+                               ids_dev ? ids_dev + s : nullptr, first_id + s, m, chunks->n, seq, cu, chunk_of, ctx->host_flags,
                                tok_count_dev, ctx->prof_on ? (int64_t *)ctx->prof_tokens.p : nullptr);
         }
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
             hipLaunchKernelGGL(embed_ln_kernel, dim3((unsigned)(((int64_t)m * seq + 3) / 4)), dim3(256), 0, ctx->stream,
                                chunks->tokens, chunk_of, cu, m, seq, d, e.vocab, ctx->tok_emb, ctx->pos_emb, ctx->seg_emb,
-                               ctx->emb_g, ctx->emb_b, e.ln_eps, x, err_dev);
+                               ctx->emb_g, ctx->emb_b, e.ln_eps, x, ctx->host_flags);
         }
         // as many blocks as are resident at once (measured: 10 % faster than a row per wave, and than twice as
         // many blocks); their waves go through several rows each

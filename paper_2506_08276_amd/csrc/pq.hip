@@ -800,11 +800,8 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
         leann_set_error("lookup table of %d bytes does not fit the ADC kernel's LDS budget", smem);
         return LEANN_ESHAPE;
     }
-    // the flag lies in pinned host memory: a kernel that meets a bad id writes it there, nothing is cleared or copied on
-    // the device.  Calls on a context wait for their kernels, so nobody else holds it now.
-    if (!ctx->host_flag) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flag, sizeof(int), hipHostMallocDefault));
-    volatile int *flag = ctx->host_flag;
-    *flag = 0;
+    LEANN_TRY(clear_host_flags(ctx));
+    int *flag = ctx->host_flags + FLAG_CANDIDATE;
     // A lookup table holds 256 entries per subspace: for fewer candidates than that, and few enough of them in all that
     // launches and not work are what counts, computing the entries that are used is less of both (d = 768, 32 subspaces,
     // whole call: one query, 64 candidates 18 us, with a table 23; 64 x 64 20 and 31 us; 128 x 128 29 us, 256 x 128
@@ -813,7 +810,7 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
         ProfScope prof(ctx, LEANN_PROF_ADC);
         hipLaunchKernelGGL(adc_direct_kernel, dim3((unsigned)nq, (nc + DIRECT_CAND - 1) / DIRECT_CAND), dim3(256),
                            DIRECT_CAND * (pq->m_sub | 1) * sizeof(float), ctx->stream, queries_dev, pq->d, pq->m_sub, pq->codebook,
-                           pq->codes, pq->n, cand_ids_dev, nc, out_dev, ctx->host_flag);
+                           pq->codes, pq->n, cand_ids_dev, nc, out_dev, flag);
     } else {
         LEANN_TRY(ctx->s_lut.reserve((size_t)nq * pq->m_sub * KSUB * sizeof(float)));
         LEANN_TRY(pq_build_lut(ctx, queries_dev, nq, pq, (float *)ctx->s_lut.p));
@@ -822,11 +819,11 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
         adc_launch_shape(nq, nc, &parts, &per_block);
         hipLaunchKernelGGL(adc_kernel, dim3((unsigned)nq, parts), dim3(256), smem, ctx->stream,
                            (const float *)ctx->s_lut.p, pq->codes, pq->n, pq->m_sub, cand_ids_dev, nc, per_block, out_dev,
-                           ctx->host_flag);
+                           flag);
     }
     LEANN_HIP(hipGetLastError());
     LEANN_HIP(hipStreamSynchronize(ctx->stream));
-    if (*flag) {
+    if (*(volatile int *)flag) {
         leann_set_error("leann_adc: candidate id outside [0, n)");
         return LEANN_EINVAL;
     }

@@ -634,9 +634,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     LEANN_TRY(ctx->s_misc.reserve(CTR_COUNT * sizeof(long long)));
     long long *counters = (long long *)ctx->s_misc.p;
     LEANN_HIP(hipMemsetAsync(counters, 0, CTR_COUNT * sizeof(long long), st));
-    LEANN_TRY(ctx->meta.reserve(256));
-    int *enc_err = (int *)ctx->meta.p;
-    LEANN_HIP(hipMemsetAsync(enc_err, 0, sizeof(int), st));
+    LEANN_TRY(clear_host_flags(ctx));
     hipLaunchKernelGGL(maxdeg_kernel, dim3(256), dim3(256), 0, st, graph->row_ptr, n, counters);
     if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, CTR_COUNT * sizeof(long long), hipHostMallocDefault));
     long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after a synchronisation only
@@ -781,7 +779,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             }
             const int64_t n_enc = h_ctr[CTR_NENC];
             if (n_enc > 0) {
-                rc = enc_forward(ctx, chunks, s.enc_ids, 0, n_enc, (float *)ctx->s_emb.p, enc_err,
+                rc = enc_forward(ctx, chunks, s.enc_ids, 0, n_enc, (float *)ctx->s_emb.p,
                                  (int64_t *)&counters[CTR_TOKENS], h_ctr[CTR_ROUND_TOKENS]);
                 if (rc != LEANN_OK) break;
                 encoded += n_enc;
@@ -813,18 +811,18 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                            out_scores_dev + (size_t)q0 * k);
     }
     if (rc == LEANN_OK) rc = mark();
-    int h_enc_err = 0;
     if (rc == LEANN_OK) {
         LEANN_HIP(hipMemcpyAsync(h_ctr, counters, ctr_bytes, hipMemcpyDeviceToHost, st));
-        LEANN_HIP(hipMemcpyAsync(&h_enc_err, enc_err, sizeof(int), hipMemcpyDeviceToHost, st));
     }
     hipError_t sync_rc = hipStreamSynchronize(st);
     if (rc == LEANN_OK && sync_rc != hipSuccess) {
         leann_set_error("search kernels failed: %s", hipGetErrorString(sync_rc));
         rc = LEANN_EDEVICE;
     }
-    if (rc == LEANN_OK && h_enc_err) {
-        leann_set_error("chunk store holds a token id or length outside its range (flags %d)", h_enc_err);
+    const volatile int *bad = ctx->host_flags;
+    if (rc == LEANN_OK && (bad[FLAG_CHUNK_ID] || bad[FLAG_LENGTH] || bad[FLAG_TOKEN])) {
+        leann_set_error("chunk store holds a token id or length outside its range (flags %d)",
+                        (bad[FLAG_CHUNK_ID] ? 1 : 0) | (bad[FLAG_LENGTH] ? 2 : 0) | (bad[FLAG_TOKEN] ? 4 : 0));
         rc = LEANN_EINVAL;
     }
     if (rc == LEANN_OK && stats) {
