@@ -139,6 +139,9 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
 // statistics and the normalisation are fp32.  One wave per row, the whole row in registers before anything is
 // written.  A lane owns 16-byte pieces (8 elements) j*64 + lane of the row (row length a multiple of 8, at most
 // 1024).  Two-pass statistics on the registers: mean, then the biased variance of the centred values.
+// EARLY: the first row is requested before the token count is there (a small pass is nothing but this chain of latencies;
+// the buffers reach past the last block's rows); with many rows per wavefront that order costs 3 % of the bandwidth.
+template <bool EARLY>
 __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delta, const float *__restrict__ g,
                                                  const float *__restrict__ b, bf16_t *__restrict__ x,
                                                  const int32_t *__restrict__ T_dev, int d, float eps)
@@ -147,6 +150,11 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
     const int pieces = d >> 3;
     const int nwaves = gridDim.x * 4;
     int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    int T = 0;
+    if constexpr (!EARLY) {
+        T = *T_dev;
+        if (row >= T) return;
+    }
     // a wave goes through rows row, row + nwaves, ...: the scale and shift of its pieces stay in registers, and the
     // next row's loads are issued before the current row's arithmetic
     f32x4 gg[2][2], bb[2][2];
@@ -162,7 +170,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
             dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + (size_t)row * d + c0));
             xn[j] = *reinterpret_cast<const bf16x8 *>(x + (size_t)row * d + c0);
         }
-    const int T = *T_dev;  // the loads above do not wait for it: the buffers reach past the last block's rows
+    if constexpr (EARLY) T = *T_dev;
     for (; row < T; row += nwaves) {
         bf16_t *xr = x + (size_t)row * d;
         float v[2][8];
@@ -424,7 +432,7 @@ __global__ __launch_bounds__(256, NKT == 4 ? 3 : 2) void attention_kernel(const 
 // One block per chunk.  Wave w sums rows w, w + 4, ... with 16-byte loads (a lane owns pieces j*64 + lane of a row, as
 // in the LayerNorm kernels); the four partial sums of a column are added in wave order, so the result does not depend
 // on anything but the chunk.
-constexpr int POOL_AHEAD = 8;
+constexpr int POOL_AHEAD = 4;
 
 __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x, const int32_t *__restrict__ cu, int d,
                                                    float *__restrict__ out)
@@ -496,11 +504,11 @@ int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W,
 {
     constexpr int WM = 2, WN = BN / 64;
     constexpr int smem = gemm_smem_bytes<BM, BN, WM, WN>();
-    if (N % BN || K % (4 * GEMM_BK) || (BM * BN > 128 * 128 && K < 8 * GEMM_BK)) {
+    if (N % (BM == 256 ? 128 : BN) || K % (4 * GEMM_BK) || (BM * BN > 128 * 128 && K < 8 * GEMM_BK)) {
         leann_set_error("GEMM shape N=%d K=%d not covered by the %dx%d tile", N, K, BM, BN);
         return LEANN_ESHAPE;
     }
-    const int tiles_n = N / BN;
+    const int tiles_n = (N + BN - 1) / BN;
     // W beyond the 4 MB of L2 an XCD has is evicted between its uses; if the output is wide (so that A is small next
     // to it) the column tiles go in groups that fit (measured on FFN1: +4-5 %; on QKV, whose W fits, a loss).
     int gcols = tiles_n;
@@ -570,6 +578,8 @@ int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16
 //  4000 x 3072 x  768                                    46.5     29.9      22.7
 //  8000 x  768 x 3072                                    82.9     50.6      56.4
 // 32000 x  768 x  768                                    86.3     50.8      42.6
+// 48000 x 1152 x  384                                             62.5      52.9
+// 24000 x  384 x 1536                                             46.6      37.6
 // What decides is how many tiles the busiest CU gets: with c = ceil(tiles / CUs) the larger three take about 2.5 + 3.7 c,
 // 2.5 + 8 c and 21 c - 2 (K = 768; the ratios are the same at K = 3072).  The small-pass kernel is the fastest while its
 // blocks fit the chip at once, its smallest tile first.
@@ -592,12 +602,12 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const 
 #undef LEANN_SMALL
     }
     auto busiest = [&](int tile) {  // tiles of the busiest CU
-        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * (N / tile);
+        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * ((N + tile - 1) / tile);
         return (double)((tiles + cus - 1) / cus);
     };
     const double cost128 = N % 128 == 0 ? 2.5 + 8.0 * busiest(128) : INFINITY;
     const double cost64 = fine ? 2.5 + 3.7 * busiest(64) : INFINITY;
-    const bool wide = ctx->gemm_large_tile == 256 && N % 256 == 0 && K >= 8 * GEMM_BK;
+    const bool wide = ctx->gemm_large_tile == 256 && N % 128 == 0 && K >= 8 * GEMM_BK;  // the last column tile may be half empty
     const double cost256 = wide ? 21.0 * busiest(256) - 2.0 : INFINITY;
     if (cost256 <= cost128 && cost256 <= cost64)
         return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
@@ -628,7 +638,7 @@ int gemm_allow_lds()
 int enc_ln_blocks_per_cu(int *out)
 {
     int n = 0;
-    LEANN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(ln_kernel), 256, 0));
+    LEANN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(ln_kernel<false>), 256, 0));
     *out = n > 0 ? n : 1;
     return LEANN_OK;
 }
@@ -701,7 +711,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         const int ln_grid = std::min((max_rows + 3) / 4, ctx->num_cus * ctx->ln_blocks_per_cu);
         auto layer_norm = [&](const float *g, const float *b) {
             ProfScope prof(ctx, LEANN_PROF_LAYERNORM);
-            hipLaunchKernelGGL(ln_kernel, dim3(ln_grid), dim3(256), 0, ctx->stream, delta, g, b, x, T_dev, d, e.ln_eps);
+            hipLaunchKernelGGL(rows <= 2048 ? ln_kernel<true> : ln_kernel<false>, dim3(ln_grid), dim3(256), 0, ctx->stream, delta, g, b, x, T_dev, d, e.ln_eps);
         };
         for (int l = 0; l < e.layers; ++l) {
             const LayerWeights &w = ctx->layers[l];

@@ -175,11 +175,13 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     // does not have to merge their pending loads into the waits of the long-K path.
     if constexpr (BM * BN > 128 * 128) __builtin_assume(KT >= 8);
     auto ag = GEMM_RSRC(A + (size_t)tile_m * BM * K, BM);
-    auto wg = GEMM_RSRC(W + (size_t)tile_n * BN * K, BN);
+    // the last column tile may reach past N (a multiple of 64): its missing rows of W read as zeros, its wavefronts without
+    // columns store nothing
+    auto wg = GEMM_RSRC(W + (size_t)tile_n * BN * K, min(BN, N - tile_n * BN));
     // The bias of a tile is fetched before the tile's first operand slab and put into LDS at the start of the tile:
     // a load issued in the epilogue would complete only after the next tile's prefetched slabs (loads return in
     // order), and the epilogue would wait for all of them.
-    float bnext = bias[tile_n * BN + wn * (BN / WN) + lane];
+    float bnext = bias[min(tile_n * BN + wn * (BN / WN), N - BN / WN) + lane];
     GEMM_GLOAD(ra0, rb0, ag, wg, 0)
     GEMM_GLOAD(ra1, rb1, ag, wg, BK)
     GEMM_GLOAD(ra2, rb2, ag, wg, 2 * BK)
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     int next_m = tile_m, next_n = tile_n;
     GEMM_TILE_AT(step + 1, have_next, next_m, next_n)
     const auto ag_next = GEMM_RSRC(A + (size_t)next_m * BM * K, BM);
-    const auto wg_next = GEMM_RSRC(W + (size_t)next_n * BN * K, BN);
+    const auto wg_next = GEMM_RSRC(W + (size_t)next_n * BN * K, min(BN, N - next_n * BN));
     // Slabs 0..3 of this tile are in the four register sets.  Steady state of the K loop at iteration 0: slabs 0 and
     // 1 in the ring, slabs 2, 3, 4 in sets 1, 2, 3, set 0 free.
     bf16x8 af0[TM], bf0[TN], af1[TM], bf1[TN];
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
         GEMM_ITER(, GEMM_SSTORE(ra0, rb0, st_nn))
     }
     // last four slabs: slabs KT-2 and KT-1 still go into the ring; the loads fetch the next tile
-    bnext = bias[next_n * BN + wn * (BN / WN) + lane];
+    bnext = bias[min(next_n * BN + wn * (BN / WN), N - BN / WN) + lane];
     GEMM_ITER(GEMM_GLOAD(ra0, rb0, ag_next, wg_next, 0), GEMM_SSTORE(ra1, rb1, st_nn))
     GEMM_ITER(GEMM_GLOAD(ra1, rb1, ag_next, wg_next, BK), GEMM_SSTORE(ra2, rb2, st_nn))
     GEMM_ITER(GEMM_GLOAD(ra2, rb2, ag_next, wg_next, 2 * BK), )
@@ -265,6 +267,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     // write-out: a wave-wide access covers 8 rows of eight 16-byte chunks.  The output is read by a later kernel
     // only: streaming stores keep it from displacing the operand slabs in L2 (measured: 3-7% per GEMM).
     const int orow = lane_e >> 3, och = lane_e & 7;
+    if (col0 < N)
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
         unsigned char *sl = stg + (mi & 1) * (32 * 128);  // the other slice than the previous 32 rows: their reads may still be on their way

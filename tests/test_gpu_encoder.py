@@ -127,8 +127,8 @@ def test_base_shape_sample_matches_oracle(L, orc):
 
 
 def test_small_shape_sample_matches_oracle(L, orc):
-    """The 12 x 384 encoder (second throughput point; widths that are not multiples of 256 take the 128-wide GEMM
-    tile) at seq 256; a few chunks against the oracle."""
+    """The 12 x 384 encoder (second throughput point; widths that are not multiples of 256 leave half of the 256-wide
+    GEMM tile's last column tile empty) at seq 256; a few chunks against the oracle."""
     import torch
     cfg = li.SMALL
     say("small-shape sample (12 x 384)")
