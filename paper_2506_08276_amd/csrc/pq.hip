@@ -221,25 +221,51 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
 }
 
 // Training rows of every centroid: order[m][..] holds the row numbers sorted by centroid, ascending within one;
-// first[m][c] .. first[m][c + 1] are centroid c's.  Counting sort, one block of 16 wavefronts per subspace, each wavefront a
-// run of consecutive rows.
-__global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restrict__ assign, int nt, int32_t *__restrict__ order,
-                                                          int32_t *__restrict__ first)
+// first[m][c] .. first[m][c + 1] are centroid c's.  Counting sort in two launches, GROUP_BLOCKS blocks of 16 wavefronts per
+// subspace, each wavefront a run of consecutive rows: count_rows_kernel leaves every run's rows per centroid in
+// counts[m][run][c], group_rows_kernel puts the rows behind those of the smaller centroids and the earlier runs (one block
+// per subspace left most of the chip idle: 65 us at 65536 rows and 32 subspaces).
+constexpr int GROUP_BLOCKS = 4, GROUP_RUNS = 16 * GROUP_BLOCKS;
+
+__device__ inline int run_rows(int nt) { return ((nt + GROUP_RUNS - 1) / GROUP_RUNS + 63) & ~63; }
+
+__global__ __launch_bounds__(1024) void count_rows_kernel(const uint8_t *__restrict__ assign, int nt, int32_t *__restrict__ counts)
 {
-    __shared__ int cnt[16][KSUB];  // rows per wavefront and centroid, then where the wavefront's next one goes
-    __shared__ int total[KSUB];
-    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ int cnt[16][KSUB];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint8_t *as = assign + (size_t)m * nt;
-    const int per = ((nt + 15) / 16 + 63) & ~63;
-    const int beg = min(nt, wave * per), end = min(nt, beg + per);
+    const int per = run_rows(nt), run = blockIdx.y * 16 + wave;
+    const int beg = min(nt, run * per), end = min(nt, beg + per);
     for (int i = tid; i < 16 * KSUB; i += 1024) (&cnt[0][0])[i] = 0;
     __syncthreads();
     for (int r = beg + lane; r < end; r += 64) atomicAdd(&cnt[wave][as[r]], 1);
     __syncthreads();
+    int32_t *out = counts + ((size_t)m * GROUP_RUNS + blockIdx.y * 16) * KSUB;
+    for (int i = tid; i < 16 * KSUB; i += 1024) out[i] = (&cnt[0][0])[i];
+}
+
+__global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restrict__ assign, int nt,
+                                                          const int32_t *__restrict__ counts, int32_t *__restrict__ order,
+                                                          int32_t *__restrict__ first)
+{
+    __shared__ int cnt[16][KSUB];  // where the wavefront's next row of a centroid goes
+    __shared__ int total[KSUB];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint8_t *as = assign + (size_t)m * nt;
+    const int per = run_rows(nt), run0 = blockIdx.y * 16, run = run0 + wave;
+    const int beg = min(nt, run * per), end = min(nt, beg + per);
+    const int32_t *cm = counts + (size_t)m * GROUP_RUNS * KSUB;
+    int before = 0;  // rows of centroid tid in the runs of earlier blocks
     if (tid < KSUB) {
         int s = 0;
-        for (int w = 0; w < 16; ++w) s += cnt[w][tid];
+#pragma unroll 16
+        for (int w = 0; w < GROUP_RUNS; ++w) {
+            const int c = cm[w * KSUB + tid];
+            s += c;
+            if (w < run0) before += c;
+            if (w >= run0 && w < run0 + 16) cnt[w - run0][tid] = c;
+        }
         total[tid] = s;
     }
     __syncthreads();
@@ -258,13 +284,16 @@ __global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restr
     }
     __syncthreads();
     if (tid < KSUB) {
-        int run = total[tid];
-        first[(size_t)m * (KSUB + 1) + tid] = run;
-        if (tid == 0) first[(size_t)m * (KSUB + 1) + KSUB] = nt;
+        int at = total[tid];
+        if (blockIdx.y == 0) {
+            first[(size_t)m * (KSUB + 1) + tid] = at;
+            if (tid == 0) first[(size_t)m * (KSUB + 1) + KSUB] = nt;
+        }
+        at += before;
         for (int w = 0; w < 16; ++w) {
             const int c = cnt[w][tid];
-            cnt[w][tid] = run;
-            run += c;
+            cnt[w][tid] = at;
+            at += c;
         }
     }
     __syncthreads();
@@ -310,11 +339,11 @@ __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ x
     for (int i0 = 0; i0 < cnt; i0 += 32) {
         const int r = i0 + lane32 < cnt ? rows[i0 + lane32] : -1;
         uint32_t mine = (uint32_t)(__ballot(r >= 0 && (r & 7) == group) >> shift);
-        while (__any(mine != 0)) {  // four rows' loads at a time, added in order
-            int rr[4];
-            float v[4];
+        while (__any(mine != 0)) {  // eight rows' loads at a time, added in order
+            int rr[8];
+            float v[8];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < 8; ++k) {
                 const int l = mine ? __ffs(mine) - 1 : 0;
                 rr[k] = __shfl(r, shift + l, 64);
                 if (mine == 0) rr[k] = -1;
@@ -322,7 +351,7 @@ __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ x
                 v[k] = rr[k] >= 0 && lane32 < dsub ? xm[(size_t)rr[k] * d] : 0.f;
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < 8; ++k)
                 if (rr[k] >= 0 && lane32 < dsub) part[(rr[k] & 255) * dsub + lane32] += v[k];
         }
     }
@@ -662,7 +691,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     const int64_t nt = n < MAX_TRAIN ? n : MAX_TRAIN;
     leann_pq *pq = nullptr;
     LEANN_TRY(alloc_pq(ctx, n, d, m_sub, true, &pq));
-    // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts
+    // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts | counts
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
@@ -672,6 +701,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     const size_t o_rows = carve((size_t)nt * sizeof(int64_t)), o_xt = carve((size_t)nt * d * sizeof(float));
     const size_t o_assign = carve((size_t)nt * m_sub), o_order = carve((size_t)nt * m_sub * sizeof(int32_t));
     const size_t o_first = carve((size_t)m_sub * (KSUB + 1) * sizeof(int32_t));
+    const size_t o_counts = carve((size_t)m_sub * GROUP_RUNS * KSUB * sizeof(int32_t));
     unsigned char *scr = nullptr;
     auto fail = [&](int code) {
         (void)hipFree(scr);
@@ -685,7 +715,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     int64_t *rows_dev = (int64_t *)(scr + o_rows);
     float *xt = (float *)(scr + o_xt);
     uint8_t *assign = scr + o_assign;
-    int32_t *order = (int32_t *)(scr + o_order), *first = (int32_t *)(scr + o_first);
+    int32_t *order = (int32_t *)(scr + o_order), *first = (int32_t *)(scr + o_first), *counts = (int32_t *)(scr + o_counts);
     if (hipMemcpyAsync(rows_dev, perm.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) !=
         hipSuccess)
         return fail(LEANN_EDEVICE);
@@ -693,7 +723,9 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     hipLaunchKernelGGL(first_centroids_kernel, dim3(KSUB, m_sub), dim3(64), 0, ctx->stream, xt, nt, d, m_sub, pq->codebook);
     for (int it = 0; it < iters; ++it) {
         launch_assign(ctx, xt, nt, d, m_sub, pq->codebook, assign, 1, nt);
-        hipLaunchKernelGGL(group_rows_kernel, dim3(m_sub), dim3(1024), 0, ctx->stream, assign, (int)nt, order, first);
+        hipLaunchKernelGGL(count_rows_kernel, dim3(m_sub, GROUP_BLOCKS), dim3(1024), 0, ctx->stream, assign, (int)nt, counts);
+        hipLaunchKernelGGL(group_rows_kernel, dim3(m_sub, GROUP_BLOCKS), dim3(1024), 0, ctx->stream, assign, (int)nt, counts, order,
+                           first);
         hipLaunchKernelGGL(update_kernel, dim3(KSUB, m_sub), dim3(256), (size_t)256 * dsub * sizeof(float), ctx->stream, xt, nt,
                            d, m_sub, order, first, pq->codebook);
     }
