@@ -113,7 +113,6 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
 // exact scores per query takes 0.9 ms; one wavefront per query with scans over both queues and a host round per flush
 // took 13.8 ms (78 rounds of 77 us hops, 44 us scores and 24 us packing).
 constexpr int ADV_THREADS = 256;
-constexpr int EQ_MAX = 1024;
 constexpr int AQ_LDS_MAX = 2048, AQ_GROUPS_MAX = 512;
 
 __device__ inline uint64_t readlane64(uint64_t v, int l)
