@@ -345,7 +345,8 @@ __global__ __launch_bounds__(64 * (TMB * TNB + 4)) void gemm_small_kernel(const 
     // blocks go round-robin to the 8 XCDs, which stand in a grid of xr x 8 / xr: an XCD takes every xr-th row tile and every
     // (8 / xr)-th column tile
     const int T = *T_dev;
-    const int row_tiles = (T + 32 * TMB - 1) / (32 * TMB), per_xcd = (row_tiles + xr - 1) / xr;
+    const int row_tiles = (T + 32 * TMB - 1) / (32 * TMB);  // 0 if no chunk of the pass is valid: every block leaves below
+    const int per_xcd = max(1, (row_tiles + xr - 1) / xr);
     const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3;
     const int tm = (in_xcd % per_xcd) * xr + xcd % xr, tn = (in_xcd / per_xcd) * (8 / xr) + xcd / xr;
     if (tm >= row_tiles || tn >= N / (32 * TNB)) return;

@@ -209,3 +209,25 @@ def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
         assert np.array_equal(L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy(), want)
     finally:
         L.leann_destroy(ctx)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 512), (384, 6, 1536)])
+def test_pass_without_a_valid_token(L, hidden, heads, ffn):
+    """Every requested chunk is outside the store, or its length is: the pass holds no token, whatever product kernel its
+    size would pick (one chunk up to passes beyond the small tiles).  The call is an error, and the next one is served."""
+    import torch
+    cfg = dict(layers=1, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=64, ln_eps=1e-12)
+    tokens, lengths = li.uniform_chunks(40, 64, 1, cfg["vocab"], 16, 64, 3)
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 5)))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        want = L.leann_embed(ctx, t, l, hidden=hidden)
+        for m in (1, 4, 12, 24, 40, 200):
+            say(f"no valid token, hidden {hidden}, {m} chunks")
+            with pytest.raises(L.LeannError, match="chunk id outside the store"):
+                L.leann_embed(ctx, t, l, ids=torch.full((m,), 40, dtype=torch.int64, device="cuda:0"), hidden=hidden)
+            with pytest.raises(L.LeannError, match="length outside"):
+                L.leann_embed(ctx, t, torch.full_like(l, 65), ids=torch.arange(m, device="cuda:0") % 40, hidden=hidden)
+            assert torch.equal(L.leann_embed(ctx, t, l, hidden=hidden), want)
+    finally:
+        L.leann_destroy(ctx)
