@@ -47,7 +47,7 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //  - With X = |x'|, C = max |c'|: the products and sums are off by at most (3 * 2^-18 + 2^-17) (X + C)^2, the index bits
 //    by 2^-16 (X + C)^2, and s(c) itself is rounded by less than 2^-18 (X + C)^2: 1.1 * 2^-15 (X + C)^2 in all per
 //    centroid.  A gap of more than 3 * 2^-15 (X + C)^2 between minimum and second minimum therefore leaves no doubt.  The
-//    other rows (few on embeddings; all of them where anything overflows or is not a number, or where the nearest
+//    other rows (few on embeddings; all of them where anything could overflow or is not a number, or where the nearest
 //    centroids are equal) get s(c) for all centroids by one wavefront.
 // So the result is s(c)'s for every input.  187 us on average at 65536 to 100000 rows, d = 768, 32 subspaces.
 constexpr int ASSIGN_THREADS = 512;
@@ -187,7 +187,9 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
             const uint32_t i7 = __float_as_uint(first) & 0x7fu;
             int code = (int)((i7 >> 4) * 32 + ((i7 & 15) >> 2) * 8 + (i7 & 3)) + (upper ? 4 : 0);
             const float S = X[g] + C;
-            const bool sure = second - first > fmaf(3.f / 32768.f * S, S, 1e-33f);  // the constant covers flushed denormals
+            // the constant covers flushed denormals; from S = 1e19 on an intermediate sum can overflow, and an infinity with index
+            // bits in it is a NaN to the medians
+            const bool sure = S < 1e19f && second - first > fmaf(3.f / 32768.f * S, S, 1e-33f);
             const int64_t row = r0 + g * 32 + l32;
             unsigned long long doubt = __ballot(!sure && half == 0 && row < end);
             while (doubt) {

@@ -195,6 +195,52 @@ def test_build_pq_exact_on_integer_rows(L, ctx, n, d, m_sub, offset):
         np.testing.assert_array_equal(codesb[rows], want[rows])
 
 
+def nearest_by_fp32_sums(rows, cb):
+    """Codes by the definition: s(c) = sum over j, ascending, of (x_j - c_j)^2 in fp32 with fused multiply-adds; the smallest
+    finite sum, the lowest index among equals, 0 if there is none.  The fused operation is emulated in float64: the
+    product of two fp32 values is exact there, and the sum is rounded to odd, so that the rounding to fp32 is the only one
+    (53 >= 24 + 2 bits)."""
+    m_sub, _, dsub = cb.shape
+    out = np.empty((len(rows), m_sub), np.int64)
+    with np.errstate(over="ignore", invalid="ignore"):
+        for m in range(m_sub):
+            x = rows[:, m * dsub:(m + 1) * dsub]
+            s = np.zeros((len(rows), 256), np.float32)
+            for j in range(dsub):
+                t = (x[:, j, None] - cb[m, None, :, j]).astype(np.float64)  # fp32 subtraction
+                p, a = t * t, s.astype(np.float64)
+                h = p + a
+                v = h - p
+                err = (p - (h - v)) + (a - v)
+                bits = h.view(np.int64)
+                even = np.isfinite(err) & (err != 0) & ((bits & 1) == 0)
+                s = np.where(even, bits + np.where(err > 0, 1, -1), bits).view(np.float64).astype(np.float32)
+            s = np.where(np.isfinite(s), s, np.inf)
+            out[:, m] = s.argmin(1)  # the first of the smallest; index 0 where all are infinite
+    return out
+
+
+def codes_of_first_centroids(L, ctx, x, m_sub):
+    """(codebook, codes) after no training round: the centroids are 256 of the rows."""
+    pq = L.leann_build_pq(ctx, to_dev(x), m_sub, 0, 7)
+    got = L.leann_pq_export(ctx, pq)
+    L.leann_pq_free(pq)
+    return got
+
+
+@pytest.mark.parametrize("dsub,longest", [(3, 1.5e19), (3, 1.7e19), (16, 1.7e19), (24, 2.2e19)])
+def test_pq_codes_where_products_overflow(L, ctx, dsub, longest):
+    """Rows so long that |c|^2 and |x|^2 are finite in fp32 and |c|^2 - 2 x.c is not, next to shorter ones; in the last
+    case the squares of some overflow too."""
+    say(f"pq codes of long rows, dsub {dsub} up to {longest}")
+    rng = np.random.default_rng(dsub)
+    x = rng.standard_normal((1500, 2, dsub))
+    norm = np.exp(rng.uniform(np.log(3e18), np.log(longest), (1500, 2, 1)))
+    x = (x / np.linalg.norm(x, axis=2, keepdims=True) * norm).astype(np.float32).reshape(1500, 2 * dsub)
+    cb, codes = codes_of_first_centroids(L, ctx, x, 2)
+    np.testing.assert_array_equal(codes, nearest_by_fp32_sums(x, cb))
+
+
 def test_build_pq_rejects_bad_shapes(L, ctx):
     say("build_pq bad shapes")
     x = to_dev(np.zeros((10, 130), np.float32))
