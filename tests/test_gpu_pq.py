@@ -241,6 +241,20 @@ def test_pq_codes_where_products_overflow(L, ctx, dsub, longest):
     np.testing.assert_array_equal(codes, nearest_by_fp32_sums(x, cb))
 
 
+@pytest.mark.parametrize("dsub,offset", [(1, 0.0), (5, 0.0), (8, 3.0), (24, 0.0), (32, 0.0), (32, 100.0)])
+def test_pq_codes_of_near_ties(L, ctx, dsub, offset):
+    """Clusters whose rows (and so some of their centroids) lie 1e-5 to 0.3 apart: gaps between the two nearest centroids
+    on both sides of what the matrix cores can tell apart, and far below it.  Bit for bit the codes of the fp32 sums."""
+    say(f"pq codes of near ties, dsub {dsub} offset {offset}")
+    rng = np.random.default_rng(dsub)
+    cent = rng.standard_normal((100, 2 * dsub))
+    spread = np.exp(rng.uniform(np.log(1e-5), np.log(0.3), (100, 1)))
+    own = rng.integers(0, 100, 3000)
+    x = (offset + cent[own] + spread[own] * rng.standard_normal((3000, 2 * dsub))).astype(np.float32)
+    cb, codes = codes_of_first_centroids(L, ctx, x, 2)
+    np.testing.assert_array_equal(codes, nearest_by_fp32_sums(x, cb))
+
+
 def test_build_pq_rejects_bad_shapes(L, ctx):
     say("build_pq bad shapes")
     x = to_dev(np.zeros((10, 130), np.float32))
