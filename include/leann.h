@@ -270,6 +270,7 @@ int leann_set_limits(leann_ctx *ctx, int64_t max_tokens_per_pass, int32_t aq_cap
  * from there instead of encoding it again.  The memo is empty at the start of every call: nothing computed in one call
  * is reused in another, and nothing is stored with the index.  A chunk's embedding does not depend on its batch, so
  * ids, scores and every per-query count are unchanged; encoded_chunks drops and memo_hits counts the requests served.
+ * A memo that fills up holds the first chunks by round, query and pending entry: the counts repeat from call to call.
  * Without it, requests for one chunk are merged only within a round.  max_rows = 0 turns it off and frees its memory. */
 int leann_set_call_memo(leann_ctx *ctx, int64_t max_rows);
 /* GEMM tile choice of the encoder (a tuning and test aid; results do not depend on it, every tile adds the K-slabs

@@ -521,17 +521,48 @@ __global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_
 }
 
 // The call's embedding memo: rows the encoder produced in this round are kept (while there is room) so that a later
-// round of the same call reads them instead of encoding the chunk again.  One wavefront per encoded chunk.
+// round of the same call reads them instead of encoding the chunk again.  The encoder's rows come in no fixed order, so in the
+// round that fills the memo, where not all have room, the first ones by query and pending entry are picked: what is
+// encoded again later does not depend on scheduling.  One block of 1024 threads, once per call.
+__global__ __launch_bounds__(1024) void memo_pick_kernel(SearchState s, int g, int64_t room, int32_t *__restrict__ pick)
+{
+    __shared__ int part[1024];
+    const int tid = threadIdx.x, per = (g + 1023) / 1024;
+    const int beg = min(g, tid * per), end = min(g, beg + per);
+    auto owned = [&](int q, int j) {  // entry j of query q has had its chunk encoded in this round
+        const int e = q * s.pcap + j;
+        const uint32_t c = s.pend[e];
+        return !(s.slot_of && s.slot_of[c] >= 0) && s.memo_slot[c] < 0 && s.own[e] == e;
+    };
+    int count = 0;
+    for (int q = beg; q < end; ++q)
+        for (int j = 0; j < (s.done[q] ? 0 : s.n_pend[q]); ++j) count += owned(q, j);
+    part[tid] = count;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        const int v = tid >= o ? part[tid - o] : 0;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    int64_t at = tid ? part[tid - 1] : 0;
+    for (int q = beg; q < end && at < room; ++q)
+        for (int j = 0; j < (s.done[q] ? 0 : s.n_pend[q]) && at < room; ++j)
+            if (owned(q, j)) pick[at++] = s.src[q * s.pcap + j];
+}
+
+// Row base + i of the memo takes the encoder's row pick[i] (pick NULL: row i).  One wavefront per row.
 __global__ __launch_bounds__(256) void memo_store_kernel(const float *__restrict__ enc_emb, const int64_t *__restrict__ enc_ids,
-                                                         int n_enc, int d, int64_t base, int64_t cap,
+                                                         const int32_t *__restrict__ pick, int rows, int d, int64_t base,
                                                          float *__restrict__ memo_emb, int32_t *__restrict__ memo_slot)
 {
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= n_enc || base + i >= cap) return;
-    const float *srcp = enc_emb + (size_t)i * d;
+    if (i >= rows) return;
+    const int row = pick ? pick[i] : i;
+    const float *srcp = enc_emb + (size_t)row * d;
     float *dst = memo_emb + (size_t)(base + i) * d;
     for (int c = lane; c < d; c += 64) dst[c] = srcp[c];
-    if (lane == 0) memo_slot[enc_ids[i]] = (int32_t)(base + i);
+    if (lane == 0) memo_slot[enc_ids[row]] = (int32_t)(base + i);
 }
 
 // Exact scores of the add buffer (App. B "Batched Add Operation": buffered chunks are scanned, not traversed):
@@ -669,6 +700,8 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     const size_t o_aqt = carve((size_t)G * 4), o_aql = carve((size_t)G * 4), o_pend = carve((size_t)G * pcap * 4);
     const size_t o_np = carve((size_t)G * 4), o_src = carve((size_t)G * pcap * 4), o_own = carve((size_t)G * pcap * 4);
     const size_t o_done = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
+    const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, (1 << 30) - 1);
+    const size_t o_pick = carve(memo_cap > 0 ? (size_t)std::min<int64_t>(memo_cap, (int64_t)G * pcap) * 4 : 0);
     LEANN_TRY(ctx->s_state.reserve(off));
     LEANN_TRY(ctx->s_seen.reserve((size_t)G * words * 4));
     LEANN_TRY(ctx->s_lut.reserve((size_t)G * m_sub * KSUB * sizeof(float)));
@@ -676,7 +709,6 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     LEANN_TRY(ctx->s_owner.reserve((size_t)n * sizeof(unsigned long long)));
     LEANN_HIP(hipMemsetAsync(ctx->s_owner.p, 0xff, (size_t)n * sizeof(unsigned long long), st));
     // per-call embedding memo (leann_set_call_memo): empty at the start of every call
-    const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, (1 << 30) - 1);
     int64_t memo_n = 0;
     if (memo_cap > 0) {
         LEANN_TRY(ctx->s_memo_slot.reserve((size_t)n * sizeof(int32_t)));
@@ -702,6 +734,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     s.memo_slot = memo_cap > 0 ? (int32_t *)ctx->s_memo_slot.p : nullptr;
     s.memo_emb = memo_cap > 0 ? (const float *)ctx->s_memo_emb.p : nullptr;
     s.enc_ids = (int64_t *)(base + o_eids);
+    int32_t *memo_pick = (int32_t *)(base + o_pick);
     s.counters = counters;
     s.lut = (const float *)ctx->s_lut.p;
     s.words = words;
@@ -782,11 +815,13 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                                  (int64_t *)&counters[CTR_TOKENS], h_ctr[CTR_ROUND_TOKENS]);
                 if (rc != LEANN_OK) break;
                 encoded += n_enc;
-                if (memo_cap > 0 && memo_n < memo_cap) {
-                    hipLaunchKernelGGL(memo_store_kernel, dim3((unsigned)((n_enc + 3) / 4)), dim3(256), 0, st,
-                                       (const float *)ctx->s_emb.p, s.enc_ids, (int)n_enc, d, memo_n, memo_cap,
-                                       (float *)ctx->s_memo_emb.p, s.memo_slot);
-                    memo_n = std::min<int64_t>(memo_cap, memo_n + n_enc);
+                if (memo_n < memo_cap) {
+                    const int64_t room = memo_cap - memo_n, rows = std::min<int64_t>(n_enc, room);
+                    if (rows < n_enc) hipLaunchKernelGGL(memo_pick_kernel, dim3(1), dim3(1024), 0, st, s, g, room, memo_pick);
+                    hipLaunchKernelGGL(memo_store_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st,
+                                       (const float *)ctx->s_emb.p, s.enc_ids, rows < n_enc ? memo_pick : nullptr, (int)rows, d,
+                                       memo_n, (float *)ctx->s_memo_emb.p, s.memo_slot);
+                    memo_n += rows;
                 }
             }
             ++rounds;

@@ -157,6 +157,43 @@ def test_call_memo_changes_work_not_results(L, world):
     assert torch.equal(ids0, ids3) and st3["memo_hits"] == 0 and st3["encoded_chunks"] == st0["encoded_chunks"]
 
 
+def test_small_call_memo_keeps_the_first_entries(L, orc, world):
+    """A memo with fewer rows than a call encodes keeps chunks in the order of rounds, queries and pending entries, and what it
+    holds decides what is encoded again: encoded_chunks and memo_hits equal a replay of the oracle's flushes, every time."""
+    w = world
+    queries = w["emb"][np.random.default_rng(5).choice(w["n"], 300, replace=False)].copy()
+    emb = L.leann_embed(w["ctx"], w["t"], w["l"], hidden=w["cfg"]["hidden"]).cpu().numpy()
+    ef, k, alpha, batch = 32, 3, 0.2, 32
+    flushes = []
+    for q in queries:
+        log = []
+
+        def table(ids):
+            log.append(ids)
+            return emb[ids]
+
+        orc.search_callback(q, w["row_ptr"], w["col_idx"], w["n"], w["entry"], w["cb"], w["codes"], table, ef, k, alpha, batch)
+        flushes.append(log)
+    q_dev = to_dev(queries)
+    try:
+        for rows in (1, 57, 400, 900):
+            memo, encoded, hits = set(), 0, 0
+            for r in range(max(len(f) for f in flushes)):
+                asked = [int(c) for f in flushes if r < len(f) for c in f[r]]
+                hits += sum(c in memo for c in asked)
+                fresh = [c for c in dict.fromkeys(asked) if c not in memo]
+                encoded += len(fresh)
+                memo.update(fresh[:rows - len(memo)])
+            say(f"small call memo of {rows} rows: {encoded} chunks, {hits} hits")
+            L.leann_set_call_memo(w["ctx"], rows)
+            for _ in range(4):
+                _, _, st = L.leann_search(w["ctx"], q_dev, w["graph"], w["pq"], w["t"], w["l"], ef, k, alpha, batch)
+                assert st["recomputed_chunks"] == sum(len(c) for f in flushes for c in f)
+                assert (st["encoded_chunks"], st["memo_hits"]) == (encoded, hits)
+    finally:
+        L.leann_set_call_memo(w["ctx"], 0)
+
+
 def test_queue_capacity_overflow_is_reported(L, world):
     """An approximate queue that outgrows its capacity (set far too small through leann_set_limits) ends the search
     with LEANN_ECAPACITY: the kernel's own bounds checks drop the entries that do not fit and raise the flag."""
