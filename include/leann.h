@@ -102,8 +102,8 @@ typedef struct {
     int64_t encoded_chunks;    /* chunks actually sent through the encoder (after sharing within a round) */
     int64_t encoded_tokens;    /* valid tokens of those chunks */
     int64_t flushes;           /* per-query batch flushes */
-    int64_t rounds;            /* traverse -> encode -> insert rounds over the whole query set; flushes that the
-                                * stored-embedding table serves alone are scored on the spot and need no round */
+    int64_t rounds;            /* traverse -> encode -> insert rounds over the whole query set: the flushes of the query
+                                * that has most of them (groups of queries that run one after the other add up) */
     int64_t cache_hits;        /* exact scores served by the stored-embedding table (part of recomputed_chunks) */
     int64_t memo_hits;         /* exact scores served by the call's embedding memo (leann_set_call_memo; part of recomputed_chunks) */
     float encoder_ms, traverse_ms, total_ms; /* device time (HIP events) */

@@ -34,6 +34,7 @@ struct SearchState {
     int32_t *memo_slot;   // [N] row of the call's embedding memo that holds the chunk, -1: none; NULL: memo off
     const float *memo_emb;  // [memo rows][d]
     int32_t *done;        // [G]
+    int32_t *n_flush;     // [G] flushes so far
     int64_t *enc_ids;     // [G * pcap]
     long long *counters;  // see CTR_*
     long long *host_counters;  // the same in host memory, written at the end of every round
@@ -47,8 +48,8 @@ struct SearchState {
     int32_t aq_lds;             // entries of AQ that a running block keeps in LDS (a multiple of 64)
 };
 
-// CTR_PENDING .. CTR_TICKET belong to one round
-enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET, CTR_COUNT };
+// CTR_ROUNDS: most flushes of a query, belongs to one group of queries; CTR_PENDING .. CTR_TICKET belong to one round
+enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_ROUNDS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET, CTR_COUNT };
 enum { ERR_BAD_NEIGHBOUR = 1, ERR_AQ_OVERFLOW = 2, ERR_P_OVERFLOW = 4, ERR_BAD_SLOT = 8 };
 
 __device__ inline bool better(float sa, uint32_t ia, float sb, uint32_t ib) { return sa > sb || (sa == sb && ia < ib); }
@@ -87,6 +88,8 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
     s.aq_tail[q] = 0;
     s.aq_live[q] = 0;
     s.done[q] = 0;
+    s.n_flush[q] = 0;
+    if (q == 0) s.counters[CTR_ROUNDS] = 0;
     s.n_pend[q] = 1;  // the entry point's exact score is the first flush
     s.pend[(size_t)q * s.pcap] = entry;
     s.seen[(size_t)q * s.words + (entry >> 5)] = 1u << (entry & 31);
@@ -460,7 +463,12 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
         s.aq_tail[q] = tail;
         s.aq_live[q] = live;
         s.n_pend[q] = n_pend;
-        if (finished) s.done[q] = 1;
+        const int all_flushes = s.n_flush[q] + flushes;
+        s.n_flush[q] = all_flushes;
+        if (finished) {
+            s.done[q] = 1;
+            atomicMax(&s.counters[CTR_ROUNDS], (long long)all_flushes);
+        }
         atomicAdd((unsigned long long *)&s.counters[CTR_HOPS], (unsigned long long)hops);
         atomicAdd((unsigned long long *)&s.counters[CTR_ADC], (unsigned long long)adc);
         atomicAdd((unsigned long long *)&s.counters[CTR_RECOMP], (unsigned long long)recomp);
@@ -699,7 +707,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     const size_t o_aqk = carve((size_t)G * aqcap * 8), o_aqm = carve((size_t)G * aq_groups * 8);
     const size_t o_aqt = carve((size_t)G * 4), o_aql = carve((size_t)G * 4), o_pend = carve((size_t)G * pcap * 4);
     const size_t o_np = carve((size_t)G * 4), o_src = carve((size_t)G * pcap * 4), o_own = carve((size_t)G * pcap * 4);
-    const size_t o_done = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
+    const size_t o_done = carve((size_t)G * 4), o_nfl = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
     const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, (1 << 30) - 1);
     const size_t o_pick = carve(memo_cap > 0 ? (size_t)std::min<int64_t>(memo_cap, (int64_t)G * pcap) * 4 : 0);
     LEANN_TRY(ctx->s_state.reserve(off));
@@ -730,6 +738,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     s.src = (int32_t *)(base + o_src);
     s.own = (int32_t *)(base + o_own);
     s.done = (int32_t *)(base + o_done);
+    s.n_flush = (int32_t *)(base + o_nfl);
     s.owner = (unsigned long long *)ctx->s_owner.p;
     s.memo_slot = memo_cap > 0 ? (int32_t *)ctx->s_memo_slot.p : nullptr;
     s.memo_emb = memo_cap > 0 ? (const float *)ctx->s_memo_emb.p : nullptr;
@@ -807,6 +816,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                     (void)hipEventDestroy(evs.back());
                     evs.pop_back();
                 }
+                rounds += h_ctr[CTR_ROUNDS];
                 break;
             }
             const int64_t n_enc = h_ctr[CTR_NENC];
@@ -824,7 +834,6 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                     memo_n += rows;
                 }
             }
-            ++rounds;
         }
         if (rc != LEANN_OK) break;
         const int nb = upd ? (int)upd->buffer_n : 0;

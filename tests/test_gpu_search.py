@@ -194,6 +194,28 @@ def test_small_call_memo_keeps_the_first_entries(L, orc, world):
         L.leann_set_call_memo(w["ctx"], 0)
 
 
+def test_rounds_are_the_longest_query_s_flushes(L, orc, world):
+    """A round is one flush of every query that still runs, whoever serves the embeddings: stored for all, some or none of
+    the nodes, the count is the largest number of flushes of one query, and that of the groups of a large call add up."""
+    w = world
+    say("rounds")
+    rows = L.leann_embed(w["ctx"], w["t"], w["l"], hidden=w["cfg"]["hidden"])
+    emb = rows.cpu().numpy()
+    args = (w["graph"], w["pq"], w["t"], w["l"], 32, 3, 0.2, 32)
+    want = max(r["stats"]["flushes"] for r in oracle_runs(orc, w, w["queries"], emb, 32, 3, 0.2, 32))
+    every = np.arange(w["n"], dtype=np.int32)
+    half = np.where(every % 2 == 0, every, -1).astype(np.int32)
+    for slot_of in (every, half, None):
+        cache = None if slot_of is None else (to_dev(slot_of), rows)
+        _, _, st = L.leann_search(w["ctx"], w["q"], *args, cache=cache)
+        assert st["rounds"] == want
+    many = to_dev(np.concatenate([np.tile(w["queries"], (256, 1)), w["queries"][:1]]))  # 4096 + 1
+    cache = (to_dev(every), rows)
+    _, _, st = L.leann_search(w["ctx"], many, *args, cache=cache)
+    _, _, one = L.leann_search(w["ctx"], w["q"][:1].contiguous(), *args, cache=cache)
+    assert st["rounds"] == want + one["rounds"]
+
+
 def test_queue_capacity_overflow_is_reported(L, world):
     """An approximate queue that outgrows its capacity (set far too small through leann_set_limits) ends the search
     with LEANN_ECAPACITY: the kernel's own bounds checks drop the entries that do not fit and raise the flag."""
