@@ -106,7 +106,8 @@ typedef struct {
                                 * that has most of them (groups of queries that run one after the other add up) */
     int64_t cache_hits;        /* exact scores served by the stored-embedding table (part of recomputed_chunks) */
     int64_t memo_hits;         /* exact scores served by the call's embedding memo (leann_set_call_memo; part of recomputed_chunks) */
-    float encoder_ms, traverse_ms, total_ms; /* device time (HIP events) */
+    float encoder_ms, traverse_ms, total_ms; /* device time (HIP events): traverse_ms the hops, exact scores and packing,
+                                              * encoder_ms the rest of total_ms */
 } leann_search_stats;
 
 /* Message of the last error on the calling thread.  ctx is accepted for symmetry with the other calls and may be
@@ -283,7 +284,8 @@ int leann_set_gemm_tiles(leann_ctx *ctx, int32_t large_tile, int32_t small_rows)
  * the library launches on this context is bracketed by HIP events on the context's stream.  ms[i] / launches[i]
  * give summed duration and launch count per kernel family; tokens = valid tokens that went through the encoder,
  * so that the GEMM work is tokens * layers * 2 * (4*hidden^2 + 2*hidden*ffn) flops.  leann_profile_end
- * synchronises the stream.
+ * synchronises the stream.  TRAVERSE holds the exact scores too, which its kernel takes; SCORE_INSERT has no kernel of its own
+ * and stays 0.
  */
 enum {
     LEANN_PROF_GEMM_QKV = 0, LEANN_PROF_GEMM_O, LEANN_PROF_GEMM_FFN1, LEANN_PROF_GEMM_FFN2, LEANN_PROF_ATTENTION,

@@ -811,11 +811,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                                 : "a per-query queue outgrew its capacity (see leann_set_limits)");
                 break;
             }
-            if (h_ctr[CTR_PENDING] == 0) {
-                for (int i = 0; i < 2; ++i) {
-                    (void)hipEventDestroy(evs.back());
-                    evs.pop_back();
-                }
+            if (h_ctr[CTR_PENDING] == 0) {  // the launch that found that has scored and traversed all the same: its events count
                 rounds += h_ctr[CTR_ROUNDS];
                 break;
             }

@@ -216,6 +216,24 @@ def test_rounds_are_the_longest_query_s_flushes(L, orc, world):
     assert st["rounds"] == want + one["rounds"]
 
 
+def test_times_are_booked_where_they_are_spent(L, world):
+    """With every embedding stored a search is hops and exact scores: that is where its time is, in the call's statistics and in
+    the profile, and the encoder has none of it."""
+    w = world
+    say("times of a search over stored embeddings")
+    args = (w["ctx"], w["q"], w["graph"], w["pq"], w["t"], w["l"], 1024, 3, 0.5, 32)
+    L.leann_search(*args, cache=w["full_cache"])
+    _, _, st = L.leann_search(*args, cache=w["full_cache"])
+    assert st["encoded_chunks"] == 0
+    assert st["traverse_ms"] > 0.5 * st["total_ms"] > 0
+    assert abs(st["traverse_ms"] + st["encoder_ms"] - st["total_ms"]) <= 1e-5 * st["total_ms"]
+    L.leann_profile_begin(w["ctx"])
+    L.leann_search(*args, cache=w["full_cache"])
+    prof = L.leann_profile_end(w["ctx"])
+    assert prof["launches"]["traverse"] == 1 and prof["ms"]["traverse"] > 0.5 * st["traverse_ms"]
+    assert prof["launches"]["score_insert"] == 0 and prof["tokens"] == 0
+
+
 def test_queue_capacity_overflow_is_reported(L, world):
     """An approximate queue that outgrows its capacity (set far too small through leann_set_limits) ends the search
     with LEANN_ECAPACITY: the kernel's own bounds checks drop the entries that do not fit and raise the flag."""
