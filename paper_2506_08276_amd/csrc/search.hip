@@ -282,6 +282,13 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
 #pragma unroll
                                 for (int m = 0; m < 16; ++m) sc += tab[(16 * i + m) * KSUB + ((c[i][m >> 2] >> (8 * (m & 3))) & 255u)];
                             }
+                    } else if ((m_sub & 15) == 0) {
+                        const uint8_t *row = codes + (size_t)v * m_sub;
+                        for (int m0 = 0; m0 < m_sub; m0 += 16) {
+                            const u32x4 w = *reinterpret_cast<const u32x4 *>(row + m0);
+#pragma unroll
+                            for (int m = 0; m < 16; ++m) sc += tab[(m0 + m) * KSUB + ((w[m >> 2] >> (8 * (m & 3))) & 255u)];
+                        }
                     } else {
                         const uint8_t *row = codes + (size_t)v * m_sub;
                         for (int m = 0; m < m_sub; ++m) sc += tab[m * KSUB + row[m]];

@@ -253,10 +253,10 @@ def test_queue_capacity_overflow_is_reported(L, world):
     assert torch.equal(ids0, ids1) and torch.equal(sc0, sc1)
 
 
-@pytest.mark.parametrize("m_sub,ef,alpha,batch", [(8, 300, 0.5, 20), (64, 1000, 0.1, 64), (16, 40, 1.0, 200)])
+@pytest.mark.parametrize("m_sub,ef,alpha,batch", [(8, 300, 0.5, 20), (64, 1000, 0.1, 64), (16, 40, 1.0, 200), (128, 60, 0.3, 50)])
 def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
     """An approximate queue of thousands of entries, rows longer than a wavefront, empty rows, repeated neighbours, and
-    lookup tables with and without 16-byte code pieces.  Everything is integer-valued, so every score is exact and
+    lookup tables with and without 16-byte code pieces, fetched ahead or not.  Everything is integer-valued, so every score is exact and
     there are many ties: ids, scores and counts equal the oracle's.  Then the smallest queue capacity that the search gets
     by with: at it (holes have to be squeezed out) and above it the result is the same, one below it overflows; and a
     capacity that makes the queue's runs longer than a wavefront."""
