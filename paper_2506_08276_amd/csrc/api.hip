@@ -43,6 +43,7 @@ void DevBuf::release()
 int clear_host_flags(leann_ctx *ctx)
 {
     if (!ctx->host_flags) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flags, FLAG_COUNT * sizeof(int), hipHostMallocDefault));
+    if (!ctx->pass_event) LEANN_HIP(hipEventCreateWithFlags(&ctx->pass_event, hipEventDisableTiming));
     volatile int *f = ctx->host_flags;
     for (int i = 0; i < FLAG_COUNT; ++i) f[i] = 0;
     return LEANN_OK;
@@ -234,6 +235,7 @@ void leann_destroy(leann_ctx *ctx)
     ctx->prof_tokens.release();
     if (ctx->host_counters) (void)hipHostFree(ctx->host_counters);
     if (ctx->host_flags) (void)hipHostFree(ctx->host_flags);
+    if (ctx->pass_event) (void)hipEventDestroy(ctx->pass_event);
     for (auto &sp : ctx->prof_spans) {
         (void)hipEventDestroy(sp.a);
         (void)hipEventDestroy(sp.b);

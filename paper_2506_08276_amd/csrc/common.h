@@ -68,6 +68,7 @@ struct leann_ctx {
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
     int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags
+    hipEvent_t pass_event = nullptr;     // recorded behind the kernel that counts an encoder pass's tokens
     int64_t memo_rows = 0;  // rows of the per-call embedding memo (leann_set_call_memo), 0 = off
     // optional per-kernel timing (leann_profile_begin / leann_profile_end)
     bool prof_on = false;
@@ -82,8 +83,8 @@ struct leann_ctx {
 
 // Error flags of a call, in pinned host memory: kernels store 1 to what they find wrong, the host reads them after it has
 // waited for the stream.  Nothing has to be cleared or copied on the device.  Calls on a context wait for their kernels, so
-// nothing of an earlier call is still to be written.
-enum { FLAG_CHUNK_ID = 0, FLAG_LENGTH, FLAG_TOKEN, FLAG_CANDIDATE, FLAG_COUNT };
+// nothing of an earlier call is still to be written.  PASS_TOKENS: the valid tokens of the encoder pass.
+enum { FLAG_CHUNK_ID = 0, FLAG_LENGTH, FLAG_TOKEN, FLAG_CANDIDATE, PASS_TOKENS, FLAG_COUNT };
 int clear_host_flags(leann_ctx *ctx);
 
 // Brackets one kernel launch with HIP events on the context's stream when profiling is on.

@@ -231,3 +231,33 @@ def test_pass_without_a_valid_token(L, hidden, heads, ffn):
             assert torch.equal(L.leann_embed(ctx, t, l, hidden=hidden), want)
     finally:
         L.leann_destroy(ctx)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 512), (768, 12, 3072)])
+def test_tiles_for_any_fill_give_the_same_bits(L, hidden, heads, ffn):
+    """How full the chunks are decides the tiles of passes of more than 4096 padded rows: full, a quarter full, nearly empty and
+    mixed chunks, in one pass and in several, give the bits that the 128 x 128 tile alone gives; a bad length in such a
+    pass is still an error."""
+    import torch
+    cfg = dict(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=64, ln_eps=1e-12)
+    n, seq = 150, 64
+    tokens, mixed = li.uniform_chunks(n, seq, 1, cfg["vocab"], 1, seq, 4)
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 6, bf16_exact=True)).to(torch.bfloat16))
+    try:
+        t = to_dev(tokens)
+        for name, lengths in (("full", np.full(n, seq)), ("quarter", np.full(n, seq // 4)), ("one token", np.ones(n)), ("mixed", mixed)):
+            say(f"fill {name}, hidden {hidden}")
+            l = to_dev(lengths.astype(np.int32))
+            L.leann_set_gemm_tiles(ctx, 128, 0)
+            want = L.leann_embed(ctx, t, l, hidden=hidden)
+            L.leann_set_gemm_tiles(ctx, 256, 2048)
+            assert torch.isfinite(want).all()
+            for per_pass in (262144, 75 * seq):
+                L.leann_set_limits(ctx, max_tokens_per_pass=per_pass)
+                assert torch.equal(L.leann_embed(ctx, t, l, hidden=hidden), want)
+        bad = mixed.copy()
+        bad[n - 1] = seq + 1
+        with pytest.raises(L.LeannError, match="length outside"):
+            L.leann_embed(ctx, t, to_dev(bad), hidden=hidden)
+    finally:
+        L.leann_destroy(ctx)
