@@ -451,8 +451,8 @@ int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d
             epoch = 1;
             if (e != hipSuccess) break;
         }
-        // wavefronts per node: as many as the chip holds (16 per CU with 128 registers each), so that small batches, which
-        // are bound by one node's chain of hops, spread each hop widest
+        // wavefronts per node: 16 per CU in all, so that small batches, which are bound by one node's chain of hops, spread each
+        // hop widest (the registers, 60 at d = 768, would let 32 stay on a CU)
         const int threads = 64 * (b <= ctx->num_cus ? 16 : b <= 2 * ctx->num_cus ? 8 : 4);
         hipLaunchKernelGGL(kernels.search_select, dim3((unsigned)b), dim3(threads), words * sizeof(uint32_t), st, s, ins,
                            epoch, words);

@@ -448,7 +448,9 @@ __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x,
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[j][i] = 0.f;
-    for (int t = wave; t < L; t += 4 * POOL_AHEAD) {  // the rows' loads are issued together, their sums keep the order
+    // POOL_AHEAD rows are read, then added in order.  The reads are guarded one by one and the compiled code waits for each before
+    // the next: what is in flight is the wavefronts' loads side by side, not a wavefront's rows.
+    for (int t = wave; t < L; t += 4 * POOL_AHEAD) {
         bf16x8 r[POOL_AHEAD][2];
 #pragma unroll
         for (int k = 0; k < POOL_AHEAD; ++k)

@@ -105,12 +105,13 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
 // Latency bounds it: a hop is a chain of dependent reads, so the chain is kept short.
 //  - EQ is sorted (keys of score and id, LDS).  It does not change between flushes, so the next hops are known: their CSR
 //    rows are fetched two hops ahead, the PQ codes of all neighbours (seen or not) one hop ahead, and the visited marks one
-//    hop ahead where it is certain that the next hop will be run.
+//    hop ahead where it is certain that the next hop will be run.  So a hop has one wait for all of these instead of
+//    a chain of three; it does have that one, as the marks' result is made a flag where they are set.
 //  - AQ is unsorted in runs of aq_run entries, the best entry of every run on the side: taking out the best of some
 //    thousand entries reads the runs' best and one run.  A taken entry leaves a hole; holes are squeezed out when the
 //    end reaches the capacity, so AQ overflows when more than aqcap entries are alive, not earlier.
-//  - a flush's exact scores are taken side by side (four wavefronts, four rows in flight each), and merged into EQ by
-//    counting.  "Insert if there is room or better than the worst" entry by entry leaves the ef best of both, which is
+//  - a flush's exact scores are taken side by side (four wavefronts, each with one or two rows in flight), and merged into EQ
+//    by counting.  "Insert if there is room or better than the worst" entry by entry leaves the ef best of both, which is
 //    what the merge keeps.
 // Measured with every embedding stored (500 queries, ef 200, N = 12288, d = 768): a search of 239 hops, 37 flushes and 248
 // exact scores per query takes 0.9 ms; one wavefront per query with scans over both queues and a host round per flush

@@ -111,8 +111,8 @@ struct RowDots {
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
         return (const float *)((uint64_t)hi << 32 | lo);
     }
-    // out[k] = <anchor, row_at(k)> for k < c <= 4.  The rows' loads are all issued before the first sum: a row comes
-    // from beyond L2 as a rule, and four in flight per wavefront cost little more time than one.
+    // out[k] = <anchor, row_at(k)> for k < c <= 4.  A row's NV loads are in flight together.  The rows are not, or two by
+    // two at most: both loops below test k < c, and the compiled code joins each row's loads with its sum.
     template <class RowAt>
     __device__ inline void four(RowAt row_at, int c, float (&out)[4]) const
     {
