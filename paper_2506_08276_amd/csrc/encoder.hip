@@ -22,7 +22,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ 
                                                     int64_t first_id, int n, int64_t n_store, int seq,
                                                     int32_t *__restrict__ cu, int64_t *__restrict__ chunk_of,
                                                     int *__restrict__ err, int64_t *__restrict__ tok_count,
-                                                    int64_t *__restrict__ tok_count2)
+                                                    int64_t *__restrict__ tok_count2, bool report)
 {
     __shared__ int part[1024];
     const int tid = threadIdx.x;
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ 
     }
     if (tid == 1023) {
         cu[n] = part[1023];
-        err[PASS_TOKENS] = part[1023];
+        if (report) err[PASS_TOKENS] = part[1023];
         if (tok_count) *tok_count += part[1023];
         if (tok_count2) *tok_count2 += part[1023];
     }
@@ -709,7 +709,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
             hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, ctx->stream, chunks->lengths,
                                ids_dev ? ids_dev + s : nullptr, first_id + s, m, chunks->n, seq, cu, chunk_of, ctx->host_flags,
-                               tok_count_dev, ctx->prof_on ? (int64_t *)ctx->prof_tokens.p : nullptr);
+                               tok_count_dev, ctx->prof_on ? (int64_t *)ctx->prof_tokens.p : nullptr, ask);
         }
         if (ask) LEANN_HIP(hipEventRecord(ctx->pass_event, ctx->stream));
         {
