@@ -60,7 +60,7 @@ __host__ __device__ constexpr int assign_smem(int ks, int dsub)
 
 template <int KS>  // 16-element steps of the (zero-padded) sub-vector
 __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__restrict__ x, int64_t n, int d, int m_sub,
-                                                                const float *__restrict__ codebook, int64_t rows_per_block,
+                                                                const float *__restrict__ codebook, int64_t rows_per_block, int xcd_bits,
                                                                 uint8_t *__restrict__ out, int64_t row_pitch, int64_t m_pitch)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -72,10 +72,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
     float *cbf = reinterpret_cast<float *>(cmax + 4);  // [256][P]
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // blocks go round-robin to the 8 XCDs: all subspaces of a run of rows on one XCD, whose L2 then holds the 128-byte
-    // lines that neighbouring subspaces share
-    const int m = (blockIdx.x >> 3) % m_sub;
-    const int64_t chunk = (int64_t)((blockIdx.x >> 3) / m_sub) * 8 + (blockIdx.x & 7);
+    // blocks go round-robin to the 8 XCDs: with xcd_bits = 3 all subspaces of a run of rows are on one XCD, whose L2 then holds
+    // the 128-byte lines that neighbouring subspaces share
+    const int m = (blockIdx.x >> xcd_bits) % m_sub;
+    const int64_t chunk = ((int64_t)((blockIdx.x >> xcd_bits) / m_sub) << xcd_bits) + (blockIdx.x & ((1 << xcd_bits) - 1));
     const int64_t beg = chunk * rows_per_block, end = beg + rows_per_block < n ? beg + rows_per_block : n;
     if (beg >= end) return;
 
@@ -563,19 +563,22 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
     if (bad) *err = 1;
 }
 
-// A few blocks per CU, each with a multiple of what its wavefronts take at once.  The runs of rows go to the XCDs in turn: an
-// even share where their number is a multiple of 8 (32 at 32 subspaces and 65536 rows; 28 at 100000).  Few rows or many subspaces
-// leave XCDs idle (10 runs at 96 subspaces, 5 at 192, 2 at 1000 rows).
+// A few blocks per CU, each with a multiple of what its wavefronts take at once.  The number of runs of rows is a multiple of 8
+// where there are rows enough, so that the XCDs get even shares; with fewer than 8 runs the subspaces are spread over the XCDs
+// instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch, 1000 rows of 192 subspaces of one 49; where all
+// subspaces of a run were on one XCD however few the runs (two in both cases), they took 5358 and 129.
 void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, const float *codebook, uint8_t *out,
                    int64_t row_pitch, int64_t m_pitch)
 {
     const int dsub = d / m_sub;
-    const int64_t want = std::max<int64_t>(1, 4 * ctx->num_cus / m_sub);
+    const int64_t want = std::max<int64_t>(8, (4 * ctx->num_cus / m_sub + 7) / 8 * 8);
     const int64_t rows = ((n + want - 1) / want + ASSIGN_THREADS - 1) / ASSIGN_THREADS * ASSIGN_THREADS;
-    const int64_t chunks = ((n + rows - 1) / rows + 7) / 8 * 8;
+    const int64_t runs = (n + rows - 1) / rows;
+    const int xcd_bits = runs >= 8 ? 3 : 0;
+    const int64_t blocks = ((((runs - 1) >> xcd_bits) + 1) << xcd_bits) * m_sub;
     auto *kernel = dsub <= 16 ? assign_kernel<1> : assign_kernel<2>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(chunks * m_sub)), dim3(ASSIGN_THREADS), assign_smem(dsub <= 16 ? 1 : 2, dsub),
-                       ctx->stream, x, n, d, m_sub, codebook, rows, out, row_pitch, m_pitch);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(ASSIGN_THREADS), assign_smem(dsub <= 16 ? 1 : 2, dsub),
+                       ctx->stream, x, n, d, m_sub, codebook, rows, xcd_bits, out, row_pitch, m_pitch);
 }
 
 // Launch shape of adc_kernel: enough blocks to fill the chip several times over, each with as large a share of its

@@ -255,6 +255,16 @@ def test_pq_codes_of_near_ties(L, ctx, dsub, offset):
     np.testing.assert_array_equal(codes, nearest_by_fp32_sums(x, cb))
 
 
+@pytest.mark.parametrize("n,dsub,m_sub", [(5000, 2, 100), (1500, 3, 40), (4097, 4, 33), (700, 1, 200), (9000, 1, 7), (65, 2, 300)])
+def test_pq_codes_of_many_subspaces(L, ctx, n, dsub, m_sub):
+    """Few and many runs of rows, numbers of them that are no multiple of the XCDs, and sub-vectors of one element: every code is
+    that of the fp32 sums."""
+    say(f"pq codes n={n} dsub={dsub} m_sub={m_sub}")
+    x = np.random.default_rng(n).standard_normal((n, dsub * m_sub)).astype(np.float32)
+    cb, codes = codes_of_first_centroids(L, ctx, x, m_sub)
+    np.testing.assert_array_equal(codes, nearest_by_fp32_sums(x, cb))
+
+
 def test_build_pq_rejects_bad_shapes(L, ctx):
     say("build_pq bad shapes")
     x = to_dev(np.zeros((10, 130), np.float32))
