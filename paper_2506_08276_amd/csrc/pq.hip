@@ -46,10 +46,11 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    operation and two medians per value.
 //  - With X = |x'|, C = max |c'|, U = (X + C)^2 and bf16's rounding of 2^-8, a centroid's value is off by, in units of
 //    2^-16 U: the split 1 (each low part rounded by 2^-17 of its operand and low.low left out: 4 * 2^-17 of |2x'||c'| <= U / 2),
-//    the index bits 1 (2^7 units in the last place), the additions of the six MFMAs at most 0.75 (each of the 96 counted
-//    with 2^-23 U, a whole unit), |c'|^2 0.13, s(c) itself 0.13, the centring 0.01: 3.02 in all.  So two centroids are told
-//    apart by a gap of 6.04 * 2^-16 U; 8 are asked for.  The other rows (few on embeddings; all of them where anything could
-//    overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
+//    the additions of the six MFMAs at most 0.75 (each of the 96 counted with 2^-23 U, a whole unit), |c'|^2 0.13, s(c) itself
+//    0.13, the centring 0.01: 4.04 for two centroids.  The index bits (2^7 units in the last place) move a value by 2^-16 of
+//    itself; p - 2^-16 |p| grows with p, so the second minimum's share covers all other centroids.  A gap of more than
+//    2^-16 (5.5 U + |minimum| + |second|) therefore leaves no doubt.  The other rows (few on embeddings; all of them where anything
+//    could overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
 // So the result is s(c)'s for every input.  189 us on average at 65536 to 100000 rows, d = 768, 32 subspaces.
 constexpr int ASSIGN_THREADS = 512;
 
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
             const float S = X[g] + C;
             // the constant covers flushed denormals; from S = 1e19 on an intermediate sum can overflow, and an infinity with index
             // bits in it is a NaN to the medians
-            const bool sure = S < 1e19f && second - first > fmaf(S / 8192.f, S, 1e-33f);
+            const bool sure = S < 1e19f && second - first > fmaf(5.5f / 65536.f * S, S, fmaf(fabsf(first) + fabsf(second), 1.f / 65536.f, 1e-33f));
             const int64_t row = r0 + g * 32 + l32;
             unsigned long long doubt = __ballot(!sure && half == 0 && row < end);
             while (doubt) {
