@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
     if (bad) *err = 1;
 }
 
-// A few blocks per CU, each with a multiple of what its wavefronts take at once.  The number of runs of rows is a multiple of 8
+// A few blocks per CU, each with a multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
 // where there are rows enough, so that the XCDs get even shares; with fewer than 8 runs the subspaces are spread over the XCDs
 // instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch, 1000 rows of 192 subspaces of one 49; where all
 // subspaces of a run were on one XCD however few the runs (two in both cases), they took 5358 and 129.
@@ -572,7 +572,7 @@ void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, 
                    int64_t row_pitch, int64_t m_pitch)
 {
     const int dsub = d / m_sub;
-    const int64_t want = std::max<int64_t>(8, (4 * ctx->num_cus / m_sub + 7) / 8 * 8);
+    const int64_t want = std::max<int64_t>(8, 4 * ctx->num_cus / m_sub / 8 * 8);
     const int64_t rows = ((n + want - 1) / want + ASSIGN_THREADS - 1) / ASSIGN_THREADS * ASSIGN_THREADS;
     const int64_t runs = (n + rows - 1) / rows;
     const int xcd_bits = runs >= 8 ? 3 : 0;
