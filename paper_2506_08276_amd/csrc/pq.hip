@@ -51,7 +51,7 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    itself; p - 2^-16 |p| grows with p, so the second minimum's share covers all other centroids.  A gap of more than
 //    2^-16 (5.5 U + |minimum| + |second|) therefore leaves no doubt.  The other rows (few on embeddings; all of them where anything
 //    could overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
-// So the result is s(c)'s for every input.  189 us on average at 65536 to 100000 rows, d = 768, 32 subspaces.
+// So the result is s(c)'s for every input.  186 us on average at 65536 to 100000 rows, d = 768, 32 subspaces.
 constexpr int ASSIGN_THREADS = 512;
 
 __host__ __device__ constexpr int assign_smem(int ks, int dsub)
@@ -565,9 +565,10 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
 }
 
 // A few blocks per CU, each with a multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
-// where there are rows enough, so that the XCDs get even shares; with fewer than 8 runs the subspaces are spread over the XCDs
-// instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch, 1000 rows of 192 subspaces of one 49; where all
-// subspaces of a run were on one XCD however few the runs (two in both cases), they took 5358 and 129.
+// where there are rows enough, so that the XCDs get even shares (rounded down: up, 24 subspaces were 6 % slower); with fewer than
+// 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch,
+// 1000 rows of 192 subspaces of one 49; where all subspaces of a run were on one XCD however few the runs (two in both cases),
+// they took 5358 and 129.
 void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, const float *codebook, uint8_t *out,
                    int64_t row_pitch, int64_t m_pitch)
 {
