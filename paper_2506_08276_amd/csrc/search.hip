@@ -8,6 +8,7 @@
 // against their own query and try-inserts them into EQ.  Per query this is exactly the sequential algorithm; batching
 // across queries changes no value because the encoder's output for a chunk does not depend on the rest of the batch.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -16,13 +17,15 @@
 namespace {
 
 constexpr int KSUB = 256;
+constexpr int EF_MAX = 1024;  // leann_search refuses longer queues
 
 struct SearchState {
     uint64_t *eq_key;     // [G][ef] exact queue, best first (queue_key)
+    uint64_t *eq_row;     // [G][ef] CSR row of the entry, see pack_row
     uint8_t *eq_vis;      // [G][ef]
     int32_t *eq_n;        // [G]
-    uint64_t *aq_key;     // [G][aqcap] approximate queue, 0 where an entry has been taken out
-    uint64_t *aq_max;     // [G][aq_groups] best entry of each run of aq_run entries
+    uint64_t *aq_key;     // [G][64][aq_rows] approximate queue in 64 columns, 0 where an entry has been taken out
+    uint64_t *aq_max;     // [G][64] best entry of each column
     int32_t *aq_tail;     // [G] end of the used part
     int32_t *aq_live;     // [G] entries in it
     uint32_t *seen;       // [G][words]
@@ -44,8 +47,8 @@ struct SearchState {
     int64_t cache_rows;
     int64_t words;
     int32_t ef, aqcap, pcap;
-    int32_t aq_run, aq_groups;  // run length (a multiple of 64), number of runs
-    int32_t aq_lds;             // entries of AQ that a running block keeps in LDS (a multiple of 64)
+    int32_t aq_rows;   // entries per column of AQ
+    int32_t aq_near;   // of these, the first ones that a running block keeps in LDS
 };
 
 // CTR_ROUNDS: most flushes of a query, belongs to one group of queries; CTR_PENDING .. CTR_TICKET belong to one round
@@ -72,12 +75,16 @@ __device__ inline void wave_best(float &s, uint32_t &id, int &pos)
 
 __global__ void maxdeg_kernel(const uint64_t *__restrict__ row_ptr, int64_t n, long long *__restrict__ counters)
 {
+    __shared__ long long part[4];
     long long best = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         best = max(best, (long long)(row_ptr[i + 1] - row_ptr[i]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) best = max(best, (long long)__shfl_xor(best, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(&counters[CTR_MAXDEG], best);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = best;
+    __syncthreads();
+    // one atomic per block: a thousand of them on one word, one per wavefront, were most of the kernel's 13.5 us
+    if (threadIdx.x == 0) atomicMax(&counters[CTR_MAXDEG], max(max(part[0], part[1]), max(part[2], part[3])));
 }
 
 __global__ void init_kernel(SearchState s, int g, uint32_t entry)
@@ -102,26 +109,51 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
 // the spot and the hops go on; otherwise the block claims its chunks (see claim below) and leaves.  So a search over
 // stored embeddings is one launch, and with recomputation a round is this kernel, collect_kernel and the encoder.
 //
-// Latency bounds it: a hop is a chain of dependent reads, so the chain is kept short.
-//  - EQ is sorted (keys of score and id, LDS).  It does not change between flushes, so the next hops are known: their CSR
-//    rows are fetched two hops ahead, the PQ codes of all neighbours (seen or not) one hop ahead, and the visited marks one
-//    hop ahead where it is certain that the next hop will be run.  So a hop has one wait for all of these instead of
-//    a chain of three; it does have that one, as the marks' result is made a flag where they are set.
-//  - AQ is unsorted in runs of aq_run entries, the best entry of every run on the side: taking out the best of some
-//    thousand entries reads the runs' best and one run.  A taken entry leaves a hole; holes are squeezed out when the
+// Latency bounds it: a hop is a chain of dependent reads, so everything that does not depend on the hop before is taken out
+// of the chain.
+//  - EQ is sorted (keys of score and id, LDS).  It does not change between flushes, so the next hops are known: a group of
+//    up to GROUP_HOPS of them is prepared by the whole block.  Their neighbours' ids come in together, three wavefronts
+//    take the approximate scores of all of them (seen or not) while the first one sets the visited marks, hop after hop, without
+//    waiting in between: the atomics of a wavefront on one word are performed in order, so what they return is what each
+//    hop would have found.  Marks of hops that turn out not to be run (a flush is due first) are taken back.  What is left of
+//    a hop, for one wavefront, is the new neighbours into AQ and the best ones of AQ out of it, in some hundred instructions.
+//  - AQ is unsorted.  Entry p is in column p % 64, which belongs to lane p % 64: an entry that comes in is compared with its
+//    lane's best, nothing else.  Taking out the best is one maximum over the lanes and one over the column it was in, whose
+//    entries (adjacent in memory, one per lane) are read meanwhile.  A taken entry leaves a hole; holes are squeezed out when the
 //    end reaches the capacity, so AQ overflows when more than aqcap entries are alive, not earlier.
-//  - a flush's exact scores are taken side by side (four wavefronts, each with one or two rows in flight), and merged into EQ
+//  - a flush's exact scores are taken side by side (four wavefronts, each with up to four rows in flight), and merged into EQ
 //    by counting.  "Insert if there is room or better than the worst" entry by entry leaves the ef best of both, which is
 //    what the merge keeps.
-// Measured with every embedding stored (500 queries, ef 200, N = 12288, d = 768): a search of 239 hops, 37 flushes and 248
-// exact scores per query takes 0.9 ms; one wavefront per query with scans over both queues and a host round per flush
-// took 13.8 ms (78 rounds of 77 us hops, 44 us scores and 24 us packing).
+// Measured with every embedding stored (500 queries, ef 200, N = 12288, d = 768; 238 hops and 37 flushes per query on average, 78 in
+// the longest): 466 us; 720 us where a hop waited for its own marks and neighbours (2750 of 4300 clocks) and AQ was kept in
+// runs.  Now a hop takes 1290 clocks, a flush and its group 10300.
 constexpr int ADV_THREADS = 256;
-constexpr int AQ_LDS_MAX = 2048, AQ_GROUPS_MAX = 512;
+constexpr int GROUP_HOPS = 16;                 // hops that are prepared together
+constexpr int GROUP_CAND = ADV_THREADS - 64;   // their neighbours (of a row, the first 64) at most
+constexpr int PEND_LDS = 128;                  // pending entries that a running block keeps in LDS
+constexpr int AQ_NEAR_MIN = 32, AQ_NEAR_MAX = 64;  // rows of AQ's columns in LDS
 
-__device__ inline uint64_t readlane64(uint64_t v, int l)
+// LDS pointers that say so: of "LDS or memory" by index the compiler otherwise makes one flat access, which waits for both.
+template <class T>
+using lds_ptr = __attribute__((address_space(3))) T *;
+template <class T>
+__device__ inline lds_ptr<T> in_lds(T *p)
 {
-    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+    return (lds_ptr<T>)p;
+}
+
+// A CSR row as one word: where it begins (40 bits) and its length; a length that does not fit is ROW_LONG and read again.
+constexpr uint32_t ROW_LONG = (1u << 24) - 1;
+__device__ inline uint64_t pack_row(uint64_t beg, uint64_t end) { return beg << 24 | min(end - beg, (uint64_t)ROW_LONG); }
+
+// Sum over lanes 0 .. lane, for the first 16 lanes of a wavefront.
+__device__ inline int sum_to_lane16(int v)
+{
+    v += (int)dpp_mov<0x111>((uint32_t)v);  // row_shr 1, 2, 4, 8: zeros come in at the row's start
+    v += (int)dpp_mov<0x112>((uint32_t)v);
+    v += (int)dpp_mov<0x114>((uint32_t)v);
+    v += (int)dpp_mov<0x118>((uint32_t)v);
+    return v;
 }
 
 template <int NV>  // 4-byte pieces of an embedding row per lane
@@ -132,71 +164,262 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
                                                               const float *__restrict__ enc_emb, bool have_results, uint32_t round)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int pitch = s.aq_near | 1;  // odd: the lanes' columns begin in different banks
     float *tab = reinterpret_cast<float *>(smem);                        // [m_sub][256]
     uint64_t *eqk = reinterpret_cast<uint64_t *>(tab + m_sub * KSUB);    // [ef]
-    uint64_t *aqm = eqk + s.ef;                                          // [aq_groups]
-    uint64_t *aql = aqm + s.aq_groups;                                   // [aq_lds]
-    uint8_t *eqv = reinterpret_cast<uint8_t *>(aql + s.aq_lds);          // [ef]
-    __shared__ uint64_t new_key[64];
+    uint64_t *eqr = eqk + s.ef;                                          // [ef]
+    uint64_t *aql = eqr + s.ef;                                          // [64][pitch]
+    uint8_t *eqv = reinterpret_cast<uint8_t *>(aql + 64 * pitch);        // [ef], read in steps of 256
+    __shared__ __attribute__((aligned(16))) uint64_t new_key[64];
     __shared__ const float *new_row[64];
     __shared__ uint32_t new_id[64];
-    __shared__ int list[64];
-    __shared__ int sh_pend, sh_tail;
+    __shared__ uint64_t new_csr[64];
+    __shared__ int better_old[ADV_THREADS / 64][64];  // entries of EQ that are better than a newcomer, per wavefront's share of them
+    __shared__ int list[GROUP_HOPS];             // the group's hops: positions in EQ
+    __shared__ uint64_t hop_beg[GROUP_HOPS];     // where their CSR rows begin
+    __shared__ int hop_off[GROUP_HOPS + 1];      // where their candidates begin
+    __shared__ uint64_t hop_fresh[GROUP_HOPS];   // the candidates that are met for the first time
+    __shared__ int hop_base[GROUP_HOPS];         // where those begin in fresh_key
+    __shared__ uint32_t cand_id[GROUP_CAND];
+    __shared__ uint64_t fresh_key[GROUP_CAND];
+    __shared__ uint32_t pend_l[PEND_LDS];
+    __shared__ int sh_pend, sh_tail, sh_hops, sh_missing, sh_bad;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (q == 0 && tid == 0)  // the round's counters: collect_kernel, which runs next, adds to them
         for (int i = CTR_PENDING; i <= CTR_TICKET; ++i) s.counters[i] = 0;
     if (s.done[q]) return;
     uint32_t *pend = s.pend + (size_t)q * s.pcap;
-    uint64_t *aqg = s.aq_key + (size_t)q * s.aqcap;
+    uint64_t *aqg = s.aq_key + (size_t)q * 64 * s.aq_rows;
     uint32_t *seen = s.seen + (size_t)q * s.words;
     int n_pend = s.n_pend[q], n_eq = s.eq_n[q], tail = s.aq_tail[q], live = s.aq_live[q];
     int hops = 0, adc = 0, err = 0, recomp = 0, flushes = 0, hits = 0;
     for (int i = tid; i < n_eq; i += ADV_THREADS) {
         eqk[i] = s.eq_key[(size_t)q * s.ef + i];
+        eqr[i] = s.eq_row[(size_t)q * s.ef + i];
         eqv[i] = s.eq_vis[(size_t)q * s.ef + i];
     }
-    for (int i = tid; i < s.aq_groups; i += ADV_THREADS) aqm[i] = i * s.aq_run < tail ? s.aq_max[(size_t)q * s.aq_groups + i] : 0;
-    for (int i = tid; i < min(tail, s.aq_lds); i += ADV_THREADS) aql[i] = aqg[i];
+    const lds_ptr<uint64_t> aq_near = in_lds(aql);
+    auto copy_near = [&](int end, bool in) {  // the rows that are in use, between memory and LDS
+        const int rows = min((end + 63) >> 6, s.aq_near);
+        for (int i = tid; i < 64 * rows; i += ADV_THREADS) {
+            const int c = i / rows, r = i - c * rows;
+            if (in) aq_near[c * pitch + r] = aqg[(size_t)c * s.aq_rows + r];
+            else aqg[(size_t)c * s.aq_rows + r] = aq_near[c * pitch + r];
+        }
+    };
+    copy_near(tail, true);
     {
         const float4 *src = reinterpret_cast<const float4 *>(s.lut + (size_t)q * m_sub * KSUB);
         for (int i = tid; i < m_sub * KSUB / 4; i += ADV_THREADS) reinterpret_cast<float4 *>(tab)[i] = src[i];
     }
+    for (int i = tid; i < min(n_pend, PEND_LDS); i += ADV_THREADS) pend_l[i] = pend[i];
     RowDots<NV> dots;
     dots.load(queries + (size_t)q * d, d, lane);
-    if (tid == 0) sh_tail = tail;
+    if (tid == 0) {
+        sh_tail = tail;
+        sh_missing = sh_bad = 0;
+    }
+    const lds_ptr<uint32_t> pend_near = in_lds(pend_l);
+    auto pending = [&](int j) -> uint32_t {
+        if (j < PEND_LDS) return pend_near[j];
+        return pend[j];
+    };
+    auto adc_score = [&](uint32_t v) -> float {  // table entries summed in subspace order
+        const uint8_t *row = codes + (size_t)v * m_sub;
+        float sc = 0.f;
+        if ((m_sub & 15) == 0) {
+            u32x4 w = *reinterpret_cast<const u32x4 *>(row);
+            for (int m0 = 0; m0 < m_sub; m0 += 16) {
+                const u32x4 next = *reinterpret_cast<const u32x4 *>(row + min(m0 + 16, m_sub - 16));
+#pragma unroll
+                for (int m = 0; m < 16; ++m) sc += tab[(m0 + m) * KSUB + ((w[m >> 2] >> (8 * (m & 3))) & 255u)];
+                w = next;
+            }
+        } else {
+            for (int m = 0; m < m_sub; ++m) sc += tab[m * KSUB + row[m]];
+        }
+        return sc;
+    };
+    // The cnt newcomers in new_key go into EQ.  An entry moves down by the number of better newcomers; a newcomer (lane j of
+    // wavefront 0: newcomer j) goes behind everything better, old or new.
+    auto merge = [&](int cnt, auto shares) {
+        constexpr int SHARES = decltype(shares)::value;  // of EQ per thread
+        uint64_t k[SHARES], csr[SHARES];
+        uint8_t vis[SHARES];
+        int to[SHARES];
+#pragma unroll
+        for (int c = 0; c < SHARES; ++c) {
+            const int i = c * ADV_THREADS + tid;
+            to[c] = s.ef;
+            k[c] = 0;
+            if (i < n_eq) {
+                k[c] = eqk[i];
+                csr[c] = eqr[i];
+                vis[c] = eqv[i];
+                to[c] = i;
+            }
+        }
+        const uint64_t mine = lane < cnt ? new_key[lane] : ~0ull;
+        int old = 0, fresh_rank = 0;
+        for (int j0 = 0; j0 < cnt; j0 += 4) {
+            uint64_t kj[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kj[i] = new_key[j0 + i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                fresh_rank += kj[i] > mine;
+                int count = 0;
+#pragma unroll
+                for (int c = 0; c < SHARES; ++c)
+                    if (c * ADV_THREADS < n_eq) {
+                        to[c] += kj[i] > k[c];
+                        count += (int)__popcll(__ballot(k[c] > kj[i]));
+                    }
+                if (lane == j0 + i) old = count;
+            }
+        }
+        better_old[wave][lane] = old;
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < SHARES; ++c)
+            if (c * ADV_THREADS + tid < n_eq && to[c] < s.ef) {
+                eqk[to[c]] = k[c];
+                eqr[to[c]] = csr[c];
+                eqv[to[c]] = vis[c];
+            }
+        if (tid < cnt) {
+            int p = fresh_rank;
+#pragma unroll
+            for (int w = 0; w < ADV_THREADS / 64; ++w) p += better_old[w][lane];
+            if (p < s.ef) {
+                eqk[p] = mine;
+                eqr[p] = new_csr[lane];
+                eqv[p] = 0;
+            }
+        }
+    };
+    // AQ belongs to wavefront 0.
+    auto aq_get = [&](int c, int r) -> uint64_t {
+        if (r < s.aq_near) return aq_near[c * pitch + r];
+        return aqg[(size_t)c * s.aq_rows + r];
+    };
+    auto aq_put = [&](int c, int r, uint64_t k) {
+        if (r < s.aq_near) aq_near[c * pitch + r] = k;
+        else aqg[(size_t)c * s.aq_rows + r] = k;
+    };
+    uint64_t col_best = wave == 0 && lane < tail ? s.aq_max[(size_t)q * 64 + lane] : 0;
+    // What pop() takes out leaves its column by settle(), which the next one calls first: the column's entries come in meanwhile.
+    uint64_t taken = 0, taken_k = 0;
+    int taken_col = -1;
+    auto column = [&](int r0) -> uint64_t {  // entry r0 + lane of that column
+        const int r = r0 + lane;
+        if (r * 64 + taken_col >= tail) return 0;
+        return aq_get(taken_col, r);
+    };
+    auto settle = [&]() {
+        if (taken_col < 0) return;
+        uint64_t rest = 0;
+        for (int r0 = 0; r0 * 64 < tail; r0 += 64) {
+            const uint64_t k = r0 ? column(r0) : taken_k;
+            if (k == taken) aq_put(taken_col, r0 + lane, 0);
+            else rest = max(rest, k);
+        }
+        rest = wave_max_key(rest);
+        if (lane == taken_col) col_best = max(col_best, rest);
+        taken_col = -1;
+    };
+    // key: of the lane whose column comes next the first one, and so on; cnt of them
+    auto push = [&](uint64_t key, int cnt) {
+        if (__builtin_expect(tail + cnt > s.aqcap, 0)) {
+            if (live + cnt <= s.aqcap) {  // squeeze the holes out, and bring the keys to the lanes of the new end
+                settle();
+                const uint64_t in_order = shfl_key(key, (tail + lane) & 63);
+                int out = 0;
+                for (int r = 0; r * 64 < tail; ++r) {
+                    __threadfence_block();
+                    const uint64_t k = r * 64 + lane < tail ? aq_get(lane, r) : 0;
+                    const unsigned long long full = __ballot(k != 0);
+                    const int p = out + __popcll(full & ((1ull << lane) - 1ull));
+                    if (k) aq_put(p & 63, p >> 6, k);
+                    out += __popcll(full);
+                }
+                __threadfence_block();
+                tail = out;
+                col_best = 0;
+                for (int r = 0; r * 64 + lane < tail; ++r) col_best = max(col_best, aq_get(lane, r));
+                key = shfl_key(in_order, (lane - tail) & 63);
+            } else {
+                err |= ERR_AQ_OVERFLOW;
+                cnt = min(cnt, s.aqcap - tail);
+            }
+        }
+        const int i = (lane - tail) & 63;
+        if (i < cnt) {
+            aq_put(lane, (tail + i) >> 6, key);
+            col_best = max(col_best, key);
+        }
+        tail += cnt;
+        live += cnt;
+    };
+    auto pop = [&]() {  // the best entry of AQ moves to the pending list
+        settle();
+        taken = wave_max_key(col_best);
+        taken_col = __ffsll((long long)__ballot(col_best == taken)) - 1;
+        if (tail > s.aq_near * 64) __threadfence_block();  // this wave's AQ stores to memory before the reads
+        taken_k = column(0);
+        if (lane == taken_col) col_best = 0;
+        if (lane == 0) {
+            if (n_pend < PEND_LDS) pend_near[n_pend] = key_id(taken);
+            else if (n_pend < s.pcap) pend[n_pend] = key_id(taken);
+        }
+        if (n_pend >= s.pcap) err |= ERR_P_OVERFLOW;
+        n_pend = min(n_pend + 1, s.pcap);
+        --live;
+    };
+    auto mark = [&](uint32_t v, bool on) -> uint32_t {  // the word of marks before; v's bit set where it has been met
+        return on ? atomicOr(&seen[v >> 5], 1u << (v & 31)) : ~0u;
+    };
     __syncthreads();
 
     bool ready = have_results;  // the pending chunks' embeddings are there
     bool finished = false;
     for (;;) {
+        if (tid < 64) new_key[tid] = 0;  // the padding of keys_above
         if (!ready) {  // all of them in the stored table?
-            int missing = 0, bad = 0;
             for (int j = tid; j < n_pend; j += ADV_THREADS) {
-                const int slot = s.slot_of ? s.slot_of[pend[j]] : -1;
-                missing |= slot < 0;
-                bad |= slot >= 0 && slot >= s.cache_rows;
+                const uint32_t id = pending(j);
+                const int slot = s.slot_of ? s.slot_of[id] : -1;
+                if (slot < 0) sh_missing = 1;
+                else if (slot >= s.cache_rows) sh_bad = 1;
+                if (j < 64) {
+                    new_id[j] = id;
+                    new_csr[j] = pack_row(row_ptr[id], row_ptr[id + 1]);
+                    new_row[j] = s.cache_emb + (size_t)max(slot, 0) * d;
+                }
             }
-            if (__syncthreads_or(bad)) {  // reported; the host ends the search before anything reads through the slot
-                err |= ERR_BAD_SLOT;
-                break;
-            }
-            if (__syncthreads_or(missing)) break;
+            __syncthreads();
+            if (sh_bad) err |= ERR_BAD_SLOT;  // reported; the host ends the search before anything reads through the slot
+            if (sh_missing | sh_bad) break;
             hits += n_pend;
         }
         // exact scores, 64 entries at a time, and their merge into EQ
         for (int j0 = 0; j0 < n_pend; j0 += 64) {
             const int cnt = min(64, n_pend - j0);
-            if (tid < cnt) {
-                const uint32_t id = pend[j0 + tid];
-                const int slot = s.slot_of ? s.slot_of[id] : -1;
-                const int mslot = slot < 0 && s.memo_slot ? s.memo_slot[id] : -1;
-                new_id[tid] = id;
-                new_row[tid] = slot >= 0    ? s.cache_emb + (size_t)slot * d
-                               : mslot >= 0 ? s.memo_emb + (size_t)mslot * d
-                                            : enc_emb + (size_t)s.src[s.own[(size_t)q * s.pcap + j0 + tid]] * d;
+            if (ready || j0 > 0) {
+                if (tid < 64) new_key[tid] = 0;
+                if (tid < cnt) {
+                    const uint32_t id = pending(j0 + tid);
+                    const int slot = s.slot_of ? s.slot_of[id] : -1;
+                    const int mslot = slot < 0 && s.memo_slot ? s.memo_slot[id] : -1;
+                    new_id[tid] = id;
+                    new_csr[tid] = pack_row(row_ptr[id], row_ptr[id + 1]);
+                    new_row[tid] = slot >= 0    ? s.cache_emb + (size_t)slot * d
+                                   : mslot >= 0 ? s.memo_emb + (size_t)mslot * d
+                                                : enc_emb + (size_t)s.src[s.own[(size_t)q * s.pcap + j0 + tid]] * d;
+                }
+                __syncthreads();
             }
-            __syncthreads();
             for (int i0 = wave; i0 < cnt; i0 += ADV_THREADS / 16) {
                 const int c = min(4, (cnt - i0 + 3) / 4);
                 float dv[4];
@@ -206,42 +429,8 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
                     if (k < c && lane == 0) new_key[i0 + 4 * k] = queue_key(dv[k], new_id[i0 + 4 * k]);
             }
             __syncthreads();
-            int to = s.ef;  // where newcomer tid goes: behind everything better, old or new
-            uint64_t mine = 0;
-            if (tid < cnt) {
-                mine = new_key[tid];
-                int lo = 0, hi = n_eq;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (eqk[mid] > mine) lo = mid + 1;
-                    else hi = mid;
-                }
-                to = lo;
-                for (int j = 0; j < cnt; ++j) to += new_key[j] > mine;
-            }
-            __syncthreads();
-            for (int base = (n_eq - 1) / ADV_THREADS * ADV_THREADS; base >= 0; base -= ADV_THREADS) {  // from the back: entries only move down
-                const int i = base + tid;
-                uint64_t k = 0;
-                uint8_t v = 0;
-                int p = s.ef;
-                if (i < n_eq) {
-                    k = eqk[i];
-                    v = eqv[i];
-                    p = i;
-                    for (int j = 0; j < cnt; ++j) p += new_key[j] > k;
-                }
-                __syncthreads();
-                if (p < s.ef) {
-                    eqk[p] = k;
-                    eqv[p] = v;
-                }
-                __syncthreads();
-            }
-            if (to < s.ef) {
-                eqk[to] = mine;
-                eqv[to] = 0;
-            }
+            if (n_eq <= ADV_THREADS) merge(cnt, std::integral_constant<int, 1>());
+            else merge(cnt, std::integral_constant<int, EF_MAX / ADV_THREADS>());
             n_eq = min(s.ef, n_eq + cnt);
             __syncthreads();
         }
@@ -252,190 +441,194 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
         n_pend = 0;
         ready = false;
 
-        if (wave == 0) {
-            const int runs64 = s.aq_run >> 6;
-            auto aq_get = [&](int p) -> uint64_t { return p < s.aq_lds ? aql[p] : aqg[p]; };
-            auto aq_put = [&](int p, uint64_t k) {
-                if (p < s.aq_lds) aql[p] = k;
-                else aqg[p] = k;
-            };
-            const int n16 = (m_sub & 15) == 0 && m_sub <= 64 ? m_sub >> 4 : 0;  // 16-byte pieces of a code row that are fetched ahead
-            auto fetch_codes = [&](uint32_t v, bool on, u32x4 (&c)[4]) {
-                if (!on) return;
-                const uint8_t *row = codes + (size_t)v * m_sub;
+        bool last = false;             // no open entry of EQ is left after this group
+        int hop_pos = 0, hop_deg = 0;  // wavefront 0, lane h: hop h's position in EQ, its row's length
+        for (;;) {
+            if (wave == 0) {  // the next hops: the best entries of EQ that have not been expanded
+                int m = 0, found = 0;
+                if (n_pend < batch && !last)
+                    for (int b = 0; b < n_eq && found <= GROUP_HOPS; b += 256) {  // lane l looks at positions b + 4l .. b + 4l + 3
+                        const uint32_t vis = *reinterpret_cast<const uint32_t *>(eqv + b + 4 * lane);
+                        bool open[4];
+                        int at = found;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (i < n16) c[i] = *reinterpret_cast<const u32x4 *>(row + 16 * i);
-            };
-            auto mark = [&](uint32_t v, bool on) -> bool {  // first time this query meets v?
-                if (!on) return false;
-                const uint32_t bit = 1u << (v & 31);
-                return !(atomicOr(&seen[v >> 5], bit) & bit);
-            };
-            // the neighbours that are new go to AQ with their approximate scores; returns how many there are
-            auto take = [&](uint32_t v, bool is_new, const u32x4 (&c)[4]) -> int {
-                float sc = 0.f;
-                if (is_new) {  // table entries summed in subspace order
-                    if (n16 > 0) {
+                        for (int i = 0; i < 4; ++i) {
+                            open[i] = b + 4 * lane + i < n_eq && !(vis >> (8 * i) & 255u);
+                            const unsigned long long mask = __ballot(open[i]);
+                            at += __popcll(mask & ((1ull << lane) - 1ull));
+                            found += (int)__popcll(mask);
+                        }
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            if (i < n16) {
-#pragma unroll
-                                for (int m = 0; m < 16; ++m) sc += tab[(16 * i + m) * KSUB + ((c[i][m >> 2] >> (8 * (m & 3))) & 255u)];
+                            if (open[i]) {
+                                if (at < GROUP_HOPS) list[at] = b + 4 * lane + i;
+                                ++at;
                             }
-                    } else if ((m_sub & 15) == 0) {
-                        const uint8_t *row = codes + (size_t)v * m_sub;
-                        for (int m0 = 0; m0 < m_sub; m0 += 16) {
-                            const u32x4 w = *reinterpret_cast<const u32x4 *>(row + m0);
-#pragma unroll
-                            for (int m = 0; m < 16; ++m) sc += tab[(m0 + m) * KSUB + ((w[m >> 2] >> (8 * (m & 3))) & 255u)];
-                        }
-                    } else {
-                        const uint8_t *row = codes + (size_t)v * m_sub;
-                        for (int m = 0; m < m_sub; ++m) sc += tab[m * KSUB + row[m]];
                     }
-                }
-                const unsigned long long mask = __ballot(is_new);
-                const int cnt = __popcll(mask);
-                if (tail + cnt > s.aqcap && live + cnt <= s.aqcap) {  // squeeze the holes out
-                    __threadfence_block();
-                    int out = 0;
-                    for (int b = 0; b < tail; b += 64) {
-                        const uint64_t k = b + lane < tail ? aq_get(b + lane) : 0;
-                        const unsigned long long full = __ballot(k != 0);
-                        if (k) aq_put(out + __popcll(full & ((1ull << lane) - 1ull)), k);
-                        out += __popcll(full);
-                    }
-                    tail = out;
-                    __threadfence_block();
-                    for (int g = 0; g < s.aq_groups; ++g) {
-                        uint64_t best = 0;
-                        for (int b = g * s.aq_run + lane; b < min(tail, (g + 1) * s.aq_run); b += 64) best = max(best, aq_get(b));
-                        best = wave_max_key(best);
-                        if (lane == 0) aqm[g] = best;
-                    }
-                }
-                const int pos = tail + __popcll(mask & ((1ull << lane) - 1ull));
-                if (is_new) {
-                    if (pos < s.aqcap) {
-                        const uint64_t k = queue_key(sc, v);
-                        aq_put(pos, k);
-                        atomicMax(reinterpret_cast<unsigned long long *>(&aqm[pos / s.aq_run]), (unsigned long long)k);
-                    } else {
-                        err |= ERR_AQ_OVERFLOW;
-                    }
-                }
-                const int fit = min(cnt, s.aqcap - tail);
-                tail += fit;
-                live += fit;
-                return cnt;
-            };
-            bool more = true;
-            while (more && n_pend < batch) {
-                // the next hops: the best 64 entries of EQ that have not been expanded
-                int m = 0;
-                for (int b = 0; b < n_eq && m < 64; b += 64) {
-                    const bool open = b + lane < n_eq && !eqv[b + lane];
-                    const unsigned long long mask = __ballot(open);
-                    const int at = m + __popcll(mask & ((1ull << lane) - 1ull));
-                    if (open && at < 64) list[at] = b + lane;
-                    m = min(64, m + __popcll(mask));
-                }
-                if (m == 0) break;
-                more = m == 64;
+                m = min(GROUP_HOPS, found);
                 __builtin_amdgcn_wave_barrier();
-                const int at = lane < m ? list[lane] : 0;
-                const uint32_t u = lane < m ? key_id(eqk[at]) : 0;
-                uint64_t beg = 0;
-                int deg = 0;
-                if (lane < m) {
-                    beg = row_ptr[u];
-                    deg = (int)(row_ptr[u + 1] - beg);
-                }
-                auto fetch_row = [&](int h) -> uint32_t {  // the first 64 neighbours of hop h
-                    uint32_t v = 0;
-                    if (h < m && lane < __builtin_amdgcn_readlane(deg, h)) v = col_idx[readlane64(beg, h) + lane];
-                    return v;
-                };
-                uint32_t v0 = fetch_row(0), v1 = fetch_row(1);
-                u32x4 c0[4], c1[4];
-                bool on0 = lane < __builtin_amdgcn_readlane(deg, 0) && v0 < n;
-                fetch_codes(v0, on0, c0);
-                bool marked = false, fresh = false;  // hop h's marks have been set a hop ahead; what that said
-                int h = 0;
-                for (; h < m && n_pend < batch; ++h) {
-                    const int dh = __builtin_amdgcn_readlane(deg, h);
-                    const uint64_t bh = readlane64(beg, h);
-                    if (lane == 0) eqv[__builtin_amdgcn_readlane(at, h)] = 1;
-                    ++hops;
-                    if (lane < dh && v0 >= n) err |= ERR_BAD_NEIGHBOUR;
-                    if (!marked) fresh = mark(v0, on0);
-                    // the next hop's codes, the row of the one after it
-                    const int dn = h + 1 < m ? __builtin_amdgcn_readlane(deg, h + 1) : 0;
-                    const bool on1 = lane < dn && v1 < n;
-                    fetch_codes(v1, on1, c1);
-                    const uint32_t v2 = fetch_row(h + 2);
-                    bool fresh1 = false;
-                    const bool certain = h + 1 < m && dh <= 64 && n_pend + (int)ceilf(alpha * (float)dh) < batch;
-                    if (certain) fresh1 = mark(v1, on1);
-                    int n_new = take(v0, fresh, c0);
-                    for (int b = 64; b < dh; b += 64) {  // rows longer than a wavefront
-                        uint32_t v = 0;
-                        const bool in = b + lane < dh;
-                        if (in) v = col_idx[bh + b + lane];
-                        if (in && v >= n) err |= ERR_BAD_NEIGHBOUR;
-                        u32x4 c[4];
-                        const bool is_new = mark(v, in && v < n);
-                        fetch_codes(v, is_new, c);
-                        n_new += take(v, is_new, c);
+                if (m > 0) {
+                    uint64_t beg = 0;
+                    hop_deg = 0;
+                    if (lane < m) {
+                        hop_pos = list[lane];
+                        beg = eqr[hop_pos] >> 24;
+                        hop_deg = (int)(eqr[hop_pos] & ROW_LONG);
+                        if (hop_deg == (int)ROW_LONG) hop_deg = (int)(row_ptr[key_id(eqk[hop_pos]) + 1] - beg);
                     }
-                    adc += n_new;
-                    if (tail > s.aq_lds) __threadfence_block();  // orders this wave's AQ stores before the reads below
-                    // move the r best entries of AQ to the pending list
-                    const int r = (int)ceilf(alpha * (float)n_new);
-                    const int groups = (tail + s.aq_run - 1) / s.aq_run;
-                    for (int t = 0; t < r && live > 0; ++t) {
-                        uint64_t best = 0;
-                        int from = 0;
-                        for (int g = lane; g < groups; g += 64)
-                            if (aqm[g] > best) {
-                                best = aqm[g];
-                                from = g;
+                    // a row longer than a wavefront ends the group: the rest of it is taken when its hop is run
+                    const unsigned long long longer = __ballot(hop_deg > 64);
+                    if (longer) m = min(m, (int)__ffsll((long long)longer));
+                    const int end = sum_to_lane16(min(hop_deg, 64));
+                    m = min(m, (int)__popcll(__ballot(lane < GROUP_HOPS && end <= GROUP_CAND)));
+                    if (lane < m) {
+                        hop_beg[lane] = beg;
+                        hop_off[lane + 1] = end;
+                    }
+                    if (lane == 0) hop_off[0] = 0;
+                    last = found == m;
+                }
+                if (lane == 0) {
+                    sh_hops = m;
+                    sh_pend = n_pend;
+                    sh_tail = tail;
+                }
+            }
+            __syncthreads();
+            const int m = __builtin_amdgcn_readfirstlane(sh_hops);
+            if (m == 0) break;
+            const int off = hop_off[min(lane, m)];
+            const int t = tid - 64;  // wavefronts 1 to 3: a candidate each
+            int hop = 0;
+            uint32_t v = 0;
+            const bool mine = t >= 0 && t < __builtin_amdgcn_readlane(off, m);
+            if (mine) {
+                for (int i = 1; i < m; ++i) hop += t >= __builtin_amdgcn_readlane(off, i);
+                v = col_idx[hop_beg[hop] + (t - hop_off[hop])];
+                cand_id[t] = v;
+            }
+            __syncthreads();
+            uint64_t key = 0, fresh_h = 0;  // lane h of wavefront 0: hop h's mask
+            int base_h = 0;
+            bool bad_h = false;
+            if (wave == 0) {
+                uint32_t before[GROUP_HOPS], bit[GROUP_HOPS];
+#pragma unroll
+                for (int h0 = 0; h0 < GROUP_HOPS; h0 += 4) {
+#pragma unroll
+                    for (int h = h0; h < h0 + 4; ++h) before[h] = bit[h] = 0;
+                    if (h0 < m) {
+                        uint32_t w[4];
+                        bool on[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int o = __builtin_amdgcn_readlane(off, h0 + i);
+                            on[i] = lane < __builtin_amdgcn_readlane(off, h0 + i + 1) - o;
+                            w[i] = cand_id[min(o + lane, GROUP_CAND - 1)];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if (__ballot(on[i] && w[i] >= n) && lane == h0 + i) bad_h = true;
+                            bit[h0 + i] = on[i] ? 1u << (w[i] & 31) : 0u;
+                            before[h0 + i] = mark(w[i], on[i] && w[i] < n);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < GROUP_HOPS; ++h) {
+                    const unsigned long long mask = __ballot(bit[h] & ~before[h]);
+                    if (lane == h) fresh_h = mask;
+                }
+                const int cnt = __popcll(fresh_h);
+                base_h = sum_to_lane16(cnt) - cnt;
+                if (lane < GROUP_HOPS) {
+                    hop_fresh[lane] = fresh_h;
+                    hop_base[lane] = base_h;
+                }
+            } else if (mine && v < n) {
+                key = queue_key(adc_score(v), v);
+            }
+            __syncthreads();
+            if (mine) {
+                const int j = t - hop_off[hop];
+                const uint64_t fresh = hop_fresh[hop];
+                if (fresh >> j & 1u) fresh_key[hop_base[hop] + __popcll(fresh & ((1ull << j) - 1ull))] = key;
+            }
+            __syncthreads();
+            if (wave != 0) continue;
+            const int r_h = (int)ceilf(alpha * (float)__popcll(fresh_h));
+            const int fresh_end = base_h + (int)__popcll(fresh_h);
+            int h = 0;
+            uint64_t next = fresh_key[(lane - tail) & 63];
+            if (tail + __builtin_amdgcn_readlane(fresh_end, m - 1) <= min(s.aq_near * 64, s.aqcap) && __builtin_amdgcn_readlane(hop_deg, m - 1) <= 64) {
+                // all in LDS, and no row is longer than a wavefront: the usual case
+                for (; h < m && n_pend < batch; ++h) {
+                    const int end = __builtin_amdgcn_readlane(fresh_end, h), n_new = end - __builtin_amdgcn_readlane(base_h, h);
+                    const int i = (lane - tail) & 63;
+                    if (i < n_new) {
+                        aq_near[lane * pitch + ((tail + i) >> 6)] = next;
+                        col_best = max(col_best, next);
+                    }
+                    tail += n_new;
+                    live += n_new;
+                    next = fresh_key[min(end + ((lane - tail) & 63), GROUP_CAND - 1)];  // the next hop's, for the lanes they go to
+                    for (int r = __builtin_amdgcn_readlane(r_h, h); r > 0 && live > 0; --r) {
+                        if (taken_col >= 0) {
+                            if (taken_k == taken) {
+                                aq_near[taken_col * pitch + lane] = 0;
+                                taken_k = 0;
                             }
-                        const uint64_t top = wave_max_key(best);
-                        const int g = __builtin_amdgcn_readlane(from, __ffsll((long long)__ballot(best == top)) - 1);
-                        uint64_t rest = 0;
-                        for (int i = 0; i < runs64; ++i) {
-                            const int p = g * s.aq_run + i * 64 + lane;
-                            const uint64_t k = p < tail ? aq_get(p) : 0;
-                            if (k == top) aq_put(p, 0);
-                            else rest = max(rest, k);
+                            const uint64_t rest = wave_max_key(taken_k);
+                            if (lane == taken_col) col_best = max(col_best, rest);
                         }
-                        rest = wave_max_key(rest);
+                        taken_col = wave_max_lane(col_best);
+                        taken = key_of_lane(col_best, taken_col);
+                        taken_k = 0;
+                        if (lane * 64 + taken_col < tail) taken_k = aq_near[taken_col * pitch + lane];
+                        if (lane == taken_col) col_best = 0;
                         if (lane == 0) {
-                            aqm[g] = rest;
-                            if (n_pend < s.pcap) pend[n_pend] = key_id(top);
+                            if (n_pend < PEND_LDS) pend_near[n_pend] = key_id(taken);
+                            else if (n_pend < s.pcap) pend[n_pend] = key_id(taken);
                         }
-                        if (tail > s.aq_lds) __threadfence_block();
                         if (n_pend >= s.pcap) err |= ERR_P_OVERFLOW;
                         n_pend = min(n_pend + 1, s.pcap);
                         --live;
                     }
-                    v0 = v1;
-                    on0 = on1;
-                    v1 = v2;
-                    marked = certain;
-                    fresh = fresh1;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) c0[i] = c1[i];
+                }
+                adc += h > 0 ? __builtin_amdgcn_readlane(fresh_end, h - 1) : 0;
+            } else {
+                for (; h < m && n_pend < batch; ++h) {
+                    int n_new = __builtin_amdgcn_readlane(fresh_end, h) - __builtin_amdgcn_readlane(base_h, h), r = __builtin_amdgcn_readlane(r_h, h);
+                    push(fresh_key[min(__builtin_amdgcn_readlane(base_h, h) + ((lane - tail) & 63), GROUP_CAND - 1)], n_new);
+                    const int deg = __builtin_amdgcn_readlane(hop_deg, h);
+                    if (deg > 64) {  // the rest of a row longer than a wavefront
+                        for (int b = 64; b < deg; b += 64) {
+                            const bool in = b + lane < deg;
+                            const uint32_t w = in ? col_idx[hop_beg[h] + b + lane] : 0;
+                            if (w >= n) err |= ERR_BAD_NEIGHBOUR;
+                            const bool first_time = !(mark(w, in && w < n) >> (w & 31) & 1u);
+                            const unsigned long long mask = __ballot(first_time);
+                            if (first_time) new_key[__popcll(mask & ((1ull << lane) - 1ull))] = queue_key(adc_score(w), w);
+                            __builtin_amdgcn_wave_barrier();
+                            push(new_key[(lane - tail) & 63], __popcll(mask));
+                            __builtin_amdgcn_wave_barrier();
+                            n_new += __popcll(mask);
+                        }
+                        r = (int)ceilf(alpha * (float)n_new);
+                    }
+                    adc += n_new;
+                    for (int i = 0; i < r && live > 0; ++i) pop();
                 }
             }
-            if (lane == 0) {
-                sh_pend = n_pend;
-                sh_tail = tail;
+            settle();
+            hops += h;
+            if (lane < h) eqv[hop_pos] = 1;
+            if (__ballot(lane < h && bad_h)) err |= ERR_BAD_NEIGHBOUR;
+            for (; h < m; ++h) {  // not run: the marks are taken back
+                const uint32_t w = cand_id[min(__builtin_amdgcn_readlane(off, h) + lane, GROUP_CAND - 1)];
+                if (key_of_lane(fresh_h, h) >> lane & 1u) atomicAnd(&seen[w >> 5], ~(1u << (w & 31)));
             }
         }
-        __syncthreads();
         n_pend = sh_pend;
         if (n_pend == 0) {  // no unvisited node and nothing pending
             finished = true;
@@ -445,19 +638,20 @@ __global__ __launch_bounds__(ADV_THREADS) void advance_kernel(SearchState s, con
 
     for (int i = tid; i < n_eq; i += ADV_THREADS) {
         s.eq_key[(size_t)q * s.ef + i] = eqk[i];
+        s.eq_row[(size_t)q * s.ef + i] = eqr[i];
         s.eq_vis[(size_t)q * s.ef + i] = eqv[i];
     }
     int mine = 0, memo_hits = 0;  // of the pending entries: served by the stored table, by the memo
     if (!finished) {
-        const int end = sh_tail;
-        for (int i = tid; i < min(end, s.aq_lds); i += ADV_THREADS) aqg[i] = aql[i];
-        for (int i = tid; i < s.aq_groups; i += ADV_THREADS) s.aq_max[(size_t)q * s.aq_groups + i] = aqm[i];
+        copy_near(sh_tail, false);
+        if (wave == 0) s.aq_max[(size_t)q * 64 + lane] = col_best;
         // Claim.  Chunks that several queries ask for in the same round are encoded once: the pending entry with the
         // smallest number (q * pcap + j) owns the chunk.  The encoder's output for a chunk does not depend on its batch, so
         // every query still sees exactly the scores it would compute alone.  Newer rounds have smaller values: nothing has
         // to be taken back.
         for (int j = tid; j < n_pend; j += ADV_THREADS) {
-            const uint32_t c = pend[j];
+            const uint32_t c = pending(j);
+            if (j < PEND_LDS) pend[j] = c;
             if (s.slot_of && s.slot_of[c] >= 0) ++mine;
             else if (s.memo_slot && s.memo_slot[c] >= 0) ++memo_hits;  // encoded earlier in this call
             else atomicMin(&s.owner[c], (unsigned long long)~round << 32 | (uint32_t)(q * s.pcap + j));
@@ -652,7 +846,8 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace {
 
-constexpr int LDS_LIMIT = 158 * 1024;  // dynamic LDS of advance_kernel, beside its few fixed arrays
+constexpr int LDS_LIMIT = 154 * 1024;  // dynamic LDS of advance_kernel, beside its fixed arrays of 6.0 KB
+constexpr int LDS_SHARED = 74 * 1024;  // with two blocks on a CU
 
 // advance_kernel for rows of d elements (the encoder's widths end at 1024)
 auto advance_for(int d) -> decltype(&advance_kernel<2>)
@@ -681,7 +876,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     long long *counters = (long long *)ctx->s_misc.p;
     LEANN_HIP(hipMemsetAsync(counters, 0, CTR_COUNT * sizeof(long long), st));
     LEANN_TRY(clear_host_flags(ctx));
-    hipLaunchKernelGGL(maxdeg_kernel, dim3(256), dim3(256), 0, st, graph->row_ptr, n, counters);
+    hipLaunchKernelGGL(maxdeg_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (n + 2047) / 2048))), dim3(256), 0, st, graph->row_ptr, n, counters);
     if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, CTR_COUNT * sizeof(long long), hipHostMallocDefault));
     long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after a synchronisation only
     const size_t ctr_bytes = CTR_COUNT * sizeof(long long);
@@ -709,10 +904,9 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         off = align_up(off + bytes, 256);
         return o;
     };
-    const int32_t aq_run = (int32_t)(((int64_t)aqcap + AQ_GROUPS_MAX * 64 - 1) / (AQ_GROUPS_MAX * 64) * 64);
-    const int32_t aq_groups = (int32_t)(((int64_t)aqcap + aq_run - 1) / aq_run);
-    const size_t o_eqk = carve((size_t)G * ef * 8), o_eqv = carve((size_t)G * ef), o_eqn = carve((size_t)G * 4);
-    const size_t o_aqk = carve((size_t)G * aqcap * 8), o_aqm = carve((size_t)G * aq_groups * 8);
+    const int32_t aq_rows = (aqcap + 63) / 64;
+    const size_t o_eqk = carve((size_t)G * ef * 8), o_eqr = carve((size_t)G * ef * 8), o_eqv = carve((size_t)G * ef), o_eqn = carve((size_t)G * 4);
+    const size_t o_aqk = carve((size_t)G * 64 * aq_rows * 8), o_aqm = carve((size_t)G * 64 * 8);
     const size_t o_aqt = carve((size_t)G * 4), o_aql = carve((size_t)G * 4), o_pend = carve((size_t)G * pcap * 4);
     const size_t o_np = carve((size_t)G * 4), o_src = carve((size_t)G * pcap * 4), o_own = carve((size_t)G * pcap * 4);
     const size_t o_done = carve((size_t)G * 4), o_nfl = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
@@ -734,6 +928,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     char *base = (char *)ctx->s_state.p;
     SearchState s;
     s.eq_key = (uint64_t *)(base + o_eqk);
+    s.eq_row = (uint64_t *)(base + o_eqr);
     s.eq_vis = (uint8_t *)(base + o_eqv);
     s.eq_n = (int32_t *)(base + o_eqn);
     s.aq_key = (uint64_t *)(base + o_aqk);
@@ -758,8 +953,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     s.ef = ef;
     s.aqcap = aqcap;
     s.pcap = pcap;
-    s.aq_run = aq_run;
-    s.aq_groups = aq_groups;
+    s.aq_rows = aq_rows;
     s.host_counters = h_ctr;
     s.slot_of = cache ? cache->slot_of : nullptr;
     s.cache_emb = cache ? cache->emb : nullptr;
@@ -770,10 +964,15 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", table_smem);
         return LEANN_ESHAPE;
     }
-    // what is left holds the head of AQ
-    const int aq_room = (LDS_LIMIT - table_smem - aq_groups * 8) / (64 * 8) * 64;
-    s.aq_lds = std::min(AQ_LDS_MAX, aq_room);
-    const int adv_smem = table_smem + aq_groups * 8 + s.aq_lds * 8;
+    // what is left holds the head of AQ: as much as lets two blocks share a CU, but no less than AQ_NEAR_MIN rows if there is room
+    const int fixed_smem = m_sub * KSUB * (int)sizeof(float) + ef * 16 + (ef + 255) / 256 * 256;
+    auto rows_in = [&](int limit) { return std::max(0, (limit - fixed_smem) / (64 * 8) - 1); };  // - 1: the pitch is odd
+    s.aq_near = std::min(std::max(std::min(AQ_NEAR_MIN, rows_in(LDS_LIMIT)), rows_in(LDS_SHARED)), AQ_NEAR_MAX);
+    const int adv_smem = fixed_smem + 64 * (s.aq_near | 1) * 8;
+    if (adv_smem > LDS_LIMIT) {  // not with the widths that encoders and PQ tables have: at most 128 subspaces get here
+        leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", adv_smem);
+        return LEANN_ESHAPE;
+    }
     const auto advance = advance_for(d);
     uint32_t launches = 0;
 

@@ -10,7 +10,7 @@ __device__ inline uint32_t dpp_mov(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
 }
-constexpr int DPP_ROW_ROR8 = 0x128, DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR2 = 0x122, DPP_QUAD_XOR1 = 0xB1;
+constexpr int DPP_ROW_ROR8 = 0x128, DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR2 = 0x122, DPP_QUAD_XOR1 = 0xB1, DPP_QUAD_XOR2 = 0x4E;
 
 // Sum over the wave, in every lane.  The additions are those of a butterfly over lane ^ 32, 16, 8, 4, 2, 1 (after the
 // step over lane ^ 8 the values repeat every 8 lanes, so a rotation by 4 reaches lane ^ 4, and so on), so the bits are the
@@ -69,12 +69,47 @@ __device__ inline float key_score(uint64_t k)
     return __uint_as_float((h & 0x80000000u) ? (h & 0x7fffffffu) : ~h);
 }
 
-// Largest key over the wave, in every lane (0 where no lane has one).
-__device__ inline uint64_t wave_max_key(uint64_t k)
+// Lane l's key, l the same in all lanes.
+__device__ inline uint64_t key_of_lane(uint64_t k, int l)
 {
-    const uint32_t hi = (uint32_t)(k >> 32), top = wave_max(hi);
-    const uint32_t low = wave_max(hi == top ? (uint32_t)k : 0u);
-    return ((uint64_t)top << 32) | low;
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(k >> 32), l) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)k, l);
+}
+
+// Key of lane l, another l in every lane.
+__device__ inline uint64_t shfl_key(uint64_t k, int l)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)(k >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)k);
+}
+
+// The lane with the largest key (the first one of equals).
+__device__ inline int wave_max_lane(uint64_t k)
+{
+    const uint32_t hi = (uint32_t)(k >> 32);
+    unsigned long long at = __ballot(hi == wave_max(hi));
+    if (__builtin_expect((at & (at - 1)) != 0, 0)) {
+        const uint32_t low = hi == wave_max(hi) ? (uint32_t)k : 0u;
+        at &= __ballot(low == wave_max(low));
+    }
+    return __ffsll((long long)at) - 1;
+}
+
+// Largest key over the wave, in every lane (0 where no lane has one).
+__device__ inline uint64_t wave_max_key(uint64_t k) { return key_of_lane(k, wave_max_lane(k)); }
+
+// Keys of LDS list `key` that are larger than k; the list is padded with zeros to a multiple of 8 entries (no key is 0).
+// Eight at a time: one by one, each would wait for its own read.
+__device__ inline int keys_above(const uint64_t *key, int cnt, uint64_t k)
+{
+    int above = 0;
+    for (int j = 0; j < cnt; j += 8) {
+        uint64_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = key[j + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) above += v[i] > k;
+    }
+    return above;
 }
 
 // One anchor row against other rows, fp32.  NV = 4-byte pieces per lane (lane l owns elements l, l + 64, ...), 0: rows
@@ -111,28 +146,38 @@ struct RowDots {
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
         return (const float *)((uint64_t)hi << 32 | lo);
     }
-    // out[k] = <anchor, row_at(k)> for k < c <= 4.  A row's NV loads are in flight together.  The rows are not, or two by
-    // two at most: both loops below test k < c, and the compiled code joins each row's loads with its sum.
+    // C rows, their C * NV loads in flight together, then their sums side by side.
+    template <int C, class RowAt>
+    __device__ inline void rows(RowAt row_at, float (&out)[4]) const
+    {
+        float r[C][NV];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const auto rs = rsrc(uniform(row_at(k)));
+#pragma unroll
+            for (int j = 0; j < NV; ++j) r[k][j] = piece(rs, lane, j);
+        }
+        float acc[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            acc[k] = 0.f;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) acc[k] = fmaf(a[j], r[k][j], acc[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) out[k] = wave_sum(acc[k]);
+    }
+    // out[k] = <anchor, row_at(k)> for k < c, 1 <= c <= 4, c the same in all lanes.  What bounds it is one row's latency from beyond L2, so
+    // the count is settled once, outside: with a test per row the compiled code waits for each row before it asks for the next.
     template <class RowAt>
     __device__ inline void four(RowAt row_at, int c, float (&out)[4]) const
     {
         if constexpr (NV > 0) {
-            float r[4][NV];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < c) {
-                    const auto rs = rsrc(uniform(row_at(k)));
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) r[k][j] = piece(rs, lane, j);
-                }
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < c) {
-                    float acc = 0.f;
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) acc = fmaf(a[j], r[k][j], acc);
-                    out[k] = wave_sum(acc);
-                }
+            c = __builtin_amdgcn_readfirstlane(c);
+            if (c == 1) rows<1>(row_at, out);
+            else if (c == 2) rows<2>(row_at, out);
+            else if (c == 3) rows<3>(row_at, out);
+            else rows<4>(row_at, out);
         } else {
             for (int k = 0; k < c; ++k) {
                 const float *e = uniform(row_at(k));

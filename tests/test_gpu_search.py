@@ -312,6 +312,41 @@ def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
         L.leann_destroy(ctx)
 
 
+@pytest.mark.parametrize("hidden,m_sub,ef,alpha,batch", [(128, 16, 40, 0.3, 3), (128, 128, 257, 0.3, 20), (128, 32, 300, 0.1, 70),
+                                                         (640, 128, 1024, 0.2, 33)])
+def test_state_between_rounds_and_in_one_launch(L, hidden, m_sub, ef, alpha, batch):
+    """Recomputed embeddings (a launch per round: queues, marks and CSR rows go through memory in between) and the same embeddings
+    stored (one launch) give the same bits and counts: hops that were prepared but not run, rows longer than a wavefront,
+    an approximate queue beyond what the block holds, more than one share of the exact queue per thread, and the largest
+    lookup table with the longest queue."""
+    import torch
+    rng = np.random.default_rng(m_sub)
+    n, seq, k, nq = 6000, 12, 5, 3
+    cfg = dict(li.TINY, hidden=hidden, heads=hidden // 64, ffn=4 * hidden, layers=1)
+    tokens = rng.integers(1, cfg["vocab"], (n, seq)).astype(np.int32)
+    lengths = rng.integers(2, seq + 1, n).astype(np.int32)
+    deg = rng.integers(0, 40, n)
+    deg[0], deg[1::500] = 200, 70
+    row_ptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.uint64)
+    col_idx = rng.integers(0, n, int(row_ptr[-1])).astype(np.uint32)
+    say(f"rounds against one launch hidden={hidden} m_sub={m_sub} ef={ef} alpha={alpha} batch={batch}")
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 1)))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        emb = L.leann_embed(ctx, t, l, hidden=hidden)
+        pq = L.leann_build_pq(ctx, emb, m_sub, 2, 5)
+        args = (ctx, emb[:nq].contiguous(), (to_dev(row_ptr.view(np.int64)), to_dev(col_idx.view(np.int32)), 0), pq, t, l, ef, k, alpha, batch)
+        ids, scores, st = L.leann_search(*args)
+        ids1, scores1, st1 = L.leann_search(*args, cache=(to_dev(np.arange(n, dtype=np.int32)), emb))
+        assert torch.equal(ids, ids1) and torch.equal(scores, scores1)
+        for key in ("hops", "adc_candidates", "recomputed_chunks", "flushes", "rounds"):
+            assert st[key] == st1[key], key
+        print(f"{st['hops']} hops, {st['flushes']} flushes, {st['adc_candidates']} neighbours scored")
+        L.leann_pq_free(pq)
+    finally:
+        L.leann_destroy(ctx)
+
+
 def pack_bits(flags):
     """uint8 flags [n] -> int32 words, bit (v & 31) of word (v >> 5)."""
     n = len(flags)
