@@ -98,19 +98,24 @@ __device__ inline int block_shrink(const BuildState &s, const uint64_t *key, int
 // Latency bounds it: a hop is a chain of reads (list, vectors) and the next hop depends on its similarities.  So all the
 // wavefronts of a block share a hop: the neighbours' similarities are taken side by side, and the queue W is kept sorted
 // (two copies, the hop's newcomers are merged from one into the other by counting), which makes "closest not expanded" one
-// ballot and dropping the worst a bound.  Measured at n = 8192, d = 768, efC = 128, batches of up to 1024: 219 us per
-// batch on average, one wavefront per node with an unsorted queue took 2632.  words > 0: the visited marks are a bitmap of that many words in LDS (the caller
-// has made sure that it fits), else 16-bit stamps in memory.
+// ballot and dropping the worst a bound.  The next node to expand is the closest open entry of the queue before the hop (the
+// runner-up, known while the vectors are on their way; its list is requested then) or the closest newcomer: wavefront 0
+// takes it on, reads its list and marks its neighbours while the others merge the queue.
+// Measured at n = 8192, d = 768, efC = 128, batches of up to 1024: 171 us per batch on average (a hop of 11 newcomers 3760
+// clocks); 220 us (4800) with the merge before the next list and a wavefront's vectors one after the other.
+// words > 0: the visited marks are a bitmap of that many words in LDS (the caller has made sure that it fits), else 16-bit
+// stamps in memory.
 template <int NV>
 __global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(BuildState s, int64_t inserted, int epoch, int words)
 {
     extern __shared__ uint32_t seen[];
-    __shared__ uint64_t w_key[2][EFC_MAX];
-    __shared__ __attribute__((aligned(4))) uint8_t w_vis[2][EFC_MAX];  // 1: expanded, or no entry there
+    __shared__ __attribute__((aligned(16))) uint64_t w_key[2][EFC_MAX];  // 0 behind the last entry
+    __shared__ __attribute__((aligned(4))) uint8_t w_vis[2][EFC_MAX];    // 1: expanded before the node of this hop, or no entry there
     __shared__ uint64_t new_key[64];
     __shared__ int32_t new_id[64], kept_ids[M_MAX];
     __shared__ uint32_t flags[WAVES_MAX];
     __shared__ int n_new_s;
+    __shared__ uint64_t node_s;
     const int slot = blockIdx.x, tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t v = inserted + slot;
@@ -123,49 +128,71 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(Bui
     RowDots<NV> dots;
     dots.load(s.emb + (size_t)v * s.d, s.d, lane);
     for (int i = tid; i < words; i += blockDim.x) seen[i] = i == 0;  // node 0 is the entry point: seen from the start
-    for (int i = tid; i < 2 * EFC_MAX; i += blockDim.x) (&w_vis[0][0])[i] = 1;
+    for (int i = tid; i < 2 * EFC_MAX; i += blockDim.x) {
+        (&w_key[0][0])[i] = 0;
+        (&w_vis[0][0])[i] = 1;
+    }
     __syncthreads();
+
+    struct List {  // of a node: neighbour `lane` (any value from the list's end on) and the list's length, as they come from memory
+        int32_t x, deg;
+    };
+    int zero = 0;
+    asm volatile("" : "+v"(zero));  // a scalar load of the length would make the LDS reads behind it wait for memory
+    auto list_of = [&](int u) -> List {  // deg <= M: lists are under the cap between batches
+        return {s.adj[(size_t)u * s.stride + min(lane, s.stride - 1)], s.deg[u + zero]};
+    };
+    auto mark = [&](int32_t x) -> bool {  // x has not been met before
+        if (words > 0) return !(atomicOr(&seen[x >> 5], 1u << (x & 31)) >> (x & 31) & 1u);
+        if (x == 0 || stamp[x] == (uint16_t)epoch) return false;
+        stamp[x] = (uint16_t)epoch;
+        return true;
+    };
+    auto start_hop = [&](uint64_t node, const List &l) {  // wavefront 0: the neighbours to be scored
+        const bool on = node != 0 && lane < l.deg && mark(l.x);
+        const unsigned long long fresh = __ballot(on);
+        if (on) new_id[__popcll(fresh & ((1ull << lane) - 1ull))] = l.x;
+        if (lane == 0) {
+            n_new_s = __popcll(fresh);
+            node_s = node;
+        }
+    };
     float dv[4];
     if (wave == 0) {
+        const List l = list_of(0);
         dots.four([&](int) { return s.emb; }, 1, dv);
+        const uint64_t k = queue_key(dv[0], 0);
         if (lane == 0) {
-            w_key[0][0] = queue_key(dv[0], 0);
+            w_key[0][0] = k;
             w_vis[0][0] = 0;
         }
+        start_hop(k, l);
     }
     __syncthreads();
     int n_w = 1, cur = 0;
     for (;;) {
-        // the best entry that has not been expanded: lane l looks at positions 4l .. 4l + 3
-        static_assert(EFC_MAX == 256, "one 32-bit word of marks per lane");
-        const uint32_t z = ~reinterpret_cast<const uint32_t *>(w_vis[cur])[lane] & 0x01010101u;
-        const unsigned long long open = __ballot(z != 0);
-        if (!open) break;
-        const int l = __ffsll((long long)open) - 1;
-        const int pos = l * 4 + (__ffs(__builtin_amdgcn_readlane((int)z, l)) - 1) / 8;
-        if (wave == 0) {
-            const int u = __builtin_amdgcn_readfirstlane((int)key_id(w_key[cur][pos]));
-            const int32_t *nb = s.adj + (size_t)u * s.stride;
-            int32_t x = lane < s.stride ? nb[lane] : -1;
-            if (lane >= s.deg[u]) x = -1;  // deg <= M: lists are under the cap between batches
-            if (words > 0) {
-                if (x >= 0 && (atomicOr(&seen[x >> 5], 1u << (x & 31)) >> (x & 31) & 1u)) x = -1;
-            } else if (x >= 0) {
-                if (x == 0 || stamp[x] == (uint16_t)epoch) x = -1;
-                else stamp[x] = (uint16_t)epoch;
+        const int n_new = __builtin_amdgcn_readfirstlane(n_new_s);
+        const uint64_t node = node_s;  // 0: every entry has been expanded
+        if (node == 0) break;
+        uint64_t runner = 0;
+        List next_list = {0, 0};
+        if (wave == 0) {  // the best entry that has not been expanded, besides this hop's: lane l looks at positions 4l .. 4l + 3
+            static_assert(EFC_MAX == 256, "four entries per lane");
+            const uint32_t open = ~reinterpret_cast<const uint32_t *>(w_vis[cur])[lane];
+            uint64_t first = 0;
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                const uint64_t k = w_key[cur][4 * lane + i];
+                if ((open >> (8 * i) & 1u) && k != node) first = k;
             }
-            const unsigned long long fresh = __ballot(x >= 0);
-            if (x >= 0) new_id[__popcll(fresh & ((1ull << lane) - 1ull))] = x;
-            if (lane == 0) n_new_s = __popcll(fresh);
+            const unsigned long long any = __ballot(first != 0);
+            if (any) {
+                runner = key_of_lane(first, __ffsll((long long)any) - 1);
+                next_list = list_of((int)key_id(runner));
+            }
+            if (lane >= n_new) new_key[lane] = 0;  // the padding of keys_above
         }
-        __syncthreads();
-        const int n_new = n_new_s;
-        if (n_new == 0) {
-            if (tid == 0) w_vis[cur][pos] = 1;
-            __syncthreads();
-            continue;
-        }
-        for (int i0 = wave; i0 < n_new; i0 += 4 * nw) {
+        for (int i0 = wave > 0 ? wave - 1 : nw - 1; i0 < n_new; i0 += 4 * nw) {
             const int c = min(4, (n_new - i0 + nw - 1) / nw);
             dots.four([&](int k) { return row_of(s, new_id[i0 + k * nw]); }, c, dv);
 #pragma unroll
@@ -173,29 +200,54 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_search_select_kernel(Bui
                 if (k < c && lane == 0) new_key[i0 + k * nw] = queue_key(dv[k], (uint32_t)new_id[i0 + k * nw]);
         }
         __syncthreads();
-        // merge: an entry moves down by the number of better newcomers, a newcomer lands behind everything better
-        const int nxt = cur ^ 1;
         const uint64_t fresh_key = lane < n_new ? new_key[lane] : 0;
-        for (int i = tid; i < n_w; i += blockDim.x) {
-            const uint64_t k = w_key[cur][i];
-            int p = i;
-            for (int j = 0; j < n_new; ++j) p += new_key[j] > k;
-            if (p < s.efC) {
-                w_key[nxt][p] = k;
-                w_vis[nxt][p] = w_vis[cur][i] | (uint8_t)(i == pos);
+        const int nxt = cur ^ 1;
+        if (wave == 0) {
+            uint64_t best = wave_max_key(fresh_key);
+            if (n_w == s.efC && best < w_key[cur][s.efC - 1]) best = 0;  // does not get into the queue
+            // a runner-up that is better than every newcomer stays in the queue
+            const uint64_t next = max(best, runner);
+            if (next != runner) next_list = list_of((int)key_id(next));
+            start_hop(next, next_list);
+        } else {
+            // Merge.  An entry moves down by the number of better newcomers.  Where there are lanes enough, four share an entry.
+            const int share = (nw - 1) * 16 >= n_w ? 2 : 0;
+            for (int e = tid - 64; e < n_w << share; e += blockDim.x - 64) {
+                const int i = e >> share;
+                const uint64_t k = w_key[cur][i];
+                const uint8_t vis = w_vis[cur][i];
+                int p = i;
+                if (share) {
+                    int above = 0;
+                    for (int j = e & 3; j < n_new; j += 16)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) above += new_key[j + 4 * t] > k;
+                    above += (int)dpp_mov<DPP_QUAD_XOR1>((uint32_t)above);
+                    above += (int)dpp_mov<DPP_QUAD_XOR2>((uint32_t)above);
+                    p += above;
+                } else {
+                    p += keys_above(new_key, n_new, k);
+                }
+                if ((share == 0 || (e & 3) == 0) && p < s.efC) {
+                    w_key[nxt][p] = k;
+                    w_vis[nxt][p] = vis | (uint8_t)(k == node);
+                }
             }
-        }
-        uint64_t own[EFC_MAX / 64];
+            // A newcomer lands behind everything better, old or new; the wavefronts that have no entries begin.
+            if (nw - 1 - wave < n_new) {
+                uint64_t own[EFC_MAX / 64];
 #pragma unroll
-        for (int j = 0; j < EFC_MAX / 64; ++j) own[j] = j * 64 + lane < n_w ? w_key[cur][j * 64 + lane] : 0;
-        for (int i = wave; i < n_new; i += nw) {
-            const uint64_t k = new_key[i];
-            int p = __popcll(__ballot(fresh_key > k));
+                for (int j = 0; j < EFC_MAX / 64; ++j) own[j] = w_key[cur][j * 64 + lane];
+                for (int i = nw - 1 - wave; i < n_new; i += nw - 1) {
+                    const uint64_t k = key_of_lane(fresh_key, i);
+                    int p = __popcll(__ballot(fresh_key > k));
 #pragma unroll
-            for (int j = 0; j < EFC_MAX / 64; ++j) p += __popcll(__ballot(own[j] > k));
-            if (p < s.efC && lane == 0) {
-                w_key[nxt][p] = k;
-                w_vis[nxt][p] = 0;
+                    for (int j = 0; j < EFC_MAX / 64; ++j) p += __popcll(__ballot(own[j] > k));
+                    if (p < s.efC && lane == 0) {
+                        w_key[nxt][p] = k;
+                        w_vis[nxt][p] = 0;
+                    }
+                }
             }
         }
         n_w = min(n_w + n_new, s.efC);
@@ -229,7 +281,7 @@ __global__ __launch_bounds__(64) void build_commit_kernel(BuildState s, int64_t 
 
 // One block per node that received reverse edges: put the new edges in id order (the order of insertion), and if the
 // list exceeds M shrink it with the RNG rule anchored at the node (up to M * cnt / 2 similarities, shared by the block's
-// wavefronts: 22 us per batch at the sizes above, 347 with one wavefront).
+// wavefronts: 20 us per batch at the sizes above, 347 with one wavefront).
 template <int NV>
 __global__ __launch_bounds__(64 * WAVES_MAX) void build_reverse_kernel(BuildState s)
 {
@@ -264,12 +316,12 @@ __global__ __launch_bounds__(64 * WAVES_MAX) void build_reverse_kernel(BuildStat
         for (int k = 0; k < 4; ++k)
             if (k < c && lane == 0) key[i0 + k * nw] = queue_key(dv[k], (uint32_t)list[i0 + k * nw]);
     }
+    static_assert(LIST_MAX % 8 == 0, "keys_above's padding");
+    if (tid < (-cnt & 7)) key[cnt + tid] = 0;
     __syncthreads();
     for (int i = tid; i < cnt; i += blockDim.x) {
         const uint64_t k = key[i];
-        int rank = 0;
-        for (int j = 0; j < cnt; ++j) rank += key[j] > k;
-        sorted[rank] = k;
+        sorted[keys_above(key, cnt, k)] = k;
     }
     __syncthreads();
     const int kept = block_shrink<NV>(s, sorted, cnt, s.M, kept_ids, flags);
