@@ -51,7 +51,8 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    itself; p - 2^-16 |p| grows with p, so the second minimum's share covers all other centroids.  A gap of more than
 //    2^-16 (5.5 U + |minimum| + |second|) therefore leaves no doubt.  The other rows (few on embeddings; all of them where anything
 //    could overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
-// So the result is s(c)'s for every input.  186 us on average at 65536 to 100000 rows, d = 768, 32 subspaces.
+// So the result is s(c)'s for every input.  163 us on average at 65536 to 100000 rows, d = 768, 32 subspaces (187 with five
+// instructions per value and twice as many blocks).
 constexpr int ASSIGN_THREADS = 512;
 
 __host__ __device__ constexpr int assign_smem(int ks, int dsub)
@@ -60,7 +61,7 @@ __host__ __device__ constexpr int assign_smem(int ks, int dsub)
 }
 
 template <int KS>  // 16-element steps of the (zero-padded) sub-vector
-__global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__restrict__ x, int64_t n, int d, int m_sub,
+__global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *__restrict__ x, int64_t n, int d, int m_sub,
                                                                 const float *__restrict__ codebook, int64_t rows_per_block, int xcd_bits,
                                                                 uint8_t *__restrict__ out, int64_t row_pitch, int64_t m_pitch)
 {
@@ -149,6 +150,18 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
             X[g] = sqrtf(__uint_as_float(p[0]) + __uint_as_float(p[1]));
             m1[g] = m2[g] = INFINITY;
         }
+        // A tile's fragments are read while the vector ALU goes through the tile before.
+        bf16x8 ch[KS], cl[KS];
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                ch[ks] = *reinterpret_cast<const bf16x8 *>(frag + (ks * KSUB + t * 32 + l32) * 16 + half * 8);
+                cl[ks] = *reinterpret_cast<const bf16x8 *>(frag + ((KS + ks) * KSUB + t * 32 + l32) * 16 + half * 8);
+            }
+        };
+        fetch(0);
+        uint32_t keep = ~0x7fu;
+        asm("" : "+v"(keep));  // a literal and a scalar register do not fit into one instruction
 #pragma unroll 1  // unrolled, the fragments of several tiles are held at once and spill
         for (int t = 0; t < KSUB / 32; ++t) {
             f32x16 acc[2];
@@ -160,23 +173,29 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(const float *__r
             }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 ah = *reinterpret_cast<const bf16x8 *>(frag + (ks * KSUB + t * 32 + l32) * 16 + half * 8);
-                const bf16x8 al = *reinterpret_cast<const bf16x8 *>(frag + ((KS + ks) * KSUB + t * 32 + l32) * 16 + half * 8);
+#pragma unroll
+                for (int g = 0; g < 2; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch[ks], bh[g][ks], acc[g], 0, 0, 0);
+#pragma unroll
+                for (int g = 0; g < 2; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch[ks], bl[g][ks], acc[g], 0, 0, 0);
+#pragma unroll
+                for (int g = 0; g < 2; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl[ks], bh[g][ks], acc[g], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(min(t + 1, KSUB / 32 - 1));
+            asm volatile("" ::: "memory");  // here, not where they are used
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {  // register r: centroid 32t + 8(r/4) + 4 half + r%4
+                // The index in a scalar register, and the minimum by its instruction: three instructions per value.  Otherwise the
+                // compiler adds the index in two and quiets both operands of the minimum.
+                uint32_t index = t * 16 + r;
+                asm("" : "+s"(index));
 #pragma unroll
                 for (int g = 0; g < 2; ++g) {
-                    acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[g][ks], acc[g], 0, 0, 0);
-                    acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[g][ks], acc[g], 0, 0, 0);
-                    acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[g][ks], acc[g], 0, 0, 0);
+                    const float v = __uint_as_float((__float_as_uint(acc[g][r]) & keep) | index);
+                    m2[g] = __builtin_amdgcn_fmed3f(m1[g], m2[g], v);
+                    asm("v_min_f32 %0, %1, %2" : "=v"(m1[g]) : "v"(m1[g]), "v"(v));
                 }
             }
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {  // register r: centroid 32t + 8(r/4) + 4 half + r%4
-                    const float v = __uint_as_float((__float_as_uint(acc[g][r]) & ~0x7fu) | (uint32_t)(t * 16 + r));
-                    m2[g] = __builtin_amdgcn_fmed3f(m1[g], m2[g], v);
-                    m1[g] = __builtin_amdgcn_fmed3f(m1[g], v, -INFINITY);
-                }
         }
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
@@ -325,45 +344,67 @@ __global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restr
 // Centroid (c = blockIdx.x, m = blockIdx.y) <- mean of its training rows.  The sum's order is fixed: partial sum p adds the
 // rows with r % 256 == p in ascending order, then the 256 partial sums are added pairwise (p, p + 128), (p, p + 64), ...
 // The partial sums are in LDS; a group of 32 lanes (one per element) adds the rows with r % 8 equal to the group's number.
-// Reads every training row once per round: 137 us at 65536 rows, d = 768, 32 subspaces, where a block per centroid that
-// looked through all assignments for its own rows took 1676.
+// Latency bounds it (row numbers, then the rows' pieces from beyond L2): 256 row numbers are looked through at a time and each
+// group's rows listed first, so that a group has UPDATE_AHEAD of them in flight however they are spread.  Reads every training
+// row once per round: 93 us at 65536 rows, d = 768, 32 subspaces (132 with 32 row numbers at a time, four rows in flight and a
+// step of the pairwise sum per barrier).
+constexpr int UPDATE_AHEAD = 16;
+
 __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ xt, int64_t nt, int d, int m_sub,
                                                      const int32_t *__restrict__ order, const int32_t *__restrict__ first,
                                                      float *__restrict__ codebook)
 {
-    extern __shared__ float part[];  // [256][dsub]
+    extern __shared__ __attribute__((aligned(16))) float part[];  // [256][dsub]
+    __shared__ int32_t mine[8][256 + UPDATE_AHEAD];  // a group's rows among the 256, any valid row behind them
     const int c = blockIdx.x, m = blockIdx.y, dsub = d / m_sub, tid = threadIdx.x;
     const int lane32 = tid & 31, group = tid >> 5, shift = tid & 32;
     const int beg = first[(size_t)m * (KSUB + 1) + c], cnt = first[(size_t)m * (KSUB + 1) + c + 1] - beg;
     if (cnt == 0) return;  // an empty cluster keeps its centroid
-    for (int i = tid; i < 256 * dsub; i += 256) part[i] = 0.f;
-    __syncthreads();
     const int32_t *rows = order + (size_t)m * nt + beg;
-    const float *xm = xt + (size_t)m * dsub + lane32;
-    for (int i0 = 0; i0 < cnt; i0 += 32) {
-        const int r = i0 + lane32 < cnt ? rows[i0 + lane32] : -1;
-        uint32_t mine = (uint32_t)(__ballot(r >= 0 && (r & 7) == group) >> shift);
-        while (__any(mine != 0)) {  // eight rows' loads at a time, added in order
-            int rr[8];
-            float v[8];
+    const float *xm = xt + (size_t)m * dsub + min(lane32, dsub - 1);
+    int32_t r[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int l = mine ? __ffs(mine) - 1 : 0;
-                rr[k] = __shfl(r, shift + l, 64);
-                if (mine == 0) rr[k] = -1;
-                mine &= mine - 1;
-                v[k] = rr[k] >= 0 && lane32 < dsub ? xm[(size_t)rr[k] * d] : 0.f;
-            }
+    for (int k = 0; k < 8; ++k) r[k] = rows[min(k * 32 + lane32, cnt - 1)];
+    for (int i = tid; i < 256 * dsub; i += 256) part[i] = 0.f;
+    for (int i = tid; i < 8 * (256 + UPDATE_AHEAD); i += 256) (&mine[0][0])[i] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < cnt; i0 += 256) {
+        int n_mine = 0;  // the same for the group's 32 lanes
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (rr[k] >= 0 && lane32 < dsub) part[(rr[k] & 255) * dsub + lane32] += v[k];
+        for (int k = 0; k < 8; ++k) {
+            const bool on = i0 + k * 32 + lane32 < cnt && (r[k] & 7) == group;
+            const uint32_t mask = (uint32_t)(__ballot(on) >> shift);
+            if (on) mine[group][n_mine + __popc(mask & ((1u << lane32) - 1u))] = r[k];
+            n_mine += __popc(mask);
         }
+        if (i0 + 256 < cnt)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) r[k] = rows[min(i0 + 256 + k * 32 + lane32, cnt - 1)];
+        __builtin_amdgcn_wave_barrier();  // LDS serves a wavefront's accesses in order
+        for (int j0 = 0; __any(j0 < n_mine); j0 += UPDATE_AHEAD) {
+            int rr[UPDATE_AHEAD];
+            float v[UPDATE_AHEAD];
+#pragma unroll
+            for (int k = 0; k < UPDATE_AHEAD; ++k) rr[k] = mine[group][min(j0, 256) + k];
+#pragma unroll
+            for (int k = 0; k < UPDATE_AHEAD; ++k) v[k] = xm[(size_t)rr[k] * d];
+#pragma unroll
+            for (int k = 0; k < UPDATE_AHEAD; ++k)
+                if (j0 + k < n_mine && lane32 < dsub) part[(rr[k] & 255) * dsub + lane32] += v[k];
+        }
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        for (int i = tid; i < o * dsub; i += 256) part[i] += part[i + o * dsub];
-        __syncthreads();
-    }
+    // two steps of the pairwise sum at a time
+    auto halve_twice = [&](auto *sum, int width) {
+        for (int o = 64; o > 0; o >>= 2) {
+            for (int i = tid; i < o * width; i += 256)
+                sum[i] = (sum[i] + sum[i + 2 * o * width]) + (sum[i + o * width] + sum[i + 3 * o * width]);
+            __syncthreads();
+        }
+    };
+    if ((dsub & 3) == 0) halve_twice(reinterpret_cast<f32x4 *>(part), dsub >> 2);
+    else halve_twice(part, dsub);
     if (tid < dsub) codebook[((size_t)m * KSUB + c) * dsub + tid] = part[tid] / (float)cnt;
 }
 
@@ -564,7 +605,8 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
     if (bad) *err = 1;
 }
 
-// A few blocks per CU, each with a multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
+// Two blocks per CU, as many as stay there at once (four, one round after the other, pay the set-up twice: 173 us, not 162), each with a
+// multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
 // where there are rows enough, so that the XCDs get even shares (rounded down: up, 24 subspaces were 6 % slower); with fewer than
 // 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch,
 // 1000 rows of 192 subspaces of one 49; where all subspaces of a run were on one XCD however few the runs (two in both cases),
@@ -573,7 +615,7 @@ void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, 
                    int64_t row_pitch, int64_t m_pitch)
 {
     const int dsub = d / m_sub;
-    const int64_t want = std::max<int64_t>(8, 4 * ctx->num_cus / m_sub / 8 * 8);
+    const int64_t want = std::max<int64_t>(8, 2 * ctx->num_cus / m_sub / 8 * 8);
     const int64_t rows = ((n + want - 1) / want + ASSIGN_THREADS - 1) / ASSIGN_THREADS * ASSIGN_THREADS;
     const int64_t runs = (n + rows - 1) / rows;
     const int xcd_bits = runs >= 8 ? 3 : 0;

@@ -195,6 +195,28 @@ def test_build_pq_exact_on_integer_rows(L, ctx, n, d, m_sub, offset):
         np.testing.assert_array_equal(codesb[rows], want[rows])
 
 
+@pytest.mark.parametrize("n,dsub,longest", [(3000, 4, 255), (3000, 3, 256), (3000, 24, 257), (9000, 32, 6000), (3000, 1, 2999)])
+def test_pq_means_of_long_row_lists(L, ctx, n, dsub, longest):
+    """Means of centroids with many rows, with as many as are looked through at a time, and one more or fewer: `longest` rows are one
+    point and the others lie far from it and from each other.  Integer-valued, so every sum is exact."""
+    say(f"pq means n={n} dsub={dsub} longest list {longest}")
+    rng = np.random.default_rng(longest)
+    x = np.zeros((n, dsub), np.float32)
+    x[:, 0] = 100 + 10 * np.arange(n)
+    one = rng.permutation(n)[:longest]
+    x[one] = 3
+    x[one, -1] += rng.integers(-1, 2, longest)  # three points, their nearest centroids the first training rows among them
+    cb0, codes0 = codes_of_first_centroids(L, ctx, x, 1)
+    pq = L.leann_build_pq(ctx, to_dev(x), 1, 1, 7)
+    cb1, _ = L.leann_pq_export(ctx, pq)
+    L.leann_pq_free(pq)
+    want = cb0[0].copy()
+    for c in np.unique(codes0):
+        own = x[codes0[:, 0] == c]
+        want[c] = own.sum(0, dtype=np.float64).astype(np.float32) / np.float32(len(own))
+    np.testing.assert_array_equal(cb1[0], want)
+
+
 def nearest_by_fp32_sums(rows, cb):
     """Codes by the definition: s(c) = sum over j, ascending, of (x_j - c_j)^2 in fp32 with fused multiply-adds; the smallest
     finite sum, the lowest index among equals, 0 if there is none.  The fused operation is emulated in float64: the
