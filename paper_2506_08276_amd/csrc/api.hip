@@ -230,7 +230,7 @@ void leann_destroy(leann_ctx *ctx)
     (void)hipStreamSynchronize(ctx->stream);
     DevBuf *bufs[] = {&ctx->w_bf16, &ctx->w_f32, &ctx->x, &ctx->qkv, &ctx->att, &ctx->delta, &ctx->hid, &ctx->cu,
                       &ctx->len, &ctx->meta, &ctx->enc_ids, &ctx->s_state, &ctx->s_emb, &ctx->s_lut, &ctx->s_seen,
-                      &ctx->s_misc, &ctx->s_owner, &ctx->s_buf, &ctx->s_memo_slot, &ctx->s_memo_emb};
+                      &ctx->s_misc, &ctx->s_owner, &ctx->s_buf, &ctx->s_memo_slot, &ctx->s_memo_emb, &ctx->pq_work};
     for (DevBuf *b : bufs) b->release();
     ctx->prof_tokens.release();
     if (ctx->host_counters) (void)hipHostFree(ctx->host_counters);

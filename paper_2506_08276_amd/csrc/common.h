@@ -65,6 +65,7 @@ struct leann_ctx {
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
     // search workspace
+    DevBuf pq_work;  // scratch of leann_build_pq (at most 65536 rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
     int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags

@@ -647,6 +647,20 @@ uint64_t splitmix64(uint64_t &st)
     return z ^ (z >> 31);
 }
 
+// Seeded Fisher-Yates permutation of 0 .. n - 1: its first nt entries.  Index: as narrow as n allows (the swaps are random reads
+// and writes of the whole permutation).
+template <class Index>
+std::vector<int64_t> training_rows(int64_t n, int64_t nt, uint64_t seed)
+{
+    std::vector<Index> perm((size_t)n);
+    for (int64_t i = 0; i < n; ++i) perm[i] = (Index)i;
+    for (int64_t i = n - 1; i >= 1; --i) {
+        const uint64_t j = splitmix64(seed) % (uint64_t)(i + 1);
+        std::swap(perm[i], perm[j]);
+    }
+    return std::vector<int64_t>(perm.begin(), perm.begin() + nt);
+}
+
 int check_pq_shape(int64_t n, int32_t d, int32_t m_sub)
 {
     if (n < 1 || d < 1 || m_sub < 1 || d % m_sub) {
@@ -737,15 +751,8 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     LEANN_TRY(check_pq_shape(n, d, m_sub));
     LEANN_HIP(hipSetDevice(ctx->device));
     const int dsub = d / m_sub;
-    // seeded Fisher-Yates permutation; its prefix is the training sample, its first 256 rows the initial centroids
-    std::vector<int64_t> perm((size_t)n);
-    for (int64_t i = 0; i < n; ++i) perm[i] = i;
-    uint64_t st = seed;
-    for (int64_t i = n - 1; i >= 1; --i) {
-        uint64_t j = splitmix64(st) % (uint64_t)(i + 1);
-        std::swap(perm[i], perm[j]);
-    }
     const int64_t nt = n < MAX_TRAIN ? n : MAX_TRAIN;
+    const std::vector<int64_t> train = n <= 0xffffffffll ? training_rows<uint32_t>(n, nt, seed) : training_rows<int64_t>(n, nt, seed);
     leann_pq *pq = nullptr;
     LEANN_TRY(alloc_pq(ctx, n, d, m_sub, true, &pq));
     // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts | counts
@@ -759,21 +766,17 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     const size_t o_assign = carve((size_t)nt * m_sub), o_order = carve((size_t)nt * m_sub * sizeof(int32_t));
     const size_t o_first = carve((size_t)m_sub * (KSUB + 1) * sizeof(int32_t));
     const size_t o_counts = carve((size_t)m_sub * GROUP_RUNS * KSUB * sizeof(int32_t));
-    unsigned char *scr = nullptr;
     auto fail = [&](int code) {
-        (void)hipFree(scr);
         leann_pq_free(pq);
         return code;
     };
-    if (hipMalloc(&scr, off) != hipSuccess) {
-        leann_set_error("device allocation for PQ training failed");
-        return fail(LEANN_ENOMEM);
-    }
+    if (ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
+    unsigned char *scr = (unsigned char *)ctx->pq_work.p;
     int64_t *rows_dev = (int64_t *)(scr + o_rows);
     float *xt = (float *)(scr + o_xt);
     uint8_t *assign = scr + o_assign;
     int32_t *order = (int32_t *)(scr + o_order), *first = (int32_t *)(scr + o_first), *counts = (int32_t *)(scr + o_counts);
-    if (hipMemcpyAsync(rows_dev, perm.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) !=
+    if (hipMemcpyAsync(rows_dev, train.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) !=
         hipSuccess)
         return fail(LEANN_EDEVICE);
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)nt), dim3(256), 0, ctx->stream, emb_dev, rows_dev, nt, d, xt);
@@ -791,7 +794,6 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
         leann_set_error("PQ training kernels failed");
         return fail(LEANN_EDEVICE);
     }
-    (void)hipFree(scr);
     *out = pq;
     return LEANN_OK;
 }
