@@ -17,7 +17,10 @@
 namespace {
 
 // ------------------------------------------------------------------ pass set-up
-// lengths of the requested chunks -> exclusive prefix sum cu[0..n], cu[n] = T.  One block of 1024 threads.
+// lengths of the requested chunks -> exclusive prefix sum cu[0..n], cu[n] = T.  One block of 1024 threads, or of PREP_FEW for up to
+// as many chunks: a wavefront's scan without barriers, in the passes where a microsecond counts.
+constexpr int PREP_FEW = 64;
+
 __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ lengths, const int64_t *__restrict__ ids,
                                                     int64_t first_id, int n, int64_t n_store, int seq,
                                                     int32_t *__restrict__ cu, int64_t *__restrict__ chunk_of,
@@ -26,10 +29,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ 
 {
     __shared__ int part[1024];
     const int tid = threadIdx.x;
-    const int per = (n + 1023) / 1024;
-    const int beg = tid * per, end = min(n, beg + per);
-    int s = 0;
-    for (int i = beg; i < end; ++i) {
+    auto chunk_length = [&](int i) -> int {
         int64_t id = ids ? ids[i] : first_id + i;
         int len = 0;
         if (id < 0 || id >= n_store) {
@@ -43,6 +43,30 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t *__restrict__ 
             }
         }
         chunk_of[i] = id;
+        return len;
+    };
+    if (n <= PREP_FEW) {
+        const int len = tid < n ? chunk_length(tid) : 0;
+        int up_to = len;
+#pragma unroll
+        for (int o = 1; o < PREP_FEW; o <<= 1) {
+            const int before = __shfl_up(up_to, o, 64);
+            if (tid >= o) up_to += before;
+        }
+        if (tid < n) cu[tid] = up_to - len;
+        if (tid == n - 1) {
+            cu[n] = up_to;
+            if (report) err[PASS_TOKENS] = up_to;
+            if (tok_count) *tok_count += up_to;
+            if (tok_count2) *tok_count2 += up_to;
+        }
+        return;
+    }
+    const int per = (n + 1023) / 1024;
+    const int beg = tid * per, end = min(n, beg + per);
+    int s = 0;
+    for (int i = beg; i < end; ++i) {
+        const int len = chunk_length(i);
         cu[i] = len;  // temporarily the length
         s += len;
     }
@@ -433,7 +457,7 @@ __global__ __launch_bounds__(256, NKT == 4 ? 3 : 2) void attention_kernel(const 
 // One block per chunk.  Wave w sums rows w, w + 4, ... with 16-byte loads (a lane owns pieces j*64 + lane of a row, as
 // in the LayerNorm kernels); the four partial sums of a column are added in wave order, so the result does not depend
 // on anything but the chunk.
-constexpr int POOL_AHEAD = 4;
+constexpr int POOL_AHEAD = 8;
 
 __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x, const int32_t *__restrict__ cu, int d,
                                                    float *__restrict__ out)
@@ -448,27 +472,25 @@ __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x,
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[j][i] = 0.f;
-    // POOL_AHEAD rows are read, then added in order.  The reads are guarded one by one and the compiled code waits for each before
-    // the next: what is in flight is the wavefronts' loads side by side, not a wavefront's rows.
+    // POOL_AHEAD rows are in flight, then added in order.  Rows past the end and pieces past the row's are read from the last one
+    // and not used: a test per read would have every read wait for the one before.
+    const bf16_t *x0 = x + (size_t)t0 * d + lane * 8, *x1 = x + (size_t)t0 * d + min(64 + lane, pieces - 1) * 8;
+    if (lane >= pieces) x0 = x1;
     for (int t = wave; t < L; t += 4 * POOL_AHEAD) {
         bf16x8 r[POOL_AHEAD][2];
 #pragma unroll
-        for (int k = 0; k < POOL_AHEAD; ++k)
-            if (t + 4 * k < L) {
-                const bf16_t *xr = x + (size_t)(t0 + t + 4 * k) * d;
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (j * 64 + lane < pieces) r[k][j] = *reinterpret_cast<const bf16x8 *>(xr + (j * 64 + lane) * 8);
-            }
+        for (int k = 0; k < POOL_AHEAD; ++k) {
+            const size_t row = (size_t)min(t + 4 * k, L - 1) * d;
+            r[k][0] = *reinterpret_cast<const bf16x8 *>(x0 + row);
+            r[k][1] = *reinterpret_cast<const bf16x8 *>(x1 + row);
+        }
 #pragma unroll
         for (int k = 0; k < POOL_AHEAD; ++k)
             if (t + 4 * k < L) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    if (j * 64 + lane < pieces) {
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) acc[j][i] += (float)r[k][j][i];
-                    }
+                    for (int i = 0; i < 8; ++i) acc[j][i] += (float)r[k][j][i];
             }
     }
 #pragma unroll
@@ -707,7 +729,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         const int32_t *T_dev = cu + m;
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
-            hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, ctx->stream, chunks->lengths,
+            hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(m <= PREP_FEW ? PREP_FEW : 1024), 0, ctx->stream, chunks->lengths,
                                ids_dev ? ids_dev + s : nullptr, first_id + s, m, chunks->n, seq, cu, chunk_of, ctx->host_flags,
                                tok_count_dev, ctx->prof_on ? (int64_t *)ctx->prof_tokens.p : nullptr, ask);
         }

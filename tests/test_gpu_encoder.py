@@ -63,6 +63,29 @@ def test_batch_composition_and_pass_invariance(L, tiny):
     assert torch.equal(first, full[:10])
 
 
+@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 128), (640, 10, 128)])
+def test_pooled_rows_and_few_chunks_against_oracle(L, orc, hidden, heads, ffn):
+    """Means over one row, over as many as are read ahead, one more and one fewer, over rows of less than and more than a
+    wavefront's pieces; passes of as many chunks as one wavefront scans and of one more."""
+    cfg = dict(vocab=500, max_pos=160, hidden=hidden, layers=1, heads=heads, ffn=ffn, ln_eps=1e-12)
+    w = li.encoder_weights(cfg, 9, perturb=True)
+    tokens, lengths = li.uniform_chunks(65, 130, 1, 500, 1, 130, 4)
+    lengths[:12] = [1, 2, 4, 5, 31, 32, 33, 63, 64, 65, 127, 130]
+    say(f"pooled rows, hidden {hidden}")
+    ctx = L.leann_create(cfg, to_dev(w))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        got = L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy()
+        few = L.leann_embed(ctx, t, l, n_ids=64, hidden=hidden).cpu().numpy()
+        one = L.leann_embed(ctx, t, l, n_ids=1, hidden=hidden).cpu().numpy()
+    finally:
+        L.leann_destroy(ctx)
+    want = orc.embed(orc.desc(**cfg), w, tokens, lengths)
+    assert np.abs(got - want).max() <= TOL_FP32
+    np.testing.assert_array_equal(few, got[:64])
+    np.testing.assert_array_equal(one, got[:1])
+
+
 def test_padding_content_is_ignored(L, tiny):
     import torch
     say("padding invariance")
