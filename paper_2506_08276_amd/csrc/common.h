@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -46,6 +47,8 @@ struct DevBuf {
     void release();
 };
 
+constexpr size_t PQ_WORK_KEEP = (size_t)1 << 30;  // what rows of 1024 elements need, with room: 0.6 GB at one subspace per element
+
 struct leann_ctx {
     leann_encoder_desc desc;
     int device = 0;
@@ -64,8 +67,11 @@ struct leann_ctx {
     int32_t gemm_small_rows = 2048;  // passes of at most this many rows may use tiles of 64x64 and smaller
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
+    // scratch of leann_build_pq (at most 65536 rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call.  Calls on several
+    // threads take turns with it (each waits for its stream before it leaves), and what is larger than PQ_WORK_KEEP is given back.
+    DevBuf pq_work;
+    std::mutex pq_work_mutex;
     // search workspace
-    DevBuf pq_work;  // scratch of leann_build_pq (at most 65536 rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
     int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags

@@ -770,6 +770,14 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
         leann_pq_free(pq);
         return code;
     };
+    std::lock_guard<std::mutex> turn(ctx->pq_work_mutex);
+    struct GiveBack {
+        DevBuf &work;
+        ~GiveBack()
+        {
+            if (work.bytes > PQ_WORK_KEEP) work.release();
+        }
+    } give_back{ctx->pq_work};
     if (ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
     unsigned char *scr = (unsigned char *)ctx->pq_work.p;
     int64_t *rows_dev = (int64_t *)(scr + o_rows);

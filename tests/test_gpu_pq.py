@@ -242,6 +242,34 @@ def nearest_by_fp32_sums(rows, cb):
     return out
 
 
+def test_tables_trained_by_several_threads(L, ctx):
+    """Calls on one context from several threads, their sizes growing: each table is the one that a call alone gives."""
+    import threading
+    say("pq training, three threads")
+    rows = [to_dev(unit_rows(n, 48, n)) for n in (700, 3000, 9000)]
+
+    def train(x):
+        pq = L.leann_build_pq(ctx, x, 6, 3, 5)
+        out = L.leann_pq_export(ctx, pq)
+        L.leann_pq_free(pq)
+        return out
+
+    got = [None] * 3
+
+    def work(i):
+        got[i] = train(rows[i])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for x, (cb, codes) in zip(rows, got):
+        cb1, codes1 = train(x)
+        np.testing.assert_array_equal(cb, cb1)
+        np.testing.assert_array_equal(codes, codes1)
+
+
 def codes_of_first_centroids(L, ctx, x, m_sub):
     """(codebook, codes) after no training round: the centroids are 256 of the rows."""
     pq = L.leann_build_pq(ctx, to_dev(x), m_sub, 0, 7)
