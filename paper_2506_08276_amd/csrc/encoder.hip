@@ -580,13 +580,13 @@ SmallPlan plan_small(const leann_ctx *ctx, int tmb, int tnb, int rows, int N)
 
 template <int TMB, int TNB, int EPI>
 int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
-                      const int32_t *T_dev, int max_rows, int N, int K, int xr)
+                      const int32_t *T_dev, int max_rows, int likely_rows, int N, int K, int xr)
 {
     typedef SmallCfg<TMB, TNB> Cfg;
     const int rt = (max_rows + 32 * TMB - 1) / (32 * TMB), ct = N / (32 * TNB), xc = 8 / xr;
     ProfScope prof(ctx, prof_kind);
-    hipLaunchKernelGGL((gemm_small_kernel<TMB, TNB, EPI>), dim3(8 * ((ct + xc - 1) / xc) * ((rt + xr - 1) / xr)), dim3(Cfg::THREADS),
-                       Cfg::SMEM, ctx->stream, A, W, bias, out, T_dev, N, K, xr);
+    hipLaunchKernelGGL((gemm_small_kernel<TMB, TNB, EPI>), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
+                       Cfg::SMEM, ctx->stream, A, W, bias, out, T_dev, max_rows, likely_rows, N, K, __builtin_ctz(xr));
     LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
@@ -619,7 +619,7 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const 
     {                                                                                                               \
         const SmallPlan p = plan_small(ctx, TMB, TNB, rows, N);                                                     \
         if (p.rounds == 1)                                                                                          \
-            return launch_gemm_small<TMB, TNB, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K, p.xr);  \
+            return launch_gemm_small<TMB, TNB, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, rows, N, K, p.xr);  \
     }
         LEANN_SMALL(1, 1)
         LEANN_SMALL(2, 1)

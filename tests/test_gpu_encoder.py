@@ -234,6 +234,30 @@ def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
         L.leann_destroy(ctx)
 
 
+@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 128), (384, 6, 1536), (768, 12, 3072)])
+def test_small_passes_of_any_fill_give_the_same_bits(L, hidden, heads, ffn):
+    """A small pass requests its operands for the rows that it likely holds, before it knows how many there are: chunks that are
+    full, hold one token, or are mixed, from one chunk to a few row tiles, one K-slab to 24, give the bits of the 128 x 128 tile."""
+    import torch
+    cfg = dict(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=48, ln_eps=1e-12)
+    n, seq = 21, 48
+    tokens, mixed = li.uniform_chunks(n, seq, 1, cfg["vocab"], 1, seq, 11)
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 12, bf16_exact=True)).to(torch.bfloat16))
+    try:
+        t = to_dev(tokens)
+        for name, lengths in (("full", np.full(n, seq)), ("one token", np.ones(n)), ("mixed", mixed)):
+            say(f"small passes, fill {name}, hidden {hidden}")
+            l = to_dev(lengths.astype(np.int32))
+            L.leann_set_gemm_tiles(ctx, 128, 0)
+            want = L.leann_embed(ctx, t, l, hidden=hidden)
+            L.leann_set_gemm_tiles(ctx, 256, 2048)
+            assert torch.isfinite(want).all()
+            for m in (1, 2, 3, 7, 14, n):
+                assert torch.equal(L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden), want[:m]), m
+    finally:
+        L.leann_destroy(ctx)
+
+
 @pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 512), (384, 6, 1536)])
 def test_pass_without_a_valid_token(L, hidden, heads, ffn):
     """Every requested chunk is outside the store, or its length is: the pass holds no token, whatever product kernel its
