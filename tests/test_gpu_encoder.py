@@ -86,6 +86,28 @@ def test_pooled_rows_and_few_chunks_against_oracle(L, orc, hidden, heads, ffn):
     np.testing.assert_array_equal(one, got[:1])
 
 
+@pytest.mark.parametrize("seq", [128, 256])
+def test_attention_key_counts(L, orc, seq):
+    """Chunks that end before, at and behind every tile of 32 keys, each followed by another chunk's rows: what a chunk's keys end
+    with does not depend on what follows, and the oracle gives the same."""
+    import torch
+    cfg = dict(vocab=500, max_pos=256, hidden=128, layers=2, heads=2, ffn=128, ln_eps=1e-12)
+    lengths = np.array([x for e in range(32, seq + 1, 32) for x in (e - 1, e, e + 1) if x <= seq] + [1, 2, 15, 16, 17], np.int32)
+    tokens = np.random.default_rng(seq).integers(1, 500, (len(lengths), seq)).astype(np.int32)
+    w = li.encoder_weights(cfg, 17, perturb=True)
+    say(f"attention key counts, seq {seq}")
+    ctx = L.leann_create(cfg, to_dev(w))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        got = L.leann_embed(ctx, t, l, hidden=128)
+        for i in range(len(lengths)):
+            alone = L.leann_embed(ctx, t, l, ids=torch.tensor([i], dtype=torch.int64, device="cuda:0"), hidden=128)
+            assert torch.equal(alone[0], got[i]), lengths[i]
+    finally:
+        L.leann_destroy(ctx)
+    assert np.abs(got.cpu().numpy() - orc.embed(orc.desc(**cfg), w, tokens, lengths)).max() <= TOL_FP32
+
+
 def test_padding_content_is_ignored(L, tiny):
     import torch
     say("padding invariance")
