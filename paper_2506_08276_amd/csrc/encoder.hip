@@ -593,7 +593,8 @@ int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16
 }
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
-// Measured per launch, twelve layers' weights in turn, in microseconds (rows x N x K):
+// Measured per launch, twelve layers' weights in turn, in microseconds (rows x N x K; the small-pass kernel takes 0.2 to 1.0 less
+// than here since its slabs are requested before the token count and waited for one by one):
 //                       32x32   64x32   64x64 (small)   64x64   128x128   256x256
 //    80 x  768 x  768     4.2     4.7       5.8           6.2      8.5
 //    80 x  768 x 3072     8.0     9.9      14.9          18.0     26.0
