@@ -11,6 +11,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "advance_plan.h"
 #include "common.h"
 #include "wave.h"
 
@@ -131,7 +132,6 @@ constexpr int ADV_THREADS = 256;
 constexpr int GROUP_HOPS = 16;                 // hops that are prepared together
 constexpr int GROUP_CAND = ADV_THREADS - 64;   // their neighbours (of a row, the first 64) at most
 constexpr int PEND_LDS = 128;                  // pending entries that a running block keeps in LDS
-constexpr int AQ_NEAR_MIN = 32, AQ_NEAR_MAX = 64;  // rows of AQ's columns in LDS
 
 // LDS pointers that say so: of "LDS or memory" by index the compiler otherwise makes one flat access, which waits for both.
 template <class T>
@@ -846,9 +846,6 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace {
 
-constexpr int LDS_LIMIT = 154 * 1024;  // dynamic LDS of advance_kernel, beside its fixed arrays of 6.0 KB
-constexpr int LDS_SHARED = 74 * 1024;  // with two blocks on a CU
-
 // advance_kernel for rows of d elements (the encoder's widths end at 1024)
 auto advance_for(int d) -> decltype(&advance_kernel<2>)
 {
@@ -859,9 +856,16 @@ auto advance_for(int d) -> decltype(&advance_kernel<2>)
 
 int search_init_device()
 {
-    for (int d : {128, 384, 768, 1024})
-        LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(advance_for(d)), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      LDS_LIMIT));
+    for (int d : {128, 384, 768, 1024}) {
+        const void *kernel = reinterpret_cast<const void *>(advance_for(d));
+        hipFuncAttributes attr;
+        LEANN_HIP(hipFuncGetAttributes(&attr, kernel));
+        if (attr.sharedSizeBytes > (size_t)ADV_FIXED) {  // else only the largest tables with long queues would fail to launch
+            leann_set_error("advance_kernel's fixed arrays take %zu bytes of LDS, planned are %d", attr.sharedSizeBytes, ADV_FIXED);
+            return LEANN_EDEVICE;
+        }
+        LEANN_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ADV_DYNAMIC_MAX));
+    }
     return LEANN_OK;
 }
 
@@ -964,13 +968,10 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", table_smem);
         return LEANN_ESHAPE;
     }
-    // what is left holds the head of AQ: as much as lets two blocks share a CU, but no less than AQ_NEAR_MIN rows if there is room
-    const int fixed_smem = m_sub * KSUB * (int)sizeof(float) + ef * 16 + (ef + 255) / 256 * 256;
-    auto rows_in = [&](int limit) { return std::max(0, (limit - fixed_smem) / (64 * 8) - 1); };  // - 1: the pitch is odd
-    s.aq_near = std::min(std::max(std::min(AQ_NEAR_MIN, rows_in(LDS_LIMIT)), rows_in(LDS_SHARED)), AQ_NEAR_MAX);
-    const int adv_smem = fixed_smem + 64 * (s.aq_near | 1) * 8;
-    if (adv_smem > LDS_LIMIT) {  // not with the widths that encoders and PQ tables have: at most 128 subspaces get here
-        leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", adv_smem);
+    const AdvancePlan plan = plan_advance(m_sub, ef);
+    s.aq_near = plan.near;
+    if (plan.bytes > ADV_DYNAMIC_MAX) {  // not with the widths that encoders and PQ tables have: at most 128 subspaces get here
+        leann_set_error("lookup table + queue of %d bytes exceed the LDS budget", plan.bytes);
         return LEANN_ESHAPE;
     }
     const auto advance = advance_for(d);
@@ -1002,7 +1003,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             LEANN_TRY(mark());
             {
                 ProfScope prof(ctx, LEANN_PROF_TRAVERSE);
-                hipLaunchKernelGGL(advance, dim3(g), dim3(ADV_THREADS), adv_smem, st, s, graph->row_ptr, graph->col_idx, n,
+                hipLaunchKernelGGL(advance, dim3(g), dim3(ADV_THREADS), plan.bytes, st, s, graph->row_ptr, graph->col_idx, n,
                                    pq->codes, m_sub, alpha, batch, qg, d, (const float *)ctx->s_emb.p, have_results, ++launches);
             }
             {
