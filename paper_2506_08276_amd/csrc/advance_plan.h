@@ -5,20 +5,32 @@
 constexpr int CU_LDS = 160 * 1024;
 constexpr int ADV_FIXED = 6 * 1024;  // room for the kernel's fixed arrays; search_init_device compares
 constexpr int ADV_DYNAMIC_MAX = CU_LDS - ADV_FIXED;
-constexpr int ADV_DYNAMIC_SHARED = 74 * 1024;      // with two blocks on a CU
-constexpr int AQ_NEAR_MIN = 32, AQ_NEAR_MAX = 64;  // rows of AQ's 64 columns in LDS
+constexpr int LDS_GRAIN = 1280;   // LDS is handed out in pieces of
+constexpr int AQ_NEAR_MAX = 64;   // rows of AQ's 64 columns in LDS
+
+constexpr int ADV_BLOCKS = 3;     // blocks that the kernel's registers (130 to 167) let share a CU
+constexpr int ADV_MORE_BLOCKS = 4;  // as compiled for 128 registers, which rows of up to 6 pieces of 4 bytes per lane get by with
 
 struct AdvancePlan {
-    int near;   // rows of AQ's columns that a running block keeps in LDS
-    int bytes;  // dynamic LDS: lookup table, EQ (keys, CSR rows, marks in steps of 256), near rows at an odd pitch
+    int blocks;  // that share a CU; ADV_MORE_BLOCKS: the kernel compiled for it is meant
+    int near;    // rows of AQ's columns that a running block keeps in LDS
+    int bytes;   // dynamic LDS: lookup table, EQ (keys, CSR rows, marks in steps of 256), near rows at an odd pitch
 };
 
-// What table and queue leave holds the head of AQ: as much as lets two blocks share a CU, but no less than AQ_NEAR_MIN rows if there
-// is room.  bytes > ADV_DYNAMIC_MAX: does not fit.
-inline AdvancePlan plan_advance(int m_sub, int ef)
+// A block per query: a CU shall hold as many at once as there are queries for it, as far as registers, table and EQ let it.  What a
+// block's share of the LDS has left is the head of AQ.  A query waits for latencies nearly all the time, so another one on the
+// CU gains more than it costs to keep rows of AQ in memory (without any in LDS a query takes 5 % longer) or, with ADV_MORE_BLOCKS, to
+// get by with fewer registers (8 %).  4000 queries, all embeddings stored, ef 200, d = 384, N = 12288: 11.4 -> 6.6 ms with 64 subspaces
+// (one block a CU -> two), 5.7 -> 4.2 with 32 (two -> three), 5.6 -> 3.4 with 16 (two -> four); 500 queries with 64 subspaces 2.0 -> 1.3.
+// Just under three per CU with room for few rows, the longest query counts instead: 750 at ef 500, d = 768, 32 subspaces 2.75 -> 2.93.
+// pieces: of 4 bytes per lane of an embedding row.  bytes > ADV_DYNAMIC_MAX: does not fit.
+inline AdvancePlan plan_advance(int m_sub, int ef, int queries, int cus, int pieces)
 {
     const int fixed = m_sub * 256 * 4 + ef * 16 + (ef + 255) / 256 * 256;
-    auto rows_in = [&](int limit) { return std::max(0, (limit - fixed) / (64 * 8) - 1); };  // - 1: the pitch is odd
-    const int near = std::min(std::max(std::min(AQ_NEAR_MIN, rows_in(ADV_DYNAMIC_MAX)), rows_in(ADV_DYNAMIC_SHARED)), AQ_NEAR_MAX);
-    return {near, fixed + 64 * (near | 1) * 8};
+    auto bytes = [&](int near) { return fixed + 64 * 8 * (near | 1); };
+    auto share = [](int blocks) { return CU_LDS / blocks / LDS_GRAIN * LDS_GRAIN - ADV_FIXED; };
+    int blocks = std::max(1, std::min(pieces <= 6 ? ADV_MORE_BLOCKS : ADV_BLOCKS, (queries + cus - 1) / cus));
+    while (blocks > 1 && bytes(0) > share(blocks)) --blocks;
+    const int near = std::min(AQ_NEAR_MAX, std::max(0, (share(blocks) - fixed) / (64 * 8) - 1));  // - 1: the pitch is odd
+    return {blocks, near, bytes(near)};
 }

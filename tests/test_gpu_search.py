@@ -347,6 +347,45 @@ def test_state_between_rounds_and_in_one_launch(L, hidden, m_sub, ef, alpha, bat
         L.leann_destroy(ctx)
 
 
+@pytest.mark.parametrize("hidden,m_sub,ef", [(128, 16, 200), (128, 32, 64), (128, 32, 300), (640, 32, 200), (128, 64, 100)])
+def test_many_queries_get_what_few_get(L, hidden, m_sub, ef):
+    """More than three queries per CU: four blocks on a CU by registers and LDS (16 subspaces), with no row of the approximate queue
+    in LDS (32, short queue), three by the LDS (32, longer queue) or the registers (640 wide), two (64).  Half of the embeddings are
+    stored, so a query's state also goes through memory.  Ids and scores are those of calls of 100 queries, which run one block per CU."""
+    import torch
+    rng = np.random.default_rng(ef)
+    n, seq, k, nq = 5000, 8, 4, 1100
+    cfg = dict(li.TINY, hidden=hidden, heads=hidden // 64, ffn=128, layers=1)
+    tokens = rng.integers(1, cfg["vocab"], (n, seq)).astype(np.int32)
+    lengths = rng.integers(2, seq + 1, n).astype(np.int32)
+    deg = rng.integers(5, 40, n)
+    deg[1::400] = 70
+    row_ptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.uint64)
+    col_idx = rng.integers(0, n, int(row_ptr[-1])).astype(np.uint32)
+    stored = np.where(np.arange(n) % 2 == 0, np.arange(n) // 2, -1).astype(np.int32)
+    say(f"many queries hidden={hidden} m_sub={m_sub} ef={ef}")
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 1)))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        emb = L.leann_embed(ctx, t, l, hidden=hidden)
+        pq = L.leann_build_pq(ctx, emb, m_sub, 2, 5)
+        cache = (to_dev(stored), emb[::2].contiguous())
+        index = ((to_dev(row_ptr.view(np.int64)), to_dev(col_idx.view(np.int32)), 0), pq, t, l, ef, k, 0.1, 40)
+
+        def search(q):
+            ids, scores, st = L.leann_search(ctx, q.contiguous(), *index, cache=cache)
+            return ids, scores, [st[key] for key in ("hops", "adc_candidates", "recomputed_chunks", "flushes")]
+
+        ids, scores, counts = search(emb[:nq])
+        parts = [search(emb[i:i + 100]) for i in range(0, nq, 100)]
+        assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(scores, torch.cat([p[1] for p in parts]))
+        assert counts == [sum(c) for c in zip(*(p[2] for p in parts))]
+        print(f"{counts[0] // nq} hops, {counts[1] // nq} neighbours scored per query")
+        L.leann_pq_free(pq)
+    finally:
+        L.leann_destroy(ctx)
+
+
 def pack_bits(flags):
     """uint8 flags [n] -> int32 words, bit (v & 31) of word (v >> 5)."""
     n = len(flags)
