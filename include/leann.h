@@ -152,6 +152,9 @@ int leann_embed(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
  * permutation (splitmix64 Fisher-Yates; the first 256 rows of it are the initial
  * centroids; an empty cluster keeps its centroid; ties go to the lowest index),
  * then encodes all n rows.  emb_dev: fp32[n][d].  d/m_sub <= 32.
+ * Scratch (min(n, 65536) * (4 * d + 5 * m_sub + 8) bytes and a little) stays with the context for the next call: at most
+ * 1 GiB, what is larger is freed before the call returns.  It is freed when another allocation of the context finds no
+ * memory, and by leann_destroy.  Calls on one context from several threads take turns: one trains at a time.
  */
 int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, int32_t m_sub, int32_t iters,
                    uint64_t seed, leann_pq **out);

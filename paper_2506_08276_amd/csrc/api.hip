@@ -40,6 +40,16 @@ void DevBuf::release()
     bytes = 0;
 }
 
+int leann_ctx::reserve(DevBuf &buf, size_t need)
+{
+    const int rc = buf.reserve(need);
+    if (rc == LEANN_OK) return rc;
+    std::unique_lock<std::mutex> turn(pq_work_mutex, std::try_to_lock);
+    if (!turn.owns_lock() || !pq_work.p) return rc;  // a training on another thread needs it now
+    pq_work.release();
+    return buf.reserve(need);
+}
+
 int clear_host_flags(leann_ctx *ctx)
 {
     if (!ctx->host_flags) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flags, FLAG_COUNT * sizeof(int), hipHostMallocDefault));
@@ -287,7 +297,7 @@ int leann_profile_begin(leann_ctx *ctx)
         return LEANN_EINVAL;
     }
     LEANN_HIP(hipSetDevice(ctx->device));
-    LEANN_TRY(ctx->prof_tokens.reserve(sizeof(int64_t)));
+    LEANN_TRY(ctx->reserve(ctx->prof_tokens, sizeof(int64_t)));
     LEANN_HIP(hipMemsetAsync(ctx->prof_tokens.p, 0, sizeof(int64_t), ctx->stream));
     for (auto &sp : ctx->prof_spans) {
         ctx->prof_pool.push_back(sp.a);

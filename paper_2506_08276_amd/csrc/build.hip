@@ -467,12 +467,12 @@ int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d
         misc.release();
         return code;
     };
-    if ((rc = adj.reserve((size_t)n * stride * sizeof(int32_t))) != LEANN_OK) return done(rc);
-    if ((rc = deg.reserve((size_t)n * 2 * sizeof(int32_t))) != LEANN_OK) return done(rc);
+    if ((rc = ctx->reserve(adj, (size_t)n * stride * sizeof(int32_t))) != LEANN_OK) return done(rc);
+    if ((rc = ctx->reserve(deg, (size_t)n * 2 * sizeof(int32_t))) != LEANN_OK) return done(rc);
     const int words = n <= BITMAP_NODES ? (int)((n + 31) / 32) : 0;
-    if (words == 0 && (rc = stamp.reserve((size_t)batch * n * sizeof(uint16_t))) != LEANN_OK) return done(rc);
+    if (words == 0 && (rc = ctx->reserve(stamp, (size_t)batch * n * sizeof(uint16_t))) != LEANN_OK) return done(rc);
     const size_t fwd_bytes = (size_t)batch * M * sizeof(int32_t);
-    if ((rc = misc.reserve(fwd_bytes + (size_t)batch * sizeof(int32_t) + (size_t)batch * M * sizeof(int32_t) + 256)) != LEANN_OK)
+    if ((rc = ctx->reserve(misc, fwd_bytes + (size_t)batch * sizeof(int32_t) + (size_t)batch * M * sizeof(int32_t) + 256)) != LEANN_OK)
         return done(rc);
     BuildState s;
     s.emb = emb_dev;
@@ -538,7 +538,7 @@ int leann_top_degree(leann_ctx *ctx, const uint64_t *row_ptr_dev, int64_t n, dou
         return LEANN_EINVAL;
     }
     LEANN_HIP(hipSetDevice(ctx->device));
-    LEANN_TRY(ctx->meta.reserve(256));
+    LEANN_TRY(ctx->reserve(ctx->meta, 256));
     int *err = (int *)ctx->meta.p;
     LEANN_HIP(hipMemsetAsync(err, 0, sizeof(int), ctx->stream));
     int64_t want = (int64_t)ceil(beta * (double)n);

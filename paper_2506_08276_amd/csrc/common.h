@@ -68,7 +68,8 @@ struct leann_ctx {
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
     // scratch of leann_build_pq (at most 65536 rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call.  Calls on several
-    // threads take turns with it (each waits for its stream before it leaves), and what is larger than PQ_WORK_KEEP is given back.
+    // threads take turns with it (each waits for its stream before it leaves).  What is larger than PQ_WORK_KEEP is given back at the
+    // end of the call, the rest when another allocation of the context finds no memory.
     DevBuf pq_work;
     std::mutex pq_work_mutex;
     // search workspace
@@ -86,6 +87,8 @@ struct leann_ctx {
     };
     std::vector<ProfSpan> prof_spans;
     std::vector<hipEvent_t> prof_pool;
+
+    int reserve(DevBuf &buf, size_t need);  // all device memory of a call: as buf.reserve, with pq_work given back if that fails
 };
 
 // Error flags of a call, in pinned host memory: kernels store 1 to what they find wrong, the host reads them after it has

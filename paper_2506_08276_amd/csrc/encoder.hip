@@ -709,13 +709,13 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     if (per_pass < 1) per_pass = 1;
     if (per_pass > n) per_pass = n;
     const size_t rows = (size_t)per_pass * seq + 256;
-    LEANN_TRY(ctx->x.reserve(rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->qkv.reserve(rows * 3 * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->att.reserve(rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->delta.reserve(rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->hid.reserve(rows * F * sizeof(bf16_t)));
-    LEANN_TRY(ctx->cu.reserve((size_t)(per_pass + 1) * sizeof(int32_t)));
-    LEANN_TRY(ctx->enc_ids.reserve((size_t)per_pass * sizeof(int64_t)));
+    LEANN_TRY(ctx->reserve(ctx->x, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve(ctx->qkv, rows * 3 * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve(ctx->att, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve(ctx->delta, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve(ctx->hid, rows * F * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve(ctx->cu, (size_t)(per_pass + 1) * sizeof(int32_t)));
+    LEANN_TRY(ctx->reserve(ctx->enc_ids, (size_t)per_pass * sizeof(int64_t)));
     bf16_t *x = (bf16_t *)ctx->x.p, *qkv = (bf16_t *)ctx->qkv.p, *att = (bf16_t *)ctx->att.p, *hid = (bf16_t *)ctx->hid.p;
     bf16_t *delta = (bf16_t *)ctx->delta.p;  // sublayer output waiting for its residual add + LayerNorm
     int32_t *cu = (int32_t *)ctx->cu.p;

@@ -126,8 +126,8 @@ extern "C" int leann_bench_l1pull(leann_ctx *ctx, int64_t panel_rows, int32_t la
     LEANN_HIP(hipSetDevice(ctx->device));
     const int grid = ctx->num_cus, iters = 2000;
     DevBuf panel, out;
-    int rc = panel.reserve((size_t)panel_rows * 1536);
-    if (rc == LEANN_OK) rc = out.reserve((size_t)grid * 512 * sizeof(uint32_t));
+    int rc = ctx->reserve(panel, (size_t)panel_rows * 1536);
+    if (rc == LEANN_OK) rc = ctx->reserve(out, (size_t)grid * 512 * sizeof(uint32_t));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (rc == LEANN_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)) {
         leann_set_error("leann_bench_l1pull: event creation failed");
@@ -174,8 +174,8 @@ extern "C" int leann_bench_gather(leann_ctx *ctx, const uint8_t *table_dev, int6
     const int per_thread = 64, grid = 4096;                     // 67 108 864 gathers per launch
     const size_t n_ids = (size_t)grid * 256 * per_thread;
     DevBuf ids, out;
-    int rc = ids.reserve(n_ids * sizeof(uint32_t));
-    if (rc == LEANN_OK) rc = out.reserve((size_t)grid * 256 * sizeof(uint32_t));
+    int rc = ctx->reserve(ids, n_ids * sizeof(uint32_t));
+    if (rc == LEANN_OK) rc = ctx->reserve(out, (size_t)grid * 256 * sizeof(uint32_t));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (rc == LEANN_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)) {
         leann_set_error("leann_bench_gather: event creation failed");
@@ -222,8 +222,8 @@ extern "C" int leann_bench_mfma(leann_ctx *ctx, int32_t operand_kind, int32_t bl
     const int grid = ctx->num_cus * blocks_per_cu;
     const int n_in = 6 * 256 * 8;  // six fragments of eight bf16 per thread
     DevBuf in, out;
-    int rc = in.reserve((size_t)n_in * sizeof(uint16_t));
-    if (rc == LEANN_OK) rc = out.reserve((size_t)grid * 256 * sizeof(f32x16));
+    int rc = ctx->reserve(in, (size_t)n_in * sizeof(uint16_t));
+    if (rc == LEANN_OK) rc = ctx->reserve(out, (size_t)grid * 256 * sizeof(f32x16));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (rc == LEANN_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)) {
         leann_set_error("leann_bench_mfma: event creation failed");

@@ -682,11 +682,14 @@ int alloc_pq(leann_ctx *ctx, int64_t n, int32_t d, int32_t m_sub, bool own_codes
     pq->m_sub = m_sub;
     pq->device = ctx->device;
     pq->owns_codes = own_codes;
-    if (hipMalloc(&pq->codebook, (size_t)m_sub * KSUB * (d / m_sub) * sizeof(float)) != hipSuccess ||
-        (own_codes && hipMalloc(&pq->codes, (size_t)n * m_sub) != hipSuccess)) {
-        leann_set_error("device allocation for the PQ table failed");
+    DevBuf codebook, codes;
+    int rc = ctx->reserve(codebook, (size_t)m_sub * KSUB * (d / m_sub) * sizeof(float));
+    if (rc == LEANN_OK && own_codes) rc = ctx->reserve(codes, (size_t)n * m_sub);
+    pq->codebook = (float *)codebook.p;
+    pq->codes = (uint8_t *)codes.p;
+    if (rc != LEANN_OK) {
         leann_pq_free(pq);
-        return LEANN_ENOMEM;
+        return rc;
     }
     *out = pq;
     return LEANN_OK;
@@ -911,7 +914,7 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
                            DIRECT_CAND * (pq->m_sub | 1) * sizeof(float), ctx->stream, queries_dev, pq->d, pq->m_sub, pq->codebook,
                            pq->codes, pq->n, cand_ids_dev, nc, out_dev, flag);
     } else {
-        LEANN_TRY(ctx->s_lut.reserve((size_t)nq * pq->m_sub * KSUB * sizeof(float)));
+        LEANN_TRY(ctx->reserve(ctx->s_lut, (size_t)nq * pq->m_sub * KSUB * sizeof(float)));
         LEANN_TRY(pq_build_lut(ctx, queries_dev, nq, pq, (float *)ctx->s_lut.p));
         ProfScope prof(ctx, LEANN_PROF_ADC);
         int parts = 1, per_block = ADC_PER_ROUND;

@@ -270,6 +270,69 @@ def test_tables_trained_by_several_threads(L, ctx):
         np.testing.assert_array_equal(codes, codes1)
 
 
+def test_scratch_beyond_what_is_kept_is_given_back(L, ctx):
+    """65536 training rows of 4224 elements are more than the 1 GiB that a context keeps; a small table comes out as ever afterwards."""
+    import torch
+    say("pq scratch above the bound")
+    small = to_dev(unit_rows(700, 48, 1))
+
+    def train(x, m_sub):
+        pq = L.leann_build_pq(ctx, x, m_sub, 1, 5)
+        out = L.leann_pq_export(ctx, pq)
+        L.leann_pq_free(pq)
+        return out
+
+    before = train(small, 6)
+    large = torch.randn((65536, 4224), device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(3))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    train(large, 132)
+    assert torch.cuda.mem_get_info()[0] > free - (64 << 20)
+    for a, b in zip(before, train(small, 6)):
+        np.testing.assert_array_equal(a, b)
+
+
+def test_scratch_is_given_back_when_memory_runs_out(L):
+    """A search with room for more stored embeddings than any card holds is refused; the scratch of an earlier training is free again
+    then.  Without that demand the same search, and another training, give what they gave before."""
+    import torch
+    say("pq scratch given back to a search")
+    cfg = dict(li.TINY, layers=1)
+    n = 65536
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 1)))
+    try:
+        emb = to_dev(unit_rows(n, cfg["hidden"], 2))
+        t, l = to_dev(np.ones((n, 8), np.int32)), to_dev(np.full(n, 8, np.int32))
+        row_ptr, col_idx = to_dev(np.arange(n + 1, dtype=np.int64)), to_dev(((np.arange(n) + 1) % n).astype(np.int32))
+
+        def train():
+            pq = L.leann_build_pq(ctx, emb, 16, 1, 5)
+            return pq, L.leann_pq_export(ctx, pq)
+
+        def search(pq):
+            return L.leann_search(ctx, emb[:3].contiguous(), (row_ptr, col_idx, 0), pq, t, l, 10, 3, 0.5, 4)[:2]
+
+        pq, table = train()
+        found = search(pq)
+        scratch = n * (4 * cfg["hidden"] + 5 * 16 + 8)
+        free = torch.cuda.mem_get_info()[0]
+        L.leann_set_call_memo(ctx, 1 << 30)  # times 4 * hidden bytes
+        with pytest.raises(L.LeannError) as e:
+            search(pq)
+        assert e.value.status == -2
+        assert torch.cuda.mem_get_info()[0] >= free + scratch - (8 << 20)  # the memo's index of 4 bytes per node has been allocated
+        L.leann_set_call_memo(ctx, 0)
+        for a, b in zip(found, search(pq)):
+            assert torch.equal(a, b)
+        again, table1 = train()
+        for a, b in zip(table, table1):
+            np.testing.assert_array_equal(a, b)
+        L.leann_pq_free(again)
+        L.leann_pq_free(pq)
+    finally:
+        L.leann_destroy(ctx)
+
+
 def codes_of_first_centroids(L, ctx, x, m_sub):
     """(codebook, codes) after no training round: the centroids are 256 of the rows."""
     pq = L.leann_build_pq(ctx, to_dev(x), m_sub, 0, 7)
