@@ -503,8 +503,11 @@ int leann_build_graph(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d
             epoch = 1;
             if (e != hipSuccess) break;
         }
-        // wavefronts per node: 16 per CU in all, so that small batches, which are bound by one node's chain of hops, spread each
-        // hop widest (the registers, 60 at d = 768, would let 32 stay on a CU)
+        // Wavefronts per node: 16 per CU in all, so that small batches, which are bound by one node's chain of hops, spread each
+        // hop widest.  That is what the registers let stay on a CU at d = 768 and 1024 (98 and 122); they are 58 to 66 up to
+        // d = 384.  8192 nodes, efC 128, batches up to 1024: 16.3 ms at d = 768 and 19.2 at d = 1024; with 8 up to 256 nodes 16.4 and
+        // 19.3, with 16 up to 512 17.6 and 20.4, with 4 from 257 on 17.2 and 19.9, with 8 from 257 on 16.9 and 19.5.  At d = 128 and
+        // 384, 8 from 257 on would take 11.9 and 13.3 instead of 12.2 and 13.8.
         const int threads = 64 * (b <= ctx->num_cus ? 16 : b <= 2 * ctx->num_cus ? 8 : 4);
         hipLaunchKernelGGL(kernels.search_select, dim3((unsigned)b), dim3(threads), words * sizeof(uint32_t), st, s, ins,
                            epoch, words);

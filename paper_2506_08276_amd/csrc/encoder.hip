@@ -593,23 +593,24 @@ int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16
 }
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
-// Measured per launch, twelve layers' weights in turn, in microseconds (rows x N x K; the small-pass kernel takes 0.2 to 1.0 less
-// than here since its slabs are requested before the token count and waited for one by one):
+// Measured per launch inside passes of twelve layers (kernel trace, every product with the same tile), in microseconds (rows x N x K):
 //                       32x32   64x32   64x64 (small)   64x64   128x128   256x256
-//    80 x  768 x  768     4.2     4.7       5.8           6.2      8.5
-//    80 x  768 x 3072     8.0     9.9      14.9          18.0     26.0
-//   244 x 2304 x  768     9.9     8.5       6.4           6.7      9.0
-//  1040 x  768 x 3072    26.8    18.8      16.0          19.3     31.6
-//  1040 x 3072 x  768    35.8    25.8      20.7          15.9     11.9
-//  3000 x  768 x  768                                    11.6     10.2      18.2
-//  4000 x 3072 x  768                                    46.5     29.9      22.7
-//  8000 x  768 x 3072                                    82.9     50.6      56.4
-// 32000 x  768 x  768                                    86.3     50.8      42.6
-// 48000 x 1152 x  384                                             62.5      52.9
-// 24000 x  384 x 1536                                             46.6      37.6
+//    80 x  768 x  768     4.6     5.2       6.0           6.6     10.1
+//    80 x  768 x 3072     8.5    10.6      14.1          19.3     30.5
+//   244 x 2304 x  768    10.7     8.8       6.3           6.8      9.6
+//   244 x 3072 x  768    12.5    10.7       8.5           8.2     10.8
+//  1040 x  768 x 3072    26.3    17.6      14.1          21.4     38.3
+//  1040 x 2304 x  768    27.3    18.6      14.8          12.4     10.4
+//  1040 x 3072 x  768    36.2    23.3      19.8          15.8     11.6
+//  3000 x  768 x  768                                    13.0     11.6      21.4
+//  4000 x 3072 x  768                                    42.6     27.5      24.9
+//  8000 x  768 x 3072                                    94.8     61.0      73.8
+// 32000 x  768 x  768                                    87.7     58.0      49.2
+// 48000 x 1152 x  384                                             63.3      52.9
+// 24000 x  384 x 1536                                             55.0      41.7
 // What decides is how many tiles the busiest CU gets: with c = ceil(tiles / CUs) the larger three take about 2.5 + 3.7 c,
-// 2.5 + 8 c and 21 c - 2 (K = 768; the ratios are the same at K = 3072).  The small-pass kernel is the fastest while its
-// blocks fit the chip at once, its smallest tile first.
+// 2.5 + 8 c and 21 c - 2 (K = 768; the ratios are about the same at K = 3072).  The small-pass kernel is the fastest while its
+// blocks fit the chip at once, its smallest tile first; in several rounds (1040 x 2304 and 3072) the larger tiles are.
 template <int EPI>
 int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
          const int32_t *T_dev, int max_rows, int rows, int N, int K)

@@ -43,7 +43,7 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    with the spread of the data), split into two bf16 each, and |c'|^2 - 2 x'.c' is accumulated in fp32 by three MFMAs
 //    per 16 elements (hi.hi, hi.lo, lo.hi), 32 centroids by 32 rows at a time; a lane owns a row and half the centroids.
 //  - the running minimum and second minimum are kept as floats with 7 bits of index in the low mantissa bits: one bit
-//    operation and two medians per value.
+//    operation, one median and one minimum per value.
 //  - With X = |x'|, C = max |c'|, U = (X + C)^2 and bf16's rounding of 2^-8, a centroid's value is off by, in units of
 //    2^-16 U: the split 1 (each low part rounded by 2^-17 of its operand and low.low left out: 4 * 2^-17 of |2x'||c'| <= U / 2),
 //    the additions of the six MFMAs at most 0.75 (each of the 96 counted with 2^-23 U, a whole unit), |c'|^2 0.13, s(c) itself
@@ -608,9 +608,9 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
 // Two blocks per CU, as many as stay there at once (four, one round after the other, pay the set-up twice: 173 us, not 162), each with a
 // multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
 // where there are rows enough, so that the XCDs get even shares (rounded down: up, 24 subspaces were 6 % slower); with fewer than
-// 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1431 us per launch,
-// 1000 rows of 192 subspaces of one 49; where all subspaces of a run were on one XCD however few the runs (two in both cases),
-// they took 5358 and 129.
+// 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1100 us per launch,
+// 1000 rows of 192 subspaces of one 43; with the kernel of five instructions per value 1431 and 49, and 5358 and 129 where all
+// subspaces of a run were on one XCD however few the runs (two in both cases).
 void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, const float *codebook, uint8_t *out,
                    int64_t row_pitch, int64_t m_pitch)
 {
