@@ -259,7 +259,8 @@ def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
     lookup tables with and without 16-byte code pieces, fetched ahead or not.  Everything is integer-valued, so every score is exact and
     there are many ties: ids, scores and counts equal the oracle's.  Then the smallest queue capacity that the search gets
     by with: at it (holes have to be squeezed out) and above it the result is the same, one below it overflows; and a
-    capacity that makes the queue's runs longer than a wavefront."""
+    capacity above the default.  With ef 1000 a query scores more neighbours than 64 columns of 64 rows hold, so a column is
+    read in more than one pass."""
     rng = np.random.default_rng(m_sub)
     n, d, k, nq = 40_000, 128, 10, 6
     cfg = li.TINY
@@ -292,6 +293,8 @@ def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
         for key, okey in (("hops", "hops"), ("adc_candidates", "adc_candidates"), ("recomputed_chunks", "recomputed"),
                           ("flushes", "flushes")):
             assert st[key] == sum(r["stats"][okey] for r in runs), key
+        if ef >= 1000:  # nothing is squeezed out at this capacity: every scored neighbour has a place of its own
+            assert max(r["stats"]["adc_candidates"] for r in runs) > 64 * 64
         lo, hi = 0, 32768  # lo overflows, hi does not
         while hi - lo > 1:
             mid = (lo + hi) // 2
