@@ -22,15 +22,19 @@ struct AdvancePlan {
 // CU gains more than it costs to keep rows of AQ in memory (without any in LDS a query takes 5 % longer) or, with ADV_MORE_BLOCKS, to
 // get by with fewer registers (8 %).  4000 queries, all embeddings stored, ef 200, d = 384, N = 12288: 11.4 -> 6.6 ms with 64 subspaces
 // (one block a CU -> two), 5.7 -> 4.2 with 32 (two -> three), 5.6 -> 3.4 with 16 (two -> four); 500 queries with 64 subspaces 2.0 -> 1.3.
-// Just under three per CU with room for few rows, the longest query counts instead: 750 at ef 500, d = 768, 32 subspaces 2.75 -> 2.93.
+// Where hardly more queries are there than one block fewer would hold, the longest query counts instead (770 at ef 200, d = 384, 16
+// subspaces: three blocks 1.11 ms, four 1.20; 832 1.29, 1.19; 1100 1.65, 1.40; at ef 64 832 0.63, 0.64 and 960 0.69, 0.64; at ef 500
+// 960 2.57, 2.86 and 1100 3.10, 2.92), so a sixteenth of a query per CU has to be over, a quarter with ADV_MORE_BLOCKS.
+// Not looked at: what the queue will need.  535 to 850 queries at ef 500 with 32 subspaces take 6 % longer with three blocks than with two.
 // pieces: of 4 bytes per lane of an embedding row.  bytes > ADV_DYNAMIC_MAX: does not fit.
 inline AdvancePlan plan_advance(int m_sub, int ef, int queries, int cus, int pieces)
 {
     const int fixed = m_sub * 256 * 4 + ef * 16 + (ef + 255) / 256 * 256;
     auto bytes = [&](int near) { return fixed + 64 * 8 * (near | 1); };
     auto share = [](int blocks) { return CU_LDS / blocks / LDS_GRAIN * LDS_GRAIN - ADV_FIXED; };
-    int blocks = std::max(1, std::min(pieces <= 6 ? ADV_MORE_BLOCKS : ADV_BLOCKS, (queries + cus - 1) / cus));
-    while (blocks > 1 && bytes(0) > share(blocks)) --blocks;
+    const int most = pieces <= 6 ? ADV_MORE_BLOCKS : ADV_BLOCKS;
+    int blocks = 1;
+    while (blocks < most && bytes(0) <= share(blocks + 1) && queries > blocks * cus + cus / (blocks + 1 == ADV_MORE_BLOCKS ? 4 : 16)) ++blocks;
     const int near = std::min(AQ_NEAR_MAX, std::max(0, (share(blocks) - fixed) / (64 * 8) - 1));  // - 1: the pitch is odd
     return {blocks, near, bytes(near)};
 }

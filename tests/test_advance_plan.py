@@ -60,10 +60,10 @@ def test_as_many_queries_share_a_cu_as_the_table_lets(lib, pieces):
     by_registers = 4 if pieces <= 6 else 3
     for m_sub in (1, 8, 16, 24, 32, 48, 64, 96, 128):
         for ef in (1, 64, 200, 256, 257, 500, 1000, 1024):
-            room = min(by_registers, on_a_cu(lib, without_rows(m_sub, ef)))
-            for queries in (1, 256, 257, 512, 513, 768, 769, 1024, 1025, 4096):
+            for queries in (1, 272, 273, 528, 529, 832, 833, 1088, 1089, 4096):
+                room = min(by_registers, on_a_cu(lib, without_rows(m_sub, ef)))
                 total, near, blocks = plan(lib, m_sub, ef, queries, pieces)
-                want = min(room, -(-queries // 256))
+                want = min(room, 1 + (queries > 256 + 16) + (queries > 512 + 16) + (queries > 768 + 64))
                 assert on_a_cu(lib, total) >= want == blocks, (m_sub, ef, queries)
                 # and what is left is used: another two rows would not leave room for them
                 assert near == 64 or on_a_cu(lib, total + 2 * 64 * 8) < want or want == 1 and total + 3 * 64 * 8 + lib.fixed_bytes() > CU_LDS
