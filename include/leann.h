@@ -278,8 +278,9 @@ int leann_set_limits(leann_ctx *ctx, int64_t max_tokens_per_pass, int32_t aq_cap
  * Without it, requests for one chunk are merged only within a round.  max_rows = 0 turns it off and frees its memory. */
 int leann_set_call_memo(leann_ctx *ctx, int64_t max_rows);
 /* GEMM tile choice of the encoder (a tuning and test aid; results do not depend on it, every tile adds the K-slabs
- * in the same order): large_tile 256 (default) or 128 = largest block tile (0 leaves it); small_rows = passes that
- * are expected to hold at most this many tokens may use tiles of 64x64 and smaller (default 2048). */
+ * in the same order): large_tile 256 (default) or 128 = largest block tile of the kernel for large passes (0 leaves it);
+ * small_rows = passes that are expected to hold at most this many tokens may use tiles of 64x64 and smaller (default
+ * 2048); with 0 every pass goes through the kernel for large passes. */
 int leann_set_gemm_tiles(leann_ctx *ctx, int32_t large_tile, int32_t small_rows);
 
 /*

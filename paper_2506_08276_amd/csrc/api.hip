@@ -178,7 +178,9 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
     size_t bf_bytes = up256(e.vocab * d * 2) + up256(e.max_pos * d * 2) + up256(d * 2) +
                       L * (up256(3 * d * d * 2) + up256(d * d * 2) + 2 * up256(F * d * 2));
     size_t f_bytes = 2 * up256(d * 4) + L * (up256(3 * d * 4) + 6 * up256(d * 4) + up256(F * 4));
-    if (ctx->w_bf16.reserve(bf_bytes) != LEANN_OK || ctx->w_f32.reserve(f_bytes) != LEANN_OK) {
+    const size_t packed_bytes = L * (4 * d * d + 2 * F * d) * 2;
+    if (ctx->w_bf16.reserve(bf_bytes) != LEANN_OK || ctx->w_f32.reserve(f_bytes) != LEANN_OK ||
+        ctx->w_packed.reserve(packed_bytes) != LEANN_OK) {
         leann_destroy(ctx);
         return LEANN_ENOMEM;
     }
@@ -221,6 +223,24 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
         w.g2 = vec(d);
         w.be2 = vec(d);
     }
+    bf16_t *pp = (bf16_t *)ctx->w_packed.p;
+    int pack_rc = LEANN_OK;
+    auto packed = [&](const bf16_t *W, size_t N, size_t K) {
+        bf16_t *dst = pp;
+        pp += N * K;
+        if (pack_rc == LEANN_OK) pack_rc = enc_pack_weights(ctx, W, (int)N, (int)K, dst);
+        return (const bf16_t *)dst;
+    };
+    for (LayerWeights &w : ctx->layers) {
+        w.wqkv_p = packed(w.wqkv, 3 * d, d);
+        w.wo_p = packed(w.wo, d, d);
+        w.w1_p = packed(w.w1, F, d);
+        w.w2_p = packed(w.w2, d, F);
+    }
+    if (pack_rc != LEANN_OK) {
+        leann_destroy(ctx);
+        return pack_rc;
+    }
     hipError_t rc = hipGetLastError();
     if (rc == hipSuccess) rc = copy_rc;
     if (rc == hipSuccess) rc = hipStreamSynchronize(ctx->stream);
@@ -238,7 +258,7 @@ void leann_destroy(leann_ctx *ctx)
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    DevBuf *bufs[] = {&ctx->w_bf16, &ctx->w_f32, &ctx->x, &ctx->qkv, &ctx->att, &ctx->delta, &ctx->hid, &ctx->cu,
+    DevBuf *bufs[] = {&ctx->w_bf16, &ctx->w_f32, &ctx->w_packed, &ctx->x, &ctx->qkv, &ctx->att, &ctx->delta, &ctx->hid, &ctx->cu,
                       &ctx->len, &ctx->meta, &ctx->enc_ids, &ctx->s_state, &ctx->s_emb, &ctx->s_lut, &ctx->s_seen,
                       &ctx->s_misc, &ctx->s_owner, &ctx->s_buf, &ctx->s_memo_slot, &ctx->s_memo_emb, &ctx->pq_work};
     for (DevBuf *b : bufs) b->release();

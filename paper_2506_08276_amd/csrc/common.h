@@ -36,6 +36,7 @@ void leann_set_error(const char *fmt, ...);
 // Per-layer device pointers into the context's own copy of the weights.
 struct LayerWeights {
     const bf16_t *wqkv, *wo, *w1, *w2;                          // [out][in] bf16
+    const bf16_t *wqkv_p, *wo_p, *w1_p, *w2_p;                  // the same in the MFMA's operand order
     const float *bqkv, *bo, *g1, *be1, *b1, *b2, *g2, *be2;     // fp32
 };
 
@@ -56,7 +57,7 @@ struct leann_ctx {
     int ln_blocks_per_cu = 4;
     hipStream_t stream = nullptr;
     // weights
-    DevBuf w_bf16, w_f32;
+    DevBuf w_bf16, w_f32, w_packed;
     const bf16_t *tok_emb = nullptr, *pos_emb = nullptr, *seg_emb = nullptr;
     const float *emb_g = nullptr, *emb_b = nullptr;
     std::vector<LayerWeights> layers;
@@ -64,7 +65,7 @@ struct leann_ctx {
     int64_t max_tokens = 1048576;  // padded tokens per encoder pass (workspaces: about 17 KB per token at BERT-base width)
     int32_t aq_capacity = 0;  // 0 = derive from ef and graph
     int32_t gemm_large_tile = 256;   // 256: 256x256 block tiles for large passes; 128: never (leann_set_gemm_tiles)
-    int32_t gemm_small_rows = 2048;  // passes of at most this many rows may use tiles of 64x64 and smaller
+    int32_t gemm_small_rows = 2048;  // passes of at most this many rows may use tiles of 64x64 and smaller; 0: gemm_kernel only
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
     // scratch of leann_build_pq (at most 65536 rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call.  Calls on several
@@ -116,6 +117,8 @@ struct leann_pq {
 
 // Per-device set-up of each source file's kernels (LDS limits); called by leann_create with the device current.
 int enc_init_device();
+// W[N][K] in the MFMA's operand order, on the context's stream.
+int enc_pack_weights(leann_ctx *ctx, const bf16_t *W, int N, int K, bf16_t *packed);
 int enc_ln_blocks_per_cu(int *out);  // resident blocks of the LayerNorm kernel per CU on the current device
 int pq_init_device();
 int search_init_device();

@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "gemm_stream.h"
 #include "wave.h"
 
 namespace {
@@ -544,7 +545,7 @@ int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W,
     }
     const int tiles = ((max_rows + BM - 1) / BM) * tiles_n;
     // persistent blocks: one per CU slot (a multiple of 8), fewer when there are fewer tiles
-    const int slots = ctx->num_cus * (BM == 256 ? 1 : BM == 128 ? 2 : 4);
+    const int slots = ctx->num_cus * (BM == 256 ? 1 : 2);
     const int grid = std::max(8, std::min(slots, (tiles + 7) & ~7) & ~7);
     ProfScope prof(ctx, prof_kind);
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, EPI>), dim3(grid), dim3(64 * WM * WN), smem, ctx->stream, A, W, bias,
@@ -553,18 +554,23 @@ int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W,
     return LEANN_OK;
 }
 
-// How gemm_small_kernel's grid covers the 8 XCDs: xr of them side by side over the rows, the rest over the columns.  First
-// the arrangement with the fewest rounds of blocks on the fullest XCD, among those the one that reads least (an XCD
-// reads its share of the rows of A and of W once).
-struct SmallPlan {
-    int xr, rounds, blocks;
+// A product's two copies of the weights, see pack_weights_kernel.
+struct Weights {
+    const bf16_t *rows, *packed;
 };
 
-SmallPlan plan_small(const leann_ctx *ctx, int tmb, int tnb, int rows, int N)
+// How gemm_stream_kernel's grid covers the 8 XCDs: xr of them side by side over the rows, the rest over the columns.  First
+// the arrangement with the fewest rounds of blocks on the fullest XCD, among those the one that reads least (an XCD
+// reads its share of the rows of A and of W once).
+struct StreamPlan {
+    int xr, rounds;
+};
+
+StreamPlan plan_stream(const leann_ctx *ctx, int tile_rows, int tile_cols, int rows, int N)
 {
-    SmallPlan best = {1, INT_MAX, 0};
+    StreamPlan best = {1, INT_MAX};
     double best_bytes = 0;
-    const int rt = (rows + 32 * tmb - 1) / (32 * tmb), ct = N / (32 * tnb);
+    const int rt = (rows + tile_rows - 1) / tile_rows, ct = (N + tile_cols - 1) / tile_cols;
     const int cus = std::max(1, ctx->num_cus / 8);
     for (int xr = 1; xr <= 8; xr *= 2) {
         const int xc = 8 / xr;
@@ -572,82 +578,96 @@ SmallPlan plan_small(const leann_ctx *ctx, int tmb, int tnb, int rows, int N)
         const int rounds = (per_xcd + cus - 1) / cus;
         const double bytes = (double)rows * xc + (double)N * xr;
         if (rounds < best.rounds || (rounds == best.rounds && bytes < best_bytes)) {
-            best = {xr, rounds, 8 * per_xcd};
+            best = {xr, rounds};
             best_bytes = bytes;
         }
     }
     return best;
 }
 
-template <int TMB, int TNB, int EPI>
-int launch_gemm_small(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
-                      const int32_t *T_dev, int max_rows, int likely_rows, int N, int K, int xr)
+template <int R, int NM, int EPI>
+int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *Wp, const float *bias, bf16_t *out,
+                       const int32_t *T_dev, int max_rows, int likely_rows, int N, int K, int xr)
 {
-    typedef SmallCfg<TMB, TNB> Cfg;
-    const int rt = (max_rows + 32 * TMB - 1) / (32 * TMB), ct = N / (32 * TNB), xc = 8 / xr;
+    typedef StreamCfg<R, NM> Cfg;
+    const int rt = (max_rows + Cfg::ROWS - 1) / Cfg::ROWS, ct = (N + Cfg::COLS - 1) / Cfg::COLS, xc = 8 / xr;
     ProfScope prof(ctx, prof_kind);
-    hipLaunchKernelGGL((gemm_small_kernel<TMB, TNB, EPI>), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
-                       Cfg::SMEM, ctx->stream, A, W, bias, out, T_dev, max_rows, likely_rows, N, K, __builtin_ctz(xr));
+    hipLaunchKernelGGL((gemm_stream_kernel<R, NM, EPI>), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
+                       Cfg::SMEM, ctx->stream, A, Wp, bias, out, T_dev, max_rows, likely_rows, N, K, __builtin_ctz(xr));
     LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
 
+// Tiles of gemm_stream_kernel and what a launch takes while its blocks fit the chip at once: microseconds besides the K loop and per
+// 768 elements of K.
+#define LEANN_STREAM_TILES(X)                                                                            \
+    X(1, 1, 2.4, 1.18) X(1, 2, 2.5, 1.36) X(1, 3, 2.5, 1.77) X(1, 4, 2.6, 2.22) X(2, 2, 3.15, 1.94)      \
+    X(2, 3, 3.1, 2.6) X(2, 4, 3.1, 3.1) X(2, 6, 3.3, 4.15) X(2, 8, 3.4, 5.0) X(4, 6, 4.6, 7.4) X(4, 8, 4.9, 8.8)
+
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
-// Measured per launch inside passes of twelve layers (kernel trace, every product with the same tile), in microseconds (rows x N x K):
-//                       32x32   64x32   64x64 (small)   64x64   128x128   256x256
-//    80 x  768 x  768     4.6     5.2       6.0           6.6     10.1
-//    80 x  768 x 3072     8.5    10.6      14.1          19.3     30.5
-//   244 x 2304 x  768    10.7     8.8       6.3           6.8      9.6
-//   244 x 3072 x  768    12.5    10.7       8.5           8.2     10.8
-//  1040 x  768 x 3072    26.3    17.6      14.1          21.4     38.3
-//  1040 x 2304 x  768    27.3    18.6      14.8          12.4     10.4
-//  1040 x 3072 x  768    36.2    23.3      19.8          15.8     11.6
-//  3000 x  768 x  768                                    13.0     11.6      21.4
-//  4000 x 3072 x  768                                    42.6     27.5      24.9
-//  8000 x  768 x 3072                                    94.8     61.0      73.8
-// 32000 x  768 x  768                                    87.7     58.0      49.2
-// 48000 x 1152 x  384                                             63.3      52.9
-// 24000 x  384 x 1536                                             55.0      41.7
-// What decides is how many tiles the busiest CU gets: with c = ceil(tiles / CUs) the larger three take about 2.5 + 3.7 c,
-// 2.5 + 8 c and 21 c - 2 (K = 768; the ratios are about the same at K = 3072).  The small-pass kernel is the fastest while its
-// blocks fit the chip at once, its smallest tile first; in several rounds (1040 x 2304 and 3072) the larger tiles are.
+// Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; 32 R x 32 NM: stream):
+//                       32x32   32x64   32x96  32x128   64x64   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
+//    80 x  768 x  768     3.4     3.6     3.9     4.3     4.8     5.1                                          |   8.6
+//    80 x  768 x 3072     7.0     7.5     8.9    10.8    10.5                                                  |  26.1
+//   450 x 2304 x  768                     6.8     7.7     8.6     5.6     6.0     6.8     7.2                  |   9.8
+//  1040 x  768 x  768             6.2     6.6     4.9     5.2     5.5     5.8     6.6                          |   9.1
+//  1040 x 2304 x  768                                            10.0             7.4     7.9    10.7          |  10.7
+//  2000 x 3072 x  768                                                            14.6    15.8    13.4    14.1  |  19.0    19.0
+//  2000 x  768 x 3072                                            14.2    15.1    18.0                          |  31.4    56.4
+//  2500 x 1152 x  384                                             8.2             5.7     5.9     7.8     8.2  |   6.6    11.3
+//  3500 x 1152 x  384                                                     9.1     9.4     9.9     8.1     8.6  |   6.9    11.2
+//  3500 x 3072 x  768                                                                            23.6    25.1  |  28.3    21.6
+//  8000 x  768 x 3072                                                            42.7    47.1    37.0    37.5  |  51.2    56.5
+// 10000 x  384 x 1536                                                            21.5    23.9    17.5    18.5  |  18.9    30.4
+// 12000 x  768 x  768                                                                            22.3    24.3  |  23.7    19.1
+// The stream kernel's smallest tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands'
+// way); its figures above are for N = 2304 at K = 768.  gemm_kernel walks over its tiles: what decides is how many the busiest CU gets,
+// c = ceil(tiles / CUs).  128x128 takes about 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or,
+// next to the stream kernel, 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.
 template <int EPI>
-int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
+int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const float *bias, bf16_t *out,
          const int32_t *T_dev, int max_rows, int rows, int N, int K)
 {
     const int cus = ctx->num_cus;
-    const bool fine = rows <= ctx->gemm_small_rows && N % 64 == 0;
-    if (fine && K % SMALL_BK == 0) {
-#define LEANN_SMALL(TMB, TNB)                                                                                       \
-    {                                                                                                               \
-        const SmallPlan p = plan_small(ctx, TMB, TNB, rows, N);                                                     \
-        if (p.rounds == 1)                                                                                          \
-            return launch_gemm_small<TMB, TNB, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, rows, N, K, p.xr);  \
-    }
-        LEANN_SMALL(1, 1)
-        LEANN_SMALL(2, 1)
-        LEANN_SMALL(2, 2)
-#undef LEANN_SMALL
-    }
     auto busiest = [&](int tile) {  // tiles of the busiest CU
         const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * ((N + tile - 1) / tile);
         return (double)((tiles + cus - 1) / cus);
     };
-    const double cost128 = N % 128 == 0 ? 2.5 + 8.0 * busiest(128) : INFINITY;
-    const double cost64 = fine ? 2.5 + 3.7 * busiest(64) : INFINITY;
-    const bool wide = ctx->gemm_large_tile == 256 && N % 128 == 0 && K >= 8 * GEMM_BK;  // the last column tile may be half empty
-    const double cost256 = wide ? 21.0 * busiest(256) - 2.0 : INFINITY;
-    if (cost256 <= cost128 && cost256 <= cost64)
-        return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
-    if (cost64 < cost128) return launch_gemm<64, 64, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
-    return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K);
+    const double k = K / 768.0, c128 = busiest(128), c256 = busiest(256);
+    const bool wide = ctx->gemm_large_tile == 256 && K >= 8 * GEMM_BK && 21.0 * c256 - 2.0 <= 2.5 + 8.0 * c128;
+    if (ctx->gemm_small_rows > 0) {
+        const double large_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
+        double best_us = INFINITY;
+        int best = -1, best_xr = 1, tile = 0;
+#define LEANN_TILE(R, NM, US, US_K)                                                                                   \
+        {                                                                                                             \
+            const StreamPlan p = plan_stream(ctx, 32 * R, 32 * NM, rows, N);                                          \
+            const double us = US + US_K * k;                                                                          \
+            if (p.rounds == 1 && us < best_us && us < large_us && (R * NM > 4 || rows <= ctx->gemm_small_rows)) {     \
+                best_us = us;                                                                                         \
+                best = tile;                                                                                          \
+                best_xr = p.xr;                                                                                       \
+            }                                                                                                         \
+            ++tile;                                                                                                   \
+        }
+        LEANN_STREAM_TILES(LEANN_TILE)
+#undef LEANN_TILE
+        tile = 0;
+#define LEANN_TILE(R, NM, US, US_K)                                                                                   \
+        if (best == tile++)                                                                                           \
+            return launch_gemm_stream<R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, best_xr);
+        LEANN_STREAM_TILES(LEANN_TILE)
+#undef LEANN_TILE
+    }
+    if (wide) return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);  // the last column tile may be half empty
+    return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);
 }
 
-template <int TMB, int TNB, int EPI>
-int gemm_small_allow_lds()
+template <int R, int NM, int EPI>
+int gemm_stream_allow_lds()
 {
-    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_small_kernel<TMB, TNB, EPI>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SmallCfg<TMB, TNB>::SMEM));
+    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_stream_kernel<R, NM, EPI>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, StreamCfg<R, NM>::SMEM));
     return LEANN_OK;
 }
 
@@ -677,16 +697,20 @@ int enc_init_device()
     LEANN_TRY((gemm_allow_lds<256, 256, EPI_BIAS_GELU>()));
     LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS>()));
     LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS_GELU>()));
-    LEANN_TRY((gemm_allow_lds<64, 64, EPI_BIAS>()));
-    LEANN_TRY((gemm_allow_lds<64, 64, EPI_BIAS_GELU>()));
-    LEANN_TRY((gemm_small_allow_lds<1, 1, EPI_BIAS>()));
-    LEANN_TRY((gemm_small_allow_lds<1, 1, EPI_BIAS_GELU>()));
-    LEANN_TRY((gemm_small_allow_lds<2, 1, EPI_BIAS>()));
-    LEANN_TRY((gemm_small_allow_lds<2, 1, EPI_BIAS_GELU>()));
-    LEANN_TRY((gemm_small_allow_lds<2, 2, EPI_BIAS>()));
-    LEANN_TRY((gemm_small_allow_lds<2, 2, EPI_BIAS_GELU>()));
+#define LEANN_TILE(R, NM, US, US_K)                               \
+    LEANN_TRY((gemm_stream_allow_lds<R, NM, EPI_BIAS>()));         \
+    LEANN_TRY((gemm_stream_allow_lds<R, NM, EPI_BIAS_GELU>()));
+    LEANN_STREAM_TILES(LEANN_TILE)
+#undef LEANN_TILE
     LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(attention_kernel<8>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, AttCfg<8>::SMEM));
+    return LEANN_OK;
+}
+
+int enc_pack_weights(leann_ctx *ctx, const bf16_t *W, int N, int K, bf16_t *packed)
+{
+    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)(((int64_t)N * K / 8 + 255) / 256)), dim3(256), 0, ctx->stream, W, N, K, packed);
+    LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
 
@@ -757,7 +781,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         };
         for (int l = 0; l < e.layers; ++l) {
             const LayerWeights &w = ctx->layers[l];
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_QKV, x, w.wqkv, w.bqkv, qkv, T_dev, max_rows, rows, 3 * d, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_QKV, x, {w.wqkv, w.wqkv_p}, w.bqkv, qkv, T_dev, max_rows, rows, 3 * d, d));
             {
                 ProfScope prof(ctx, LEANN_PROF_ATTENTION);
                 if (seq <= 128)
@@ -767,10 +791,10 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
                     hipLaunchKernelGGL(attention_kernel<8>, dim3((unsigned)m * H), dim3(256), AttCfg<8>::SMEM, ctx->stream, qkv, cu,
                                        att, d, scale_log2e);
             }
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, w.wo, w.bo, delta, T_dev, max_rows, rows, d, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, {w.wo, w.wo_p}, w.bo, delta, T_dev, max_rows, rows, d, d));
             layer_norm(w.g1, w.be1);
-            LEANN_TRY(gemm<EPI_BIAS_GELU>(ctx, LEANN_PROF_GEMM_FFN1, x, w.w1, w.b1, hid, T_dev, max_rows, rows, F, d));
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_FFN2, hid, w.w2, w.b2, delta, T_dev, max_rows, rows, d, F));
+            LEANN_TRY(gemm<EPI_BIAS_GELU>(ctx, LEANN_PROF_GEMM_FFN1, x, {w.w1, w.w1_p}, w.b1, hid, T_dev, max_rows, rows, F, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_FFN2, hid, {w.w2, w.w2_p}, w.b2, delta, T_dev, max_rows, rows, d, F));
             layer_norm(w.g2, w.be2);
         }
         {

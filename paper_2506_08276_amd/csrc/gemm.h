@@ -311,162 +311,4 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
 #undef SGB
 }
 
-// The same product for passes of few rows.  Latency bounds it: the weights come from beyond L2 (a layer's are used once per
-// pass), so what counts is how many bytes a CU has on their way, and each output element's sum over K is one chain of
-// MFMAs.  A block has TMB x TNB wavefronts that multiply, each one 32 x 32 tile (so that many CUs take part), and four that
-// fetch: K-slabs of 128 (a row's slab is two whole 128-byte lines), DEPTH slabs in registers ahead of the one that goes to
-// LDS.  A multiplying wavefront reads slab s + 1 into registers while its MFMAs go through slab s, so its chain does not
-// wait for LDS; one barrier per slab, two stages.  A slab row is 16 chunks of 16 bytes; chunk c of row r sits at
-// c ^ (r & 15): the stores (16 lanes, one row) and the operand reads (16 lanes, 16 rows) both reach all banks.  The MFMAs
-// and their order over K are those of gemm_kernel, the sums start at the bias there as here: the same bits.
-// The first requests go out before the token count is there, and each slab waits for its own loads only (they were all waited for
-// once in DEPTH slabs): one query embedded 463 -> 447 us, 13 chunks 777 -> 735 (48 of these products each, or 24).
-constexpr int SMALL_BK = 128;
-
-template <int TMB, int TNB>
-struct SmallCfg {
-    static constexpr int ROWS = 32 * (TMB + TNB);                 // rows of A and W per slab
-    static constexpr int STAGE = ROWS * SMALL_BK;                 // elements per stage
-    static constexpr int SMEM = 2 * STAGE * (int)sizeof(bf16_t) + TMB * TNB * 32 * 64;  // stages, output staging
-    static constexpr int THREADS = 64 * (TMB * TNB + 4);
-    static constexpr int DEPTH = TMB * TNB == 1 ? 8 : TMB * TNB == 2 ? 6 : 4;  // 128 or 144 registers
-};
-
-template <int TMB, int TNB, int EPI>
-__global__ __launch_bounds__(64 * (TMB * TNB + 4)) void gemm_small_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W,
-                                                                          const float *__restrict__ bias, bf16_t *__restrict__ out,
-                                                                          const int32_t *__restrict__ T_dev, int max_rows, int likely_rows,
-                                                                          int N, int K, int xr_bits)
-{
-    typedef SmallCfg<TMB, TNB> Cfg;
-    constexpr int BK = SMALL_BK, DEPTH = Cfg::DEPTH;
-    constexpr int LPT = Cfg::ROWS / 16;  // 16-byte loads per fetching thread and slab
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    bf16_t *stage = reinterpret_cast<bf16_t *>(smem);  // [2][ROWS][128]
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // blocks go round-robin to the 8 XCDs (gridDim.x is a multiple of 8), which stand in a grid of xr x 8 / xr: an XCD takes every
-    // xr-th row tile and every (8 / xr)-th column tile, the row tiles that may turn out to be empty last
-    const int xcd = blockIdx.x & 7;
-    const int tm = (blockIdx.y << xr_bits) + (xcd & ((1 << xr_bits) - 1)), tn = ((blockIdx.x >> 3) << (3 - xr_bits)) + (xcd >> xr_bits);
-    const int m0 = tm * 32 * TMB, n0 = tn * 32 * TNB;
-    if (m0 >= max_rows || n0 >= N) return;
-    // Tiles that likely hold rows request their slabs before the token count is there: it is the same chain of latencies as a slab's.
-    if (m0 >= likely_rows && m0 >= *T_dev) return;
-    const int slabs = K / BK;  // the host checks K % 128 == 0
-
-    if (wave >= TMB * TNB) {  // fetch
-        const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * K), 0, 32 * TMB * K * (int)sizeof(bf16_t), 0x00020000);
-        const auto wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(W + (size_t)n0 * K), 0, 32 * TNB * K * (int)sizeof(bf16_t), 0x00020000);
-        const int ft = tid - 64 * TMB * TNB, lrow = ft >> 4, lch = ft & 15;
-        const int toff = (lrow * K + lch * 8) * (int)sizeof(bf16_t);
-        const int soff = lrow * BK + ((lch ^ lrow) << 3);  // rows 16 apart share the swizzle term
-        u32x4 rg[DEPTH][LPT];
-        // Every step issues its loads: a slab past the end gets an offset beyond the buffer (nothing is fetched, zeros
-        // come back).  Loads return in order and a wait counts the loads behind the one it is for; where a load may or may
-        // not have been issued, the compiler would have to wait for all of them.
-#define SMALL_LOAD(p, slab)                                                                              \
-    {                                                                                                    \
-        const int o_ = (slab) < slabs ? toff + (slab) * (BK * 2) : 0x7ff00000;                           \
-        _Pragma("unroll") for (int i = 2 * TMB; i < LPT; ++i)                                            \
-            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, o_, (i - 2 * TMB) * 16 * K * 2, 0)); \
-        _Pragma("unroll") for (int i = 0; i < 2 * TMB; ++i)                                              \
-            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * K * 2, 0)); \
-    }
-#pragma unroll
-        for (int p = 0; p < DEPTH; ++p) {
-            SMALL_LOAD(p, p)
-            __builtin_amdgcn_sched_barrier(0);  // slab after slab: in the compiler's own order the first wait was for all of them
-        }
-        // One exit, at the loop's end: with one per step the compiled code has ways back from each step to the first, and the first
-        // waits for all loads.  Nor does a test stand between the first requests and the loop, they would be moved behind it.
-        const int end = m0 < *T_dev ? slabs : 1;
-        int s0 = 0;
-        do {
-#pragma unroll
-            for (int p = 0; p < DEPTH; ++p) {
-                const int s = s0 + p;
-                bf16_t *to = stage + (s & 1) * Cfg::STAGE + soff;
-                if (s < end)
-#pragma unroll
-                    for (int i = 0; i < LPT; ++i) *reinterpret_cast<u32x4 *>(to + i * 16 * BK) = rg[p][i];
-                SMALL_LOAD(p, s + DEPTH)
-                if (s < end) __syncthreads();  // slab s is there; slab s - 1 has been read
-            }
-            s0 += DEPTH;
-        } while (s0 < end);
-        return;
-    }
-#undef SMALL_LOAD
-
-    const int wm = wave / TNB, wn = wave % TNB;
-    f32x16 acc;  // the sum starts at the bias: register 4g + i of a lane is column 8g + 4 half + i
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + n0 + wn * 32 + 8 * g + 4 * half);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[4 * g + i] = b[i];
-    }
-    const bf16_t *fa = stage + (wm * 32 + l32) * BK, *fw = stage + (32 * TMB + wn * 32 + l32) * BK;
-    bf16x8 af[2][BK / 16], wf[2][BK / 16];
-#define SMALL_FRAGS(set, st)                                                                             \
-    _Pragma("unroll") for (int k = 0; k < BK / 16; ++k) {                                                \
-        const int c_ = (st) * Cfg::STAGE + (((2 * k + half) ^ (l32 & 15)) << 3);                         \
-        af[set][k] = *reinterpret_cast<const bf16x8 *>(fa + c_);                                         \
-        wf[set][k] = *reinterpret_cast<const bf16x8 *>(fw + c_);                                         \
-    }
-#define SMALL_MFMA(set)                                                                                  \
-    _Pragma("unroll") for (int k = 0; k < BK / 16; ++k)                                                  \
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][k], af[set][k], acc, 0, 0, 0);
-    // an MFMA of the chain can only start when the one before it has ended: the reads go in between
-#define SMALL_INTERLEAVE                                                                                 \
-    _Pragma("unroll") for (int k = 0; k < BK / 16; ++k) {                                                \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                               \
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                               \
-    }
-    const int T = *T_dev;
-    __syncthreads();
-    if (m0 >= T) return;
-    SMALL_FRAGS(0, 0)
-    int s = 0;
-    for (; s + 2 < slabs; s += 2) {
-        __syncthreads();
-        SMALL_FRAGS(1, 1)
-        SMALL_MFMA(0)
-        SMALL_INTERLEAVE
-        __syncthreads();
-        SMALL_FRAGS(0, 0)
-        SMALL_MFMA(1)
-        SMALL_INTERLEAVE
-    }
-    if (s + 1 < slabs) {
-        __syncthreads();
-        SMALL_FRAGS(1, 1)
-        SMALL_MFMA(0)
-        SMALL_INTERLEAVE
-        SMALL_MFMA(1)
-    } else {
-        SMALL_MFMA(0)
-    }
-#undef SMALL_INTERLEAVE
-#undef SMALL_FRAGS
-#undef SMALL_MFMA
-    // 32 x 32 outputs through the wavefront's own 2 KB: 16-byte chunk c of a row at c ^ ((row >> 1) & 3), then 16-byte stores
-    unsigned char *stg = smem + 2 * Cfg::STAGE * sizeof(bf16_t) + wave * (32 * 64);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        bf16x4 o4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o4[i] = (bf16_t)(EPI == EPI_BIAS_GELU ? gelu_erf(acc[4 * g + i]) : acc[4 * g + i]);
-        *reinterpret_cast<bf16x4 *>(stg + l32 * 64 + ((g ^ ((l32 >> 1) & 3)) << 4) + half * 8) = o4;
-    }
-    __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int r = j * 16 + (lane >> 2), ch = lane & 3;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + r * 64 + ((ch ^ ((r >> 1) & 3)) << 4));
-        *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + wm * 32 + r) * N + n0 + wn * 32 + ch * 8) = v;
-    }
-}
-
 }  // namespace

@@ -1,0 +1,208 @@
+// bf16 MFMA products of passes that fill the chip once: W from memory to registers, A through LDS (gfx950).
+#pragma once
+#include "common.h"
+#include "gemm.h"
+
+namespace {
+
+// W[N][K] in the order in which the MFMA reads it: 32 rows by 16 elements are 1 KB, lane l's 16 bytes (row l % 32, elements
+// 8 (l / 32) ..) at l; then the next 16 elements along K, then the next 32 rows.  One thread per 16 bytes, once per context.
+__global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restrict__ W, int N, int K, bf16_t *__restrict__ packed)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)N * K / 8) return;
+    const int lane = (int)(i & 63);
+    const int64_t frag = i >> 6;
+    const int ks = (int)(frag % (K / 16)), ct = (int)(frag / (K / 16));
+    reinterpret_cast<u32x4 *>(packed)[i] =
+        *reinterpret_cast<const u32x4 *>(W + (size_t)(ct * 32 + (lane & 31)) * K + ks * 16 + (lane >> 5) * 8);
+}
+
+// The product of gemm_kernel (same MFMAs, same order over K, sums that start at the bias: the same bits) for passes in which
+// every CU gets one tile at most.  Latency bounds it: a launch is some 2.3 us, the first operands come from beyond L2, and no other
+// tile's work hides a wait.  What counts then is how many bytes a CU has on their way and that nothing on the chain over K waits for LDS:
+//  - W is kept a second time in operand order, so a multiplying wavefront reads its own 32 columns straight into registers, DW
+//    steps of 16 elements ahead, 1 KB per request.  W takes no LDS space, stores or reads, and no barrier.
+//  - A goes through LDS: four wavefronts fetch K-slabs of 128 (a row's slab is two whole lines), DA slabs ahead in registers, into
+//    a ring of three stages.  A multiplying wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead,
+//    across slabs: the slab after the current one is always there already.  One barrier per slab, at which only the
+//    fetching wavefronts wait for their LDS stores.  A slab row is 16 chunks of 16 bytes; chunk c of row r sits at c ^ (r & 15): the
+//    stores (16 lanes, one row) and the reads (16 lanes, 16 rows) both reach all banks.
+//  - The first requests go out before the token count is there.
+// Three slabs per turn of the loop, with one exit at its end: with more of them, or with a test between the first requests and the
+// loop, the compiled code moves requests behind it and waits for all that are in flight (the first build did: 1.3 us more at 80
+// rows, 4 us more at K = 3072).  Where K is no multiple of 384, the slabs behind its end are zeros.
+// Before, operands of both matrices went through LDS (48 KB of LDS traffic per slab at a 64 x 64 tile, which bounded it) and through
+// gemm_kernel<64,64> / <128,128> above 64 x 64; microseconds per launch in a row of dependent launches, W not in L2:
+//     rows x N x K     before   now           rows x N x K     before   now
+//    80 x  768 x  768    3.9    3.4         1040 x 2304 x  768   10.7    7.4
+//    80 x 3072 x  768    4.9    4.0         1040 x  768 x 3072   13.9   11.0
+//    80 x  768 x 3072    7.7    7.0         2000 x 3072 x  768   19.0   13.4
+//   450 x 2304 x  768    9.8    5.6         2000 x  768 x 3072   26.2   14.2
+//   450 x  768 x 3072    9.6    8.0         8000 x  768 x 3072   51.2   37.0
+constexpr int STREAM_BK = 128;
+
+// R: 32-row blocks of the tile, all of them in every multiplying wavefront; NM: multiplying wavefronts, 32 columns each.
+template <int R, int NM>
+struct StreamCfg {
+    static constexpr int ROWS = 32 * R, COLS = 32 * NM;
+    static constexpr int THREADS = 64 * (NM + 4);
+    static constexpr int TURN = 3;                             // slabs per turn of the loop = stages
+    static constexpr int STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
+    static constexpr int SMEM = TURN * STAGE + NM * 2048;      // stages, output staging
+    static constexpr int DA = NM >= 6 ? 3 : 6;                 // slabs of A in flight, a multiple of TURN
+    static constexpr int DW = NM >= 6 ? 12 : 24;               // steps of W in flight, a divisor of a turn's 24; ten wavefronts have 168 registers each
+    static constexpr int AHEAD = R == 1 ? 7 : R == 2 ? 3 : 1;  // steps of A read ahead
+};
+
+template <int R, int NM, int EPI>
+__global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Wp,
+                                                                    const float *__restrict__ bias, bf16_t *__restrict__ out,
+                                                                    const int32_t *__restrict__ T_dev, int max_rows, int likely_rows,
+                                                                    int N, int K, int xr_bits)
+{
+    typedef StreamCfg<R, NM> Cfg;
+    constexpr int DA = Cfg::DA, DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // blocks go round-robin to the 8 XCDs (gridDim.x is a multiple of 8), which stand in a grid of xr x 8 / xr: an XCD takes every
+    // xr-th row tile and every (8 / xr)-th column tile, the row tiles that may turn out to be empty last
+    const int xcd = blockIdx.x & 7;
+    const int tm = (blockIdx.y << xr_bits) + (xcd & ((1 << xr_bits) - 1)), tn = ((blockIdx.x >> 3) << (3 - xr_bits)) + (xcd >> xr_bits);
+    const int m0 = tm * Cfg::ROWS, n0 = tn * Cfg::COLS;
+    if (m0 >= max_rows || n0 >= N) return;
+    // Tiles that likely hold rows request their slabs before the token count is there: it is the same chain of latencies as a slab's.
+    if (m0 >= likely_rows && m0 >= *T_dev) return;
+    const int slabs = K / STREAM_BK;  // the host checks K % 128 == 0
+    const int turns_end = (slabs + TURN - 1) / TURN * TURN;
+    // A tile that turns out to hold no row goes through one turn and stores nothing.
+
+    if (wave >= NM) {  // fetch A
+        constexpr int LPT = 2 * R;  // 16-byte loads per thread and slab
+        const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * K), 0, Cfg::ROWS * K * (int)sizeof(bf16_t), 0x00020000);
+        const int ft = tid - 64 * NM, lrow = ft >> 4, lch = ft & 15;
+        const int toff = (lrow * K + lch * 8) * (int)sizeof(bf16_t);
+        const int soff = lrow * 256 + ((lch ^ lrow) << 4);  // rows 16 apart share the swizzle term
+        u32x4 rg[DA][LPT];
+        // Every step issues its loads: a slab past the end gets an offset beyond the buffer (nothing is fetched, zeros
+        // come back).  Loads return in order and a wait counts the loads behind the one it is for; where a load may or may
+        // not have been issued, the compiler would have to wait for all of them.
+#define STREAM_ALOAD(p, slab)                                                                            \
+    {                                                                                                    \
+        const int o_ = (slab) < slabs ? toff + (slab) * (STREAM_BK * 2) : 0x7ff00000;                    \
+        _Pragma("unroll") for (int i = 0; i < LPT; ++i)                                                  \
+            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * K * 2, 0)); \
+    }
+#pragma unroll
+        for (int p = 0; p < DA; ++p) {
+            STREAM_ALOAD(p, p)
+            __builtin_amdgcn_sched_barrier(0);  // slab after slab: in the compiler's own order the first wait was for all of them
+        }
+        const int end = m0 < *T_dev ? turns_end : TURN;
+        int s0 = 0;
+        do {
+#pragma unroll
+            for (int p = 0; p < DA; ++p) {
+                const int s = s0 + p;
+                unsigned char *to = smem + p % TURN * Cfg::STAGE + soff;
+                if (s < end)
+#pragma unroll
+                    for (int i = 0; i < LPT; ++i) *reinterpret_cast<u32x4 *>(to + i * 16 * 256) = rg[p][i];
+                STREAM_ALOAD(p, s + DA)
+                if (s < end) __syncthreads();  // slab s is there; slab s - 2 has been read
+            }
+            s0 += DA;
+        } while (s0 < end);
+        return;
+    }
+#undef STREAM_ALOAD
+
+    const int ct = (n0 >> 5) + wave;  // the wavefront's 32 columns; the last tile may reach past N: zeros, not stored
+    const bool on = ct * 32 < N;
+    const int steps = K >> 4;
+    const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Wp + (size_t)ct * 32 * K), 0, on ? K * 64 : 0, 0x00020000);
+    u32x4 wr[DW];
+#define STREAM_WLOAD(p, step)                                                                            \
+    wr[p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, (step) < steps ? lane * 16 + (step) * 1024 : 0x7ff00000, 0, 0));
+    f32x16 acc[R];  // the sums start at the bias: register 4g + i of a lane is column 8g + 4 half + i
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + min(ct, (N >> 5) - 1) * 32 + 8 * g + 4 * half);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[r][4 * g + i] = b[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < DW; ++p) {
+        STREAM_WLOAD(p, p)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int aoff[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) aoff[j] = l32 * 256 + (((2 * j + half) ^ (l32 & 15)) << 4);
+    bf16x8 af[AHEAD + 1][R];
+#define STREAM_AREAD(step, stage)                                                                        \
+    _Pragma("unroll") for (int r = 0; r < R; ++r)                                                        \
+        af[(step) % (AHEAD + 1)][r] = *reinterpret_cast<const bf16x8 *>(smem + (stage) * Cfg::STAGE + aoff[(step) & 7] + r * 32 * 256);
+    // the turn's slab u, the pass's slab s
+#define STREAM_SLAB(s, u)                                                                                \
+    _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                                      \
+        STREAM_AREAD(j + AHEAD, (j + AHEAD < 8 ? (u) : (u) + 1) % TURN)                                  \
+        _Pragma("unroll") for (int r = 0; r < R; ++r)                                                    \
+            acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[((u) * 8 + j) % DW]), af[j % (AHEAD + 1)][r], acc[r], 0, 0, 0); \
+        STREAM_WLOAD(((u) * 8 + j) % DW, (s) * 8 + j + DW)                                               \
+        __builtin_amdgcn_sched_barrier(0);                                                               \
+    }
+    // The barrier without the wait for this wavefront's LDS reads that __syncthreads() adds: what it has read of the slab before has
+    // been used by an MFMA, and the slabs it is reading are not stored to until the next barrier.
+#define STREAM_BARRIER                                                                                   \
+    asm volatile("" ::: "memory");                                                                       \
+    __builtin_amdgcn_s_barrier();                                                                        \
+    asm volatile("" ::: "memory");
+    const int T = *T_dev;
+    const int end = m0 < T ? turns_end : TURN;
+    STREAM_BARRIER  // the fetching wavefronts' first one: slab 0
+    STREAM_BARRIER  // slab 1; before slab s there have been s + 2 of them, end in all
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) { STREAM_AREAD(j, 0) }
+    int s = 0;
+    do {
+        STREAM_SLAB(s, 0)
+        STREAM_BARRIER
+        STREAM_SLAB(s + 1, 1)
+        if (s + TURN < end) { STREAM_BARRIER }
+        STREAM_SLAB(s + 2, 2)  // its reads ahead at the very end are of a stage that is there and go unused
+        s += TURN;
+        if (s < end) { STREAM_BARRIER }
+    } while (s < end);
+#undef STREAM_BARRIER
+#undef STREAM_SLAB
+#undef STREAM_AREAD
+#undef STREAM_WLOAD
+    if (!on || m0 >= T) return;
+    // 32 x 32 outputs at a time through the wavefront's own 2 KB: 16-byte chunk c of a row at c ^ ((row >> 1) & 3), then 16-byte stores
+    unsigned char *stg = smem + TURN * Cfg::STAGE + wave * 2048;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            bf16x4 o4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o4[i] = (bf16_t)(EPI == EPI_BIAS_GELU ? gelu_erf(acc[r][4 * g + i]) : acc[r][4 * g + i]);
+            *reinterpret_cast<bf16x4 *>(stg + l32 * 64 + ((g ^ ((l32 >> 1) & 3)) << 4) + half * 8) = o4;
+        }
+        __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int rr = j * 16 + (lane >> 2), ch = lane & 3;
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + rr * 64 + ((ch ^ ((rr >> 1) & 3)) << 4));
+            *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + r * 32 + rr) * N + ct * 32 + ch * 8) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+}  // namespace

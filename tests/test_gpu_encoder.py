@@ -256,6 +256,32 @@ def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
         L.leann_destroy(ctx)
 
 
+@pytest.mark.parametrize("hidden,heads,ffn", [(640, 10, 1280), (768, 12, 3072), (1024, 16, 1920)])
+def test_tiles_of_one_round_give_the_same_bits(L, hidden, heads, ffn):
+    """Passes that fill the chip once, from one row tile to those that no longer do (all tiles from 32 x 32 to 128 x 256), with K
+    a multiple of 384 or not (the slabs behind its end are zeros), rows at, below and above a tile's edge: the bits of the
+    128 x 128 tile of the kernel for large passes."""
+    import torch
+    cfg = dict(layers=1, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=64, ln_eps=1e-12)
+    n, seq = 180, 64
+    tokens, _ = li.uniform_chunks(n, seq, 1, cfg["vocab"], 1, seq, 21)
+    lengths = np.full(n, seq, np.int32)
+    lengths[0] = 63  # rows = 64 m - 1, one less than whole tiles
+    ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 22, perturb=True, bf16_exact=True)).to(torch.bfloat16))
+    try:
+        t, l = to_dev(tokens), to_dev(lengths)
+        L.leann_set_gemm_tiles(ctx, 128, 0)
+        want = L.leann_embed(ctx, t, l, hidden=hidden)
+        L.leann_set_gemm_tiles(ctx, 256, 2048)
+        assert torch.isfinite(want).all()
+        for m in (1, 2, 4, 7, 11, 16, 24, 33, 48, 70, 100, 140, n):
+            say(f"one round of tiles, hidden {hidden}, {m} chunks")
+            assert torch.equal(L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden), want[:m]), m
+            assert torch.equal(L.leann_embed(ctx, t[1:], l[1:], n_ids=min(m, n - 1), hidden=hidden), want[1:m + 1]), m
+    finally:
+        L.leann_destroy(ctx)
+
+
 @pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 128), (384, 6, 1536), (768, 12, 3072)])
 def test_small_passes_of_any_fill_give_the_same_bits(L, hidden, heads, ffn):
     """A small pass requests its operands for the rows that it likely holds, before it knows how many there are: chunks that are
