@@ -248,17 +248,22 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
 
 // ------------------------------------------------------------------ attention
 // One block per (chunk, head), head size 64, up to 256 keys.  K (row-major, swizzled) and V^T live in LDS.
-// Each wave takes 32 query rows at a time and computes S^T = K Q^T with MFMA, so that a lane owns one
+// Each wave takes 32 query rows and computes S^T = K Q^T with MFMA, so that a lane owns one
 // query column: the softmax reductions run over the lane's own registers plus one exchange with lane^32.
 // P^T (bf16) then feeds O^T = V^T P^T directly from registers: accumulator registers 8u..8u+7 of key tile t
 // are exactly the eight k-slots of one MFMA step when V^T is read with the matching key order.
-// NKT = key tiles (of 32) the block can hold: 4 for sequences up to 128 (half the registers and LDS, twice the
-// blocks per CU), 8 for up to 256.
-template <int NKT>
+// NW = wavefronts, one per 32 query rows and 32 keys the block can hold: 4 for sequences up to 128, 8 for up to 256.
+// The scores are computed twice, once for the maxima and once tile by tile for the rest: the matrix cores have the time, and a
+// wavefront that does not hold the scores of 256 keys (128 registers) leaves room for three more on its SIMD, so that every 32
+// queries have their own.  It also makes the key tiles loops (4.9 KB of code; unrolled 12.8), which counts in passes of few chunks,
+// whose every launch fetches its code anew.  Per launch, before and now: one chunk of 80 tokens 5.8 and 5.0 us, 13 chunks 5.9 and
+// 5.3, 300 x 160 tokens of 384 elements 49.5 and 43, 2048 x 160 tokens of 768 605 and 542 (3.7 TB/s of the 4.8 that a copy reaches;
+// two blocks' loads and arithmetic take turns on a CU).
+template <int NW>
 struct AttCfg {
-    static constexpr int LP = NKT * 32;           // padded key capacity = V^T row pitch (bf16)
+    static constexpr int LP = NW * 32;            // padded key capacity = V^T row pitch (bf16)
     static constexpr int KV_BYTES = (LP * 64 + 64 * LP) * (int)sizeof(bf16_t);
-    static constexpr int SMEM = KV_BYTES + 4 * 16 * 128;  // plus, per wave, 16 output rows of 64 bf16
+    static constexpr int SMEM = KV_BYTES + NW * 16 * 128;  // plus, per wave, 16 output rows of 64 bf16
 };
 
 // V^T in LDS: row = output dimension (64 of them), LP keys per row in 16-byte groups of eight.  Inside a group of 16
@@ -268,17 +273,16 @@ struct AttCfg {
 // that one pass of the staging stores serves, then fall into 16 different bank groups (no bank conflicts either way).
 __device__ inline int vt_swizzle(int row) { return (row & 15) ^ (((row >> 4) & 3) << 1); }
 
-template <int NKT>
-__global__ __launch_bounds__(256, NKT == 4 ? 3 : 2) void attention_kernel(const bf16_t *__restrict__ qkv,
-                                                                          const int32_t *__restrict__ cu,
-                                                                          bf16_t *__restrict__ out, int d,
-                                                                          float scale_log2e)
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__restrict__ qkv, const int32_t *__restrict__ cu,
+                                                               bf16_t *__restrict__ out, int d, float scale_log2e)
 {
-    constexpr int LP = AttCfg<NKT>::LP;
+    constexpr int LP = AttCfg<NW>::LP;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t *Ks = reinterpret_cast<bf16_t *>(smem);  // [LP][64], 16-byte chunks XOR-swizzled by row
     bf16_t *Vt = Ks + LP * 64;                      // [64][LP], see vt_swizzle
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive blocks are the heads of one chunk: they read adjacent 128-byte pieces of the same QKV rows at
     // about the same time
     const int H = d >> 6;
@@ -289,169 +293,157 @@ __global__ __launch_bounds__(256, NKT == 4 ? 3 : 2) void attention_kernel(const 
     const int Lp = nkt << 5;
     const size_t ld = (size_t)3 * d;
     // Of K and V the chunk's rows and no more: reads of keys >= L bring zeros.  With a test per read the compiled code waited twice for all
-    // earlier ones in between: 6.4 us per launch for one chunk of 80 tokens, 7.2 for 13 chunks; now 5.7 and 6.2.
+    // earlier ones in between, half a microsecond each.
     const int kv_bytes = ((L - 1) * 3 * d + 64) * (int)sizeof(bf16_t), row_bytes = 3 * d * (int)sizeof(bf16_t);
-    const auto kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv + (size_t)t0 * ld + d + h * 64), 0, kv_bytes, 0x00020000);
-    const auto vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv + (size_t)t0 * ld + 2 * d + h * 64), 0, kv_bytes, 0x00020000);
     const int half = lane >> 5, l32 = lane & 31;
+    const int qb = wave, qrow = qb * 32 + l32;
 
-    // the wave's first query block goes to registers while K and V are on their way to LDS
-    bf16x8 qf[4];
-    {
-        const int qload = min(wave * 32 + l32, L - 1);
-        const bf16_t *qp = qkv + (size_t)(t0 + qload) * ld + h * 64;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16 + half * 8);
-    }
-    // Staging.  All global loads of the thread are issued before the first LDS store.  Keys >= L are zero.
+    // Staging.  Half of the wavefronts bring V, half K; all global loads of a thread are issued before its first LDS store.
+    // Keys >= L are zero.
     // V: thread (j16, hf, ch) takes the eight keys 16 j16 + 4 hf + {0..3, 8..11} of the 16-byte chunk ch (eight
     // output dimensions) and writes, per dimension, the eight keys as one 16-byte group.  Eight adjacent lanes read
     // one whole 128-byte piece of a V row.
     // K: rows as they are, 16-byte chunk ch of row key at position ch ^ ((key >> 1) & 7).
+    const bool brings_v = wave < NW / 2;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv + (size_t)t0 * ld + (brings_v ? 2 : 1) * d + h * 64), 0, kv_bytes, 0x00020000);
+    const int ch = tid & 7, st = tid & (32 * NW - 1), hf = (st >> 3) & 1, j16 = st >> 4;
+    u32x4 in[8];
     {
-        const int ch = tid & 7, hf = (tid >> 3) & 1, j16 = tid >> 4;
-        const bool v_on = j16 * 16 < Lp;
-        u32x4 vv[8], kk[NKT];
+        // V: rows key0 + {0..3, 8..11}; K: rows st / 8 + r * 4 NW
+        const int key0 = brings_v ? j16 * 16 + 4 * hf : st >> 3, step = brings_v ? 1 : 4 * NW, step4 = brings_v ? 8 : 16 * NW;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            in[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (key0 + (r & 3) * step + (r >> 2) * step4) * row_bytes + ch * 16, 0, 0));
+    }
+    // the wave's query rows go to registers while K and V are on their way to LDS
+    bf16x8 qf[4];
+    {
+        const bf16_t *qp = qkv + (size_t)(t0 + min(qrow, L - 1)) * ld + h * 64;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16 + half * 8);
+    }
+    if (!brings_v) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            const int key = j16 * 16 + 4 * hf + (r & 3) + 8 * (r >> 2);
-            vv[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, key * row_bytes + ch * 16, 0, 0));
+            const int key = (st >> 3) + r * 4 * NW;
+            if (key < Lp) *reinterpret_cast<u32x4 *>(Ks + key * 64 + ((ch ^ ((key >> 1) & 7)) << 3)) = in[r];
         }
+    } else if (j16 * 16 < Lp) {
 #pragma unroll
-        for (int r = 0; r < NKT; ++r) {
-            const int key = r * 32 + (tid >> 3);
-            kk[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, key * row_bytes + ch * 16, 0, 0));
-        }
+        for (int i = 0; i < 8; ++i) {  // output dimension ch * 8 + i: element i of each of the eight key rows
+            u32x4 o;
 #pragma unroll
-        for (int r = 0; r < NKT; ++r) {
-            const int key = r * 32 + (tid >> 3);
-            if (r == 0 || r < nkt) *reinterpret_cast<u32x4 *>(Ks + key * 64 + ((ch ^ ((key >> 1) & 7)) << 3)) = kk[r];
-        }
-        if (v_on) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {  // output dimension ch * 8 + i: element i of each of the eight key rows
-                u32x4 o;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t a = vv[2 * w][i >> 1], b = vv[2 * w + 1][i >> 1];
-                    o[w] = (i & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
-                }
-                const int row = ch * 8 + i;
-                *reinterpret_cast<u32x4 *>(Vt + row * LP + (((2 * j16 + hf) ^ vt_swizzle(row)) << 3)) = o;
+            for (int w = 0; w < 4; ++w) {
+                const uint32_t a = in[2 * w][i >> 1], b = in[2 * w + 1][i >> 1];
+                o[w] = (i & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
             }
+            const int row = ch * 8 + i;
+            *reinterpret_cast<u32x4 *>(Vt + row * LP + (((2 * j16 + hf) ^ vt_swizzle(row)) << 3)) = o;
         }
     }
     __syncthreads();
+    if (qb >= nkt) return;
 
-    for (int qb = wave; qb < nkt; qb += 4) {
-        const int qrow = qb * 32 + l32;
-        if (qb != wave) {
-            const int qload = min(qrow, L - 1);
-            const bf16_t *qp = qkv + (size_t)(t0 + qload) * ld + h * 64;
+    const int kswz = (l32 >> 1) & 7;  // rows 32 apart share the swizzle term
+    bf16x8 kf[4];
+    auto read_k = [&](int t) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16 + half * 8);
+        for (int s = 0; s < 4; ++s) kf[s] = *reinterpret_cast<const bf16x8 *>(Ks + (t * 32 + l32) * 64 + (((s * 2 + half) ^ kswz) << 3));
+    };
+    // Scores of key tile t, whose rows are in kf; then kf holds tile `next`.  The lane owns query column l32 and keys
+    // 32t + 8(r/4) + 4*half + r%4; only the last tile can hold keys >= L.
+    auto scores = [&](int t, int next) -> f32x16 {
+        f32x16 sc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], sc, 0, 0, 0);
+        read_k(next);
+        if (t == nkt - 1) {
+            const int keys = L - t * 32 - 4 * half;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + (r & 3) >= keys) sc[r] = -INFINITY;
         }
-        f32x16 sc[NKT];
+        return sc;
+    };
+    read_k(0);
+    float mx = -INFINITY;
+#pragma unroll 1
+    for (int t = 0; t < nkt; ++t) {
+        const f32x16 sc = scores(t, t + 1 < nkt ? t + 1 : 0);
 #pragma unroll
-        for (int t = 0; t < NKT; ++t) {
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float moff = mx * scale_log2e;
+    float den = 0.f;
+    f32x16 oacc[2];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sc[t][r] = 0.f;
-            if (t < nkt) {
+    for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int row = t * 32 + l32, ch = s * 2 + half;
-                    bf16x8 kf = *reinterpret_cast<const bf16x8 *>(Ks + row * 64 + ((ch ^ ((row >> 1) & 7)) << 3));
-                    sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sc[t], 0, 0, 0);
-                }
+        for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < nkt; ++t) {
+        f32x16 sc = scores(t, t + 1 < nkt ? t + 1 : 0);
+        bf16x8 vf[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) {
+                const int pg = 4 * t + 2 * u + half;  // the lane's group: slots 0..3 = keys 32t + 16u + 4 half + 0..3, slots 4..7 = those + 8
+                const int row = dt * 32 + l32;
+                vf[u][dt] = *reinterpret_cast<const bf16x8 *>(Vt + row * LP + ((pg ^ vt_swizzle(row)) << 3));
             }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - moff);  // argument <= 0: no overflow, underflow to 0 is exact enough
+            sc[r] = p;
+            den += p;
         }
-        // lane owns query column l32 and keys 32t + 8(r/4) + 4*half + r%4; only the last tile can hold keys >= L.
-        // The bound is re-read per query block (the empty statement hides that it does not change): hoisted out of
-        // the loop, the 128 comparison results of the unrolled tiles would be kept in scalar registers and spilled.
-        int l_cmp = L - 4 * half;
-        asm volatile("" : "+v"(l_cmp));
-        float mx = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < NKT; ++t)
-            if (t < nkt) {
-                if (t == nkt - 1) {
+        for (int u = 0; u < 2; ++u) {
+            bf16x8 pf;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (t * 32 + 8 * (r >> 2) + (r & 3) >= l_cmp) sc[t][r] = -INFINITY;
-                }
+            for (int i = 0; i < 8; ++i) pf[i] = (bf16_t)sc[8 * u + i];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[t][r]);
-            }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float moff = mx * scale_log2e;
-        float den = 0.f;
-#pragma unroll
-        for (int t = 0; t < NKT; ++t)
-            if (t < nkt) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float p = __builtin_amdgcn_exp2f(sc[t][r] * scale_log2e - moff);  // argument <= 0: no overflow, underflow to 0 is exact enough
-                    sc[t][r] = p;
-                    den += p;
-                }
-            }
-        den += __shfl_xor(den, 32, 64);
+            for (int dt = 0; dt < 2; ++dt) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], pf, oacc[dt], 0, 0, 0);
+        }
+    }
+    den += __shfl_xor(den, 32, 64);
 
-        f32x16 oacc[2];
+    // The lane owns query l32 and, per (dt, g), the four adjacent outputs dt*32 + 8g + 4*half + 0..3.  Sixteen
+    // queries at a time go through the wave's own 2 KB of LDS (8-byte unit u of a row at position u ^ swz(row):
+    // the 16 lanes served together hit all banks once), so that the global stores are 16 bytes per lane and
+    // whole 128-byte lines per 8 lanes (stores of 8 bytes per lane to 32 rows cost a quarter of the kernel's time).
+    const float inv = 1.0f / den;
+    unsigned char *ostg = smem + AttCfg<NW>::KV_BYTES + wave * (16 * 128);
+    const int r16 = l32 & 15;
+    const int wswz = ((r16 & 7) << 1) | (r16 >> 3);
+    const int orow = lane >> 3, och = lane & 7;
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+    for (int hp = 0; hp < 2; ++hp) {
+        if ((l32 >> 4) == hp) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
+            for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-        for (int t = 0; t < NKT; ++t)
-            if (t < nkt) {
+                for (int g = 0; g < 4; ++g) {
+                    bf16x4 o4;
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    bf16x8 pf;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) pf[i] = (bf16_t)sc[t][8 * u + i];
-                    const int pg = 4 * t + 2 * u + half;  // the lane's group: slots 0..3 = keys 32t + 16u + 4 half + 0..3, slots 4..7 = those + 8
-#pragma unroll
-                    for (int dt = 0; dt < 2; ++dt) {
-                        const int row = dt * 32 + l32;
-                        const bf16x8 vf = *reinterpret_cast<const bf16x8 *>(Vt + row * LP + ((pg ^ vt_swizzle(row)) << 3));
-                        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, oacc[dt], 0, 0, 0);
-                    }
+                    for (int i = 0; i < 4; ++i) o4[i] = (bf16_t)(oacc[dt][4 * g + i] * inv);
+                    const int u = dt * 8 + 2 * g + half;
+                    *reinterpret_cast<bf16x4 *>(ostg + r16 * 128 + ((u ^ wswz) << 3)) = o4;
                 }
-            }
-        // The lane owns query l32 and, per (dt, g), the four adjacent outputs dt*32 + 8g + 4*half + 0..3.  Sixteen
-        // queries at a time go through the wave's own 2 KB of LDS (8-byte unit u of a row at position u ^ swz(row):
-        // the 16 lanes served together hit all banks once), so that the global stores are 16 bytes per lane and
-        // whole 128-byte lines per 8 lanes (stores of 8 bytes per lane to 32 rows cost a quarter of the kernel's time).
-        const float inv = 1.0f / den;
-        unsigned char *ostg = smem + AttCfg<NKT>::KV_BYTES + wave * (16 * 128);
-        const int r16 = l32 & 15;
-        const int wswz = ((r16 & 7) << 1) | (r16 >> 3);
-        const int orow = lane >> 3, och = lane & 7;
-#pragma unroll
-        for (int hp = 0; hp < 2; ++hp) {
-            if ((l32 >> 4) == hp) {
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        bf16x4 o4;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o4[i] = (bf16_t)(oacc[dt][4 * g + i] * inv);
-                        const int u = dt * 8 + 2 * g + half;
-                        *reinterpret_cast<bf16x4 *>(ostg + r16 * 128 + ((u ^ wswz) << 3)) = o4;
-                    }
-            }
-            __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int lr = j * 8 + orow, q = qb * 32 + hp * 16 + lr;
-                u32x4 v = *reinterpret_cast<const u32x4 *>(ostg + lr * 128 + ((och ^ orow) << 4));
-                if (j & 1) v = u32x4{v[2], v[3], v[0], v[1]};  // rows 8..15 hold the halves of a chunk swapped
-                if (q < L) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + (size_t)(t0 + q) * d + h * 64 + och * 8));
-            }
-            __builtin_amdgcn_wave_barrier();
         }
+        __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int lr = j * 8 + orow, q = qb * 32 + hp * 16 + lr;
+            u32x4 v = *reinterpret_cast<const u32x4 *>(ostg + lr * 128 + ((och ^ orow) << 4));
+            if (j & 1) v = u32x4{v[2], v[3], v[0], v[1]};  // rows 8..15 hold the halves of a chunk swapped
+            if (q < L) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + (size_t)(t0 + q) * d + h * 64 + och * 8));
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -785,10 +777,10 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
             {
                 ProfScope prof(ctx, LEANN_PROF_ATTENTION);
                 if (seq <= 128)
-                    hipLaunchKernelGGL(attention_kernel<4>, dim3((unsigned)m * H), dim3(256), AttCfg<4>::SMEM, ctx->stream, qkv, cu,
+                    hipLaunchKernelGGL(attention_kernel<4>, dim3((unsigned)m * H), dim3(64 * 4), AttCfg<4>::SMEM, ctx->stream, qkv, cu,
                                        att, d, scale_log2e);
                 else
-                    hipLaunchKernelGGL(attention_kernel<8>, dim3((unsigned)m * H), dim3(256), AttCfg<8>::SMEM, ctx->stream, qkv, cu,
+                    hipLaunchKernelGGL(attention_kernel<8>, dim3((unsigned)m * H), dim3(64 * 8), AttCfg<8>::SMEM, ctx->stream, qkv, cu,
                                        att, d, scale_log2e);
             }
             LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, {w.wo, w.wo_p}, w.bo, delta, T_dev, max_rows, rows, d, d));
