@@ -169,6 +169,10 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
         if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount >= 8)
             ctx->num_cus = prop.multiProcessorCount;
     }
+    {
+        int khz = 0;
+        if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) ctx->clock_khz = khz;
+    }
     if (enc_ln_blocks_per_cu(&ctx->ln_blocks_per_cu) != LEANN_OK) {
         leann_destroy(ctx);
         return LEANN_EDEVICE;

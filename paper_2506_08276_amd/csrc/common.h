@@ -78,6 +78,7 @@ struct leann_ctx {
     long long *host_counters = nullptr;  // pinned host memory: a search round's counters
     int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags
     hipEvent_t pass_event = nullptr;     // recorded behind the kernel that counts an encoder pass's tokens
+    double clock_khz = 1e5;              // of the kernels' wall_clock64()
     int64_t memo_rows = 0;  // rows of the per-call embedding memo (leann_set_call_memo), 0 = off
     // optional per-kernel timing (leann_profile_begin / leann_profile_end)
     bool prof_on = false;

@@ -8,8 +8,8 @@
 // against their own query and try-inserts them into EQ.  Per query this is exactly the sequential algorithm; batching
 // across queries changes no value because the encoder's output for a chunk does not depend on the rest of the batch.
 #include <algorithm>
+#include <chrono>
 #include <type_traits>
-#include <vector>
 
 #include "advance_plan.h"
 #include "common.h"
@@ -41,7 +41,7 @@ struct SearchState {
     int32_t *n_flush;     // [G] flushes so far
     int64_t *enc_ids;     // [G * pcap]
     long long *counters;  // see CTR_*
-    long long *host_counters;  // the same in host memory, written at the end of every round
+    long long *host_counters;  // the same in host memory and, behind them, the number of the last publish()
     const float *lut;     // [G][m_sub][256]
     const int32_t *slot_of;     // stored-embedding table, NULL: none
     const float *cache_emb;
@@ -53,7 +53,9 @@ struct SearchState {
 };
 
 // CTR_ROUNDS: most flushes of a query, belongs to one group of queries; CTR_PENDING .. CTR_TICKET belong to one round
-enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_ROUNDS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET, CTR_COUNT };
+enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_ROUNDS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET,
+       CTR_T_START, CTR_T_ROUND, CTR_T_TRAVERSE, CTR_T_END,  // wall_clock64(): of the call's start, of the round's, between round start and collect_kernel's end in all
+       CTR_COUNT };
 enum { ERR_BAD_NEIGHBOUR = 1, ERR_AQ_OVERFLOW = 2, ERR_P_OVERFLOW = 4, ERR_BAD_SLOT = 8 };
 
 __device__ inline bool better(float sa, uint32_t ia, float sb, uint32_t ib) { return sa > sb || (sa == sb && ia < ib); }
@@ -74,7 +76,33 @@ __device__ inline void wave_best(float &s, uint32_t &id, int &pos)
     }
 }
 
-__global__ void maxdeg_kernel(const uint64_t *__restrict__ row_ptr, int64_t n, long long *__restrict__ counters)
+template <class T>
+__device__ inline void store_through(T *p, T v)  // past the L2
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ inline void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The counters to the host, and then `seq`, which it waits for: by the last of a grid's blocks to get here, one wavefront of each.  Lane
+// 0 has done its block's atomics on them.  A round's end is a chain of latencies from the last hop to the encoder's first kernel:
+// hipStreamSynchronize comes back 10.7 us after an empty kernel's launch, a host that looks at a word of pinned memory 6.3 us after it.
+// Only the counters have to be there (device-scope atomics and stores past the L2, in order by waits; a fence would also write back
+// the L2): the kernels that use a round's other results come behind it in the stream.
+__device__ inline void publish(long long *counters, long long *host_counters, long long seq)
+{
+    const int lane = threadIdx.x & 63;
+    int last = 0;
+    wait_for_stores();  // the atomics: those whose results nobody reads, too
+    if (lane == 0) last = gridDim.x == 1 || __hip_atomic_fetch_add(&counters[CTR_TICKET], 1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    if (lane == CTR_TICKET) __hip_atomic_store(&counters[CTR_TICKET], 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < CTR_COUNT) store_through(&host_counters[lane], __hip_atomic_load(&counters[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    wait_for_stores();
+    if (lane == 0) store_through(&host_counters[CTR_COUNT], seq);
+}
+
+__global__ __launch_bounds__(256) void maxdeg_kernel(const uint64_t *__restrict__ row_ptr, int64_t n, long long *__restrict__ counters,
+                                                     long long *__restrict__ host_counters, long long seq)
 {
     __shared__ long long part[4];
     long long best = 0;
@@ -86,12 +114,19 @@ __global__ void maxdeg_kernel(const uint64_t *__restrict__ row_ptr, int64_t n, l
     __syncthreads();
     // one atomic per block: a thousand of them on one word, one per wavefront, were most of the kernel's 13.5 us
     if (threadIdx.x == 0) atomicMax(&counters[CTR_MAXDEG], max(max(part[0], part[1]), max(part[2], part[3])));
+    if (threadIdx.x < 64) publish(counters, host_counters, seq);
 }
 
-__global__ void init_kernel(SearchState s, int g, uint32_t entry)
+// The state of a group of queries at its start, grid (any, queries).  n > 0: the call's first group, the owners of its n chunks are
+// cleared too.
+__global__ __launch_bounds__(256) void init_kernel(SearchState s, uint32_t entry, int64_t n)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= g) return;
+    const int q = blockIdx.y;
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x, across = (int64_t)gridDim.x * 256;
+    for (int64_t i = q * across + x; i < n; i += gridDim.y * across) s.owner[i] = ~0ull;
+    for (int64_t w = x; w < s.words; w += across) s.seen[q * s.words + w] = w == entry >> 5 ? 1u << (entry & 31) : 0u;
+    if (x > 0) return;
+    if (q == 0 && n > 0) s.counters[CTR_T_START] = wall_clock64();
     s.eq_n[q] = 0;
     s.aq_tail[q] = 0;
     s.aq_live[q] = 0;
@@ -100,7 +135,6 @@ __global__ void init_kernel(SearchState s, int g, uint32_t entry)
     if (q == 0) s.counters[CTR_ROUNDS] = 0;
     s.n_pend[q] = 1;  // the entry point's exact score is the first flush
     s.pend[(size_t)q * s.pcap] = entry;
-    s.seen[(size_t)q * s.words + (entry >> 5)] = 1u << (entry & 31);
 }
 
 // Score, expand, score again: one block per query takes its query as far as it goes without the encoder.
@@ -192,8 +226,10 @@ __global__ __launch_bounds__(ADV_THREADS, BLOCKS) void advance_kernel(SearchStat
     __shared__ int sh_pend, sh_tail, sh_hops, sh_missing, sh_bad;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (q == 0 && tid == 0)  // the round's counters: collect_kernel, which runs next, adds to them
-        for (int i = CTR_PENDING; i <= CTR_TICKET; ++i) s.counters[i] = 0;
+    if (q == 0 && tid == 0) {  // the round's counters: collect_kernel, which runs next, adds to them
+        for (int i = CTR_PENDING; i < CTR_TICKET; ++i) s.counters[i] = 0;
+        s.counters[CTR_T_ROUND] = wall_clock64();
+    }
     if (s.done[q]) return;
     uint32_t *pend = s.pend + (size_t)q * s.pcap;
     uint64_t *aqg = s.aq_key + (size_t)q * 64 * s.aq_rows;
@@ -687,7 +723,7 @@ __global__ __launch_bounds__(ADV_THREADS, BLOCKS) void advance_kernel(SearchStat
 
 // Pack the round: encoder input list (one entry per owned chunk; the order does not matter), owners' rows, the round's
 // totals.  One wavefront per query; the last block hands the counters to the host.
-__global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_t *__restrict__ lengths, int seq)
+__global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_t *__restrict__ lengths, int seq, long long number)
 {
     const int q = blockIdx.x, lane = threadIdx.x;
     const int np = s.done[q] ? 0 : s.n_pend[q];
@@ -718,22 +754,21 @@ __global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) tokens += __shfl_xor(tokens, o, 64);
-    int last = 0;
     if (lane == 0) {
         if (np) {
             atomicAdd((unsigned long long *)&s.counters[CTR_PENDING], (unsigned long long)np);
             atomicAdd((unsigned long long *)&s.counters[CTR_ROUND_TOKENS], (unsigned long long)tokens);
         }
-        __threadfence();
-        last = atomicAdd((unsigned long long *)&s.counters[CTR_TICKET], 1ull) == gridDim.x - 1;
+        if (q == 0) atomicAdd((unsigned long long *)&s.counters[CTR_T_TRAVERSE], (unsigned long long)(wall_clock64() - s.counters[CTR_T_ROUND]));
     }
-    if (__builtin_amdgcn_readfirstlane(last)) {
-        __threadfence();
-        if (lane < CTR_COUNT)
-            __hip_atomic_store(&s.host_counters[lane], __hip_atomic_load(&s.counters[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __threadfence_system();
-    }
+    publish(s.counters, s.host_counters, number);
+}
+
+// The call's end: behind the last finalize_kernel, whose results are then where all readers see them.
+__global__ __launch_bounds__(64) void end_kernel(SearchState s, long long seq)
+{
+    if (threadIdx.x == 0) __hip_atomic_store(&s.counters[CTR_T_END], (long long)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    publish(s.counters, s.host_counters, seq);
 }
 
 // The call's embedding memo: rows the encoder produced in this round are kept (while there is room) so that a later
@@ -879,6 +914,21 @@ int search_init_device()
     return LEANN_OK;
 }
 
+// Looks at the word until it is seq (or a later number): false if that takes long, as where a kernel is slow, has faulted or was not
+// run (stream capture).  The caller then waits for the stream, which reports what is wrong.
+static bool word_arrives(const uint32_t *word, uint32_t seq)
+{
+    constexpr auto LONG = std::chrono::milliseconds(20);
+    const auto begin = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int i = 0; i < 256; ++i) {
+            if ((int32_t)(__atomic_load_n(word, __ATOMIC_ACQUIRE) - seq) >= 0) return true;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() - begin > LONG) return false;
+    }
+}
+
 int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_graph *graph, const leann_pq *pq,
                const leann_chunks *chunks, const leann_emb_cache *cache, const leann_updates *upd, int32_t ef, int32_t k,
                float alpha, int32_t batch, int64_t *out_ids_dev, float *out_scores_dev, leann_search_stats *stats)
@@ -890,12 +940,18 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     long long *counters = (long long *)ctx->s_misc.p;
     LEANN_HIP(hipMemsetAsync(counters, 0, CTR_COUNT * sizeof(long long), st));
     LEANN_TRY(clear_host_flags(ctx));
-    hipLaunchKernelGGL(maxdeg_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (n + 2047) / 2048))), dim3(256), 0, st, graph->row_ptr, n, counters);
-    if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, CTR_COUNT * sizeof(long long), hipHostMallocDefault));
-    long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after a synchronisation only
-    const size_t ctr_bytes = CTR_COUNT * sizeof(long long);
-    LEANN_HIP(hipMemcpyAsync(h_ctr, counters, ctr_bytes, hipMemcpyDeviceToHost, st));
-    LEANN_HIP(hipStreamSynchronize(st));
+    if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, (CTR_COUNT + 1) * sizeof(long long), hipHostMallocDefault));
+    long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after wait() only
+    uint32_t published = 0;
+    h_ctr[CTR_COUNT] = 0;  // every call waits for its last publish()
+    auto wait = [&]() -> int {  // for the publish() that was launched last
+        LEANN_HIP(hipGetLastError());
+        if (!word_arrives(reinterpret_cast<const uint32_t *>(&h_ctr[CTR_COUNT]), published)) LEANN_HIP(hipStreamSynchronize(st));
+        return LEANN_OK;
+    };
+    hipLaunchKernelGGL(maxdeg_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (n + 2047) / 2048))), dim3(256), 0, st,
+                       graph->row_ptr, n, counters, h_ctr, (long long)++published);
+    LEANN_TRY(wait());
     const long long maxdeg = h_ctr[CTR_MAXDEG];
 
     // capacities
@@ -931,7 +987,6 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     LEANN_TRY(ctx->reserve(ctx->s_lut, (size_t)G * m_sub * KSUB * sizeof(float)));
     LEANN_TRY(ctx->reserve(ctx->s_emb, (size_t)G * pcap * d * sizeof(float)));
     LEANN_TRY(ctx->reserve(ctx->s_owner, (size_t)n * sizeof(unsigned long long)));
-    LEANN_HIP(hipMemsetAsync(ctx->s_owner.p, 0xff, (size_t)n * sizeof(unsigned long long), st));
     // per-call embedding memo (leann_set_call_memo): empty at the start of every call
     int64_t memo_n = 0;
     if (memo_cap > 0) {
@@ -987,30 +1042,15 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     const auto advance = advance_for(d, plan.blocks);
     uint32_t launches = 0;
 
-    struct Events : std::vector<hipEvent_t> {  // destroyed on every way out of this function
-        ~Events()
-        {
-            for (hipEvent_t e : *this) (void)hipEventDestroy(e);
-        }
-    } evs;
-    auto mark = [&]() -> int {
-        hipEvent_t e;
-        LEANN_HIP(hipEventCreate(&e));
-        LEANN_HIP(hipEventRecord(e, st));
-        evs.push_back(e);
-        return LEANN_OK;
-    };
     int rc = LEANN_OK;
     int64_t rounds = 0, encoded = 0;
-    LEANN_TRY(mark());  // evs[0]: start
     for (int64_t q0 = 0; q0 < nq && rc == LEANN_OK; q0 += G) {
         const int g = (int)std::min<int64_t>(G, nq - q0);
         const float *qg = queries_dev + (size_t)q0 * d;
-        LEANN_HIP(hipMemsetAsync(s.seen, 0, (size_t)g * words * 4, st));
-        hipLaunchKernelGGL(init_kernel, dim3((g + 255) / 256), dim3(256), 0, st, s, g, graph->entry);
+        const int64_t per_query = std::min<int64_t>((words + 255) / 256, (8 * ctx->num_cus + g - 1) / g);
+        hipLaunchKernelGGL(init_kernel, dim3((unsigned)per_query, g), dim3(256), 0, st, s, graph->entry, q0 == 0 ? n : 0);
         LEANN_TRY(pq_build_lut(ctx, qg, g, pq, (float *)ctx->s_lut.p));
         for (bool have_results = false;; have_results = true) {
-            LEANN_TRY(mark());
             {
                 ProfScope prof(ctx, LEANN_PROF_TRAVERSE);
                 hipLaunchKernelGGL(advance, dim3(g), dim3(ADV_THREADS), plan.bytes, st, s, graph->row_ptr, graph->col_idx, n,
@@ -1018,10 +1058,9 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             }
             {
                 ProfScope prof(ctx, LEANN_PROF_COLLECT);
-                hipLaunchKernelGGL(collect_kernel, dim3(g), dim3(64), 0, st, s, chunks->lengths, chunks->seq);
+                hipLaunchKernelGGL(collect_kernel, dim3(g), dim3(64), 0, st, s, chunks->lengths, chunks->seq, (long long)++published);
             }
-            LEANN_TRY(mark());
-            LEANN_HIP(hipStreamSynchronize(st));
+            LEANN_TRY(wait());
             if (h_ctr[CTR_ERR]) {
                 rc = (h_ctr[CTR_ERR] & (ERR_BAD_NEIGHBOUR | ERR_BAD_SLOT)) ? LEANN_EINVAL : LEANN_ECAPACITY;
                 leann_set_error((h_ctr[CTR_ERR] & ERR_BAD_NEIGHBOUR) ? "graph holds a neighbour id >= n"
@@ -1067,11 +1106,9 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                            upd ? upd->buffer_ids : nullptr, nb, out_ids_dev + (size_t)q0 * k,
                            out_scores_dev + (size_t)q0 * k);
     }
-    if (rc == LEANN_OK) rc = mark();
-    if (rc == LEANN_OK) {
-        LEANN_HIP(hipMemcpyAsync(h_ctr, counters, ctr_bytes, hipMemcpyDeviceToHost, st));
-    }
-    hipError_t sync_rc = hipStreamSynchronize(st);
+    if (rc == LEANN_OK) hipLaunchKernelGGL(end_kernel, dim3(1), dim3(64), 0, st, s, (long long)++published);
+    // The call's last wait is for the stream: a caller who waits for it next, as most do, would otherwise pay for that.
+    const hipError_t sync_rc = hipStreamSynchronize(st);
     if (rc == LEANN_OK && sync_rc != hipSuccess) {
         leann_set_error("search kernels failed: %s", hipGetErrorString(sync_rc));
         rc = LEANN_EDEVICE;
@@ -1092,14 +1129,8 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
         stats->encoded_tokens = h_ctr[CTR_TOKENS];
         stats->flushes = h_ctr[CTR_FLUSH];
         stats->rounds = rounds;
-        float total = 0.f, trav = 0.f;
-        (void)hipEventElapsedTime(&total, evs.front(), evs.back());
-        // events come in (round start, after collect) pairs between the first and the last one
-        for (size_t i = 1; i + 1 < evs.size(); i += 2) {
-            float t = 0.f;
-            (void)hipEventElapsedTime(&t, evs[i], evs[i + 1]);
-            trav += t;
-        }
+        const float total = (float)((h_ctr[CTR_T_END] - h_ctr[CTR_T_START]) / ctx->clock_khz);
+        const float trav = (float)(h_ctr[CTR_T_TRAVERSE] / ctx->clock_khz);
         stats->total_ms = total;
         stats->traverse_ms = trav;
         stats->encoder_ms = total - trav;
