@@ -9,6 +9,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm.h"
@@ -577,43 +578,61 @@ StreamPlan plan_stream(const leann_ctx *ctx, int tile_rows, int tile_cols, int r
     return best;
 }
 
-template <int R, int NM, int EPI>
+// A tile of the stream kernels: R blocks of W rows by NM wavefronts of W columns.
+template <int W, int R, int NM, int EPI>
+struct StreamTile {
+    static_assert(W == 16 || W == 32, "the MFMA's width");
+    typedef std::conditional_t<W == 16, Stream16Cfg<R, NM>, StreamCfg<R, NM>> Cfg;
+    static auto kernel()
+    {
+        if constexpr (W == 16) return gemm_stream16_kernel<R, NM, EPI>;
+        else return gemm_stream_kernel<R, NM, EPI>;
+    }
+};
+
+template <int W, int R, int NM, int EPI>
 int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *Wp, const float *bias, bf16_t *out,
                        const int32_t *T_dev, int max_rows, int likely_rows, int N, int K, int xr)
 {
-    typedef StreamCfg<R, NM> Cfg;
+    typedef StreamTile<W, R, NM, EPI> Tile;
+    typedef typename Tile::Cfg Cfg;
     const int rt = (max_rows + Cfg::ROWS - 1) / Cfg::ROWS, ct = (N + Cfg::COLS - 1) / Cfg::COLS, xc = 8 / xr;
     ProfScope prof(ctx, prof_kind);
-    hipLaunchKernelGGL((gemm_stream_kernel<R, NM, EPI>), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
+    hipLaunchKernelGGL(Tile::kernel(), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
                        Cfg::SMEM, ctx->stream, A, Wp, bias, out, T_dev, max_rows, likely_rows, N, K, __builtin_ctz(xr));
     LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
 
-// Tiles of gemm_stream_kernel and what a launch takes while its blocks fit the chip at once: microseconds besides the K loop and per
-// 768 elements of K.
+// Tiles of the stream kernels (width, blocks of rows, wavefronts) and what a launch takes while its blocks fit the chip at once:
+// microseconds besides the K loop and per 768 elements of K.
 #define LEANN_STREAM_TILES(X)                                                                            \
-    X(1, 1, 2.4, 1.18) X(1, 2, 2.5, 1.36) X(1, 3, 2.5, 1.77) X(1, 4, 2.6, 2.22) X(2, 2, 3.15, 1.94)      \
-    X(2, 3, 3.1, 2.6) X(2, 4, 3.1, 3.1) X(2, 6, 3.3, 4.15) X(2, 8, 3.4, 5.0) X(4, 6, 4.6, 7.4) X(4, 8, 4.9, 8.8)
+    X(16, 2, 1, 1.85, 0.85) X(16, 2, 2, 2.25, 0.92) X(16, 2, 3, 2.35, 1.08) X(16, 2, 4, 2.2, 1.3) X(32, 1, 3, 2.5, 1.68) X(32, 1, 4, 2.55, 2.1) \
+    X(16, 4, 4, 2.85, 1.82) X(32, 2, 3, 3.2, 2.25) X(32, 2, 4, 3.2, 2.65) X(32, 2, 6, 3.3, 4.15) X(32, 2, 8, 3.4, 5.0) X(32, 4, 6, 4.6, 7.4)   \
+    X(32, 4, 8, 4.9, 8.8)
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
-// Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; 32 R x 32 NM: stream):
-//                       32x32   32x64   32x96  32x128   64x64   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
-//    80 x  768 x  768     3.4     3.6     3.9     4.3     4.8     5.1                                          |   8.6
-//    80 x  768 x 3072     7.0     7.5     8.9    10.8    10.5                                                  |  26.1
-//   450 x 2304 x  768                     6.8     7.7     8.6     5.6     6.0     6.8     7.2                  |   9.8
-//  1040 x  768 x  768             6.2     6.6     4.9     5.2     5.5     5.8     6.6                          |   9.1
-//  1040 x 2304 x  768                                            10.0             7.4     7.9    10.7          |  10.7
-//  2000 x 3072 x  768                                                            14.6    15.8    13.4    14.1  |  19.0    19.0
-//  2000 x  768 x 3072                                            14.2    15.1    18.0                          |  31.4    56.4
-//  2500 x 1152 x  384                                             8.2             5.7     5.9     7.8     8.2  |   6.6    11.3
-//  3500 x 1152 x  384                                                     9.1     9.4     9.9     8.1     8.6  |   6.9    11.2
-//  3500 x 3072 x  768                                                                            23.6    25.1  |  28.3    21.6
-//  8000 x  768 x 3072                                                            42.7    47.1    37.0    37.5  |  51.2    56.5
-// 10000 x  384 x 1536                                                            21.5    23.9    17.5    18.5  |  18.9    30.4
-// 12000 x  768 x  768                                                                            22.3    24.3  |  23.7    19.1
-// The stream kernel's smallest tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands'
-// way); its figures above are for N = 2304 at K = 768.  gemm_kernel walks over its tiles: what decides is how many the busiest CU gets,
+// Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
+// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
+//                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
+//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.2 |     3.6     4.0     4.6     4.9                                 |   8.6
+//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.7 |     8.6    10.6    11.2    12.9                                 |  26.1
+//   244 x 2304 x  768                                     4.7 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
+//   244 x  768 x 3072             5.8     6.6     7.2     9.8 |     8.8    10.7    11.3    13.0                                 |
+//   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |   9.8
+//   450 x  768 x 3072                     7.2     7.2     9.9 |     8.9    10.7    11.3    12.9                                 |
+//  1040 x  768 x  768                                     4.9 |             4.9     5.2     5.4     6.5                         |   9.1
+//  1040 x  768 x 3072                                    10.4 |            12.0    11.9    13.4    17.2                         |
+//  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |  10.7
+//  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |  19.0    19.0
+//  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |   6.6    11.3
+//  3500 x 1152 x  384                                         |                                     9.4     9.9     8.1     8.6 |   6.9    11.2
+//  3500 x 3072 x  768                                         |                                                    23.6    25.1 |  28.3    21.6
+//  8000 x  768 x 3072                                         |                                    42.7    47.1    37.0    37.5 |  51.2    56.5
+// 10000 x  384 x 1536                                         |                                    21.5    23.9    17.5    18.5 |  18.9    30.4
+// 12000 x  768 x  768                                         |                                                    22.3    24.3 |  23.7    19.1
+// The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).  Tiles
+// of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2 and 4.6).  gemm_kernel walks over its tiles: what decides is how many the busiest CU gets,
 // c = ceil(tiles / CUs).  128x128 takes about 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or,
 // next to the stream kernel, 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.
 template <int EPI>
@@ -631,11 +650,11 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const
         const double large_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
         double best_us = INFINITY;
         int best = -1, best_xr = 1, tile = 0;
-#define LEANN_TILE(R, NM, US, US_K)                                                                                   \
+#define LEANN_TILE(W, R, NM, US, US_K)                                                                                \
         {                                                                                                             \
-            const StreamPlan p = plan_stream(ctx, 32 * R, 32 * NM, rows, N);                                          \
+            const StreamPlan p = plan_stream(ctx, W * R, W * NM, rows, N);                                            \
             const double us = US + US_K * k;                                                                          \
-            if (p.rounds == 1 && us < best_us && us < large_us && (R * NM > 4 || rows <= ctx->gemm_small_rows)) {     \
+            if (p.rounds == 1 && us < best_us && us < large_us && (W * R * W * NM > 4096 || rows <= ctx->gemm_small_rows)) { \
                 best_us = us;                                                                                         \
                 best = tile;                                                                                          \
                 best_xr = p.xr;                                                                                       \
@@ -645,9 +664,9 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const
         LEANN_STREAM_TILES(LEANN_TILE)
 #undef LEANN_TILE
         tile = 0;
-#define LEANN_TILE(R, NM, US, US_K)                                                                                   \
+#define LEANN_TILE(WIDTH, R, NM, US, US_K)                                                                            \
         if (best == tile++)                                                                                           \
-            return launch_gemm_stream<R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, best_xr);
+            return launch_gemm_stream<WIDTH, R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, best_xr);
         LEANN_STREAM_TILES(LEANN_TILE)
 #undef LEANN_TILE
     }
@@ -655,11 +674,11 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const
     return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);
 }
 
-template <int R, int NM, int EPI>
+template <int W, int R, int NM, int EPI>
 int gemm_stream_allow_lds()
 {
-    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_stream_kernel<R, NM, EPI>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, StreamCfg<R, NM>::SMEM));
+    typedef StreamTile<W, R, NM, EPI> Tile;
+    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(Tile::kernel()), hipFuncAttributeMaxDynamicSharedMemorySize, Tile::Cfg::SMEM));
     return LEANN_OK;
 }
 
@@ -689,9 +708,9 @@ int enc_init_device()
     LEANN_TRY((gemm_allow_lds<256, 256, EPI_BIAS_GELU>()));
     LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS>()));
     LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS_GELU>()));
-#define LEANN_TILE(R, NM, US, US_K)                               \
-    LEANN_TRY((gemm_stream_allow_lds<R, NM, EPI_BIAS>()));         \
-    LEANN_TRY((gemm_stream_allow_lds<R, NM, EPI_BIAS_GELU>()));
+#define LEANN_TILE(W, R, NM, US, US_K)                            \
+    LEANN_TRY((gemm_stream_allow_lds<W, R, NM, EPI_BIAS>()));      \
+    LEANN_TRY((gemm_stream_allow_lds<W, R, NM, EPI_BIAS_GELU>()));
     LEANN_STREAM_TILES(LEANN_TILE)
 #undef LEANN_TILE
     LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(attention_kernel<8>),

@@ -23,8 +23,8 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 // tile's work hides a wait.  What counts then is how many bytes a CU has on their way and that nothing on the chain over K waits for LDS:
 //  - W is kept a second time in operand order, so a multiplying wavefront reads its own 32 columns straight into registers, DW
 //    steps of 16 elements ahead, 1 KB per request.  W takes no LDS space, stores or reads, and no barrier.
-//  - A goes through LDS: four wavefronts fetch K-slabs of 128 (a row's slab is two whole lines), DA slabs ahead in registers, into
-//    a ring of three stages.  A multiplying wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead,
+//  - A goes through LDS: four wavefronts fetch K-slabs of 128 (a row's slab is two whole lines), three slabs ahead in registers, into
+//    a ring of three stages (with six ahead, the first one waits longer: 0.1 to 0.4 us per launch up to 64 x 128).  A multiplying wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead,
 //    across slabs: the slab after the current one is always there already.  One barrier per slab, at which only the
 //    fetching wavefronts wait for their LDS stores.  A slab row is 16 chunks of 16 bytes; chunk c of row r sits at c ^ (r & 15): the
 //    stores (16 lanes, one row) and the reads (16 lanes, 16 rows) both reach all banks.
@@ -35,12 +35,51 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 // Before, operands of both matrices went through LDS (48 KB of LDS traffic per slab at a 64 x 64 tile, which bounded it) and through
 // gemm_kernel<64,64> / <128,128> above 64 x 64; microseconds per launch in a row of dependent launches, W not in L2:
 //     rows x N x K     before   now           rows x N x K     before   now
-//    80 x  768 x  768    3.9    3.4         1040 x 2304 x  768   10.7    7.4
-//    80 x 3072 x  768    4.9    4.0         1040 x  768 x 3072   13.9   11.0
-//    80 x  768 x 3072    7.7    7.0         2000 x 3072 x  768   19.0   13.4
-//   450 x 2304 x  768    9.8    5.6         2000 x  768 x 3072   26.2   14.2
-//   450 x  768 x 3072    9.6    8.0         8000 x  768 x 3072   51.2   37.0
+//   450 x 2304 x  768    9.8    5.5         2000 x  768 x 3072   26.2   14.2
+//  1040 x 2304 x  768   10.7    7.4         8000 x  768 x 3072   51.2   37.0
+//  2000 x 3072 x  768   19.0   13.4
 constexpr int STREAM_BK = 128;
+
+// The four wavefronts that fetch A (thread ft of them) for a tile of 16 RB rows from row m0 on, see gemm_stream_kernel.
+template <int RB, int TURN>
+__device__ inline void fetch_a(const bf16_t *A, const int32_t *T_dev, unsigned char *smem, int ft, int m0, int K, int slabs, int turns_end)
+{
+    constexpr int ROWS = 16 * RB, STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
+    constexpr int LPT = RB;  // 16-byte loads per thread and slab
+    const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * K), 0, ROWS * K * (int)sizeof(bf16_t), 0x00020000);
+    const int lrow = ft >> 4, lch = ft & 15;
+    const int toff = (lrow * K + lch * 8) * (int)sizeof(bf16_t);
+    const int soff = lrow * 256 + ((lch ^ lrow) << 4);  // rows 16 apart share the swizzle term
+    u32x4 rg[TURN][LPT];
+    // Every step issues its loads: a slab past the end gets an offset beyond the buffer (nothing is fetched, zeros
+    // come back).  Loads return in order and a wait counts the loads behind the one it is for; where a load may or may
+    // not have been issued, the compiler would have to wait for all of them.
+#define STREAM_ALOAD(p, slab)                                                                            \
+    {                                                                                                    \
+        const int o_ = (slab) < slabs ? toff + (slab) * (STREAM_BK * 2) : 0x7ff00000;                    \
+        _Pragma("unroll") for (int i = 0; i < LPT; ++i)                                                  \
+            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * K * 2, 0)); \
+    }
+#pragma unroll
+    for (int p = 0; p < TURN; ++p) {
+        STREAM_ALOAD(p, p)
+        __builtin_amdgcn_sched_barrier(0);  // slab after slab: in the compiler's own order the first wait was for all of them
+    }
+    const int end = m0 < *T_dev ? turns_end : TURN;
+    int s0 = 0;
+    do {
+#pragma unroll
+        for (int p = 0; p < TURN; ++p) {
+            unsigned char *to = smem + p * STAGE + soff;
+#pragma unroll
+            for (int i = 0; i < LPT; ++i) *reinterpret_cast<u32x4 *>(to + i * 16 * 256) = rg[p][i];
+            STREAM_ALOAD(p, s0 + p + TURN)
+            __syncthreads();  // slab s0 + p is there; slab s0 + p - 2 has been read
+        }
+        s0 += TURN;
+    } while (s0 < end);
+#undef STREAM_ALOAD
+}
 
 // R: 32-row blocks of the tile, all of them in every multiplying wavefront; NM: multiplying wavefronts, 32 columns each.
 template <int R, int NM>
@@ -50,7 +89,6 @@ struct StreamCfg {
     static constexpr int TURN = 3;                             // slabs per turn of the loop = stages
     static constexpr int STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
     static constexpr int SMEM = TURN * STAGE + NM * 2048;      // stages, output staging
-    static constexpr int DA = NM >= 6 ? 3 : 6;                 // slabs of A in flight, a multiple of TURN
     static constexpr int DW = NM >= 6 ? 12 : 24;               // steps of W in flight, a divisor of a turn's 24; ten wavefronts have 168 registers each
     static constexpr int AHEAD = R == 1 ? 7 : R == 2 ? 3 : 1;  // steps of A read ahead
 };
@@ -62,7 +100,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
                                                                     int N, int K, int xr_bits)
 {
     typedef StreamCfg<R, NM> Cfg;
-    constexpr int DA = Cfg::DA, DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
+    constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -78,45 +116,10 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
     const int turns_end = (slabs + TURN - 1) / TURN * TURN;
     // A tile that turns out to hold no row goes through one turn and stores nothing.
 
-    if (wave >= NM) {  // fetch A
-        constexpr int LPT = 2 * R;  // 16-byte loads per thread and slab
-        const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * K), 0, Cfg::ROWS * K * (int)sizeof(bf16_t), 0x00020000);
-        const int ft = tid - 64 * NM, lrow = ft >> 4, lch = ft & 15;
-        const int toff = (lrow * K + lch * 8) * (int)sizeof(bf16_t);
-        const int soff = lrow * 256 + ((lch ^ lrow) << 4);  // rows 16 apart share the swizzle term
-        u32x4 rg[DA][LPT];
-        // Every step issues its loads: a slab past the end gets an offset beyond the buffer (nothing is fetched, zeros
-        // come back).  Loads return in order and a wait counts the loads behind the one it is for; where a load may or may
-        // not have been issued, the compiler would have to wait for all of them.
-#define STREAM_ALOAD(p, slab)                                                                            \
-    {                                                                                                    \
-        const int o_ = (slab) < slabs ? toff + (slab) * (STREAM_BK * 2) : 0x7ff00000;                    \
-        _Pragma("unroll") for (int i = 0; i < LPT; ++i)                                                  \
-            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * K * 2, 0)); \
-    }
-#pragma unroll
-        for (int p = 0; p < DA; ++p) {
-            STREAM_ALOAD(p, p)
-            __builtin_amdgcn_sched_barrier(0);  // slab after slab: in the compiler's own order the first wait was for all of them
-        }
-        const int end = m0 < *T_dev ? turns_end : TURN;
-        int s0 = 0;
-        do {
-#pragma unroll
-            for (int p = 0; p < DA; ++p) {
-                const int s = s0 + p;
-                unsigned char *to = smem + p % TURN * Cfg::STAGE + soff;
-                if (s < end)
-#pragma unroll
-                    for (int i = 0; i < LPT; ++i) *reinterpret_cast<u32x4 *>(to + i * 16 * 256) = rg[p][i];
-                STREAM_ALOAD(p, s + DA)
-                if (s < end) __syncthreads();  // slab s is there; slab s - 2 has been read
-            }
-            s0 += DA;
-        } while (s0 < end);
+    if (wave >= NM) {
+        fetch_a<2 * R, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, slabs, turns_end);
         return;
     }
-#undef STREAM_ALOAD
 
     const int ct = (n0 >> 5) + wave;  // the wavefront's 32 columns; the last tile may reach past N: zeros, not stored
     const bool on = ct * 32 < N;
@@ -202,6 +205,124 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
             *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + r * 32 + rr) * N + ct * 32 + ch * 8) = v;
         }
         __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// The same product for the smallest tiles, where one wavefront's MFMAs over K are the chain (32 x 32 outputs keep a SIMD's matrix core
+// busy for 32 clocks per 16 elements of K, with three SIMDs idle): a multiplying wavefront has 16 columns instead of 32, and 16 RB rows,
+// by MFMA 16x16x32, whose result for 32 elements of K has the bits of two 32x32x16 on this part (sums over groups of eight elements,
+// one after the other; the tests compare the tiles bit for bit).  So a tile's columns spread over twice as many SIMDs.  W is read
+// from the same copy: of its 2 KB per 32 columns and 32 elements of K a lane takes the row and the eight elements that its operand slot
+// has.  Per launch, before (32x32 of gemm_stream_kernel) and now: 80 x 768 x 768 3.2 and 2.7 us, 80 x 768 x 3072 6.7 and 5.2,
+// 244 x 768 x 3072 7.0 and 5.8, 1040 x 768 x 3072 11.4 and 10.4 (64x64).  24 steps of W ahead instead of 12, in turns of six slabs, were 0.2 us
+// slower at K = 768 and no faster at 3072.
+template <int RB, int NM>
+struct Stream16Cfg {
+    static constexpr int ROWS = 16 * RB, COLS = 16 * NM;
+    static constexpr int THREADS = 64 * (NM + 4);
+    static constexpr int TURN = 3, DW = 4 * TURN;              // slabs per turn of the loop = stages; steps of W in flight, a turn's
+    static constexpr int STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
+    static constexpr int SMEM = TURN * STAGE + NM * RB * 512;  // stages, output staging
+    static constexpr int AHEAD = RB == 2 ? 3 : 1;              // steps of A read ahead
+};
+
+template <int RB, int NM, int EPI>
+__global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Wp,
+                                                                      const float *__restrict__ bias, bf16_t *__restrict__ out,
+                                                                      const int32_t *__restrict__ T_dev, int max_rows, int likely_rows,
+                                                                      int N, int K, int xr_bits)
+{
+    typedef Stream16Cfg<RB, NM> Cfg;
+    constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
+    const int tid = threadIdx.x, lane = tid & 63, quarter = lane >> 4, l16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int xcd = blockIdx.x & 7;  // as in gemm_stream_kernel
+    const int tm = (blockIdx.y << xr_bits) + (xcd & ((1 << xr_bits) - 1)), tn = ((blockIdx.x >> 3) << (3 - xr_bits)) + (xcd >> xr_bits);
+    const int m0 = tm * Cfg::ROWS, n0 = tn * Cfg::COLS;
+    if (m0 >= max_rows || n0 >= N) return;
+    if (m0 >= likely_rows && m0 >= *T_dev) return;
+    const int slabs = K / STREAM_BK;  // the host checks K % 128 == 0
+    const int turns_end = (slabs + TURN - 1) / TURN * TURN;
+
+    if (wave >= NM) {
+        fetch_a<RB, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, slabs, turns_end);
+        return;
+    }
+
+    const int ct = (n0 >> 4) + wave;  // the wavefront's 16 columns; the last tile may reach past N: zeros, not stored
+    const bool on = ct * 16 < N;
+    const int steps = K >> 5;
+    const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Wp + (size_t)(ct >> 1) * 32 * K), 0, on ? K * 64 : 0, 0x00020000);
+    const int woff = (quarter >> 1) * 1024 + ((quarter & 1) * 32 + (ct & 1) * 16 + l16) * 16;
+    u32x4 wr[DW];
+#define STREAM_WLOAD(p, step)                                                                            \
+    wr[p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, (step) < steps ? woff + (step) * 2048 : 0x7ff00000, 0, 0));
+    f32x4 acc[RB];  // the sums start at the bias: register i of a lane is column 4 quarter + i
+    {
+        const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + min(ct, (N >> 4) - 1) * 16 + 4 * quarter);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) acc[r] = b;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < DW; ++p) {
+        STREAM_WLOAD(p, p)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int aoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) aoff[j] = l16 * 256 + (((4 * j + quarter) ^ l16) << 4);
+    bf16x8 af[AHEAD + 1][RB];
+#define STREAM_AREAD(step, stage)                                                                        \
+    _Pragma("unroll") for (int r = 0; r < RB; ++r)                                                       \
+        af[(step) % (AHEAD + 1)][r] = *reinterpret_cast<const bf16x8 *>(smem + (stage) * Cfg::STAGE + aoff[(step) & 3] + r * 16 * 256);
+#define STREAM_BARRIER                                                                                   \
+    asm volatile("" ::: "memory");                                                                       \
+    __builtin_amdgcn_s_barrier();                                                                        \
+    asm volatile("" ::: "memory");
+    const int T = *T_dev;
+    const int end = m0 < T ? turns_end : TURN;
+    STREAM_BARRIER  // the fetching wavefronts' first one: slab 0
+    STREAM_BARRIER  // slab 1; before slab s there have been s + 2 of them, end in all
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) { STREAM_AREAD(j, 0) }
+    int s = 0;
+    do {
+#pragma unroll
+        for (int u = 0; u < TURN; ++u) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                STREAM_AREAD(j + AHEAD, (j + AHEAD < 4 ? u : u + 1) % TURN)  // at the very end of a stage that is there, unused
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[u * 4 + j]), af[j % (AHEAD + 1)][r], acc[r], 0, 0, 0);
+                STREAM_WLOAD(u * 4 + j, (s + u) * 4 + j + DW)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (u < TURN - 2 || s + TURN < end) { STREAM_BARRIER }
+        }
+        s += TURN;
+    } while (s < end);
+#undef STREAM_BARRIER
+#undef STREAM_AREAD
+#undef STREAM_WLOAD
+    if (!on || m0 >= T) return;
+    // 16 RB x 16 outputs through the wavefront's own LDS, a row's 32 bytes together, 8-byte unit u at u ^ 2 in every other eight rows; then 16-byte stores
+    unsigned char *stg = smem + TURN * Cfg::STAGE + wave * (RB * 512);
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        bf16x4 o4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o4[i] = (bf16_t)(EPI == EPI_BIAS_GELU ? gelu_erf(acc[r][i]) : acc[r][i]);
+        *reinterpret_cast<bf16x4 *>(stg + (r * 16 + l16) * 32 + ((quarter ^ ((l16 >> 2) & 2)) << 3)) = o4;
+    }
+    __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
+#pragma unroll
+    for (int i = 0; i < RB / 2; ++i) {
+        const int row = i * 32 + (lane >> 1), ch = lane & 1;
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + row * 32 + ((ch ^ ((row >> 3) & 1)) << 4));
+        *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + row) * N + ct * 16 + ch * 8) = v;
     }
 }
 

@@ -258,7 +258,7 @@ def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
 
 @pytest.mark.parametrize("hidden,heads,ffn", [(640, 10, 1280), (768, 12, 3072), (1024, 16, 1920)])
 def test_tiles_of_one_round_give_the_same_bits(L, hidden, heads, ffn):
-    """Passes that fill the chip once, from one row tile to those that no longer do (all tiles from 32 x 32 to 128 x 256), with K
+    """Passes that fill the chip once, from one row tile to those that no longer do (all tiles from 32 x 16 to 128 x 256), with K
     a multiple of 384 or not (the slabs behind its end are zeros), rows at, below and above a tile's edge: the bits of the
     128 x 128 tile of the kernel for large passes."""
     import torch
