@@ -608,21 +608,21 @@ int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf1
 // microseconds besides the K loop and per 768 elements of K.
 #define LEANN_STREAM_TILES(X)                                                                            \
     X(16, 2, 1, 1.85, 0.85) X(16, 2, 2, 2.25, 0.92) X(16, 2, 3, 2.35, 1.08) X(16, 2, 4, 2.2, 1.3) X(32, 1, 3, 2.5, 1.68) X(32, 1, 4, 2.55, 2.1) \
-    X(16, 4, 4, 2.85, 1.82) X(32, 2, 3, 3.2, 2.25) X(32, 2, 4, 3.2, 2.65) X(32, 2, 6, 3.3, 4.15) X(32, 2, 8, 3.4, 5.0) X(32, 4, 6, 4.6, 7.4)   \
+    X(16, 4, 4, 2.65, 1.75) X(32, 2, 3, 3.2, 2.25) X(32, 2, 4, 3.2, 2.65) X(32, 2, 6, 3.3, 4.15) X(32, 2, 8, 3.4, 5.0) X(32, 4, 6, 4.6, 7.4)   \
     X(32, 4, 8, 4.9, 8.8)
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
 // Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
 // gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
 //                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
-//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.2 |     3.6     4.0     4.6     4.9                                 |   8.6
-//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.7 |     8.6    10.6    11.2    12.9                                 |  26.1
-//   244 x 2304 x  768                                     4.7 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
-//   244 x  768 x 3072             5.8     6.6     7.2     9.8 |     8.8    10.7    11.3    13.0                                 |
+//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |   8.6
+//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |  26.1
+//   244 x 2304 x  768                                     4.4 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
+//   244 x  768 x 3072             5.8     6.6     7.2     9.2 |     8.8    10.7    11.3    13.0                                 |
 //   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |   9.8
-//   450 x  768 x 3072                     7.2     7.2     9.9 |     8.9    10.7    11.3    12.9                                 |
-//  1040 x  768 x  768                                     4.9 |             4.9     5.2     5.4     6.5                         |   9.1
-//  1040 x  768 x 3072                                    10.4 |            12.0    11.9    13.4    17.2                         |
+//   450 x  768 x 3072                     7.1     7.2     9.2 |     8.9    10.7    11.3    12.9                                 |
+//  1040 x  768 x  768                                     4.7 |             4.9     5.2     5.4     6.5                         |   9.1
+//  1040 x  768 x 3072                                    10.1 |            12.0    11.9    13.4    17.2                         |
 //  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |  10.7
 //  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |  19.0    19.0
 //  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |   6.6    11.3

@@ -214,8 +214,8 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
 // one after the other; the tests compare the tiles bit for bit).  So a tile's columns spread over twice as many SIMDs.  W is read
 // from the same copy: of its 2 KB per 32 columns and 32 elements of K a lane takes the row and the eight elements that its operand slot
 // has.  Per launch, before (32x32 of gemm_stream_kernel) and now: 80 x 768 x 768 3.2 and 2.7 us, 80 x 768 x 3072 6.7 and 5.2,
-// 244 x 768 x 3072 7.0 and 5.8, 1040 x 768 x 3072 11.4 and 10.4 (64x64).  24 steps of W ahead instead of 12, in turns of six slabs, were 0.2 us
-// slower at K = 768 and no faster at 3072.
+// 244 x 768 x 3072 7.0 and 5.8, 1040 x 768 x 3072 11.4 and 10.1 (64x64).  24 steps of W ahead instead of 12, in turns of six slabs, were 0.2 us
+// slower at K = 768 and no faster at 3072; slabs of 256 elements, with half the barriers, 0.1 to 0.5 us slower.
 template <int RB, int NM>
 struct Stream16Cfg {
     static constexpr int ROWS = 16 * RB, COLS = 16 * NM;
@@ -223,7 +223,7 @@ struct Stream16Cfg {
     static constexpr int TURN = 3, DW = 4 * TURN;              // slabs per turn of the loop = stages; steps of W in flight, a turn's
     static constexpr int STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
     static constexpr int SMEM = TURN * STAGE + NM * RB * 512;  // stages, output staging
-    static constexpr int AHEAD = RB == 2 ? 3 : 1;              // steps of A read ahead
+    static constexpr int AHEAD = 2, SLOTS = AHEAD + 1;         // steps of A read ahead; its registers, a divisor of a turn's 12 steps
 };
 
 template <int RB, int NM, int EPI>
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
                                                                       int N, int K, int xr_bits)
 {
     typedef Stream16Cfg<RB, NM> Cfg;
-    constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
+    constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD, SLOTS = Cfg::SLOTS;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
     const int tid = threadIdx.x, lane = tid & 63, quarter = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -273,10 +273,10 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
     int aoff[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) aoff[j] = l16 * 256 + (((4 * j + quarter) ^ l16) << 4);
-    bf16x8 af[AHEAD + 1][RB];
+    bf16x8 af[SLOTS][RB];
 #define STREAM_AREAD(step, stage)                                                                        \
     _Pragma("unroll") for (int r = 0; r < RB; ++r)                                                       \
-        af[(step) % (AHEAD + 1)][r] = *reinterpret_cast<const bf16x8 *>(smem + (stage) * Cfg::STAGE + aoff[(step) & 3] + r * 16 * 256);
+        af[(step) % SLOTS][r] = *reinterpret_cast<const bf16x8 *>(smem + (stage) * Cfg::STAGE + aoff[(step) & 3] + r * 16 * 256);
 #define STREAM_BARRIER                                                                                   \
     asm volatile("" ::: "memory");                                                                       \
     __builtin_amdgcn_s_barrier();                                                                        \
@@ -293,10 +293,10 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
         for (int u = 0; u < TURN; ++u) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                STREAM_AREAD(j + AHEAD, (j + AHEAD < 4 ? u : u + 1) % TURN)  // at the very end of a stage that is there, unused
+                STREAM_AREAD(u * 4 + j + AHEAD, (j + AHEAD < 4 ? u : u + 1) % TURN)  // at the very end of a stage that is there, unused
 #pragma unroll
                 for (int r = 0; r < RB; ++r)
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[u * 4 + j]), af[j % (AHEAD + 1)][r], acc[r], 0, 0, 0);
+                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[u * 4 + j]), af[(u * 4 + j) % SLOTS][r], acc[r], 0, 0, 0);
                 STREAM_WLOAD(u * 4 + j, (s + u) * 4 + j + DW)
                 __builtin_amdgcn_sched_barrier(0);
             }
