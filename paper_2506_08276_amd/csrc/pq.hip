@@ -16,25 +16,37 @@ constexpr int KSUB = 256;
 constexpr int MAX_TRAIN = 65536;
 constexpr int MAX_DSUB = 32;
 
-// rows[i] of x (fp32 [n][d]) -> xt[i][d]
-__global__ void gather_rows_kernel(const float *__restrict__ x, const int64_t *__restrict__ rows, int64_t nt, int d,
-                                   float *__restrict__ xt)
+// The training rows: rows[i] of x (fp32 [n][d]) -> xt[m][i][d / m_sub], a plane per subspace, so that kernels that work on one
+// subspace read nothing else: pieces of 96 bytes straddle 128-byte lines, and in rows the line's rest belongs to other subspaces.  A block
+// takes GATHER_ROWS rows: that many pieces of a plane lie together.  65536 x 768 from 100000: 73 us, copied row by row 98; the
+// assignment of such rows 142, before 147.
+constexpr int GATHER_ROWS = 16;
+
+template <class Piece>  // f32x4 where every sub-vector consists of such and begins at one
+__global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ x, const int64_t *__restrict__ rows, int64_t nt, int d,
+                                                          int dsub, float *__restrict__ xt)
 {
-    const int64_t i = blockIdx.x;
-    if (i >= nt) return;
-    const float *src = x + rows[i] * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) xt[i * d + c] = src[c];
+    constexpr int W = sizeof(Piece) / sizeof(float);
+    const int64_t t0 = (int64_t)blockIdx.x * GATHER_ROWS;
+    const uint32_t per_row = dsub / W, per_plane = GATHER_ROWS * per_row, all = GATHER_ROWS * (d / W);
+    for (uint32_t e = threadIdx.x; e < all; e += 256) {
+        const uint32_t m = e / per_plane, in_plane = e - m * per_plane, i = in_plane / per_row, j = in_plane - i * per_row;
+        if (t0 + i >= nt) continue;
+        *reinterpret_cast<Piece *>(xt + ((int64_t)m * nt + t0 + i) * dsub + j * W) =
+            *reinterpret_cast<const Piece *>(x + rows[t0 + i] * d + m * dsub + j * W);
+    }
 }
 
 // The first 256 training rows (wrapping when there are fewer) as the centroids training starts from.
-__global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt, int d, int m_sub, float *__restrict__ codebook)
+__global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt, int dsub, float *__restrict__ codebook)
 {
-    const int dsub = d / m_sub, m = blockIdx.y;
+    const int m = blockIdx.y;
     for (int i = threadIdx.x; i < dsub; i += blockDim.x)
-        codebook[((size_t)m * KSUB + blockIdx.x) * dsub + i] = xt[(size_t)(blockIdx.x % nt) * d + m * dsub + i];
+        codebook[((size_t)m * KSUB + blockIdx.x) * dsub + i] = xt[((size_t)m * nt + blockIdx.x % nt) * dsub + i];
 }
 
-// Nearest centroid (squared L2, ties to the lowest index) of every row in one subspace; out[r * row_pitch + m * m_pitch].
+// Nearest centroid (squared L2, ties to the lowest index) of every row in one subspace; row r's sub-vector m begins at
+// x[r * x_row + m * x_sub], its code is out[r * row_pitch + m * m_pitch].
 //
 // What decides is the fp32 sum s(c) = sum_j (x_j - c_j)^2, j ascending.  Computing all 256 of them on the vector ALU bounds
 // the kernel there (two instructions per element: 1814 us at 65536 rows, d = 768, 32 subspaces), so the matrix cores
@@ -61,12 +73,12 @@ __host__ __device__ constexpr int assign_smem(int ks, int dsub)
 }
 
 template <int KS>  // 16-element steps of the (zero-padded) sub-vector
-__global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *__restrict__ x, int64_t n, int d, int m_sub,
+__global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *__restrict__ x, int64_t x_row, int64_t x_sub, int64_t n, int dsub, int m_sub,
                                                                 const float *__restrict__ codebook, int64_t rows_per_block, int xcd_bits,
                                                                 uint8_t *__restrict__ out, int64_t row_pitch, int64_t m_pitch)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int dsub = d / m_sub, P = dsub | 1;  // odd row pitch: 64 centroids' elements lie in different banks
+    const int P = dsub | 1;  // odd row pitch: 64 centroids' elements lie in different banks
     bf16_t *frag = reinterpret_cast<bf16_t *>(smem);  // [hi, lo][KS][256][16]
     float *c2 = reinterpret_cast<float *>(frag + 2 * KS * KSUB * 16);  // |c'|^2, read four at a time
     float *mu = c2 + KSUB;
@@ -120,7 +132,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const int64_t row = min(r0 + g * 32 + l32, end - 1);
-            const float *xr = x + row * d + m * dsub;
+            const float *xr = x + row * x_row + m * x_sub;
             float sq = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -216,7 +228,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *
             while (doubt) {
                 const int who = __ffsll((long long)doubt) - 1;
                 doubt &= doubt - 1;
-                const float *xr = x + (r0 + g * 32 + who) * d + m * dsub;
+                const float *xr = x + (r0 + g * 32 + who) * x_row + m * x_sub;
                 float s[4] = {0.f, 0.f, 0.f, 0.f};
                 for (int j = 0; j < dsub; ++j) {
                     const float xv = xr[j];
@@ -346,22 +358,25 @@ __global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restr
 // The partial sums are in LDS; a group of 32 lanes (one per element) adds the rows with r % 8 equal to the group's number.
 // Latency bounds it (row numbers, then the rows' pieces from beyond L2): 256 row numbers are looked through at a time and each
 // group's rows listed first, so that a group has UPDATE_AHEAD of them in flight however they are spread.  Reads every training
-// row once per round: 93 us at 65536 rows, d = 768, 32 subspaces (132 with 32 row numbers at a time, four rows in flight and a
-// step of the pairwise sum per barrier).
+// row once per round: 77 us at 65536 rows, d = 768, 32 subspaces (82 with the subspaces' pieces in the rows; 132 with 32 row numbers at
+// a time, four rows in flight and a step of the pairwise sum per barrier).
 constexpr int UPDATE_AHEAD = 16;
 
-__global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ xt, int64_t nt, int d, int m_sub,
+__global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ xt, int64_t nt, int dsub, int xcd_bits,
                                                      const int32_t *__restrict__ order, const int32_t *__restrict__ first,
                                                      float *__restrict__ codebook)
 {
     extern __shared__ __attribute__((aligned(16))) float part[];  // [256][dsub]
     __shared__ int32_t mine[8][256 + UPDATE_AHEAD];  // a group's rows among the 256, any valid row behind them
-    const int c = blockIdx.x, m = blockIdx.y, dsub = d / m_sub, tid = threadIdx.x;
+    // with xcd_bits = 3 all centroids of a subspace are on one XCD: its blocks go through the same plane at about the same pace, and
+    // lines that pieces of different centroids share come into its L2 once
+    const int c = (blockIdx.x >> xcd_bits) % KSUB, tid = threadIdx.x;
+    const int m = ((int)(blockIdx.x >> xcd_bits) / KSUB << xcd_bits) + (blockIdx.x & ((1 << xcd_bits) - 1));
     const int lane32 = tid & 31, group = tid >> 5, shift = tid & 32;
     const int beg = first[(size_t)m * (KSUB + 1) + c], cnt = first[(size_t)m * (KSUB + 1) + c + 1] - beg;
     if (cnt == 0) return;  // an empty cluster keeps its centroid
     const int32_t *rows = order + (size_t)m * nt + beg;
-    const float *xm = xt + (size_t)m * dsub + min(lane32, dsub - 1);
+    const float *xm = xt + (size_t)m * nt * dsub + min(lane32, dsub - 1);
     int32_t r[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) r[k] = rows[min(k * 32 + lane32, cnt - 1)];
@@ -387,7 +402,7 @@ __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ x
 #pragma unroll
             for (int k = 0; k < UPDATE_AHEAD; ++k) rr[k] = mine[group][min(j0, 256) + k];
 #pragma unroll
-            for (int k = 0; k < UPDATE_AHEAD; ++k) v[k] = xm[(size_t)rr[k] * d];
+            for (int k = 0; k < UPDATE_AHEAD; ++k) v[k] = xm[(size_t)rr[k] * dsub];
 #pragma unroll
             for (int k = 0; k < UPDATE_AHEAD; ++k)
                 if (j0 + k < n_mine && lane32 < dsub) part[(rr[k] & 255) * dsub + lane32] += v[k];
@@ -611,10 +626,9 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
 // 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1100 us per launch,
 // 1000 rows of 192 subspaces of one 43; with the kernel of five instructions per value 1431 and 49, and 5358 and 129 where all
 // subspaces of a run were on one XCD however few the runs (two in both cases).
-void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, const float *codebook, uint8_t *out,
+void launch_assign(leann_ctx *ctx, const float *x, int64_t x_row, int64_t x_sub, int64_t n, int dsub, int m_sub, const float *codebook, uint8_t *out,
                    int64_t row_pitch, int64_t m_pitch)
 {
-    const int dsub = d / m_sub;
     const int64_t want = std::max<int64_t>(8, 2 * ctx->num_cus / m_sub / 8 * 8);
     const int64_t rows = ((n + want - 1) / want + ASSIGN_THREADS - 1) / ASSIGN_THREADS * ASSIGN_THREADS;
     const int64_t runs = (n + rows - 1) / rows;
@@ -622,7 +636,7 @@ void launch_assign(leann_ctx *ctx, const float *x, int64_t n, int d, int m_sub, 
     const int64_t blocks = ((((runs - 1) >> xcd_bits) + 1) << xcd_bits) * m_sub;
     auto *kernel = dsub <= 16 ? assign_kernel<1> : assign_kernel<2>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(ASSIGN_THREADS), assign_smem(dsub <= 16 ? 1 : 2, dsub),
-                       ctx->stream, x, n, d, m_sub, codebook, rows, xcd_bits, out, row_pitch, m_pitch);
+                       ctx->stream, x, x_row, x_sub, n, dsub, m_sub, codebook, rows, xcd_bits, out, row_pitch, m_pitch);
 }
 
 // Launch shape of adc_kernel: enough blocks to fill the chip several times over, each with as large a share of its
@@ -790,17 +804,20 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     if (hipMemcpyAsync(rows_dev, train.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) !=
         hipSuccess)
         return fail(LEANN_EDEVICE);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)nt), dim3(256), 0, ctx->stream, emb_dev, rows_dev, nt, d, xt);
-    hipLaunchKernelGGL(first_centroids_kernel, dim3(KSUB, m_sub), dim3(64), 0, ctx->stream, xt, nt, d, m_sub, pq->codebook);
+    const bool by_four = (dsub & 3) == 0 && (reinterpret_cast<uintptr_t>(emb_dev) & 15) == 0;
+    hipLaunchKernelGGL(by_four ? gather_rows_kernel<f32x4> : gather_rows_kernel<float>, dim3((unsigned)((nt + GATHER_ROWS - 1) / GATHER_ROWS)),
+                       dim3(256), 0, ctx->stream, emb_dev, rows_dev, nt, d, dsub, xt);
+    hipLaunchKernelGGL(first_centroids_kernel, dim3(KSUB, m_sub), dim3(64), 0, ctx->stream, xt, nt, dsub, pq->codebook);
+    const int xcd_bits = m_sub % 8 == 0 ? 3 : 0;  // other numbers of subspaces would not spread evenly over the XCDs
     for (int it = 0; it < iters; ++it) {
-        launch_assign(ctx, xt, nt, d, m_sub, pq->codebook, assign, 1, nt);
+        launch_assign(ctx, xt, dsub, nt * dsub, nt, dsub, m_sub, pq->codebook, assign, 1, nt);
         hipLaunchKernelGGL(count_rows_kernel, dim3(m_sub, GROUP_BLOCKS), dim3(1024), 0, ctx->stream, assign, (int)nt, counts);
         hipLaunchKernelGGL(group_rows_kernel, dim3(m_sub, GROUP_BLOCKS), dim3(1024), 0, ctx->stream, assign, (int)nt, counts, order,
                            first);
-        hipLaunchKernelGGL(update_kernel, dim3(KSUB, m_sub), dim3(256), (size_t)256 * dsub * sizeof(float), ctx->stream, xt, nt,
-                           d, m_sub, order, first, pq->codebook);
+        hipLaunchKernelGGL(update_kernel, dim3(KSUB * m_sub), dim3(256), (size_t)256 * dsub * sizeof(float), ctx->stream, xt, nt, dsub, xcd_bits,
+                           order, first, pq->codebook);
     }
-    launch_assign(ctx, emb_dev, n, d, m_sub, pq->codebook, pq->codes, m_sub, 1);
+    launch_assign(ctx, emb_dev, d, dsub, n, dsub, m_sub, pq->codebook, pq->codes, m_sub, 1);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(ctx->stream) != hipSuccess) {
         leann_set_error("PQ training kernels failed");
         return fail(LEANN_EDEVICE);

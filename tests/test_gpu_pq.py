@@ -195,6 +195,24 @@ def test_build_pq_exact_on_integer_rows(L, ctx, n, d, m_sub, offset):
         np.testing.assert_array_equal(codesb[rows], want[rows])
 
 
+@pytest.mark.parametrize("n,d,m_sub", [(300, 64, 8), (1000, 96, 16), (17, 24, 2), (257, 40, 8)])
+def test_pq_training_of_rows_at_any_address(L, ctx, n, d, m_sub):
+    """Training rows are brought into planes by four elements where they begin at 16 bytes, else one by one, sixteen rows per
+    block (here whole blocks, a remainder, fewer): the same table either way."""
+    import torch
+    say(f"pq training rows, {n} x {d}, {m_sub}")
+    x = to_dev(unit_rows(n, d, 12))
+    shifted = torch.empty(n * d + 1, dtype=torch.float32, device="cuda:0")[1:].view(n, d)
+    shifted.copy_(x)
+    tables = []
+    for rows in (x, shifted):
+        pq = L.leann_build_pq(ctx, rows, m_sub, 3, 5)
+        tables.append(L.leann_pq_export(ctx, pq))
+        L.leann_pq_free(pq)
+    for a, b in zip(*tables):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("n,dsub,longest", [(3000, 4, 255), (3000, 3, 256), (3000, 24, 257), (9000, 32, 6000), (3000, 1, 2999)])
 def test_pq_means_of_long_row_lists(L, ctx, n, dsub, longest):
     """Means of centroids with many rows, with as many as are looked through at a time, and one more or fewer: `longest` rows are one
