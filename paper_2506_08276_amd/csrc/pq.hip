@@ -499,11 +499,27 @@ void launch_lut(hipStream_t st, const float *queries, int64_t nq, const leann_pq
 // same operations: the same bits) and added in subspace order.  grid (nq, ceil(nc / DIRECT_CAND)), 256 threads.
 constexpr int DIRECT_CAND = 16;
 
-__global__ __launch_bounds__(256) void adc_direct_kernel(const float *__restrict__ queries, int d, int m_sub,
-                                                         const float *__restrict__ codebook, const uint8_t *__restrict__ codes,
-                                                         int64_t n, const uint32_t *__restrict__ cand, int nc,
-                                                         float *__restrict__ out, int *__restrict__ err)
+// A struct, so that the arguments are read from memory: brought into registers with the dispatch they let a chain of launches run
+// closer together, but this kernel runs alone and starts later for it (one query, 64 candidates, whole call 18.1 us; 17.8 read).
+struct DirectArgs {
+    const float *queries;
+    const float *codebook;
+    const uint8_t *codes;
+    const uint32_t *cand;
+    float *out;
+    int *err;
+    int64_t n;
+    int d, m_sub, nc;
+};
+
+__global__ __launch_bounds__(256) void adc_direct_kernel(DirectArgs a)
 {
+    const float *__restrict__ queries = a.queries, *__restrict__ codebook = a.codebook;
+    const uint8_t *__restrict__ codes = a.codes;
+    const uint32_t *__restrict__ cand = a.cand;
+    float *__restrict__ out = a.out;
+    const int d = a.d, m_sub = a.m_sub, nc = a.nc;
+    const int64_t n = a.n;
     extern __shared__ float part[];  // [DIRECT_CAND][m_sub | 1]
     const int q = blockIdx.x, j0 = blockIdx.y * DIRECT_CAND, here = min(DIRECT_CAND, nc - j0);
     const int dsub = d / m_sub, pitch = m_sub | 1;
@@ -522,7 +538,7 @@ __global__ __launch_bounds__(256) void adc_direct_kernel(const float *__restrict
         for (int m = 0; m < m_sub; ++m) s += part[threadIdx.x * pitch + m];
         if (cq[threadIdx.x] >= n) {
             s = -INFINITY;
-            *err = 1;
+            *a.err = 1;
         }
         out[(size_t)q * nc + j0 + threadIdx.x] = s;
     }
@@ -928,8 +944,8 @@ int leann_adc(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_
     if (nc <= KSUB && nq * nc <= ADC_DIRECT_MAX) {
         ProfScope prof(ctx, LEANN_PROF_ADC);
         hipLaunchKernelGGL(adc_direct_kernel, dim3((unsigned)nq, (nc + DIRECT_CAND - 1) / DIRECT_CAND), dim3(256),
-                           DIRECT_CAND * (pq->m_sub | 1) * sizeof(float), ctx->stream, queries_dev, pq->d, pq->m_sub, pq->codebook,
-                           pq->codes, pq->n, cand_ids_dev, nc, out_dev, flag);
+                           DIRECT_CAND * (pq->m_sub | 1) * sizeof(float), ctx->stream,
+                           DirectArgs{queries_dev, pq->codebook, pq->codes, cand_ids_dev, out_dev, flag, pq->n, pq->d, pq->m_sub, nc});
     } else {
         LEANN_TRY(ctx->reserve(ctx->s_lut, (size_t)nq * pq->m_sub * KSUB * sizeof(float)));
         LEANN_TRY(pq_build_lut(ctx, queries_dev, nq, pq, (float *)ctx->s_lut.p));
