@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/leann.h"
+#include "host_word.h"
 
 typedef __bf16 bf16_t;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -75,7 +76,8 @@ struct leann_ctx {
     std::mutex pq_work_mutex;
     // search workspace
     DevBuf s_state, s_emb, s_lut, s_seen, s_misc, s_owner, s_buf, s_memo_slot, s_memo_emb;
-    long long *host_counters = nullptr;  // pinned host memory: a search round's counters
+    long long *host_counters = nullptr;  // pinned host memory: a search round's counters and the word behind them
+    HostWord published;                  // the word's numbers
     int *host_flags = nullptr;           // pinned host memory: what kernels report, see clear_host_flags
     hipEvent_t pass_event = nullptr;     // recorded behind the kernel that counts an encoder pass's tokens
     double clock_khz = 1e5;              // of the kernels' wall_clock64()

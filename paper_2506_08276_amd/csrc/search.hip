@@ -8,7 +8,6 @@
 // against their own query and try-inserts them into EQ.  Per query this is exactly the sequential algorithm; batching
 // across queries changes no value because the encoder's output for a chunk does not depend on the rest of the batch.
 #include <algorithm>
-#include <chrono>
 #include <type_traits>
 
 #include "advance_plan.h"
@@ -914,21 +913,6 @@ int search_init_device()
     return LEANN_OK;
 }
 
-// Looks at the word until it is seq (or a later number): false if that takes long, as where a kernel is slow, has faulted or was not
-// run (stream capture).  The caller then waits for the stream, which reports what is wrong.
-static bool word_arrives(const uint32_t *word, uint32_t seq)
-{
-    constexpr auto LONG = std::chrono::milliseconds(20);
-    const auto begin = std::chrono::steady_clock::now();
-    for (;;) {
-        for (int i = 0; i < 256; ++i) {
-            if ((int32_t)(__atomic_load_n(word, __ATOMIC_ACQUIRE) - seq) >= 0) return true;
-            __builtin_ia32_pause();
-        }
-        if (std::chrono::steady_clock::now() - begin > LONG) return false;
-    }
-}
-
 int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_graph *graph, const leann_pq *pq,
                const leann_chunks *chunks, const leann_emb_cache *cache, const leann_updates *upd, int32_t ef, int32_t k,
                float alpha, int32_t batch, int64_t *out_ids_dev, float *out_scores_dev, leann_search_stats *stats)
@@ -940,17 +924,19 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     long long *counters = (long long *)ctx->s_misc.p;
     LEANN_HIP(hipMemsetAsync(counters, 0, CTR_COUNT * sizeof(long long), st));
     LEANN_TRY(clear_host_flags(ctx));
-    if (!ctx->host_counters) LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, (CTR_COUNT + 1) * sizeof(long long), hipHostMallocDefault));
+    HostWord &published = ctx->published;
+    if (!ctx->host_counters) {
+        LEANN_HIP(hipHostMalloc((void **)&ctx->host_counters, (CTR_COUNT + 1) * sizeof(long long), hipHostMallocDefault));
+        ctx->host_counters[CTR_COUNT] = 0;
+    }
     long long *h_ctr = ctx->host_counters;  // device kernels write it too: read after wait() only
-    uint32_t published = 0;
-    h_ctr[CTR_COUNT] = 0;  // every call waits for its last publish()
     auto wait = [&]() -> int {  // for the publish() that was launched last
         LEANN_HIP(hipGetLastError());
-        if (!word_arrives(reinterpret_cast<const uint32_t *>(&h_ctr[CTR_COUNT]), published)) LEANN_HIP(hipStreamSynchronize(st));
+        if (!published.arrives(reinterpret_cast<const uint32_t *>(&h_ctr[CTR_COUNT]))) LEANN_HIP(hipStreamSynchronize(st));
         return LEANN_OK;
     };
     hipLaunchKernelGGL(maxdeg_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (n + 2047) / 2048))), dim3(256), 0, st,
-                       graph->row_ptr, n, counters, h_ctr, (long long)++published);
+                       graph->row_ptr, n, counters, h_ctr, (long long)published.next());
     LEANN_TRY(wait());
     const long long maxdeg = h_ctr[CTR_MAXDEG];
 
@@ -1058,7 +1044,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
             }
             {
                 ProfScope prof(ctx, LEANN_PROF_COLLECT);
-                hipLaunchKernelGGL(collect_kernel, dim3(g), dim3(64), 0, st, s, chunks->lengths, chunks->seq, (long long)++published);
+                hipLaunchKernelGGL(collect_kernel, dim3(g), dim3(64), 0, st, s, chunks->lengths, chunks->seq, (long long)published.next());
             }
             LEANN_TRY(wait());
             if (h_ctr[CTR_ERR]) {
@@ -1106,7 +1092,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                            upd ? upd->buffer_ids : nullptr, nb, out_ids_dev + (size_t)q0 * k,
                            out_scores_dev + (size_t)q0 * k);
     }
-    if (rc == LEANN_OK) hipLaunchKernelGGL(end_kernel, dim3(1), dim3(64), 0, st, s, (long long)++published);
+    if (rc == LEANN_OK) hipLaunchKernelGGL(end_kernel, dim3(1), dim3(64), 0, st, s, (long long)published.next());
     // The call's last wait is for the stream: a caller who waits for it next, as most do, would otherwise pay for that.
     const hipError_t sync_rc = hipStreamSynchronize(st);
     if (rc == LEANN_OK && sync_rc != hipSuccess) {

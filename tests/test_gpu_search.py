@@ -253,6 +253,39 @@ def test_queue_capacity_overflow_is_reported(L, world):
     assert torch.equal(ids0, ids1) and torch.equal(sc0, sc1)
 
 
+def test_calls_that_follow_one_another_and_an_error_get_their_own_results(L, world):
+    """Searches of two graphs of different size and degree take turns on one context, with calls in between that end with an error
+    in their first or a later round: what the host reads between rounds is always the call's own, so ids, scores and counts repeat."""
+    import torch
+    w = world
+    say("searches of two graphs and failing calls in turn")
+    n = 40
+    ring = [np.array([(v + 1) % n, (v + 7) % n, (v + 20) % n]) for v in range(n)]
+    row_ptr, col_idx = li.to_csr(ring)
+    bad_col = col_idx.copy()
+    bad_col[3 * (n - 1)] = n  # the last node's first neighbour: an id outside the graph, found by the kernel's own check
+    pq = L.leann_pq_import(w["ctx"], w["cb"], w["codes"][:n])
+    t, l = w["t"][:n].contiguous(), w["l"][:n].contiguous()
+    small_cache = (to_dev(np.arange(n, dtype=np.int32)), to_dev(w["emb"][:n]))
+    large = lambda cache: L.leann_search(w["ctx"], w["q"], w["graph"], w["pq"], w["t"], w["l"], 32, 3, 0.2, 8, cache=cache)
+    small = lambda cols, entry, cache: L.leann_search(w["ctx"], w["q"][:3].contiguous(), (to_dev(row_ptr), to_dev(cols), entry), pq, t, l, n, 3,
+                                                      1.0, 4, cache=cache)
+    calls = [lambda: large(None), lambda: small(col_idx, 0, None), lambda: large(w["full_cache"]), lambda: small(col_idx, 0, small_cache)]
+    try:
+        want = [call() for call in calls]
+        for turn in range(3):
+            for call, (ids, scores, stats) in zip(calls, want):
+                with pytest.raises(L.LeannError) as ei:
+                    small(bad_col, n - 1 if turn == 0 else 0, None if turn < 2 else small_cache)  # met in the first round, in a later one
+                assert ei.value.status == -1
+                got = call()
+                assert torch.equal(got[0], ids) and torch.equal(got[1], scores)
+                for key in stats:
+                    assert key.endswith("_ms") or got[2][key] == stats[key], key
+    finally:
+        L.leann_pq_free(pq)
+
+
 @pytest.mark.parametrize("m_sub,ef,alpha,batch", [(8, 300, 0.5, 20), (64, 1000, 0.1, 64), (16, 40, 1.0, 200), (128, 60, 0.3, 50)])
 def test_long_queues_exact_on_integer_world(L, orc, m_sub, ef, alpha, batch):
     """An approximate queue of thousands of entries, rows longer than a wavefront, empty rows, repeated neighbours, and
