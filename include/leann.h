@@ -106,8 +106,9 @@ typedef struct {
                                 * that has most of them (groups of queries that run one after the other add up) */
     int64_t cache_hits;        /* exact scores served by the stored-embedding table (part of recomputed_chunks) */
     int64_t memo_hits;         /* exact scores served by the call's embedding memo (leann_set_call_memo; part of recomputed_chunks) */
-    float encoder_ms, traverse_ms, total_ms; /* device time (HIP events): traverse_ms the hops, exact scores and packing,
-                                              * encoder_ms the rest of total_ms */
+    float encoder_ms, traverse_ms, total_ms; /* device time (the GPU's own clock): total_ms from the first kernel that sets up the
+                                              * queries to the last one's end, traverse_ms of it the hops, exact scores and
+                                              * packing, to the end of each round's last wavefront, encoder_ms the rest */
 } leann_search_stats;
 
 /* Message of the last error on the calling thread.  ctx is accepted for symmetry with the other calls and may be
@@ -221,7 +222,8 @@ int leann_adc_noalloc(leann_ctx *ctx, const float *queries_dev, int64_t nq, cons
  * Errors: k < 1, k > ef, ef > 1024, rerank_ratio outside (0,1], batch < 1, entry >= n,
  * graph/chunk/PQ sizes that disagree -> LEANN_EINVAL / LEANN_ESHAPE; a neighbour id >= n
  * or a per-query queue overflow -> LEANN_EINVAL / LEANN_ECAPACITY after the run
- * (outputs then undefined).  Synchronises the stream before returning.
+ * (outputs then undefined).  Synchronises the stream before returning.  Between rounds the calling thread looks at a
+ * word of pinned memory: it keeps a core busy for as long as the call takes, as a wait for a stream does by default.
  */
 int leann_search(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann_graph *graph,
                  const leann_pq *pq, const leann_chunks *chunks, const leann_emb_cache *cache, int32_t ef,

@@ -53,7 +53,9 @@ struct SearchState {
 
 // CTR_ROUNDS: most flushes of a query, belongs to one group of queries; CTR_PENDING .. CTR_TICKET belong to one round
 enum { CTR_HOPS = 0, CTR_ADC, CTR_RECOMP, CTR_FLUSH, CTR_ERR, CTR_TOKENS, CTR_MAXDEG, CTR_HITS, CTR_MEMO_HITS, CTR_ROUNDS, CTR_PENDING, CTR_NENC, CTR_ROUND_TOKENS, CTR_TICKET,
-       CTR_T_START, CTR_T_ROUND, CTR_T_TRAVERSE, CTR_T_END,  // wall_clock64(): of the call's start, of the round's, between round start and collect_kernel's end in all
+       // wall_clock64() at the start of the first init_kernel, of the round's advance_kernel; from there to collect_kernel's end, all
+       // rounds added up; at the call's end
+       CTR_T_START, CTR_T_ROUND, CTR_T_TRAVERSE, CTR_T_END,
        CTR_COUNT };
 enum { ERR_BAD_NEIGHBOUR = 1, ERR_AQ_OVERFLOW = 2, ERR_P_OVERFLOW = 4, ERR_BAD_SLOT = 8 };
 
@@ -86,8 +88,9 @@ __device__ inline void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" :::
 // 0 has done its block's atomics on them.  A round's end is a chain of latencies from the last hop to the encoder's first kernel:
 // hipStreamSynchronize comes back 10.7 us after an empty kernel's launch, a host that looks at a word of pinned memory 6.3 us after it.
 // Only the counters have to be there (device-scope atomics and stores past the L2, in order by waits; a fence would also write back
-// the L2): the kernels that use a round's other results come behind it in the stream.
-__device__ inline void publish(long long *counters, long long *host_counters, long long seq)
+// the L2): the kernels that use a round's other results come behind it in the stream.  ends_round: the time since the round's start is
+// added to CTR_T_TRAVERSE, by whose clock it does not matter (the XCDs' differ by half a microsecond at most).
+__device__ inline void publish(long long *counters, long long *host_counters, long long seq, bool ends_round)
 {
     const int lane = threadIdx.x & 63;
     int last = 0;
@@ -95,7 +98,13 @@ __device__ inline void publish(long long *counters, long long *host_counters, lo
     if (lane == 0) last = gridDim.x == 1 || __hip_atomic_fetch_add(&counters[CTR_TICKET], 1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     if (lane == CTR_TICKET) __hip_atomic_store(&counters[CTR_TICKET], 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lane < CTR_COUNT) store_through(&host_counters[lane], __hip_atomic_load(&counters[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    long long value = lane < CTR_COUNT ? __hip_atomic_load(&counters[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const long long round_start = __shfl(value, CTR_T_ROUND, 64);
+    if (ends_round && lane == CTR_T_TRAVERSE) {
+        value += (long long)wall_clock64() - round_start;
+        __hip_atomic_store(&counters[CTR_T_TRAVERSE], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane < CTR_COUNT) store_through(&host_counters[lane], value);
     wait_for_stores();
     if (lane == 0) store_through(&host_counters[CTR_COUNT], seq);
 }
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(256) void maxdeg_kernel(const uint64_t *__restrict_
     __syncthreads();
     // one atomic per block: a thousand of them on one word, one per wavefront, were most of the kernel's 13.5 us
     if (threadIdx.x == 0) atomicMax(&counters[CTR_MAXDEG], max(max(part[0], part[1]), max(part[2], part[3])));
-    if (threadIdx.x < 64) publish(counters, host_counters, seq);
+    if (threadIdx.x < 64) publish(counters, host_counters, seq, false);
 }
 
 // The state of a group of queries at its start, grid (any, queries).  n > 0: the call's first group, the owners of its n chunks are
@@ -122,10 +131,10 @@ __global__ __launch_bounds__(256) void init_kernel(SearchState s, uint32_t entry
 {
     const int q = blockIdx.y;
     const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x, across = (int64_t)gridDim.x * 256;
+    if (q == 0 && x == 0 && n > 0) s.counters[CTR_T_START] = wall_clock64();
     for (int64_t i = q * across + x; i < n; i += gridDim.y * across) s.owner[i] = ~0ull;
     for (int64_t w = x; w < s.words; w += across) s.seen[q * s.words + w] = w == entry >> 5 ? 1u << (entry & 31) : 0u;
     if (x > 0) return;
-    if (q == 0 && n > 0) s.counters[CTR_T_START] = wall_clock64();
     s.eq_n[q] = 0;
     s.aq_tail[q] = 0;
     s.aq_live[q] = 0;
@@ -758,16 +767,15 @@ __global__ __launch_bounds__(64) void collect_kernel(SearchState s, const int32_
             atomicAdd((unsigned long long *)&s.counters[CTR_PENDING], (unsigned long long)np);
             atomicAdd((unsigned long long *)&s.counters[CTR_ROUND_TOKENS], (unsigned long long)tokens);
         }
-        if (q == 0) atomicAdd((unsigned long long *)&s.counters[CTR_T_TRAVERSE], (unsigned long long)(wall_clock64() - s.counters[CTR_T_ROUND]));
     }
-    publish(s.counters, s.host_counters, number);
+    publish(s.counters, s.host_counters, number, true);
 }
 
 // The call's end: behind the last finalize_kernel, whose results are then where all readers see them.
 __global__ __launch_bounds__(64) void end_kernel(SearchState s, long long seq)
 {
     if (threadIdx.x == 0) __hip_atomic_store(&s.counters[CTR_T_END], (long long)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    publish(s.counters, s.host_counters, seq);
+    publish(s.counters, s.host_counters, seq, false);
 }
 
 // The call's embedding memo: rows the encoder produced in this round are kept (while there is room) so that a later

@@ -234,6 +234,32 @@ def test_times_are_booked_where_they_are_spent(L, world):
     assert prof["launches"]["score_insert"] == 0 and prof["tokens"] == 0
 
 
+@pytest.mark.parametrize("nq,stored", [(1, False), (16, False), (1, True), (300, True)])
+def test_times_fit_into_one_another(L, world, nq, stored):
+    """One query and many, one launch and many rounds: the rounds' traversals are part of the device's time for the call, and that
+    is part of the time that the host sees.  The kernels of the traversal, each with two events round it (up to 10 us more than its own
+    time), are no longer than the traversal."""
+    import time
+    import torch
+    w = world
+    say(f"times of a search, {nq} queries, stored {stored}")
+    q = w["q"].repeat(-(-nq // w["q"].shape[0]), 1)[:nq].contiguous()
+    args = (w["ctx"], q, w["graph"], w["pq"], w["t"], w["l"], 64, 3, 0.3, 16)
+    cache = w["full_cache"] if stored else None
+    for _ in range(3):
+        torch.cuda.synchronize()
+        begin = time.perf_counter()
+        _, _, st = L.leann_search(*args, cache=cache)
+        seen = (time.perf_counter() - begin) * 1e3
+        assert 0 < st["traverse_ms"] < st["total_ms"] < seen
+    L.leann_profile_begin(w["ctx"])
+    _, _, st = L.leann_search(*args, cache=cache)
+    prof = L.leann_profile_end(w["ctx"])
+    launches = prof["launches"]["traverse"]
+    assert launches == prof["launches"]["collect"] == (1 if stored else st["rounds"] + 1)
+    assert st["traverse_ms"] > prof["ms"]["traverse"] + prof["ms"]["collect"] - 0.02 * launches
+
+
 def test_queue_capacity_overflow_is_reported(L, world):
     """An approximate queue that outgrows its capacity (set far too small through leann_set_limits) ends the search
     with LEANN_ECAPACITY: the kernel's own bounds checks drop the entries that do not fit and raise the flag."""
