@@ -123,7 +123,11 @@ const char *leann_last_error(const leann_ctx *ctx);
  *     per layer: Wqkv[3d][d] (query rows, key rows, value rows), bqkv[3d], Wo[d][d], bo[d],
  *                ln1_g[d], ln1_b[d], W1[F][d], b1[F], W2[d][F], b2[d], ln2_g[d], ln2_b[d].
  *   The library keeps its own copy (matrices and embedding tables in bf16, the
- *   rest in fp32); the caller may free weights_dev after the call returns.
+ *   rest in fp32) and, if the device has memory for it, the layers' matrices a second
+ *   time in another order, which small passes are faster with (layers * (8 * hidden^2 +
+ *   4 * hidden * ffn) bytes; results do not depend on it; freed when leann_embed or
+ *   leann_search find no memory for their workspaces); the caller may free weights_dev
+ *   after the call returns.
  *   Shapes covered: hidden/heads == 64, hidden % 128 == 0, ffn % 128 == 0,
  *   sequence length <= 256; anything else is LEANN_ESHAPE.
  *   device: HIP device ordinal; hip_stream: a hipStream_t (NULL = default stream).

@@ -50,6 +50,15 @@ int leann_ctx::reserve(DevBuf &buf, size_t need)
     return buf.reserve(need);
 }
 
+int leann_ctx::reserve_for_pass(DevBuf &buf, size_t need)
+{
+    const int rc = reserve(buf, need);
+    if (rc == LEANN_OK || !w_packed.p) return rc;
+    for (LayerWeights &w : layers) w.wqkv_p = w.wo_p = w.w1_p = w.w2_p = nullptr;
+    w_packed.release();  // waits for passes that read it
+    return buf.reserve(need);
+}
+
 int clear_host_flags(leann_ctx *ctx)
 {
     if (!ctx->host_flags) LEANN_HIP(hipHostMalloc((void **)&ctx->host_flags, FLAG_COUNT * sizeof(int), hipHostMallocDefault));
@@ -183,11 +192,11 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
                       L * (up256(3 * d * d * 2) + up256(d * d * 2) + 2 * up256(F * d * 2));
     size_t f_bytes = 2 * up256(d * 4) + L * (up256(3 * d * 4) + 6 * up256(d * 4) + up256(F * 4));
     const size_t packed_bytes = L * (4 * d * d + 2 * F * d) * 2;
-    if (ctx->w_bf16.reserve(bf_bytes) != LEANN_OK || ctx->w_f32.reserve(f_bytes) != LEANN_OK ||
-        ctx->w_packed.reserve(packed_bytes) != LEANN_OK) {
+    if (ctx->w_bf16.reserve(bf_bytes) != LEANN_OK || ctx->w_f32.reserve(f_bytes) != LEANN_OK) {
         leann_destroy(ctx);
         return LEANN_ENOMEM;
     }
+    const bool pack = ctx->w_packed.reserve(packed_bytes) == LEANN_OK;  // without them small passes are slower, nothing else
     char *pb = (char *)ctx->w_bf16.p, *pf = (char *)ctx->w_f32.p;
     size_t so = 0;  // element offset in the packed source
     hipError_t copy_rc = hipSuccess;
@@ -229,11 +238,12 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
     }
     bf16_t *pp = (bf16_t *)ctx->w_packed.p;
     int pack_rc = LEANN_OK;
-    auto packed = [&](const bf16_t *W, size_t N, size_t K) {
+    auto packed = [&](const bf16_t *W, size_t N, size_t K) -> const bf16_t * {
+        if (!pack) return nullptr;
         bf16_t *dst = pp;
         pp += N * K;
         if (pack_rc == LEANN_OK) pack_rc = enc_pack_weights(ctx, W, (int)N, (int)K, dst);
-        return (const bf16_t *)dst;
+        return dst;
     };
     for (LayerWeights &w : ctx->layers) {
         w.wqkv_p = packed(w.wqkv, 3 * d, d);

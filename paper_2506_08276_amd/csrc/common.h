@@ -37,7 +37,7 @@ void leann_set_error(const char *fmt, ...);
 // Per-layer device pointers into the context's own copy of the weights.
 struct LayerWeights {
     const bf16_t *wqkv, *wo, *w1, *w2;                          // [out][in] bf16
-    const bf16_t *wqkv_p, *wo_p, *w1_p, *w2_p;                  // the same in the MFMA's operand order
+    const bf16_t *wqkv_p, *wo_p, *w1_p, *w2_p;                  // the same in the MFMA's operand order, or none
     const float *bqkv, *bo, *g1, *be1, *b1, *b2, *g2, *be2;     // fp32
 };
 
@@ -93,6 +93,7 @@ struct leann_ctx {
     std::vector<hipEvent_t> prof_pool;
 
     int reserve(DevBuf &buf, size_t need);  // all device memory of a call: as buf.reserve, with pq_work given back if that fails
+    int reserve_for_pass(DevBuf &buf, size_t need);  // for calls that run the encoder: then the packed matrices, too
 };
 
 // Error flags of a call, in pinned host memory: kernels store 1 to what they find wrong, the host reads them after it has

@@ -547,7 +547,7 @@ int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W,
     return LEANN_OK;
 }
 
-// A product's two copies of the weights, see pack_weights_kernel.
+// A product's two copies of the weights, see pack_weights_kernel; no packed one where the context found no memory for it.
 struct Weights {
     const bf16_t *rows, *packed;
 };
@@ -646,7 +646,7 @@ int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const
     };
     const double k = K / 768.0, c128 = busiest(128), c256 = busiest(256);
     const bool wide = ctx->gemm_large_tile == 256 && K >= 8 * GEMM_BK && 21.0 * c256 - 2.0 <= 2.5 + 8.0 * c128;
-    if (ctx->gemm_small_rows > 0) {
+    if (ctx->gemm_small_rows > 0 && W.packed) {
         const double large_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
         double best_us = INFINITY;
         int best = -1, best_xr = 1, tile = 0;
@@ -745,13 +745,13 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     if (per_pass < 1) per_pass = 1;
     if (per_pass > n) per_pass = n;
     const size_t rows = (size_t)per_pass * seq + 256;
-    LEANN_TRY(ctx->reserve(ctx->x, rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->reserve(ctx->qkv, rows * 3 * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->reserve(ctx->att, rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->reserve(ctx->delta, rows * d * sizeof(bf16_t)));
-    LEANN_TRY(ctx->reserve(ctx->hid, rows * F * sizeof(bf16_t)));
-    LEANN_TRY(ctx->reserve(ctx->cu, (size_t)(per_pass + 1) * sizeof(int32_t)));
-    LEANN_TRY(ctx->reserve(ctx->enc_ids, (size_t)per_pass * sizeof(int64_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->x, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->qkv, rows * 3 * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->att, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->delta, rows * d * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->hid, rows * F * sizeof(bf16_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->cu, (size_t)(per_pass + 1) * sizeof(int32_t)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->enc_ids, (size_t)per_pass * sizeof(int64_t)));
     bf16_t *x = (bf16_t *)ctx->x.p, *qkv = (bf16_t *)ctx->qkv.p, *att = (bf16_t *)ctx->att.p, *hid = (bf16_t *)ctx->hid.p;
     bf16_t *delta = (bf16_t *)ctx->delta.p;  // sublayer output waiting for its residual add + LayerNorm
     int32_t *cu = (int32_t *)ctx->cu.p;

@@ -928,7 +928,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     const int d = ctx->desc.hidden, m_sub = pq->m_sub;
     const int64_t n = graph->n;
     hipStream_t st = ctx->stream;
-    LEANN_TRY(ctx->reserve(ctx->s_misc, CTR_COUNT * sizeof(long long)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_misc, CTR_COUNT * sizeof(long long)));
     long long *counters = (long long *)ctx->s_misc.p;
     LEANN_HIP(hipMemsetAsync(counters, 0, CTR_COUNT * sizeof(long long), st));
     LEANN_TRY(clear_host_flags(ctx));
@@ -976,16 +976,16 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
     const size_t o_done = carve((size_t)G * 4), o_nfl = carve((size_t)G * 4), o_eids = carve((size_t)G * pcap * 8);
     const int64_t memo_cap = std::min<int64_t>(ctx->memo_rows, (1 << 30) - 1);
     const size_t o_pick = carve(memo_cap > 0 ? (size_t)std::min<int64_t>(memo_cap, (int64_t)G * pcap) * 4 : 0);
-    LEANN_TRY(ctx->reserve(ctx->s_state, off));
-    LEANN_TRY(ctx->reserve(ctx->s_seen, (size_t)G * words * 4));
-    LEANN_TRY(ctx->reserve(ctx->s_lut, (size_t)G * m_sub * KSUB * sizeof(float)));
-    LEANN_TRY(ctx->reserve(ctx->s_emb, (size_t)G * pcap * d * sizeof(float)));
-    LEANN_TRY(ctx->reserve(ctx->s_owner, (size_t)n * sizeof(unsigned long long)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_state, off));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_seen, (size_t)G * words * 4));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_lut, (size_t)G * m_sub * KSUB * sizeof(float)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_emb, (size_t)G * pcap * d * sizeof(float)));
+    LEANN_TRY(ctx->reserve_for_pass(ctx->s_owner, (size_t)n * sizeof(unsigned long long)));
     // per-call embedding memo (leann_set_call_memo): empty at the start of every call
     int64_t memo_n = 0;
     if (memo_cap > 0) {
-        LEANN_TRY(ctx->reserve(ctx->s_memo_slot, (size_t)n * sizeof(int32_t)));
-        LEANN_TRY(ctx->reserve(ctx->s_memo_emb, (size_t)memo_cap * d * sizeof(float)));
+        LEANN_TRY(ctx->reserve_for_pass(ctx->s_memo_slot, (size_t)n * sizeof(int32_t)));
+        LEANN_TRY(ctx->reserve_for_pass(ctx->s_memo_emb, (size_t)memo_cap * d * sizeof(float)));
         LEANN_HIP(hipMemsetAsync(ctx->s_memo_slot.p, 0xff, (size_t)n * sizeof(int32_t), st));
     }
     char *base = (char *)ctx->s_state.p;
@@ -1091,7 +1091,7 @@ int search_run(leann_ctx *ctx, const float *queries_dev, int64_t nq, const leann
                 rc = LEANN_ECAPACITY;
                 break;
             }
-            LEANN_TRY(ctx->reserve(ctx->s_buf, (size_t)g * nb * sizeof(float)));
+            LEANN_TRY(ctx->reserve_for_pass(ctx->s_buf, (size_t)g * nb * sizeof(float)));
             buf_scores = (const float *)ctx->s_buf.p;
             hipLaunchKernelGGL(buffer_score_kernel, dim3((nb + 3) / 4, g), dim3(256), 0, st, queries_dev + (size_t)q0 * d,
                                upd->buffer_emb, nb, d, (float *)ctx->s_buf.p);

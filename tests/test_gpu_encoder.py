@@ -282,6 +282,62 @@ def test_tiles_of_one_round_give_the_same_bits(L, hidden, heads, ffn):
         L.leann_destroy(ctx)
 
 
+def test_weights_that_fit_the_device_once(L):
+    """A device that has not the room for the second copy of the layers' matrices: a context is made without it, or a larger pass
+    takes its place.  Small and large passes give the bits of a context that has memory."""
+    import torch
+    cfg = dict(layers=192, hidden=1024, heads=16, ffn=4096, vocab=500, max_pos=256, ln_eps=1e-12)
+    matrices = cfg["layers"] * 2 * (4 * 1024 * 1024 + 2 * 1024 * 4096)  # bytes, once: 4.8 GB
+    say("weights that fit the device once")
+    count = sum(int(np.prod(shape)) for _, shape, _ in li.weight_layout(cfg))
+    w = torch.randn(count, generator=torch.Generator("cuda:0").manual_seed(5), device="cuda:0", dtype=torch.bfloat16) * 0.03
+    tokens, lengths = li.uniform_chunks(600, 256, 1, cfg["vocab"], 1, 20, 31)
+    t, l = to_dev(tokens), to_dev(lengths)
+    free = lambda: torch.cuda.mem_get_info()[0]
+
+    def with_room_for(room, use):
+        """`use`, while other allocations leave about `room` bytes of the device (up to half a gigabyte more has been seen)."""
+        torch.cuda.empty_cache()
+        hold = torch.empty(free() - room, dtype=torch.uint8, device="cuda:0")
+        try:
+            return use()
+        finally:
+            del hold
+            torch.cuda.empty_cache()
+
+    def embed(ctx, counts=(1, 600)):  # 600: workspaces for 153 600 padded rows, 3.1 GB
+        return [L.leann_embed(ctx, t, l, n_ids=m, hidden=1024) for m in counts]
+
+    before = free()
+    ctx = L.leann_create(cfg, w)
+    try:
+        assert before - free() >= 2 * matrices - (64 << 20)
+        want = embed(ctx)
+    finally:
+        L.leann_destroy(ctx)
+
+    def without():
+        ctx = L.leann_create(cfg, w)
+        try:
+            return free(), embed(ctx, (1, 8))
+        finally:
+            L.leann_destroy(ctx)
+
+    left, got = with_room_for(matrices + (3 << 29), without)
+    assert left > 1 << 30  # a second copy would have left next to nothing
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1][:8])
+
+    ctx = L.leann_create(cfg, w)
+    try:
+        assert torch.equal(embed(ctx, (1,))[0], want[0])
+        before, got, after = with_room_for(1 << 30, lambda: (free(), embed(ctx), free()))
+        assert after > before  # 3.1 GB taken, 4.8 given back
+        for a, b in zip(got, want):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
+    finally:
+        L.leann_destroy(ctx)
+
+
 @pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 128), (384, 6, 1536), (768, 12, 3072)])
 def test_small_passes_of_any_fill_give_the_same_bits(L, hidden, heads, ffn):
     """A small pass requests its operands for the rows that it likely holds, before it knows how many there are: chunks that are
