@@ -5,7 +5,6 @@
 // Tokens of all chunks of a pass are packed back to back (no padding rows): chunk i owns rows
 // cu[i] .. cu[i+1] of every activation matrix.  The number of valid rows T is only known on the device,
 // so grids are sized for the worst case and blocks beyond T leave at once.
-#include <limits.h>
 #include <math.h>
 
 #include <algorithm>
@@ -13,6 +12,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "gemm_plan.h"
 #include "gemm_stream.h"
 #include "wave.h"
 
@@ -552,32 +552,6 @@ struct Weights {
     const bf16_t *rows, *packed;
 };
 
-// How gemm_stream_kernel's grid covers the 8 XCDs: xr of them side by side over the rows, the rest over the columns.  First
-// the arrangement with the fewest rounds of blocks on the fullest XCD, among those the one that reads least (an XCD
-// reads its share of the rows of A and of W once).
-struct StreamPlan {
-    int xr, rounds;
-};
-
-StreamPlan plan_stream(const leann_ctx *ctx, int tile_rows, int tile_cols, int rows, int N)
-{
-    StreamPlan best = {1, INT_MAX};
-    double best_bytes = 0;
-    const int rt = (rows + tile_rows - 1) / tile_rows, ct = (N + tile_cols - 1) / tile_cols;
-    const int cus = std::max(1, ctx->num_cus / 8);
-    for (int xr = 1; xr <= 8; xr *= 2) {
-        const int xc = 8 / xr;
-        const int per_xcd = ((ct + xc - 1) / xc) * ((rt + xr - 1) / xr);
-        const int rounds = (per_xcd + cus - 1) / cus;
-        const double bytes = (double)rows * xc + (double)N * xr;
-        if (rounds < best.rounds || (rounds == best.rounds && bytes < best_bytes)) {
-            best = {xr, rounds};
-            best_bytes = bytes;
-        }
-    }
-    return best;
-}
-
 // A tile of the stream kernels: R blocks of W rows by NM wavefronts of W columns.
 template <int W, int R, int NM, int EPI>
 struct StreamTile {
@@ -604,73 +578,19 @@ int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf1
     return LEANN_OK;
 }
 
-// Tiles of the stream kernels (width, blocks of rows, wavefronts) and what a launch takes while its blocks fit the chip at once:
-// microseconds besides the K loop and per 768 elements of K.
-#define LEANN_STREAM_TILES(X)                                                                            \
-    X(16, 2, 1, 1.85, 0.85) X(16, 2, 2, 2.25, 0.92) X(16, 2, 3, 2.35, 1.08) X(16, 2, 4, 2.2, 1.3) X(32, 1, 3, 2.5, 1.68) X(32, 1, 4, 2.55, 2.1) \
-    X(16, 4, 4, 2.65, 1.75) X(32, 2, 3, 3.2, 2.25) X(32, 2, 4, 3.2, 2.65) X(32, 2, 6, 3.3, 4.15) X(32, 2, 8, 3.4, 5.0) X(32, 4, 6, 4.6, 7.4)   \
-    X(32, 4, 8, 4.9, 8.8)
-
-// Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
-// Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
-// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
-//                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
-//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |   8.6
-//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |  26.1
-//   244 x 2304 x  768                                     4.4 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
-//   244 x  768 x 3072             5.8     6.6     7.2     9.2 |     8.8    10.7    11.3    13.0                                 |
-//   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |   9.8
-//   450 x  768 x 3072                     7.1     7.2     9.2 |     8.9    10.7    11.3    12.9                                 |
-//  1040 x  768 x  768                                     4.7 |             4.9     5.2     5.4     6.5                         |   9.1
-//  1040 x  768 x 3072                                    10.1 |            12.0    11.9    13.4    17.2                         |
-//  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |  10.7
-//  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |  19.0    19.0
-//  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |   6.6    11.3
-//  3500 x 1152 x  384                                         |                                     9.4     9.9     8.1     8.6 |   6.9    11.2
-//  3500 x 3072 x  768                                         |                                                    23.6    25.1 |  28.3    21.6
-//  8000 x  768 x 3072                                         |                                    42.7    47.1    37.0    37.5 |  51.2    56.5
-// 10000 x  384 x 1536                                         |                                    21.5    23.9    17.5    18.5 |  18.9    30.4
-// 12000 x  768 x  768                                         |                                                    22.3    24.3 |  23.7    19.1
-// The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).  Tiles
-// of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2 and 4.6).  gemm_kernel walks over its tiles: what decides is how many the busiest CU gets,
-// c = ceil(tiles / CUs).  128x128 takes about 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or,
-// next to the stream kernel, 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.
+// One product, through the tile that choose_gemm (gemm_plan.h) takes.
 template <int EPI>
 int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const float *bias, bf16_t *out,
          const int32_t *T_dev, int max_rows, int rows, int N, int K)
 {
-    const int cus = ctx->num_cus;
-    auto busiest = [&](int tile) {  // tiles of the busiest CU
-        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * ((N + tile - 1) / tile);
-        return (double)((tiles + cus - 1) / cus);
-    };
-    const double k = K / 768.0, c128 = busiest(128), c256 = busiest(256);
-    const bool wide = ctx->gemm_large_tile == 256 && K >= 8 * GEMM_BK && 21.0 * c256 - 2.0 <= 2.5 + 8.0 * c128;
-    if (ctx->gemm_small_rows > 0 && W.packed) {
-        const double large_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
-        double best_us = INFINITY;
-        int best = -1, best_xr = 1, tile = 0;
-#define LEANN_TILE(W, R, NM, US, US_K)                                                                                \
-        {                                                                                                             \
-            const StreamPlan p = plan_stream(ctx, W * R, W * NM, rows, N);                                            \
-            const double us = US + US_K * k;                                                                          \
-            if (p.rounds == 1 && us < best_us && us < large_us && (W * R * W * NM > 4096 || rows <= ctx->gemm_small_rows)) { \
-                best_us = us;                                                                                         \
-                best = tile;                                                                                          \
-                best_xr = p.xr;                                                                                       \
-            }                                                                                                         \
-            ++tile;                                                                                                   \
-        }
-        LEANN_STREAM_TILES(LEANN_TILE)
-#undef LEANN_TILE
-        tile = 0;
+    const GemmChoice c = choose_gemm(ctx->num_cus, ctx->gemm_large_tile, W.packed ? ctx->gemm_small_rows : 0, rows, N, K);
+    int tile = 0;
 #define LEANN_TILE(WIDTH, R, NM, US, US_K)                                                                            \
-        if (best == tile++)                                                                                           \
-            return launch_gemm_stream<WIDTH, R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, best_xr);
-        LEANN_STREAM_TILES(LEANN_TILE)
+    if (c.stream == tile++)                                                                                           \
+        return launch_gemm_stream<WIDTH, R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, c.xr);
+    LEANN_STREAM_TILES(LEANN_TILE)
 #undef LEANN_TILE
-    }
-    if (wide) return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);  // the last column tile may be half empty
+    if (c.large == 256) return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);  // the last column tile may be half empty
     return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);
 }
 
@@ -725,12 +645,6 @@ int enc_pack_weights(leann_ctx *ctx, const bf16_t *W, int N, int K, bf16_t *pack
     return LEANN_OK;
 }
 
-// Padded rows above which a pass whose caller does not know its tokens asks the device for their number before it chooses
-// tiles (four layers of 768: 48 x 256 tokens, all valid, 1237 us with tiles for five eighths of them, 1159 us asked; 24 x 256, a
-// quarter valid, 456 and 345; five eighths valid, 4 us are lost to the wait).  Below, the wrong tile costs no more than the
-// wait: 17 x 128, all valid, 436 us guessed, 448 asked.
-constexpr int ASK_ROWS = 4096;
-
 int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_dev, int64_t first_id, int64_t n,
                 float *out_dev, int64_t *tok_count_dev, int64_t tokens)
 {
@@ -763,7 +677,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         // How many of the rows hold tokens decides the tiles.  Where the caller does not know, the host waits for the count while
         // the embedding kernel runs, or, in small passes, takes chunks to be five eighths full.
         const bool ask = tokens <= 0 && max_rows > ASK_ROWS;
-        int rows = (int)std::min<int64_t>(max_rows, tokens > 0 ? (tokens * m + n - 1) / n : ((int64_t)max_rows * 5 + 7) / 8);
+        int rows = (int)std::min<int64_t>(max_rows, tokens > 0 ? (tokens * m + n - 1) / n : guessed_rows(max_rows));
         const int32_t *T_dev = cu + m;
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);

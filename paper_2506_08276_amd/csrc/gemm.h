@@ -1,6 +1,7 @@
 // bf16 MFMA GEMM with fused epilogues for the encoder's four linear maps (gfx950).
 #pragma once
 #include "common.h"
+#include "gemm_plan.h"
 
 namespace {
 
@@ -33,8 +34,6 @@ __device__ inline float gelu_erf(float v)
     const float p = fmaf(u, fmaf(u, 0.0010142733f, -0.10677579f), -2.3011213f);  // -p(u)
     return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * p));  // raw 2^x: overflow gives inf -> 0, underflow 0 -> v
 }
-
-constexpr int GEMM_BK = 32;
 
 // dynamic LDS of a block: three operand stages and, per wave, the bias of its 64 output columns
 template <int BM, int BN, int WM, int WN>

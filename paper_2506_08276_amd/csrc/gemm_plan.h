@@ -1,0 +1,116 @@
+// Which tile a product of the encoder goes through.  Host code without HIP types.
+#pragma once
+#include <limits.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+constexpr int GEMM_BK = 32;  // gemm_kernel's K-slab
+
+// How gemm_stream_kernel's grid covers the 8 XCDs: xr of them side by side over the rows, the rest over the columns.  First
+// the arrangement with the fewest rounds of blocks on the fullest XCD, among those the one that reads least (an XCD
+// reads its share of the rows of A and of W once).
+struct StreamPlan {
+    int xr, rounds;
+};
+
+inline StreamPlan plan_stream(int cus, int tile_rows, int tile_cols, int rows, int N)
+{
+    StreamPlan best = {1, INT_MAX};
+    double best_bytes = 0;
+    const int rt = (rows + tile_rows - 1) / tile_rows, ct = (N + tile_cols - 1) / tile_cols;
+    const int per_xcd_cus = std::max(1, cus / 8);
+    for (int xr = 1; xr <= 8; xr *= 2) {
+        const int xc = 8 / xr;
+        const int per_xcd = ((ct + xc - 1) / xc) * ((rt + xr - 1) / xr);
+        const int rounds = (per_xcd + per_xcd_cus - 1) / per_xcd_cus;
+        const double bytes = (double)rows * xc + (double)N * xr;
+        if (rounds < best.rounds || (rounds == best.rounds && bytes < best_bytes)) {
+            best = {xr, rounds};
+            best_bytes = bytes;
+        }
+    }
+    return best;
+}
+
+// Tiles of the stream kernels (width, blocks of rows, wavefronts) and what a launch takes while its blocks fit the chip at once:
+// microseconds besides the K loop and per 768 elements of K.
+#define LEANN_STREAM_TILES(X)                                                                            \
+    X(16, 2, 1, 1.85, 0.85) X(16, 2, 2, 2.25, 0.92) X(16, 2, 3, 2.35, 1.08) X(16, 2, 4, 2.2, 1.3) X(32, 1, 3, 2.5, 1.68) X(32, 1, 4, 2.55, 2.1) \
+    X(16, 4, 4, 2.65, 1.75) X(32, 2, 3, 3.2, 2.25) X(32, 2, 4, 3.2, 2.65) X(32, 2, 6, 3.3, 4.15) X(32, 2, 8, 3.4, 5.0) X(32, 4, 6, 4.6, 7.4)   \
+    X(32, 4, 8, 4.9, 8.8)
+
+struct GemmChoice {
+    int stream;  // number of the stream tile, -1: gemm_kernel
+    int xr;      // the stream kernel's grid, see plan_stream
+    int large;   // gemm_kernel's tile, 128 or 256
+};
+
+// Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
+// Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
+// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
+//                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
+//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |   8.6
+//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |  26.1
+//   244 x 2304 x  768                                     4.4 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
+//   244 x  768 x 3072             5.8     6.6     7.2     9.2 |     8.8    10.7    11.3    13.0                                 |
+//   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |   9.8
+//   450 x  768 x 3072                     7.1     7.2     9.2 |     8.9    10.7    11.3    12.9                                 |
+//  1040 x  768 x  768                                     4.7 |             4.9     5.2     5.4     6.5                         |   9.1
+//  1040 x  768 x 3072                                    10.1 |            12.0    11.9    13.4    17.2                         |
+//  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |  10.7
+//  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |  19.0    19.0
+//  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |   6.6    11.3
+//  3500 x 1152 x  384                                         |                                     9.4     9.9     8.1     8.6 |   6.9    11.2
+//  3500 x 3072 x  768                                         |                                                    23.6    25.1 |  28.3    21.6
+//  8000 x  768 x 3072                                         |                                    42.7    47.1    37.0    37.5 |  51.2    56.5
+// 10000 x  384 x 1536                                         |                                    21.5    23.9    17.5    18.5 |  18.9    30.4
+// 12000 x  768 x  768                                         |                                                    22.3    24.3 |  23.7    19.1
+// The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).
+// Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
+// and 4.6).
+// gemm_kernel walks over its tiles: what decides is how many the busiest CU gets, c = ceil(tiles / CUs).  128x128 takes about
+// 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or, next to the stream kernel,
+// 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.  Between the two of them K is left out: the second pair
+// of formulas would take 128x128 for most products of K = 384, where 256x256 is the faster one, as the first pair says (128x128 and
+// 256x256, microseconds per launch between two events: 24064 x 1152 x 384 35.0 and 29.7, 48128 x 384 x 384 31.2 and 29.3, x 1152 64.6 and
+// 52.4, x 1536 91.8 and 81.5, 100096 x 384 x 384 57.6 and 56.3; against it 16128 x 1152 x 384 25.6 and 26.2, 24064 x 1536 x 384 48.4 and 49.0).
+//
+// rows: that the product is expected to have; large_tile, small_rows: see leann_set_gemm_tiles (0 also: no packed weights).
+inline GemmChoice choose_gemm(int cus, int large_tile, int small_rows, int rows, int N, int K)
+{
+    auto busiest = [&](int tile) {  // tiles of the busiest CU
+        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * ((N + tile - 1) / tile);
+        return (double)((tiles + cus - 1) / cus);
+    };
+    const double k = K / 768.0, c128 = busiest(128), c256 = busiest(256);
+    const bool wide = large_tile == 256 && K >= 8 * GEMM_BK && 21.0 * c256 - 2.0 <= 2.5 + 8.0 * c128;
+    GemmChoice best = {-1, 1, wide ? 256 : 128};
+    if (small_rows <= 0) return best;
+    double best_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
+    int tile = 0;
+#define LEANN_TILE(W, R, NM, US, US_K)                                                                                \
+    {                                                                                                                 \
+        const StreamPlan p = plan_stream(cus, W * R, W * NM, rows, N);                                                \
+        const double us = US + US_K * k;                                                                              \
+        if (p.rounds == 1 && us < best_us && (W * R * W * NM > 4096 || rows <= small_rows)) {                         \
+            best_us = us;                                                                                             \
+            best.stream = tile;                                                                                       \
+            best.xr = p.xr;                                                                                           \
+        }                                                                                                             \
+        ++tile;                                                                                                       \
+    }
+    LEANN_STREAM_TILES(LEANN_TILE)
+#undef LEANN_TILE
+    return best;
+}
+
+// Padded rows above which a pass whose caller does not know its tokens asks the device for their number before it chooses
+// tiles (four layers of 768: 48 x 256 tokens, all valid, 1237 us with tiles for five eighths of them, 1159 us asked; 24 x 256, a
+// quarter valid, 456 and 345; five eighths valid, 4 us are lost to the wait).  Below, the wrong tile costs no more than the
+// wait: 17 x 128, all valid, 436 us guessed, 448 asked.
+constexpr int ASK_ROWS = 4096;
+
+// Rows that a smaller one of those is taken to hold: chunks are five eighths full.
+inline int guessed_rows(int max_rows) { return (int)(((int64_t)max_rows * 5 + 7) / 8); }

@@ -1,0 +1,36 @@
+"""CPU checks of the encoder's choice of GEMM tiles (csrc/gemm_plan.h)."""
+import pytest
+
+import gemm_plan
+
+WIDTHS = range(128, 1025, 128)
+ROWS = sorted({int(1.03 ** i) for i in range(330)} | {31, 32, 33, 63, 64, 65, 127, 128, 129, 2048, 2049})  # 1 to 16 800
+
+
+def products(d):
+    for F in (128, d, 2 * d, 4 * d):
+        yield from ((3 * d, d, False), (d, d, False), (F, d, True), (d, F, False))
+
+
+@pytest.mark.parametrize("d", WIDTHS)
+def test_a_stream_tile_is_taken_where_its_blocks_fit_the_chip_at_once(d):
+    """One block per CU; the tiles of 64x64 and smaller only
+    up to the row limit; the 256x256 tile only with K-slabs enough for its pipeline."""
+    area = lambda size: size[0] * size[1]
+    for N, K, _ in products(d):
+        for rows in ROWS:
+            name = gemm_plan.tile(rows, N, K)
+            size = tuple(int(v) for v in name.split()[-1].split("x"))
+            blocks = lambda s: -(-rows // s[0]) * -(-N // s[1])
+            if name.startswith("stream"):
+                assert blocks(size) <= gemm_plan.CUS
+                assert area(size) > 4096 or rows <= 2048
+            else:
+                assert size[0] == 128 or K >= 256
+            assert not gemm_plan.tile(rows, N, K, small_rows=0).startswith("stream")
+            assert gemm_plan.tile(rows, N, K, large_tile=128) != "256x256"
+
+
+def test_every_tile_is_taken_by_some_product():
+    taken = {(gemm_plan.tile(rows, N, K), gelu) for d in WIDTHS for N, K, gelu in products(d) for rows in ROWS}
+    assert taken == {(tile, gelu) for tile in gemm_plan.stream_tiles() + ["128x128", "256x256"] for gelu in (False, True)}
