@@ -69,7 +69,7 @@ struct GemmChoice {
 // 12000 x  768 x  768                                         |                                                    22.3    24.3 |  23.7    19.1
 // The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
-// and 4.6).
+// and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
 // gemm_kernel walks over its tiles: what decides is how many the busiest CU gets, c = ceil(tiles / CUs).  128x128 takes about
 // 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or, next to the stream kernel,
 // 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.  Between the two of them K is left out: the second pair

@@ -2,6 +2,7 @@
 import pytest
 
 import gemm_plan
+import test_gpu_encoder as gpu
 
 WIDTHS = range(128, 1025, 128)
 ROWS = sorted({int(1.03 ** i) for i in range(330)} | {31, 32, 33, 63, 64, 65, 127, 128, 129, 2048, 2049})  # 1 to 16 800
@@ -34,3 +35,19 @@ def test_a_stream_tile_is_taken_where_its_blocks_fit_the_chip_at_once(d):
 def test_every_tile_is_taken_by_some_product():
     taken = {(gemm_plan.tile(rows, N, K), gelu) for d in WIDTHS for N, K, gelu in products(d) for rows in ROWS}
     assert taken == {(tile, gelu) for tile in gemm_plan.stream_tiles() + ["128x128", "256x256"] for gelu in (False, True)}
+
+
+def test_the_passes_that_the_gpu_tests_compare_reach_every_tile():
+    """The tests that compare tiles bit for bit launch each of them, with and without GELU, and stream tiles with K both a multiple of
+    their loop's 384 and not."""
+    every = {(tile, gelu) for tile in gemm_plan.stream_tiles() + ["128x128", "256x256"] for gelu in (False, True)}
+    reached = set()
+    for shapes, counts, lengths, seq in ((gpu.EVERY_TILE, gpu.EVERY_TILE_CHUNKS, gpu.every_tile_lengths(), 128),
+                                         (gpu.ONE_ROUND, gpu.ONE_ROUND_CHUNKS, gpu.one_round_lengths(), 64)):
+        for hidden, _, ffn in shapes:
+            for m in counts:
+                reached |= gemm_plan.tiles_of_embed(dict(hidden=hidden, ffn=ffn), lengths[:m], seq)
+    assert {(tile, gelu) for tile, _, gelu in reached} == every
+    for tile in gemm_plan.stream_tiles():
+        if tile != "stream 32x128":  # taken at K = 128 only
+            assert {K % 384 == 0 for t, K, _ in reached if t == tile} == {False, True}, tile

@@ -3,6 +3,7 @@ fp32 oracle; a tighter 3e-3 against the oracle's bf16-storage mode)."""
 import numpy as np
 import pytest
 
+import gemm_plan
 import leann_inputs as li
 from gpu_util import say, to_dev
 
@@ -153,7 +154,7 @@ def test_base_shape_sample_matches_oracle(L, orc):
     lengths[:5] = [1, 33, 64, 200, 256]
     ctx = L.leann_create(cfg, to_dev(w).to(torch.bfloat16))  # bf16 weight upload path
     try:
-        got = L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy()  # 10240 padded rows: 256 x 256 tiles
+        got = L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy()  # 5466 tokens: 256 x 256 and 128 x 192 tiles
         L.leann_set_gemm_tiles(ctx, 128, 0)  # the same pass through 128 x 128 tiles: the same bits
         assert np.array_equal(L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy(), got)
         with pytest.raises(L.LeannError):
@@ -196,28 +197,32 @@ def test_small_shape_sample_matches_oracle(L, orc):
           (np.abs(got[ids] - want).max(), np.abs(got[ids] - want_bf).max()))
 
 
-def test_width_256_all_three_gemm_tiles(L, orc):
+def test_width_256_large_and_small_gemm_tiles(L, orc):
     """hidden = 256: the 256 x 256 GEMM tile with K = 256 (eight K-slabs, the fewest it is launched for: no
     full group of four before the tail) and K = 1024; ragged rows; against the oracle.  The same chunks embedded in
-    passes small enough for the 128 x 128 and the 64 x 64 tile give the same bits (all tiles add the K-slabs in one
+    smaller passes, through the 128 x 128 tile and the stream tiles, give the same bits (all tiles add the K-slabs in one
     order)."""
     import torch
     cfg = dict(layers=3, hidden=256, heads=4, ffn=1024, vocab=2000, max_pos=128, ln_eps=1e-12)
     say("width-256 encoder, large and small GEMM tile")
     w = li.encoder_weights(cfg, li.config_seed(2) + 21, bf16_exact=True)
-    tokens, lengths = li.uniform_chunks(100, 128, 1, cfg["vocab"], 16, 128, li.config_seed(2) + 22)
+    tokens, lengths = li.uniform_chunks(600, 128, 1, cfg["vocab"], 16, 128, li.config_seed(2) + 22)
     lengths[:4] = [1, 31, 77, 128]
     ctx = L.leann_create(cfg, to_dev(w).to(torch.bfloat16))
     try:
         t, l = to_dev(tokens), to_dev(lengths)
-        got = L.leann_embed(ctx, t, l, hidden=256).cpu().numpy()            # 12800 padded rows: large tile
-        some = L.leann_embed(ctx, t, l, n_ids=48, hidden=256).cpu().numpy()  # 6144 padded rows: 128 x 128 tile
-        few = L.leann_embed(ctx, t, l, n_ids=16, hidden=256).cpu().numpy()   # 2048 padded rows: 64 x 64 tile
+        passes = {}
+        for m, tiles in ((600, {"256x256"}), (100, {"128x128", "stream 64x128"}), (16, {"stream 32x48", "stream 64x64"})):
+            reached = gemm_plan.tiles_of_embed(cfg, lengths[:m], 128)
+            assert tiles <= {tile for tile, _, _ in reached}, (m, reached)
+            passes[m] = L.leann_embed(ctx, t, l, n_ids=m, hidden=256).cpu().numpy()
+        assert {(tile, K) for tile, K, _ in gemm_plan.tiles_of_embed(cfg, lengths, 128)} == {("256x256", 256), ("256x256", 1024)}
+        got = passes[600]
     finally:
         L.leann_destroy(ctx)
-    assert np.array_equal(got[:48], some)
-    assert np.array_equal(got[:16], few)
-    ids = np.array([0, 1, 2, 3, 50, 99], np.int64)
+    assert np.array_equal(got[:100], passes[100])
+    assert np.array_equal(got[:16], passes[16])
+    ids = np.array([0, 1, 2, 3, 50, 99, 599], np.int64)
     e = orc.desc(**cfg)
     want = orc.embed(e, w, tokens, lengths, ids=ids)
     want_bf = orc.embed(e, w, tokens, lengths, ids=ids, precision=1)
@@ -228,53 +233,69 @@ def test_width_256_all_three_gemm_tiles(L, orc):
           (np.abs(got[ids] - want).max(), np.abs(got[ids] - want_bf).max()))
 
 
-@pytest.mark.parametrize("hidden,heads,ffn", [(128, 2, 512), (256, 4, 1024), (384, 6, 1536), (768, 12, 3072)])
+EVERY_TILE = [(128, 2, 512), (256, 4, 1024), (384, 6, 1536), (768, 12, 3072)]
+EVERY_TILE_CHUNKS = (1, 2, 3, 5, 9, 14, 25, 40, 80, 200, 420)
+
+
+def every_tile_lengths():
+    _, lengths = li.uniform_chunks(420, 128, 1, 500, 16, 128, li.config_seed(2) + 30)
+    lengths[:3] = [1, 33, 127]
+    return lengths
+
+
+ONE_ROUND = [(512, 8, 128), (640, 10, 1280), (768, 12, 3072), (1024, 16, 1920)]
+ONE_ROUND_CHUNKS = (1, 2, 4, 7, 11, 16, 24, 33, 48, 55, 70, 100, 140, 180)
+
+
+def one_round_lengths():
+    lengths = np.full(180, 64, np.int32)
+    lengths[0] = 63  # rows = 64 m - 1, one less than whole tiles
+    return lengths
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", EVERY_TILE)
 def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
-    """Passes from a handful of tokens to tens of thousands go through every GEMM tile (32 x 32 up to 256 x 256, one to 24
-    K-slabs, row counts that are no multiple of any tile): each chunk's embedding equals the one that the 128 x 128 tile
-    alone gives."""
+    """Passes from a handful of tokens to tens of thousands, one to 24 K-slabs, row counts that are no multiple of any tile: each
+    chunk's embedding equals the one that the 128 x 128 tile alone gives.  Together with the passes of the next test these go through
+    every tile from 32 x 16 to 256 x 256, with and without GELU (test_gemm_plan.py counts them)."""
     import torch
     cfg = dict(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=128, ln_eps=1e-12)
     say(f"all GEMM tiles, hidden {hidden}")
     w = li.encoder_weights(cfg, li.config_seed(2) + hidden, bf16_exact=True)
-    n = 420
-    tokens, lengths = li.uniform_chunks(n, 128, 1, cfg["vocab"], 16, 128, li.config_seed(2) + 30)
-    lengths[:3] = [1, 33, 127]
+    tokens, _ = li.uniform_chunks(420, 128, 1, cfg["vocab"], 16, 128, li.config_seed(2) + 30)
     ctx = L.leann_create(cfg, to_dev(w).to(torch.bfloat16))
     try:
-        t, l = to_dev(tokens), to_dev(lengths)
+        t, l = to_dev(tokens), to_dev(every_tile_lengths())
         L.leann_set_gemm_tiles(ctx, 128, 0)
         want = L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy()
         L.leann_set_gemm_tiles(ctx, 256, 2048)
         assert np.isfinite(want).all()
-        for m in (1, 2, 3, 5, 9, 14, 25, 40, 80, 200, n):
+        for m in EVERY_TILE_CHUNKS:
             got = L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden).cpu().numpy()
             assert np.array_equal(got, want[:m]), m
-        L.leann_set_gemm_tiles(ctx, 0, 1 << 20)  # the 64 x 64 tile as far as it goes
-        assert np.array_equal(L.leann_embed(ctx, t, l, hidden=hidden).cpu().numpy(), want)
+        L.leann_set_gemm_tiles(ctx, 128, 1)  # stream tiles above 64 x 64 and the 128 x 128 tile only
+        for m in (9, 80, 420):
+            assert np.array_equal(L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden).cpu().numpy(), want[:m]), m
     finally:
         L.leann_destroy(ctx)
 
 
-@pytest.mark.parametrize("hidden,heads,ffn", [(640, 10, 1280), (768, 12, 3072), (1024, 16, 1920)])
+@pytest.mark.parametrize("hidden,heads,ffn", ONE_ROUND)
 def test_tiles_of_one_round_give_the_same_bits(L, hidden, heads, ffn):
-    """Passes that fill the chip once, from one row tile to those that no longer do (all tiles from 32 x 16 to 128 x 256), with K
-    a multiple of 384 or not (the slabs behind its end are zeros), rows at, below and above a tile's edge: the bits of the
-    128 x 128 tile of the kernel for large passes."""
+    """Passes that fill the chip once, from one row tile to those that no longer do, with K a multiple of 384 or not (the slabs behind
+    its end are zeros), rows at, below and above a tile's edge: the bits of the 128 x 128 tile of the kernel for large passes."""
     import torch
     cfg = dict(layers=1, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=64, ln_eps=1e-12)
     n, seq = 180, 64
     tokens, _ = li.uniform_chunks(n, seq, 1, cfg["vocab"], 1, seq, 21)
-    lengths = np.full(n, seq, np.int32)
-    lengths[0] = 63  # rows = 64 m - 1, one less than whole tiles
     ctx = L.leann_create(cfg, to_dev(li.encoder_weights(cfg, 22, perturb=True, bf16_exact=True)).to(torch.bfloat16))
     try:
-        t, l = to_dev(tokens), to_dev(lengths)
+        t, l = to_dev(tokens), to_dev(one_round_lengths())
         L.leann_set_gemm_tiles(ctx, 128, 0)
         want = L.leann_embed(ctx, t, l, hidden=hidden)
         L.leann_set_gemm_tiles(ctx, 256, 2048)
         assert torch.isfinite(want).all()
-        for m in (1, 2, 4, 7, 11, 16, 24, 33, 48, 70, 100, 140, n):
+        for m in ONE_ROUND_CHUNKS:
             say(f"one round of tiles, hidden {hidden}, {m} chunks")
             assert torch.equal(L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden), want[:m]), m
             assert torch.equal(L.leann_embed(ctx, t[1:], l[1:], n_ids=min(m, n - 1), hidden=hidden), want[1:m + 1]), m
