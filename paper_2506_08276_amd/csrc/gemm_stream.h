@@ -24,10 +24,11 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 //  - W is kept a second time in operand order, so a multiplying wavefront reads its own 32 columns straight into registers, DW
 //    steps of 16 elements ahead, 1 KB per request.  W takes no LDS space, stores or reads, and no barrier.
 //  - A goes through LDS: four wavefronts fetch K-slabs of 128 (a row's slab is two whole lines), three slabs ahead in registers, into
-//    a ring of three stages (with six ahead, the first one waits longer: 0.1 to 0.4 us per launch up to 64 x 128).  A multiplying wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead,
-//    across slabs: the slab after the current one is always there already.  One barrier per slab, at which only the
-//    fetching wavefronts wait for their LDS stores.  A slab row is 16 chunks of 16 bytes; chunk c of row r sits at c ^ (r & 15): the
-//    stores (16 lanes, one row) and the reads (16 lanes, 16 rows) both reach all banks.
+//    a ring of three stages (with six ahead, the first one waits longer: 0.1 to 0.4 us per launch up to 64 x 128).  A multiplying
+//    wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead, across slabs: the slab after the current
+//    one is always there already.  One barrier per slab, at which only the fetching wavefronts wait for their LDS stores.  A slab
+//    row is 16 chunks of 16 bytes; chunk c of row r sits at c ^ (r & 15): the stores (16 lanes, one row) and the reads (16 lanes, 16
+//    rows) both reach all banks.
 //  - The first requests go out before the token count is there.
 // Three slabs per turn of the loop, with one exit at its end: with more of them, or with a test between the first requests and the
 // loop, the compiled code moves requests behind it and waits for all that are in flight (the first build did: 1.3 us more at 80
@@ -211,7 +212,9 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
 // The same product for the smallest tiles, where one wavefront's MFMAs over K are the chain (32 x 32 outputs keep a SIMD's matrix core
 // busy for 32 clocks per 16 elements of K, with three SIMDs idle): a multiplying wavefront has 16 columns instead of 32, and 16 RB rows,
 // by MFMA 16x16x32, whose result for 32 elements of K has the bits of two 32x32x16 on this part (sums over groups of eight elements,
-// one after the other; the tests compare the tiles bit for bit).  So a tile's columns spread over twice as many SIMDs.  W is read
+// one after the other).  A chunk's embedding would otherwise depend on the pass it is in: fp32 results were compared for eleven kinds of
+// inputs (exponents over 2^40, opposite pairs, biases up to 2^40, denormals, infinities, ties; none of 8.6 million differs), and the
+// tests compare the tiles bit for bit, with sums that cancel too.  So a tile's columns spread over twice as many SIMDs.  W is read
 // from the same copy: of its 2 KB per 32 columns and 32 elements of K a lane takes the row and the eight elements that its operand slot
 // has.  Per launch, before (32x32 of gemm_stream_kernel) and now: 80 x 768 x 768 3.2 and 2.7 us, 80 x 768 x 3072 6.7 and 5.2,
 // 244 x 768 x 3072 7.0 and 5.8, 1040 x 768 x 3072 11.4 and 10.1 (64x64).  24 steps of W ahead instead of 12, in turns of six slabs, were 0.2 us

@@ -303,6 +303,86 @@ def test_tiles_of_one_round_give_the_same_bits(L, hidden, heads, ffn):
         L.leann_destroy(ctx)
 
 
+def weights_of_hard_sums(cfg, seed):
+    """Weights whose products are sums of terms of magnitudes from 2^-8 to 2^22 that cancel to a result of order one, so that the
+    leading bits of a product already hold what its order of summation and its roundings left over.  Activations come in equal pairs, at random distances
+    inside every 64 columns (equal embeddings, scales and rows of the matrix before), and most weights of a pair are opposite.
+    Biases from 2^-4 to 2^8 are there from the start of a sum.  {name: fp32 array}, bf16-representable."""
+    rng = np.random.Generator(np.random.Philox(seed))
+    _, w = li.encoder_weights(cfg, seed, std=1.0, bf16_exact=True, as_dict=True)
+    pairs = {}
+
+    def partner(n):  # (p, q): column q[i] holds what column p[i] holds
+        if n not in pairs:
+            order = np.concatenate([64 * b + rng.permutation(64) for b in range(n // 64)]).reshape(-1, 2)
+            pairs[n] = order[:, 0], order[:, 1]
+        return pairs[n]
+
+    def equal_rows(a, n):  # of a matrix, or elements of a vector, in blocks of n
+        p, q = partner(n)
+        for block in a.reshape(-1, n, *a.shape[1:]):
+            block[q] = block[p]
+
+    for l in range(cfg["layers"]):
+        for name in ("wqkv", "wo", "w1", "w2"):
+            a = w[f"l{l}.{name}"]
+            a *= 2.0 ** rng.integers(-8, 0, a.shape)  # what does not cancel: of order one in all
+            p, q = partner(a.shape[1])
+            cancels = rng.random((a.shape[0], p.size)) < 0.7
+            big = li.to_bf16_exact(rng.standard_normal(cancels.shape, dtype=np.float32)) * 2.0 ** rng.integers(0, 23, cancels.shape)
+            a[:, p] = np.where(cancels, big, a[:, p])
+            a[:, q] = np.where(cancels, -big, a[:, q])
+            b = w[f"l{l}.b" + name[1:]]
+            b[:] = li.to_bf16_exact(rng.standard_normal(b.shape, dtype=np.float32)) * 2.0 ** rng.integers(-4, 9, b.shape)
+            equal_rows(a, cfg["ffn"] if name == "w1" else cfg["hidden"])
+            equal_rows(b, cfg["ffn"] if name == "w1" else cfg["hidden"])
+    p, q = partner(cfg["hidden"])
+    for name in ("tok_emb", "pos_emb", "seg_emb"):
+        w[name][..., q] = w[name][..., p]
+    return {name: a.astype(np.float32) for name, a in w.items()}
+
+
+def pack_weights(cfg, w):
+    return np.concatenate([w[name].reshape(-1) for name, _, _ in li.weight_layout(cfg)]).astype(np.float32)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,tiles", [(128, 2, 512, {"32x16", "32x32", "32x64"}), (256, 4, 128, {"32x16", "32x32", "32x64", "64x64"}),
+                                                    (768, 12, 3072, {"32x16", "32x32", "32x48", "32x64", "64x64"})])
+def test_sums_that_cancel_have_the_same_bits_in_every_tile(L, hidden, heads, ffn, tiles):
+    """The smallest passes multiply by MFMA 16x16x32 where the others do by 32x32x16: that one of the former rounds like two of the
+    latter is what a chunk's embedding relies on.  Sums whose roundings are a third of them would show a difference; K from 128 to 3072."""
+    import torch
+    cfg = dict(layers=1, hidden=hidden, heads=heads, ffn=ffn, vocab=300, max_pos=32, ln_eps=1e-12)
+    say(f"sums that cancel, hidden {hidden}, ffn {ffn}")
+    n, seq = 60, 32
+    tokens, lengths = li.uniform_chunks(n, seq, 1, cfg["vocab"], 1, seq, 41)
+    lengths[0] = 1
+    t, l = to_dev(tokens), to_dev(lengths)
+    w = weights_of_hard_sums(cfg, 42)
+
+    def embed(w, counts, large_tile, small_rows):
+        ctx = L.leann_create(cfg, to_dev(pack_weights(cfg, w)))
+        try:
+            L.leann_set_gemm_tiles(ctx, large_tile, small_rows)
+            return [L.leann_embed(ctx, t, l, n_ids=m, hidden=hidden) for m in counts]
+        finally:
+            L.leann_destroy(ctx)
+
+    want = embed(w, (n,), 128, 0)[0]
+    assert torch.isfinite(want).all()
+    counts = (1, 2, 4, 8, 13, 20, 30, n)
+    reached = set().union(*(gemm_plan.tiles_of_embed(cfg, lengths[:m], seq) for m in counts))
+    assert {"stream " + tile for tile in tiles} <= {tile for tile, _, _ in reached}
+    for m, got in zip(counts, embed(w, counts, 256, 2048)):
+        assert torch.equal(got, want[:m]), m
+    # another order of the same sums is another result: the FFN's units moved on by eight
+    moved = dict(w)
+    for name, axis in (("l0.w1", 0), ("l0.b1", 0), ("l0.w2", 1)):
+        moved[name] = np.roll(w[name], 8, axis)
+    other = embed(moved, (n,), 128, 0)[0]
+    assert (other != want).float().mean() > 0.5
+
+
 def test_weights_that_fit_the_device_once(L):
     """A device that has not the room for the second copy of the layers' matrices: a context is made without it, or a larger pass
     takes its place.  Small and large passes give the bits of a context that has memory."""
