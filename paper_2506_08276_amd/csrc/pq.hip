@@ -18,8 +18,8 @@ constexpr int MAX_DSUB = 32;
 
 // The training rows: rows[i] of x (fp32 [n][d]) -> xt[m][i][d / m_sub], a plane per subspace, so that kernels that work on one
 // subspace read nothing else: pieces of 96 bytes straddle 128-byte lines, and in rows the line's rest belongs to other subspaces.  A block
-// takes GATHER_ROWS rows: that many pieces of a plane lie together.  65536 x 768 from 100000: 73 us, copied row by row 98; the
-// assignment of such rows 142, before 147.
+// takes GATHER_ROWS rows: that many pieces of a plane lie together.  65536 x 768 from 100000: 73 us, copied row by row 98; a call's
+// assignments of such rows (and the last one, of rows as they are) 148 us on average, 151 with training rows as they are.
 constexpr int GATHER_ROWS = 16;
 
 template <class Piece>  // f32x4 where every sub-vector consists of such and begins at one
@@ -63,7 +63,7 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    itself; p - 2^-16 |p| grows with p, so the second minimum's share covers all other centroids.  A gap of more than
 //    2^-16 (5.5 U + |minimum| + |second|) therefore leaves no doubt.  The other rows (few on embeddings; all of them where anything
 //    could overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
-// So the result is s(c)'s for every input.  163 us on average at 65536 to 100000 rows, d = 768, 32 subspaces (187 with five
+// So the result is s(c)'s for every input.  148 us on average at 65536 to 100000 rows, d = 768, 32 subspaces (some 185 with five
 // instructions per value and twice as many blocks).
 constexpr int ASSIGN_THREADS = 512;
 
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // blocks go round-robin to the 8 XCDs: with xcd_bits = 3 all subspaces of a run of rows are on one XCD, whose L2 then holds
-    // the 128-byte lines that neighbouring subspaces share
+    // the 128-byte lines that neighbouring subspaces share where x holds whole rows (training rows lie in a plane per subspace)
     const int m = (blockIdx.x >> xcd_bits) % m_sub;
     const int64_t chunk = ((int64_t)((blockIdx.x >> xcd_bits) / m_sub) << xcd_bits) + (blockIdx.x & ((1 << xcd_bits) - 1));
     const int64_t beg = chunk * rows_per_block, end = beg + rows_per_block < n ? beg + rows_per_block : n;
@@ -358,8 +358,8 @@ __global__ __launch_bounds__(1024) void group_rows_kernel(const uint8_t *__restr
 // The partial sums are in LDS; a group of 32 lanes (one per element) adds the rows with r % 8 equal to the group's number.
 // Latency bounds it (row numbers, then the rows' pieces from beyond L2): 256 row numbers are looked through at a time and each
 // group's rows listed first, so that a group has UPDATE_AHEAD of them in flight however they are spread.  Reads every training
-// row once per round: 77 us at 65536 rows, d = 768, 32 subspaces (82 with the subspaces' pieces in the rows; 132 with 32 row numbers at
-// a time, four rows in flight and a step of the pairwise sum per barrier).
+// row once per round: 85 us at 65536 rows, d = 768, 32 subspaces (89 with the subspaces' pieces in the rows and a subspace's centroids on
+// all XCDs; some 130 with 32 row numbers at a time, four rows in flight and a step of the pairwise sum per barrier).
 constexpr int UPDATE_AHEAD = 16;
 
 __global__ __launch_bounds__(256) void update_kernel(const float *__restrict__ xt, int64_t nt, int dsub, int xcd_bits,
