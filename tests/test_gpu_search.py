@@ -234,11 +234,12 @@ def test_times_are_booked_where_they_are_spent(L, world):
     assert prof["launches"]["score_insert"] == 0 and prof["tokens"] == 0
 
 
-@pytest.mark.parametrize("nq,stored", [(1, False), (16, False), (1, True), (300, True)])
+@pytest.mark.parametrize("nq,stored", [(1, False), (16, False), (2000, False), (1, True), (4000, True)])
 def test_times_fit_into_one_another(L, world, nq, stored):
     """One query and many, one launch and many rounds: the rounds' traversals are part of the device's time for the call, and that
-    is part of the time that the host sees.  The kernels of the traversal, each with two events round it (up to 10 us more than its own
-    time), are no longer than the traversal."""
+    is part of the time that the host sees.  The traversal's two kernels of a round, each with two events round it, take no longer than the
+    traversal, which lasts until the last query's requests are packed: events and the GPU's clock agree to 0.4 us per round; a
+    traversal that ends with the first query's is 28 us per round or more too short with 2000 queries and more."""
     import time
     import torch
     w = world
@@ -257,7 +258,7 @@ def test_times_fit_into_one_another(L, world, nq, stored):
     prof = L.leann_profile_end(w["ctx"])
     launches = prof["launches"]["traverse"]
     assert launches == prof["launches"]["collect"] == (1 if stored else st["rounds"] + 1)
-    assert st["traverse_ms"] > prof["ms"]["traverse"] + prof["ms"]["collect"] - 0.02 * launches
+    assert st["traverse_ms"] > prof["ms"]["traverse"] + prof["ms"]["collect"] - 0.01 * launches
 
 
 def test_queue_capacity_overflow_is_reported(L, world):
