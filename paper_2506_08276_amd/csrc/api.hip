@@ -182,7 +182,7 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
         int khz = 0;
         if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) ctx->clock_khz = khz;
     }
-    if (enc_ln_blocks_per_cu(&ctx->ln_blocks_per_cu) != LEANN_OK) {
+    if (enc_ln_blocks_per_cu(e.hidden, &ctx->ln_blocks_per_cu) != LEANN_OK) {
         leann_destroy(ctx);
         return LEANN_EDEVICE;
     }

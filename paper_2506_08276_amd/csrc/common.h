@@ -123,7 +123,7 @@ struct leann_pq {
 int enc_init_device();
 // W[N][K] in the MFMA's operand order, on the context's stream.
 int enc_pack_weights(leann_ctx *ctx, const bf16_t *W, int N, int K, bf16_t *packed);
-int enc_ln_blocks_per_cu(int *out);  // resident blocks of the LayerNorm kernel per CU on the current device
+int enc_ln_blocks_per_cu(int d, int *out);  // resident blocks of the LayerNorm kernel for rows of d elements per CU on the current device
 int pq_init_device();
 int search_init_device();
 

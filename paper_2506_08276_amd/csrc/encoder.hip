@@ -3,7 +3,7 @@
 // working on ragged (token-packed) batches, and fp32 LayerNorm / pooling.
 //
 // Tokens of all chunks of a pass are packed back to back (no padding rows): chunk i owns rows
-// cu[i] .. cu[i+1] of every activation matrix.  The number of valid rows T is only known on the device,
+// cu[i] .. cu[i+1] of every activation matrix (in planes of 32 columns, see gemm.h).  The number of valid rows T is only known on the device,
 // so grids are sized for the worst case and blocks beyond T leave at once.
 #include <math.h>
 
@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "gemm_large.h"
 #include "gemm_plan.h"
 #include "gemm_stream.h"
 #include "wave.h"
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
                                                        const bf16_t *__restrict__ tok_emb, const bf16_t *__restrict__ pos_emb,
                                                        const bf16_t *__restrict__ seg_emb, const float *__restrict__ g,
                                                        const float *__restrict__ b, float eps, bf16_t *__restrict__ x,
-                                                       int *__restrict__ err)
+                                                       int plane, int *__restrict__ err)
 {
     const int lane = threadIdx.x & 63;
     const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
         if (lane == 0) err[FLAG_TOKEN] = 1;
         tok = 0;
     }
-    // a lane owns 16-byte pieces (8 elements) j*64 + lane of the row, as in the residual LayerNorm below
+    // a lane owns 16-byte pieces (8 elements) j*64 + lane of the row
     const int pieces = d >> 3;
     const bf16_t *te = tok_emb + (size_t)tok * d, *pe = pos_emb + (size_t)t * d;
     float v[2][8];
@@ -144,7 +145,6 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
             }
         }
     const float inv = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
-    bf16_t *xr = x + (size_t)(row0 + t) * d;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
         if (j * 64 + lane < pieces) {
@@ -157,93 +157,136 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
                 o[i] = (bf16_t)((v[j][i] - mean) * inv * g0[i] + b0[i]);
                 o[i + 4] = (bf16_t)((v[j][i + 4] - mean) * inv * g1[i] + b1[i]);
             }
-            *reinterpret_cast<bf16x8 *>(xr + c0) = o;
+            *reinterpret_cast<bf16x8 *>(x + plane_at(c0, row0 + t, plane)) = o;
         }
 }
 
 // ------------------------------------------------------------------ residual add + LayerNorm, in place
 // x[row] = LN(x[row] + delta[row]): delta is a sublayer's output (bf16, written by the O / FFN2 GEMM), the sum, the
-// statistics and the normalisation are fp32.  One wave per row, the whole row in registers before anything is
-// written.  A lane owns 16-byte pieces (8 elements) j*64 + lane of the row (row length a multiple of 8, at most
-// 1024).  Two-pass statistics on the registers: mean, then the biased variance of the centred values.
-// EARLY: the first row is requested before the token count is there (a small pass is nothing but this chain of latencies;
-// the buffers reach past the last block's rows); with many rows per wavefront that order costs 3 % of the bandwidth.
+// statistics and the normalisation are fp32.  The rows of a wave are in its registers before anything is written.  Two-pass statistics on
+// the registers: mean, then the biased variance of the centred values.
+// A row's sum is defined on its 16-byte pieces p (8 elements, at most 128): 64 sums of the elements of the pieces l and l + 64 in order, then pairwise over
+// l ^ 32, 16, 8, 4, 2, 1.
+//  - Small passes (EARLY), which are nothing but this chain of latencies: a wave takes one row, lane l the pieces l and l + 64.  The first row is
+//    requested before the token count is there (the buffers reach past the last block's rows); with many rows per wavefront that
+//    order costs 3 % of the bandwidth.
+//  - Large ones: a wave takes a pair of rows, 2p and 2p + 1, whose pieces of a plane are one 128-byte line, eight lanes of 16 bytes; lane bit 2
+//    tells the row, and the lane's other bits, q, that it has the pieces q, q + 32, q + 64 and q + 96: the sums l = q and q + 32.  An odd
+//    last row's neighbour is normalised too and means nothing (the buffers reach past it).
+// PIECES: of a lane, as many as rows of up to 512 (EARLY) or 256 elements per piece need.
 template <bool EARLY>
+__device__ inline float row_sum(float s0, float s1)  // large passes: s0 of the sums l = q, s1 of q + 32; in all lanes of the row
+{
+    if constexpr (EARLY) {
+        return wave_sum(s0);
+    } else {
+        float v = s0 + s1;
+        {
+            const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        }
+        {
+            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        }
+        v += __uint_as_float(dpp_mov<DPP_ROW_ROR8>(__float_as_uint(v)));
+        v += __uint_as_float(dpp_mov<DPP_QUAD_XOR2>(__float_as_uint(v)));
+        v += __uint_as_float(dpp_mov<DPP_QUAD_XOR1>(__float_as_uint(v)));
+        return v;
+    }
+}
+
+template <int PIECES, bool EARLY>
 __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delta, const float *__restrict__ g,
                                                  const float *__restrict__ b, bf16_t *__restrict__ x,
-                                                 const int32_t *__restrict__ T_dev, int d, float eps)
+                                                 const int32_t *__restrict__ T_dev, int d, int plane, float eps, int nwaves)
 {
+    constexpr int ROWS = EARLY ? 1 : 2, SUMS = EARLY ? 1 : 2;  // rows of a wave, sums of a lane
     const int lane = threadIdx.x & 63;
-    const int pieces = d >> 3;
-    const int nwaves = gridDim.x * 4;
-    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int planes = d / PLANE, plane0 = EARLY ? lane >> 2 : lane >> 3, apart = EARLY ? 16 : 8;  // planes of a lane: plane0, plane0 + apart, ..
+    int at = blockIdx.x * 4 + (threadIdx.x >> 6);  // row or pair
     int T = 0;
     if constexpr (!EARLY) {
         T = *T_dev;
-        if (row >= T) return;
+        if (ROWS * at >= T) return;
     }
-    // a wave goes through rows row, row + nwaves, ...: the scale and shift of its pieces stay in registers, and the
-    // next row's loads are issued before the current row's arithmetic
-    f32x4 gg[2][2], bb[2][2];
-    bf16x8 dn[2], xn[2];
+    // a wave goes through rows or pairs at, at + nwaves, ...: the scale and shift of its pieces stay in registers, and the
+    // next one's loads are issued before the current one's arithmetic (nwaves, of the grid, is an argument: as the grid's it is read from memory)
+    f32x4 gg[PIECES][2], bb[PIECES][2];
+    bf16x8 dn[PIECES], xn[PIECES];
+    const size_t step = (size_t)apart * plane;  // between a lane's pieces
+    const size_t lane_at = (size_t)plane0 * plane + (EARLY ? lane & 3 : lane & 7) * 8;
+    auto on = [&](int j) { return j * apart + plane0 < planes; };
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-        if (j * 64 + lane < pieces) {
-            const int c0 = (j * 64 + lane) * 8;
+    for (int j = 0; j < PIECES; ++j)
+        if (on(j)) {
+            const int c0 = (j * apart + plane0) * PLANE + (lane & 3) * 8;
             gg[j][0] = *reinterpret_cast<const f32x4 *>(g + c0);
             gg[j][1] = *reinterpret_cast<const f32x4 *>(g + c0 + 4);
             bb[j][0] = *reinterpret_cast<const f32x4 *>(b + c0);
             bb[j][1] = *reinterpret_cast<const f32x4 *>(b + c0 + 4);
-            dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + (size_t)row * d + c0));
-            xn[j] = *reinterpret_cast<const bf16x8 *>(x + (size_t)row * d + c0);
+            const size_t o = lane_at + j * step + (size_t)at * (ROWS * PLANE);
+            dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + o));
+            xn[j] = *reinterpret_cast<const bf16x8 *>(x + o);
         }
     if constexpr (EARLY) T = *T_dev;
-    for (; row < T; row += nwaves) {
-        bf16_t *xr = x + (size_t)row * d;
-        float v[2][8];
-        float s = 0.f;
+    for (; ROWS * at < T; at += nwaves) {
+        float v[PIECES][8], s[2] = {0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (j * 64 + lane < pieces) {
+        for (int j = 0; j < PIECES; ++j)
+            if (on(j)) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     v[j][i] = (float)xn[j][i] + (float)dn[j][i];
-                    s += v[j][i];
+                    s[j % SUMS] += v[j][i];
                 }
             }
-        const int next = row + nwaves;
-        if (next < T) {
+        const int next = at + nwaves;
+        if (ROWS * next < T) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                if (j * 64 + lane < pieces) {
-                    const int c0 = (j * 64 + lane) * 8;
-                    dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + (size_t)next * d + c0));
-                    xn[j] = *reinterpret_cast<const bf16x8 *>(x + (size_t)next * d + c0);
+            for (int j = 0; j < PIECES; ++j)
+                if (on(j)) {
+                    const size_t o = lane_at + j * step + (size_t)next * (ROWS * PLANE);
+                    dn[j] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(delta + o));
+                    xn[j] = *reinterpret_cast<const bf16x8 *>(x + o);
                 }
         }
-        const float mean = wave_sum(s) / (float)d;
-        float q = 0.f;
+        const float mean = row_sum<EARLY>(s[0], s[1]) / (float)d;
+        float q[2] = {0.f, 0.f};  // fused where it says so: every variant of the kernel has to round alike
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (j * 64 + lane < pieces) {
+        for (int j = 0; j < PIECES; ++j)
+            if (on(j)) {
+                float &sq = q[j % SUMS];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float c = v[j][i] - mean;
-                    q += c * c;
-                }
+                for (int i = 0; i < 8; ++i) v[j][i] -= mean;
+                if (j < SUMS) sq = fmaf(v[j][0], v[j][0], v[j][1] * v[j][1]);
+                else sq = fmaf(v[j][1], v[j][1], fmaf(v[j][0], v[j][0], sq));
+#pragma unroll
+                for (int i = 2; i < 8; ++i) sq = fmaf(v[j][i], v[j][i], sq);
             }
-        const float inv = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
+        const float inv = 1.0f / sqrtf(row_sum<EARLY>(q[0], q[1]) / (float)d + eps);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (j * 64 + lane < pieces) {
+        for (int j = 0; j < PIECES; ++j)
+            if (on(j)) {
                 bf16x8 o;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    o[i] = (bf16_t)((v[j][i] - mean) * inv * gg[j][0][i] + bb[j][0][i]);
-                    o[i + 4] = (bf16_t)((v[j][i + 4] - mean) * inv * gg[j][1][i] + bb[j][1][i]);
+                    o[i] = (bf16_t)fmaf(v[j][i] * inv, gg[j][0][i], bb[j][0][i]);
+                    o[i + 4] = (bf16_t)fmaf(v[j][i + 4] * inv, gg[j][1][i], bb[j][1][i]);
                 }
-                *reinterpret_cast<bf16x8 *>(xr + (j * 64 + lane) * 8) = o;
+                *reinterpret_cast<bf16x8 *>(x + lane_at + j * step + (size_t)at * (ROWS * PLANE)) = o;
             }
+    }
+}
+
+auto ln_kernel_for(int d, bool early)  // leann_create takes rows of up to 1024 elements
+{
+    if (early) return d <= 512 ? ln_kernel<1, true> : ln_kernel<2, true>;
+    switch ((d + 255) / 256) {
+    case 1: return ln_kernel<1, false>;
+    case 2: return ln_kernel<2, false>;
+    case 3: return ln_kernel<3, false>;
+    default: return ln_kernel<4, false>;
     }
 }
 
@@ -274,9 +317,12 @@ struct AttCfg {
 // that one pass of the staging stores serves, then fall into 16 different bank groups (no bank conflicts either way).
 __device__ inline int vt_swizzle(int row) { return (row & 15) ^ (((row >> 4) & 3) << 1); }
 
+// K in LDS: 16 rows' reads of one chunk reach all banks, and so do stores of four chunks of four rows.
+__device__ inline int k_swizzle(int row) { return ((row >> 1) & 1) << 2 | ((row >> 2) & 3); }
+
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__restrict__ qkv, const int32_t *__restrict__ cu,
-                                                               bf16_t *__restrict__ out, int d, float scale_log2e)
+                                                               bf16_t *__restrict__ out, int d, int plane, float scale_log2e)
 {
     constexpr int LP = AttCfg<NW>::LP;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -284,50 +330,49 @@ __global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__r
     bf16_t *Vt = Ks + LP * 64;                      // [64][LP], see vt_swizzle
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // consecutive blocks are the heads of one chunk: they read adjacent 128-byte pieces of the same QKV rows at
-    // about the same time
+    // consecutive blocks are the heads of one chunk; a head's queries, keys and values of a chunk are two runs of memory each
     const int H = d >> 6;
     const int c = blockIdx.x / H, h = blockIdx.x % H;
     const int t0 = cu[c], L = cu[c + 1] - t0;
     if (L <= 0) return;
     const int nkt = (L + 31) >> 5;
     const int Lp = nkt << 5;
-    const size_t ld = (size_t)3 * d;
-    // Of K and V the chunk's rows and no more: reads of keys >= L bring zeros.  With a test per read the compiled code waited twice for all
-    // earlier ones in between, half a microsecond each.
-    const int kv_bytes = ((L - 1) * 3 * d + 64) * (int)sizeof(bf16_t), row_bytes = 3 * d * (int)sizeof(bf16_t);
     const int half = lane >> 5, l32 = lane & 31;
     const int qb = wave, qrow = qb * 32 + l32;
 
-    // Staging.  Half of the wavefronts bring V, half K; all global loads of a thread are issued before its first LDS store.
-    // Keys >= L are zero.
+    // Staging.  Half of the wavefronts bring V, half K, each 128 keys of one plane; all global loads of a thread are issued before its first
+    // LDS store.  Of K and V the chunk's rows and no more: reads of keys >= L bring zeros.  With a test per read the compiled code waited twice
+    // for all earlier ones in between, half a microsecond each.
     // V: thread (j16, hf, ch) takes the eight keys 16 j16 + 4 hf + {0..3, 8..11} of the 16-byte chunk ch (eight
-    // output dimensions) and writes, per dimension, the eight keys as one 16-byte group.  Eight adjacent lanes read
-    // one whole 128-byte piece of a V row.
-    // K: rows as they are, 16-byte chunk ch of row key at position ch ^ ((key >> 1) & 7).
+    // output dimensions) and writes, per dimension, the eight keys as one 16-byte group.  j16 and hf are spread over the lanes so that 16 of them
+    // store to all banks.
+    // K: rows as they are, 16-byte chunk ch of row key at position ch ^ k_swizzle(key).
+    constexpr int row_bytes = PLANE * (int)sizeof(bf16_t);
     const bool brings_v = wave < NW / 2;
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv + (size_t)t0 * ld + (brings_v ? 2 : 1) * d + h * 64), 0, kv_bytes, 0x00020000);
-    const int ch = tid & 7, st = tid & (32 * NW - 1), hf = (st >> 3) & 1, j16 = st >> 4;
+    const int part = wave & (NW / 2 - 1), which = part & 1, ch = which * 4 + (lane & 3), keys0 = (part >> 1) * 128;
+    const int hf = (lane >> 2) & 1, j16 = (keys0 >> 4) + ((lane >> 5) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 4) & 1);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv + plane_at((brings_v ? 2 : 1) * d + h * 64 + which * PLANE, t0, plane)), 0,
+                                                        L * row_bytes, 0x00020000);
     u32x4 in[8];
     {
-        // V: rows key0 + {0..3, 8..11}; K: rows st / 8 + r * 4 NW
-        const int key0 = brings_v ? j16 * 16 + 4 * hf : st >> 3, step = brings_v ? 1 : 4 * NW, step4 = brings_v ? 8 : 16 * NW;
+        // V: rows key0 + {0..3, 8..11}; K: rows key0 + 16 r
+        const int key0 = brings_v ? j16 * 16 + 4 * hf : keys0 + (lane >> 2), step = brings_v ? 1 : 16, step4 = brings_v ? 8 : 64;
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-            in[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (key0 + (r & 3) * step + (r >> 2) * step4) * row_bytes + ch * 16, 0, 0));
+            in[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (key0 + (r & 3) * step + (r >> 2) * step4) * row_bytes + (lane & 3) * 16, 0, 0));
     }
     // the wave's query rows go to registers while K and V are on their way to LDS
     bf16x8 qf[4];
     {
-        const bf16_t *qp = qkv + (size_t)(t0 + min(qrow, L - 1)) * ld + h * 64;
+        const bf16_t *qp = qkv + plane_at(h * 64, t0, plane) + min(qrow, L - 1) * PLANE + half * 8;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16 + half * 8);
+        for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + (s >> 1) * (size_t)plane + (s & 1) * 16);
     }
     if (!brings_v) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            const int key = (st >> 3) + r * 4 * NW;
-            if (key < Lp) *reinterpret_cast<u32x4 *>(Ks + key * 64 + ((ch ^ ((key >> 1) & 7)) << 3)) = in[r];
+            const int key = keys0 + (lane >> 2) + 16 * r;
+            if (key < Lp) *reinterpret_cast<u32x4 *>(Ks + key * 64 + ((ch ^ k_swizzle(key)) << 3)) = in[r];
         }
     } else if (j16 * 16 < Lp) {
 #pragma unroll
@@ -345,7 +390,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__r
     __syncthreads();
     if (qb >= nkt) return;
 
-    const int kswz = (l32 >> 1) & 7;  // rows 32 apart share the swizzle term
+    const int kswz = k_swizzle(l32);  // rows 32 apart share it
     bf16x8 kf[4];
     auto read_k = [&](int t) {
 #pragma unroll
@@ -416,12 +461,13 @@ __global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__r
     // The lane owns query l32 and, per (dt, g), the four adjacent outputs dt*32 + 8g + 4*half + 0..3.  Sixteen
     // queries at a time go through the wave's own 2 KB of LDS (8-byte unit u of a row at position u ^ swz(row):
     // the 16 lanes served together hit all banks once), so that the global stores are 16 bytes per lane and
-    // whole 128-byte lines per 8 lanes (stores of 8 bytes per lane to 32 rows cost a quarter of the kernel's time).
+    // eight adjacent rows in two planes (stores of 8 bytes per lane to 32 rows cost a quarter of the kernel's time).
     const float inv = 1.0f / den;
     unsigned char *ostg = smem + AttCfg<NW>::KV_BYTES + wave * (16 * 128);
     const int r16 = l32 & 15;
     const int wswz = ((r16 & 7) << 1) | (r16 >> 3);
     const int orow = lane >> 3, och = lane & 7;
+    bf16_t *to = out + plane_at(h * 64, t0, plane) + (size_t)(och >> 2) * plane + (och & 3) * 8;
 #pragma unroll
     for (int hp = 0; hp < 2; ++hp) {
         if ((l32 >> 4) == hp) {
@@ -442,57 +488,63 @@ __global__ __launch_bounds__(64 * NW, 4) void attention_kernel(const bf16_t *__r
             const int lr = j * 8 + orow, q = qb * 32 + hp * 16 + lr;
             u32x4 v = *reinterpret_cast<const u32x4 *>(ostg + lr * 128 + ((och ^ orow) << 4));
             if (j & 1) v = u32x4{v[2], v[3], v[0], v[1]};  // rows 8..15 hold the halves of a chunk swapped
-            if (q < L) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + (size_t)(t0 + q) * d + h * 64 + och * 8));
+            if (q < L) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(to + q * PLANE));
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
 // ------------------------------------------------------------------ masked mean pool + L2 normalise
-// One block per chunk.  Wave w sums rows w, w + 4, ... with 16-byte loads (a lane owns pieces j*64 + lane of a row, as
-// in the LayerNorm kernels); the four partial sums of a column are added in wave order, so the result does not depend
-// on anything but the chunk.
+// One block per chunk.  Partial sum p of a column is of the rows p, p + 4, ... in order, then the four are added in order: the result does
+// not depend on anything but the chunk.  A wavefront reads pairs of adjacent rows, 16 bytes per lane (lane bit 2 tells which: whole lines where a chunk
+// begins at an even row): wavefronts 0 and 2 the rows of partial sums 0 and 1, the others those of 2 and 3; 0 and 1 the first half of the planes, 8
+// of them per access, 2 and 3 the others.
 constexpr int POOL_AHEAD = 8;
 
-__global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x, const int32_t *__restrict__ cu, int d,
+template <int J>  // accesses per pair of rows and half: rows of up to 512 J elements
+__global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x, const int32_t *__restrict__ cu, int d, int plane,
                                                    float *__restrict__ out)
 {
-    __shared__ float part[4][1024];
+    __shared__ __attribute__((aligned(16))) float part[4][1024];
     __shared__ float red[256];
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = cu[c], L = cu[c + 1] - t0;
-    const int pieces = d >> 3;
-    float acc[2][8];
+    const int planes = d / PLANE / 2, mine = (wave & 1) * 2 + ((lane >> 2) & 1), plane0 = (wave >> 1) * planes;
+    float acc[J][8];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[j][i] = 0.f;
-    // POOL_AHEAD rows are in flight, then added in order.  Rows past the end and pieces past the row's are read from the last one
+    // POOL_AHEAD rows of a lane are in flight, then added in order.  Rows past the end and planes past the last one are read from the last
     // and not used: a test per read would have every read wait for the one before.
-    const bf16_t *x0 = x + (size_t)t0 * d + lane * 8, *x1 = x + (size_t)t0 * d + min(64 + lane, pieces - 1) * 8;
-    if (lane >= pieces) x0 = x1;
-    for (int t = wave; t < L; t += 4 * POOL_AHEAD) {
-        bf16x8 r[POOL_AHEAD][2];
+    const bf16_t *xj[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+        xj[j] = x + (size_t)(plane0 + min(j * 8 + (lane >> 3), planes - 1)) * plane + (size_t)t0 * PLANE + (lane & 3) * 8;
+    for (int t = 0; t < L; t += 4 * POOL_AHEAD) {
+        bf16x8 r[POOL_AHEAD][J];
 #pragma unroll
         for (int k = 0; k < POOL_AHEAD; ++k) {
-            const size_t row = (size_t)min(t + 4 * k, L - 1) * d;
-            r[k][0] = *reinterpret_cast<const bf16x8 *>(x0 + row);
-            r[k][1] = *reinterpret_cast<const bf16x8 *>(x1 + row);
+            const int at = min(t + 4 * k + mine, L - 1) * PLANE;
+#pragma unroll
+            for (int j = 0; j < J; ++j) r[k][j] = *reinterpret_cast<const bf16x8 *>(xj[j] + at);
         }
 #pragma unroll
         for (int k = 0; k < POOL_AHEAD; ++k)
-            if (t + 4 * k < L) {
+            if (t + 4 * k + mine < L) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < J; ++j)
 #pragma unroll
                     for (int i = 0; i < 8; ++i) acc[j][i] += (float)r[k][j][i];
             }
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-        if (j * 64 + lane < pieces) {
+    for (int j = 0; j < J; ++j)
+        if (j * 8 + (lane >> 3) < planes) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) part[wave][(j * 64 + lane) * 8 + i] = acc[j][i];
+            for (int i = 0; i < 8; i += 4)
+                *reinterpret_cast<f32x4 *>(&part[mine][(plane0 + j * 8 + (lane >> 3)) * PLANE + (lane & 3) * 8 + i]) =
+                    f32x4{acc[j][i], acc[j][i + 1], acc[j][i + 2], acc[j][i + 3]};
         }
     __syncthreads();
     float v[4] = {0.f, 0.f, 0.f, 0.f};
@@ -518,39 +570,56 @@ __global__ __launch_bounds__(256) void pool_kernel(const bf16_t *__restrict__ x,
     }
 }
 
-template <int BM, int BN, int EPI>
-int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
-                const int32_t *T_dev, int max_rows, int N, int K)
-{
-    constexpr int WM = 2, WN = BN / 64;
-    constexpr int smem = gemm_smem_bytes<BM, BN, WM, WN>();
-    if (N % (BM == 256 ? 128 : BN) || K % (4 * GEMM_BK) || (BM * BN > 128 * 128 && K < 8 * GEMM_BK)) {
-        leann_set_error("GEMM shape N=%d K=%d not covered by the %dx%d tile", N, K, BM, BN);
-        return LEANN_ESHAPE;
-    }
-    const int tiles_n = (N + BN - 1) / BN;
-    // W beyond the 4 MB of L2 an XCD has is evicted between its uses; if the output is wide (so that A is small next
-    // to it) the column tiles go in groups that fit (measured on FFN1: +4-5 %; on QKV, whose W fits, a loss).
-    int gcols = tiles_n;
-    if ((size_t)N * K * sizeof(bf16_t) > ((size_t)4 << 20) && N >= 4 * K) {
-        const int groups = (int)(((size_t)N * K * sizeof(bf16_t) + ((size_t)5 << 19) - 1) / ((size_t)5 << 19));  // 2.5 MB each
-        gcols = (tiles_n + groups - 1) / groups;
-    }
-    const int tiles = ((max_rows + BM - 1) / BM) * tiles_n;
-    // persistent blocks: one per CU slot (a multiple of 8), fewer when there are fewer tiles
-    const int slots = ctx->num_cus * (BM == 256 ? 1 : 2);
-    const int grid = std::max(8, std::min(slots, (tiles + 7) & ~7) & ~7);
-    ProfScope prof(ctx, prof_kind);
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, EPI>), dim3(grid), dim3(64 * WM * WN), smem, ctx->stream, A, W, bias,
-                       out, T_dev, N, K, tiles_n, gcols);
-    LEANN_HIP(hipGetLastError());
-    return LEANN_OK;
-}
-
 // A product's two copies of the weights, see pack_weights_kernel; no packed one where the context found no memory for it.
 struct Weights {
     const bf16_t *rows, *packed;
 };
+
+// W beyond the 4 MB of L2 an XCD has is evicted between its uses; if the output is wide (so that A is small next
+// to it) the column tiles go in groups that fit (measured on FFN1: +4-5 %; on QKV, whose W fits, a loss).
+int column_group(int tiles_n, int N, int K)
+{
+    if ((size_t)N * K * sizeof(bf16_t) <= ((size_t)4 << 20) || N < 4 * K) return tiles_n;
+    const int groups = (int)(((size_t)N * K * sizeof(bf16_t) + ((size_t)5 << 19) - 1) / ((size_t)5 << 19));  // 2.5 MB each
+    return (tiles_n + groups - 1) / groups;
+}
+
+// Persistent blocks: one per CU slot (a multiple of 8), fewer when there are fewer tiles.
+int persistent_grid(int slots, int tiles) { return std::max(8, std::min(slots, (tiles + 7) & ~7) & ~7); }
+
+template <int EPI>
+int launch_gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf16_t *W, const float *bias, bf16_t *out,
+                const int32_t *T_dev, int max_rows, int N, int K, int plane)
+{
+    if (N % 128 || K % (4 * GEMM_BK)) {
+        leann_set_error("GEMM shape N=%d K=%d not covered by the 128x128 tile", N, K);
+        return LEANN_ESHAPE;
+    }
+    const int tiles_n = N / 128, tiles = ((max_rows + 127) / 128) * tiles_n;
+    ProfScope prof(ctx, prof_kind);
+    hipLaunchKernelGGL((gemm_kernel<EPI>), dim3(persistent_grid(2 * ctx->num_cus, tiles)), dim3(256), GEMM_SMEM, ctx->stream, A, W, bias, out, T_dev,
+                       N, K, tiles_n, column_group(tiles_n, N, K), plane);
+    LEANN_HIP(hipGetLastError());
+    return LEANN_OK;
+}
+
+template <int WM, int TM, int TN, int EPI>
+int launch_gemm_large(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const float *bias, bf16_t *out,
+                      const int32_t *T_dev, int max_rows, int N, int K, int plane)
+{
+    typedef LargeCfg<WM, TM, TN> Cfg;
+    if (N % 64 || K % (4 * GEMM_BK) || K < 8 * GEMM_BK) {
+        leann_set_error("GEMM shape N=%d K=%d not covered by the %dx%d tile", N, K, Cfg::BM, Cfg::BN);
+        return LEANN_ESHAPE;
+    }
+    const int tiles_n = (N + Cfg::BN - 1) / Cfg::BN, tiles = ((max_rows + Cfg::BM - 1) / Cfg::BM) * tiles_n;
+    ProfScope prof(ctx, prof_kind);
+    hipLaunchKernelGGL((gemm_large_kernel<WM, TM, TN, EPI>), dim3(persistent_grid(ctx->num_cus, tiles)), dim3(512), Cfg::SMEM, ctx->stream, A,
+                       W.packed ? W.packed : W.rows, bias, out, T_dev, N, K, tiles_n, column_group(tiles_n, N, K), plane,
+                       W.packed != nullptr);
+    LEANN_HIP(hipGetLastError());
+    return LEANN_OK;
+}
 
 // A tile of the stream kernels: R blocks of W rows by NM wavefronts of W columns.
 template <int W, int R, int NM, int EPI>
@@ -573,7 +642,7 @@ int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf1
     const int rt = (max_rows + Cfg::ROWS - 1) / Cfg::ROWS, ct = (N + Cfg::COLS - 1) / Cfg::COLS, xc = 8 / xr;
     ProfScope prof(ctx, prof_kind);
     hipLaunchKernelGGL(Tile::kernel(), dim3(8 * ((ct + xc - 1) / xc), (rt + xr - 1) / xr), dim3(Cfg::THREADS),
-                       Cfg::SMEM, ctx->stream, A, Wp, bias, out, T_dev, max_rows, likely_rows, N, K, __builtin_ctz(xr));
+                       Cfg::SMEM, ctx->stream, A, Wp, bias, out, T_dev, max_rows, likely_rows, stream_shape(N, K, xr));
     LEANN_HIP(hipGetLastError());
     return LEANN_OK;
 }
@@ -581,17 +650,18 @@ int launch_gemm_stream(leann_ctx *ctx, int prof_kind, const bf16_t *A, const bf1
 // One product, through the tile that choose_gemm (gemm_plan.h) takes.
 template <int EPI>
 int gemm(leann_ctx *ctx, int prof_kind, const bf16_t *A, const Weights &W, const float *bias, bf16_t *out,
-         const int32_t *T_dev, int max_rows, int rows, int N, int K)
+         const int32_t *T_dev, int max_rows, int rows, int N, int K, int plane)
 {
-    const GemmChoice c = choose_gemm(ctx->num_cus, ctx->gemm_large_tile, W.packed ? ctx->gemm_small_rows : 0, rows, N, K);
+    const GemmChoice c = choose_gemm(ctx->num_cus, ctx->gemm_large_tile, W.packed && stream_covers(N, K, plane) ? ctx->gemm_small_rows : 0, rows, N, K);
     int tile = 0;
 #define LEANN_TILE(WIDTH, R, NM, US, US_K)                                                                            \
     if (c.stream == tile++)                                                                                           \
         return launch_gemm_stream<WIDTH, R, NM, EPI>(ctx, prof_kind, A, W.packed, bias, out, T_dev, max_rows, rows, N, K, c.xr);
     LEANN_STREAM_TILES(LEANN_TILE)
 #undef LEANN_TILE
-    if (c.large == 256) return launch_gemm<256, 256, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);  // the last column tile may be half empty
-    return launch_gemm<128, 128, EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K);
+    if (c.large == 256 && c.cols == 192) return launch_gemm_large<4, 2, 3, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K, plane);
+    if (c.large == 256) return launch_gemm_large<2, 4, 2, EPI>(ctx, prof_kind, A, W, bias, out, T_dev, max_rows, N, K, plane);
+    return launch_gemm<EPI>(ctx, prof_kind, A, W.rows, bias, out, T_dev, max_rows, N, K, plane);
 }
 
 template <int W, int R, int NM, int EPI>
@@ -602,32 +672,31 @@ int gemm_stream_allow_lds()
     return LEANN_OK;
 }
 
-template <int BM, int BN, int EPI>
-int gemm_allow_lds()
+template <int WM, int TM, int TN, int EPI>
+int gemm_large_allow_lds()
 {
-    constexpr int WM = 2, WN = BN / 64;
-    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<BM, BN, WM, WN, EPI>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, gemm_smem_bytes<BM, BN, WM, WN>()));
+    LEANN_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_large_kernel<WM, TM, TN, EPI>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, LargeCfg<WM, TM, TN>::SMEM));
     return LEANN_OK;
 }
 
 }  // namespace
 
 // Kernels that use more dynamic LDS than the default limit are allowed their size on the current device.
-int enc_ln_blocks_per_cu(int *out)
+int enc_ln_blocks_per_cu(int d, int *out)
 {
     int n = 0;
-    LEANN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(ln_kernel<false>), 256, 0));
+    LEANN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(ln_kernel_for(d, false)), 256, 0));
     *out = n > 0 ? n : 1;
     return LEANN_OK;
 }
 
 int enc_init_device()
 {
-    LEANN_TRY((gemm_allow_lds<256, 256, EPI_BIAS>()));
-    LEANN_TRY((gemm_allow_lds<256, 256, EPI_BIAS_GELU>()));
-    LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS>()));
-    LEANN_TRY((gemm_allow_lds<128, 128, EPI_BIAS_GELU>()));
+    LEANN_TRY((gemm_large_allow_lds<2, 4, 2, EPI_BIAS>()));
+    LEANN_TRY((gemm_large_allow_lds<2, 4, 2, EPI_BIAS_GELU>()));
+    LEANN_TRY((gemm_large_allow_lds<4, 2, 3, EPI_BIAS>()));
+    LEANN_TRY((gemm_large_allow_lds<4, 2, 3, EPI_BIAS_GELU>()));
 #define LEANN_TILE(W, R, NM, US, US_K)                            \
     LEANN_TRY((gemm_stream_allow_lds<W, R, NM, EPI_BIAS>()));      \
     LEANN_TRY((gemm_stream_allow_lds<W, R, NM, EPI_BIAS_GELU>()));
@@ -658,7 +727,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
     int64_t per_pass = ctx->max_tokens / seq;
     if (per_pass < 1) per_pass = 1;
     if (per_pass > n) per_pass = n;
-    const size_t rows = (size_t)per_pass * seq + 256;
+    const size_t rows = pass_pitch((int)(per_pass * seq));
     LEANN_TRY(ctx->reserve_for_pass(ctx->x, rows * d * sizeof(bf16_t)));
     LEANN_TRY(ctx->reserve_for_pass(ctx->qkv, rows * 3 * d * sizeof(bf16_t)));
     LEANN_TRY(ctx->reserve_for_pass(ctx->att, rows * d * sizeof(bf16_t)));
@@ -679,6 +748,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         const bool ask = tokens <= 0 && max_rows > ASK_ROWS;
         int rows = (int)std::min<int64_t>(max_rows, tokens > 0 ? (tokens * m + n - 1) / n : guessed_rows(max_rows));
         const int32_t *T_dev = cu + m;
+        const int plane = pass_pitch(max_rows) * PLANE;
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
             hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(m <= PREP_FEW ? PREP_FEW : 1024), 0, ctx->stream, chunks->lengths,
@@ -690,7 +760,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
             hipLaunchKernelGGL(embed_ln_kernel, dim3((unsigned)(((int64_t)m * seq + 3) / 4)), dim3(256), 0, ctx->stream,
                                chunks->tokens, chunk_of, cu, m, seq, d, e.vocab, ctx->tok_emb, ctx->pos_emb, ctx->seg_emb,
-                               ctx->emb_g, ctx->emb_b, e.ln_eps, x, ctx->host_flags);
+                               ctx->emb_g, ctx->emb_b, e.ln_eps, x, plane, ctx->host_flags);
         }
         if (ask) {
             LEANN_HIP(hipEventSynchronize(ctx->pass_event));
@@ -699,32 +769,34 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         }
         // as many blocks as are resident at once (measured: 10 % faster than a row per wave, and than twice as
         // many blocks); their waves go through several rows each
-        const int ln_grid = std::min((max_rows + 3) / 4, ctx->num_cus * ctx->ln_blocks_per_cu);
+        const bool few_rows = rows <= 2048;
+        const int ln_grid = std::min((max_rows + (few_rows ? 3 : 7)) / (few_rows ? 4 : 8), ctx->num_cus * ctx->ln_blocks_per_cu);
+        const auto ln = ln_kernel_for(d, few_rows);
         auto layer_norm = [&](const float *g, const float *b) {
             ProfScope prof(ctx, LEANN_PROF_LAYERNORM);
-            hipLaunchKernelGGL(rows <= 2048 ? ln_kernel<true> : ln_kernel<false>, dim3(ln_grid), dim3(256), 0, ctx->stream, delta, g, b, x, T_dev, d, e.ln_eps);
+            hipLaunchKernelGGL(ln, dim3(ln_grid), dim3(256), 0, ctx->stream, delta, g, b, x, T_dev, d, plane, e.ln_eps, 4 * ln_grid);
         };
         for (int l = 0; l < e.layers; ++l) {
             const LayerWeights &w = ctx->layers[l];
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_QKV, x, {w.wqkv, w.wqkv_p}, w.bqkv, qkv, T_dev, max_rows, rows, 3 * d, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_QKV, x, {w.wqkv, w.wqkv_p}, w.bqkv, qkv, T_dev, max_rows, rows, 3 * d, d, plane));
             {
                 ProfScope prof(ctx, LEANN_PROF_ATTENTION);
                 if (seq <= 128)
                     hipLaunchKernelGGL(attention_kernel<4>, dim3((unsigned)m * H), dim3(64 * 4), AttCfg<4>::SMEM, ctx->stream, qkv, cu,
-                                       att, d, scale_log2e);
+                                       att, d, plane, scale_log2e);
                 else
                     hipLaunchKernelGGL(attention_kernel<8>, dim3((unsigned)m * H), dim3(64 * 8), AttCfg<8>::SMEM, ctx->stream, qkv, cu,
-                                       att, d, scale_log2e);
+                                       att, d, plane, scale_log2e);
             }
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, {w.wo, w.wo_p}, w.bo, delta, T_dev, max_rows, rows, d, d));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_O, att, {w.wo, w.wo_p}, w.bo, delta, T_dev, max_rows, rows, d, d, plane));
             layer_norm(w.g1, w.be1);
-            LEANN_TRY(gemm<EPI_BIAS_GELU>(ctx, LEANN_PROF_GEMM_FFN1, x, {w.w1, w.w1_p}, w.b1, hid, T_dev, max_rows, rows, F, d));
-            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_FFN2, hid, {w.w2, w.w2_p}, w.b2, delta, T_dev, max_rows, rows, d, F));
+            LEANN_TRY(gemm<EPI_BIAS_GELU>(ctx, LEANN_PROF_GEMM_FFN1, x, {w.w1, w.w1_p}, w.b1, hid, T_dev, max_rows, rows, F, d, plane));
+            LEANN_TRY(gemm<EPI_BIAS>(ctx, LEANN_PROF_GEMM_FFN2, hid, {w.w2, w.w2_p}, w.b2, delta, T_dev, max_rows, rows, d, F, plane));
             layer_norm(w.g2, w.be2);
         }
         {
             ProfScope prof(ctx, LEANN_PROF_ENC_OTHER);
-            hipLaunchKernelGGL(pool_kernel, dim3(m), dim3(256), 0, ctx->stream, x, cu, d, out_dev + (size_t)s * d);
+            hipLaunchKernelGGL(d <= 512 ? pool_kernel<1> : pool_kernel<2>, dim3(m), dim3(256), 0, ctx->stream, x, cu, d, plane, out_dev + (size_t)s * d);
         }
         LEANN_HIP(hipGetLastError());
     }

@@ -5,9 +5,26 @@
 
 namespace {
 
+// Activations are kept in planes: a matrix of C columns is C / 32 planes of 32 columns (64 bytes per row), so that what a K-slab
+// takes of a tile, 32 columns of adjacent rows, is one run of memory.  In rows of C elements a slab's 64 bytes are half a line each: every
+// request to L2 uses half of a line's bandwidth, and rows of 6144 bytes (C = 3072) meet in few of the memory's channels (gemm_large_kernel, T = 131072,
+// N x K = 2304 x 768 from rows 1.05 times as fast as the kernel before it, from planes 1.12; 768 x 3072 1.00 and 1.19).  In passes of one to
+// some 1000 rows, where requests are few, both layouts are the same.
+// `plane`: elements between planes.
+constexpr int PLANE = 32;
+
+__device__ inline size_t plane_at(int col, int64_t row, int plane)  // element (row, col)
+{
+    return (size_t)(col / PLANE) * plane + row * PLANE + col % PLANE;
+}
+
+// Rows that the matrices of a pass of `rows` rows have room for: tiles reach up to 255 past them.  A plane then begins an odd multiple of 256
+// bytes behind the one before it (a row's pieces lie in different channels).
+__host__ __device__ inline int pass_pitch(int rows) { return ((rows + 259) >> 2 | 1) << 2; }
+
 // C[T][N] = A[T][K] * W[N][K]^T + bias (optionally GELU), rounded to bf16.  bf16 operands, fp32 accumulation in
-// MFMA 32x32x16.
-// Block tile BM x BN, K-slabs of 32, WM x WN waves.  A slab row is four 16-byte chunks; chunk c of row r
+// MFMA 32x32x16.  This kernel has tiles of 128 x 128 on four waves; gemm_large_kernel has the larger ones.
+// K-slabs of 32, 2 x 2 waves.  A slab row is four 16-byte chunks; chunk c of row r
 // lives at chunk position c ^ ((r >> 2) & 3), so the row-wise stores and the column-of-rows MFMA operand reads
 // both spread over all LDS banks.
 // Software pipeline (slab s): global loads into one of four register sets at iteration s-5 (memory latency
@@ -15,9 +32,7 @@ namespace {
 // first operand fragments read at the end of iteration s-1, MFMAs at iteration s.  One barrier per slab, and
 // no wave waits on LDS right after it.  The last four iterations of a tile fetch the first four slabs of the
 // block's next tile instead, so those are in registers when the epilogue ends.
-// The 256x256 tile (eight waves of 128x64) halves the bytes fetched from L2 per flop compared with 128x128,
-// which is what bounds the small tile.  Each output element is one fixed-order sum over K: a row's result does
-// not depend on T.
+// Each output element is one fixed-order sum over K: a row's result does not depend on T.
 // Vector-memory loads return in order, so a wait for any load is a wait for every load issued before it.  The
 // kernel is written so that no wait falls behind the prefetched slabs: no register spills (a reload is a load),
 // no load whose result is unused, the bias fetched ahead of the slabs and kept in LDS, per-lane values of the
@@ -35,19 +50,14 @@ __device__ inline float gelu_erf(float v)
     return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * p));  // raw 2^x: overflow gives inf -> 0, underflow 0 -> v
 }
 
-// dynamic LDS of a block: three operand stages and, per wave, the bias of its 64 output columns
-template <int BM, int BN, int WM, int WN>
-constexpr int gemm_smem_bytes()
-{
-    return 3 * (BM + BN) * GEMM_BK * (int)sizeof(bf16_t) + WM * WN * 64 * (int)sizeof(float);
-}
+constexpr int GEMM_SMEM = 3 * (128 + 128) * GEMM_BK * (int)sizeof(bf16_t) + 4 * 64 * (int)sizeof(float);  // three operand stages and, per wave, the bias of its 64 output columns
 
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_kernel(
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_kernel(
     const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, const float *__restrict__ bias,
-    bf16_t *__restrict__ out, const int32_t *__restrict__ T_dev, int N, int K, int tiles_n, int gcols)
+    bf16_t *__restrict__ out, const int32_t *__restrict__ T_dev, int N, int K, int tiles_n, int gcols, int plane)
 {
-    constexpr int BK = GEMM_BK;
+    constexpr int BK = GEMM_BK, BM = 128, BN = 128, WM = 2, WN = 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t *As = reinterpret_cast<bf16_t *>(smem);  // [3][BM][BK]
     bf16_t *Bs = As + 3 * BM * BK;                  // [3][BN][BK]
@@ -76,17 +86,20 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     const int lrow = tid >> 2, lc = tid & 3;
     const int soff = lrow * BK + ((lc ^ ((lrow >> 2) & 3)) << 3);  // rows RPP apart share the swizzle term
 
-    // Operand loads are buffer loads: a descriptor per tile (scalar registers: base of the tile's BM or BN rows, size
-    // of those rows, so a load can never leave the tile), one 32-bit byte offset per thread that A and W share, and a
-    // scalar offset for the chunk and the K-slab.  No 64-bit vector address arithmetic and no per-thread pointers.
-    const int toff = (lrow * K + lc * 8) * (int)sizeof(bf16_t);
+    // Operand loads are buffer loads: a descriptor per tile of W and per slab of A (scalar registers: base and size of what
+    // is the tile's, so a load can never leave it), one 32-bit byte offset per thread, and a scalar offset for the chunk and W's
+    // K-slab.  No 64-bit vector address arithmetic and no per-thread pointers.
+    const int toff = (lrow * K + lc * 8) * (int)sizeof(bf16_t), aoff = tid * 16;
 #define GEMM_RSRC(ptr, rows)                                                                             \
     __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(ptr), 0, (rows) * K * (int)sizeof(bf16_t), 0x00020000)
 #define GEMM_GLOAD(RA, RB, AP, WP, k0)                                                                   \
-    _Pragma("unroll") for (int i = 0; i < ACH; ++i)                                                      \
-        RA[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(AP, toff, ((RPP * i) * K + (k0)) * 2, 0)); \
-    _Pragma("unroll") for (int i = 0; i < BCH; ++i)                                                      \
-        RB[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(WP, toff, ((RPP * i) * K + (k0)) * 2, 0));
+    {                                                                                                    \
+        const auto ar_ = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>((AP) + (size_t)((k0) / BK) * plane), 0, BM * BK * (int)sizeof(bf16_t), 0x00020000); \
+        _Pragma("unroll") for (int i = 0; i < ACH; ++i)                                                  \
+            RA[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar_, aoff, RPP * i * BK * 2, 0)); \
+        _Pragma("unroll") for (int i = 0; i < BCH; ++i)                                                  \
+            RB[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(WP, toff, ((RPP * i) * K + (k0)) * 2, 0)); \
+    }
 #define GEMM_SSTORE(RA, RB, stage)                                                                       \
     _Pragma("unroll") for (int i = 0; i < ACH; ++i)                                                      \
         *reinterpret_cast<u32x4 *>(As + (stage) * BM * BK + RPP * BK * i + soff) = RA[i];                 \
@@ -135,18 +148,11 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     // MFMAs, the next slab's first fragments once the first half's MFMAs no longer need those registers.
 #define SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0);
 #define GEMM_INTERLEAVE                                                                                  \
-    if constexpr (TM * TN == 8 && TM + TN == 6 && ACH + BCH == 4) {                                      \
-        SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x020, 1) SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x200, 1) \
-        SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x020, 1) SGB(0x008, 1) SGB(0x200, 1) SGB(0x008, 1)               \
-        SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x020, 1) SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x200, 1) \
-        SGB(0x008, 1) SGB(0x100, 2) SGB(0x008, 1) SGB(0x020, 1) SGB(0x008, 1) SGB(0x200, 1) SGB(0x008, 1)               \
-    } else {                                                                                             \
-        _Pragma("unroll") for (int i_ = 0; i_ < (TM + TN + 1) / 2; ++i_) { SGB(0x008, 1) SGB(0x100, 2) } \
-        _Pragma("unroll") for (int i_ = 0; i_ < ACH + BCH; ++i_) { SGB(0x008, 1) SGB(0x020, 1) }         \
-        _Pragma("unroll") for (int i_ = 0; i_ < ACH + BCH; ++i_) { SGB(0x008, 1) SGB(0x200, 1) }         \
-        _Pragma("unroll") for (int i_ = 0; i_ < (TM + TN + 1) / 2; ++i_) { SGB(0x008, 1) SGB(0x100, 2) } \
-        SGB(0x008, 2 * TM * TN)                                                                          \
-    }
+    _Pragma("unroll") for (int i_ = 0; i_ < (TM + TN + 1) / 2; ++i_) { SGB(0x008, 1) SGB(0x100, 2) }     \
+    _Pragma("unroll") for (int i_ = 0; i_ < ACH + BCH; ++i_) { SGB(0x008, 1) SGB(0x020, 1) }             \
+    _Pragma("unroll") for (int i_ = 0; i_ < ACH + BCH; ++i_) { SGB(0x008, 1) SGB(0x200, 1) }             \
+    _Pragma("unroll") for (int i_ = 0; i_ < (TM + TN + 1) / 2; ++i_) { SGB(0x008, 1) SGB(0x100, 2) }     \
+    SGB(0x008, 2 * TM * TN)
 
     // tile of this block at a step of its walk (uniform for the block); false when the walk is over.  The logical
     // order goes through the column tiles in groups of gcols: all row blocks for the first group, then for the
@@ -170,17 +176,12 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     GEMM_TILE_AT(0, have, tile_m, tile_n)
     if (!have) return;
     const int KT = K / BK;  // a multiple of 4: the host checks K % (4 * BK) == 0
-    // The large tile is launched for K >= 8 slabs only (the host checks): without the short-K paths the compiler
-    // does not have to merge their pending loads into the waits of the long-K path.
-    if constexpr (BM * BN > 128 * 128) __builtin_assume(KT >= 8);
-    auto ag = GEMM_RSRC(A + (size_t)tile_m * BM * K, BM);
-    // the last column tile may reach past N (a multiple of 64): its missing rows of W read as zeros, its wavefronts without
-    // columns store nothing
-    auto wg = GEMM_RSRC(W + (size_t)tile_n * BN * K, min(BN, N - tile_n * BN));
+    const bf16_t *ag = A + (size_t)tile_m * BM * PLANE;
+    auto wg = GEMM_RSRC(W + (size_t)tile_n * BN * K, BN);
     // The bias of a tile is fetched before the tile's first operand slab and put into LDS at the start of the tile:
     // a load issued in the epilogue would complete only after the next tile's prefetched slabs (loads return in
     // order), and the epilogue would wait for all of them.
-    float bnext = bias[min(tile_n * BN + wn * (BN / WN), N - BN / WN) + lane];
+    float bnext = bias[tile_n * BN + wn * (BN / WN) + lane];
     GEMM_GLOAD(ra0, rb0, ag, wg, 0)
     GEMM_GLOAD(ra1, rb1, ag, wg, BK)
     GEMM_GLOAD(ra2, rb2, ag, wg, 2 * BK)
@@ -190,8 +191,8 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     bool have_next;
     int next_m = tile_m, next_n = tile_n;
     GEMM_TILE_AT(step + 1, have_next, next_m, next_n)
-    const auto ag_next = GEMM_RSRC(A + (size_t)next_m * BM * K, BM);
-    const auto wg_next = GEMM_RSRC(W + (size_t)next_n * BN * K, min(BN, N - next_n * BN));
+    const bf16_t *ag_next = A + (size_t)next_m * BM * PLANE;
+    const auto wg_next = GEMM_RSRC(W + (size_t)next_n * BN * K, BN);
     // Slabs 0..3 of this tile are in the four register sets.  Steady state of the K loop at iteration 0: slabs 0 and
     // 1 in the ring, slabs 2, 3, 4 in sets 1, 2, 3, set 0 free.
     bf16x8 af0[TM], bf0[TN], af1[TM], bf1[TN];
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
         GEMM_ITER(, GEMM_SSTORE(ra0, rb0, st_nn))
     }
     // last four slabs: slabs KT-2 and KT-1 still go into the ring; the loads fetch the next tile
-    bnext = bias[min(next_n * BN + wn * (BN / WN), N - BN / WN) + lane];
+    bnext = bias[next_n * BN + wn * (BN / WN) + lane];
     GEMM_ITER(GEMM_GLOAD(ra0, rb0, ag_next, wg_next, 0), GEMM_SSTORE(ra1, rb1, st_nn))
     GEMM_ITER(GEMM_GLOAD(ra1, rb1, ag_next, wg_next, BK), GEMM_SSTORE(ra2, rb2, st_nn))
     GEMM_ITER(GEMM_GLOAD(ra2, rb2, ag_next, wg_next, 2 * BK), )
@@ -250,10 +251,9 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     // output block: lane l owns output row l%32 and, in registers 4g..4g+3, the four adjacent columns
     // 8g + 4*(l/32) + 0..3.  Each wave passes 32 rows at a time through its own 4 KB of LDS: 8-byte stores of four
     // bf16 (unit u of a row sits at position u ^ swz(row): the 16 lanes served together hit all banks once), then
-    // 16-byte reads, so that the global stores are whole 128-byte row segments per 8 lanes.
+    // 16-byte reads, so that the global stores are eight adjacent rows of two planes.
     __syncthreads();  // every wave is done with the operand stages
     constexpr int WCOLS = BN / WN;
-    static_assert(WCOLS == 64, "the epilogue's staging layout is written for 64 output columns per wave");
     unsigned char *stg = smem + wave * (2 * 32 * 128);  // two slices per wave, used in turn
     const int col0 = tile_n * BN + wn * WCOLS;
     const int row0 = tile_m * BM + wm * (BM / WM);
@@ -263,10 +263,9 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
     asm volatile("" : "+v"(lane_e));
     const int half = lane_e >> 5, l32 = lane_e & 31;
     const int wswz = ((l32 & 7) << 1) | ((l32 >> 3) & 1);
-    // write-out: a wave-wide access covers 8 rows of eight 16-byte chunks.  The output is read by a later kernel
+    // write-out: a wave-wide access covers 8 rows of eight 16-byte chunks, two planes.  The output is read by a later kernel
     // only: streaming stores keep it from displacing the operand slabs in L2 (measured: 3-7% per GEMM).
     const int orow = lane_e >> 3, och = lane_e & 7;
-    if (col0 < N)
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
         unsigned char *sl = stg + (mi & 1) * (32 * 128);  // the other slice than the previous 32 rows: their reads may still be on their way
@@ -289,7 +288,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4) ? 2 : 1) void gemm_ker
             const int lr = j * 8 + orow;
             u32x4 v = *reinterpret_cast<const u32x4 *>(sl + lr * 128 + ((och ^ orow) << 4));
             if (j & 1) v = u32x4{v[2], v[3], v[0], v[1]};  // rows 8..15 and 24..31 hold the halves of a chunk swapped
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + (size_t)(row0 + mi * 32 + lr) * N + col0 + och * 8));
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + plane_at(col0 + och * 8, row0 + mi * 32 + lr, plane)));
         }
     }
     __syncthreads();  // the staging slices are operand stages again for the next tile

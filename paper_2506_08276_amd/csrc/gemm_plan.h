@@ -44,7 +44,8 @@ inline StreamPlan plan_stream(int cus, int tile_rows, int tile_cols, int rows, i
 struct GemmChoice {
     int stream;  // number of the stream tile, -1: gemm_kernel
     int xr;      // the stream kernel's grid, see plan_stream
-    int large;   // gemm_kernel's tile, 128 or 256
+    int large;   // rows of a tile of gemm_kernel (128) or gemm_large_kernel (256)
+    int cols;    // its columns
 };
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
@@ -70,25 +71,37 @@ struct GemmChoice {
 // The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
 // and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
-// gemm_kernel walks over its tiles: what decides is how many the busiest CU gets, c = ceil(tiles / CUs).  128x128 takes about
-// 2.5 + 8 c and 256x256 about 21 c - 2 (K = 768; the ratio is about the same at K = 3072), or, next to the stream kernel,
-// 2.2 + 7.2 c and c (8 + 12.2) - 1 with the second figure by 768 elements of K.  Between the two of them K is left out: the second pair
-// of formulas would take 128x128 for most products of K = 384, where 256x256 is the faster one, as the first pair says (128x128 and
-// 256x256, microseconds per launch between two events: 24064 x 1152 x 384 35.0 and 29.7, 48128 x 384 x 384 31.2 and 29.3, x 1152 64.6 and
-// 52.4, x 1536 91.8 and 81.5, 100096 x 384 x 384 57.6 and 56.3; against it 16128 x 1152 x 384 25.6 and 26.2, 24064 x 1536 x 384 48.4 and 49.0).
+// gemm_kernel (128x128) and gemm_large_kernel (256x256, and 256x192 for what those leave of the chip or of the columns) walk over their tiles:
+// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 1.2 + 6.4 k (and 1 per launch),
+// 4.8 + 16 k, 4.1 + 13.2 k.  Microseconds per launch in a row of launches, all three measured (rows x N x K; "G": with GELU):
+//                        128x128 256x256 256x192 |                       128x128 256x256 256x192
+//   5000 x 2304 x  768      25.1    22.7    22.2 |  8000 x  384 x  384       6.7    12.3    10.4
+//  12000 x 2304 x  768      54.6    48.9    52.6 | 20000 x 1152 x  384      26.5    24.6    22.9
+//  25500 x  768 x  768      38.0    38.6    34.9 | 37000 x  384 x  384      18.9    23.5    20.4
+//  25500 x  768 x 3072     132.6   120.8   101.5 | 37000 x 1152 x  384      45.1    37.2    41.1
+//  37000 x  768 x  768      52.9    42.1    48.1 | 48000 x  384 x 1536      68.5    65.3    54.9
+//  37000 x  768 x 3072     187.6   135.2   151.4 | 65536 x  384 x  384      28.3    27.8    28.1
+//  37000 x 3072 x  768 G   226.8   181.3   204.7 | 65536 x 1536 x  384 G   118.1   112.9   121.9
 //
 // rows: that the product is expected to have; large_tile, small_rows: see leann_set_gemm_tiles (0 also: no packed weights).
 inline GemmChoice choose_gemm(int cus, int large_tile, int small_rows, int rows, int N, int K)
 {
-    auto busiest = [&](int tile) {  // tiles of the busiest CU
-        const int64_t tiles = (int64_t)((rows + tile - 1) / tile) * ((N + tile - 1) / tile);
+    auto busiest = [&](int tile_rows, int tile_cols) {  // tiles of the busiest CU
+        const int64_t tiles = (int64_t)((rows + tile_rows - 1) / tile_rows) * ((N + tile_cols - 1) / tile_cols);
         return (double)((tiles + cus - 1) / cus);
     };
-    const double k = K / 768.0, c128 = busiest(128), c256 = busiest(256);
-    const bool wide = large_tile == 256 && K >= 8 * GEMM_BK && 21.0 * c256 - 2.0 <= 2.5 + 8.0 * c128;
-    GemmChoice best = {-1, 1, wide ? 256 : 128};
+    const double k = K / 768.0;
+    GemmChoice best = {-1, 1, 128, 128};
+    double best_us = 1.0 + busiest(128, 128) * (1.2 + 6.4 * k);
+    if (large_tile == 256 && K >= 8 * GEMM_BK) {
+        const double us256 = busiest(256, 256) * (4.8 + 16.0 * k), us192 = busiest(256, 192) * (4.1 + 13.2 * k), us = std::min(us256, us192);
+        if (us <= best_us) {
+            best_us = us;
+            best.large = 256;
+            best.cols = us192 < us256 ? 192 : 256;
+        }
+    }
     if (small_rows <= 0) return best;
-    double best_us = wide ? c256 * (8.0 + 12.2 * k) - 1.0 : 2.2 + 7.2 * c128 * k;
     int tile = 0;
 #define LEANN_TILE(W, R, NM, US, US_K)                                                                                \
     {                                                                                                                 \

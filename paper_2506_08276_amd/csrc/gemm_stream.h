@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 // tile's work hides a wait.  What counts then is how many bytes a CU has on their way and that nothing on the chain over K waits for LDS:
 //  - W is kept a second time in operand order, so a multiplying wavefront reads its own 32 columns straight into registers, DW
 //    steps of 16 elements ahead, 1 KB per request.  W takes no LDS space, stores or reads, and no barrier.
-//  - A goes through LDS: four wavefronts fetch K-slabs of 128 (a row's slab is two whole lines), three slabs ahead in registers, into
+//  - A goes through LDS: four wavefronts fetch K-slabs of 128 (whole lines: rows are adjacent in their planes), three slabs ahead in registers, into
 //    a ring of three stages (with six ahead, the first one waits longer: 0.1 to 0.4 us per launch up to 64 x 128).  A multiplying
 //    wavefront has 32 R rows by 32 columns of the tile and reads A up to AHEAD steps ahead, across slabs: the slab after the current
 //    one is always there already.  One barrier per slab, at which only the fetching wavefronts wait for their LDS stores.  A slab
@@ -41,15 +41,30 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 //  2000 x 3072 x  768   19.0   13.4
 constexpr int STREAM_BK = 128;
 
-// The four wavefronts that fetch A (thread ft of them) for a tile of 16 RB rows from row m0 on, see gemm_stream_kernel.
+// A launch's N, K (multiples of 128) and grid in one word: 14 words of arguments come in registers with the dispatch, and one more, read
+// from memory, would be the first link of the chain.  A's offsets have 31 bits.
+inline bool stream_covers(int N, int K, int plane) { return N < 128 << 15 && K < 128 << 15 && (int64_t)K / PLANE * plane < (int64_t)1 << 29; }
+inline uint32_t stream_shape(int N, int K, int xr) { return (uint32_t)(N / 128) | (uint32_t)(K / 128) << 15 | (uint32_t)__builtin_ctz(xr) << 30; }
+__device__ inline int stream_n(uint32_t shape) { return (shape & 0x7fff) * 128; }
+__device__ inline int stream_k(uint32_t shape)
+{
+    int K = (shape >> 15 & 0x7fff) * 128;
+    asm("" : "+s"(K));  // any number: of one that it knows the bounds of, the compiler splits the loop over K, whose waits then count fewer requests (5.9 us instead of 5.0 at K = 3072)
+    return K;
+}
+
+// The four wavefronts that fetch A (thread ft of them) for a tile of 16 RB rows from row m0 on, see gemm_stream_kernel.  A slab is four planes'
+// 64 bytes of every row; a request is of four rows in each.
 template <int RB, int TURN>
-__device__ inline void fetch_a(const bf16_t *A, const int32_t *T_dev, unsigned char *smem, int ft, int m0, int K, int slabs, int turns_end)
+__device__ inline void fetch_a(const bf16_t *A, const int32_t *T_dev, unsigned char *smem, int ft, int m0, int K, int plane, int slabs, int turns_end)
 {
     constexpr int ROWS = 16 * RB, STAGE = ROWS * STREAM_BK * (int)sizeof(bf16_t);
     constexpr int LPT = RB;  // 16-byte loads per thread and slab
-    const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * K), 0, ROWS * K * (int)sizeof(bf16_t), 0x00020000);
     const int lrow = ft >> 4, lch = ft & 15;
-    const int toff = (lrow * K + lch * 8) * (int)sizeof(bf16_t);
+    const int plane_bytes = plane * (int)sizeof(bf16_t), toff = (lch >> 2) * plane_bytes + lrow * 64 + (lch & 3) * 16;
+    const int slab_bytes = 4 * plane_bytes;
+    const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A + (size_t)m0 * PLANE), 0,
+                                                      (K / PLANE - 1) * plane_bytes + ROWS * 64, 0x00020000);
     const int soff = lrow * 256 + ((lch ^ lrow) << 4);  // rows 16 apart share the swizzle term
     u32x4 rg[TURN][LPT];
     // Every step issues its loads: a slab past the end gets an offset beyond the buffer (nothing is fetched, zeros
@@ -57,9 +72,9 @@ __device__ inline void fetch_a(const bf16_t *A, const int32_t *T_dev, unsigned c
     // not have been issued, the compiler would have to wait for all of them.
 #define STREAM_ALOAD(p, slab)                                                                            \
     {                                                                                                    \
-        const int o_ = (slab) < slabs ? toff + (slab) * (STREAM_BK * 2) : 0x7ff00000;                    \
+        const int o_ = (slab) < slabs ? toff + (slab) * slab_bytes : 0x7ff00000;                         \
         _Pragma("unroll") for (int i = 0; i < LPT; ++i)                                                  \
-            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * K * 2, 0)); \
+            rg[p][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ar, o_, i * 16 * 64, 0)); \
     }
 #pragma unroll
     for (int p = 0; p < TURN; ++p) {
@@ -98,10 +113,11 @@ template <int R, int NM, int EPI>
 __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Wp,
                                                                     const float *__restrict__ bias, bf16_t *__restrict__ out,
                                                                     const int32_t *__restrict__ T_dev, int max_rows, int likely_rows,
-                                                                    int N, int K, int xr_bits)
+                                                                    uint32_t shape)
 {
     typedef StreamCfg<R, NM> Cfg;
     constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD;
+    const int N = stream_n(shape), K = stream_k(shape), xr_bits = shape >> 30, plane = pass_pitch(max_rows) * PLANE;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,7 +134,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
     // A tile that turns out to hold no row goes through one turn and stores nothing.
 
     if (wave >= NM) {
-        fetch_a<2 * R, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, slabs, turns_end);
+        fetch_a<2 * R, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, plane, slabs, turns_end);
         return;
     }
 
@@ -189,6 +205,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
     if (!on || m0 >= T) return;
     // 32 x 32 outputs at a time through the wavefront's own 2 KB: 16-byte chunk c of a row at c ^ ((row >> 1) & 3), then 16-byte stores
     unsigned char *stg = smem + TURN * Cfg::STAGE + wave * 2048;
+    bf16_t *to = out + plane_at(ct * 32, m0, plane);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
@@ -203,7 +220,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream_kernel(const bf16_t
         for (int j = 0; j < 2; ++j) {
             const int rr = j * 16 + (lane >> 2), ch = lane & 3;
             const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + rr * 64 + ((ch ^ ((rr >> 1) & 3)) << 4));
-            *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + r * 32 + rr) * N + ct * 32 + ch * 8) = v;
+            *reinterpret_cast<u32x4 *>(to + (r * 32 + rr) * PLANE + ch * 8) = v;
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -233,10 +250,11 @@ template <int RB, int NM, int EPI>
 __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Wp,
                                                                       const float *__restrict__ bias, bf16_t *__restrict__ out,
                                                                       const int32_t *__restrict__ T_dev, int max_rows, int likely_rows,
-                                                                      int N, int K, int xr_bits)
+                                                                      uint32_t shape)
 {
     typedef Stream16Cfg<RB, NM> Cfg;
     constexpr int DW = Cfg::DW, TURN = Cfg::TURN, AHEAD = Cfg::AHEAD, SLOTS = Cfg::SLOTS;
+    const int N = stream_n(shape), K = stream_k(shape), xr_bits = shape >> 30, plane = pass_pitch(max_rows) * PLANE;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [TURN][ROWS][128] bf16, staging
     const int tid = threadIdx.x, lane = tid & 63, quarter = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -249,7 +267,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
     const int turns_end = (slabs + TURN - 1) / TURN * TURN;
 
     if (wave >= NM) {
-        fetch_a<RB, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, slabs, turns_end);
+        fetch_a<RB, TURN>(A, T_dev, smem, tid - 64 * NM, m0, K, plane, slabs, turns_end);
         return;
     }
 
@@ -313,6 +331,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
     if (!on || m0 >= T) return;
     // 16 RB x 16 outputs through the wavefront's own LDS, a row's 32 bytes together, 8-byte unit u at u ^ 2 in every other eight rows; then 16-byte stores
     unsigned char *stg = smem + TURN * Cfg::STAGE + wave * (RB * 512);
+    bf16_t *to = out + plane_at(ct * 16, m0, plane);
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         bf16x4 o4;
@@ -325,7 +344,7 @@ __global__ __launch_bounds__(64 * (NM + 4)) void gemm_stream16_kernel(const bf16
     for (int i = 0; i < RB / 2; ++i) {
         const int row = i * 32 + (lane >> 1), ch = lane & 1;
         const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + row * 32 + ((ch ^ ((row >> 3) & 1)) << 4));
-        *reinterpret_cast<u32x4 *>(out + (size_t)(m0 + row) * N + ct * 16 + ch * 8) = v;
+        *reinterpret_cast<u32x4 *>(to + row * PLANE + ch * 8) = v;
     }
 }
 
