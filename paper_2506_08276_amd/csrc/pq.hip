@@ -16,6 +16,64 @@ constexpr int KSUB = 256;
 constexpr int MAX_TRAIN = 65536;
 constexpr int MAX_DSUB = 32;
 
+__host__ __device__ inline uint64_t splitmix64(uint64_t &st)
+{
+    uint64_t z = (st += 0x9e3779b97f4a7c15ull);
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    return z ^ (z >> 31);
+}
+
+// The seeded Fisher-Yates permutation's first nt entries on the device.  Step i = n - 1 .. 1 swaps the entries i and j(i) <= i.  After it, entry i is
+// final: what was at j(i).  Who put that there is known without running the steps: the last step before it (the smallest t > i) with
+// j(t) = j(i), which brought there what was at its own position t; so
+//   at(p) = what is at position p just before step p = at(t) for the smallest t > p with j(t) = p, or p if there is none,
+//   final entry i = at(t) for the smallest t > i with j(t) = j(i), or j(i) if there is none; entry 0: at(0).
+// The draws do not depend on each other, nor do the chains (a logarithm of n long): n = 100000 took the host 450 us and a copy of the
+// rows behind it, the three kernels take 23 us (a whole call of 6 iterations at d = 768: 2290 and 2050 us).
+constexpr uint32_t NO_STEP = 0xffffffffu;
+
+struct Steps {
+    uint32_t *j;     // [n] a step's draw
+    uint32_t *first; // [n] of position p: the smallest step t > p with j(t) = p
+    uint32_t *head, *link;  // [n] the steps with j(t) = p, in any order: head[p], then link[]
+};
+
+__global__ __launch_bounds__(256) void clear_steps_kernel(Steps s, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) s.first[i] = s.head[i] = NO_STEP;
+}
+
+__global__ __launch_bounds__(256) void draw_steps_kernel(Steps s, int64_t n, uint64_t seed)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < 1 || i >= n) return;
+    uint64_t state = seed + (uint64_t)(n - 1 - i) * 0x9e3779b97f4a7c15ull;  // of the generator before draw n - 1 - i
+    const uint32_t j = (uint32_t)(splitmix64(state) % (uint64_t)(i + 1));
+    s.j[i] = j;
+    s.link[i] = atomicExch(&s.head[j], (uint32_t)i);
+    if (j < i) atomicMin(&s.first[j], (uint32_t)i);
+}
+
+__global__ __launch_bounds__(256) void training_rows_kernel(Steps s, int64_t nt, int64_t *__restrict__ rows)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= nt) return;
+    uint32_t p = 0, t = s.first[0];
+    if (i > 0) {
+        p = s.j[i];
+        t = NO_STEP;
+        for (uint32_t u = s.head[p]; u != NO_STEP; u = s.link[u])
+            if (u > (uint32_t)i && u < t) t = u;
+    }
+    while (t != NO_STEP) {
+        p = t;
+        t = s.first[p];
+    }
+    rows[i] = p;
+}
+
 // The training rows: rows[i] of x (fp32 [n][d]) -> xt[m][i][d / m_sub], a plane per subspace, so that kernels that work on one
 // subspace read nothing else: pieces of 96 bytes straddle 128-byte lines, and in rows the line's rest belongs to other subspaces.  A block
 // takes GATHER_ROWS rows: that many pieces of a plane lie together.  65536 x 768 from 100000: 73 us, copied row by row 98; a call's
@@ -669,15 +727,7 @@ void adc_launch_shape(int64_t nq, int nc, int *parts, int *per_block)
     *parts = (rounds + rounds_per_block - 1) / rounds_per_block;
 }
 
-uint64_t splitmix64(uint64_t &st)
-{
-    uint64_t z = (st += 0x9e3779b97f4a7c15ull);
-    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-    return z ^ (z >> 31);
-}
-
-// Seeded Fisher-Yates permutation of 0 .. n - 1: its first nt entries.  Index: as narrow as n allows (the swaps are random reads
+// The same permutation on the host.  Index: as narrow as n allows (the swaps are random reads
 // and writes of the whole permutation).
 template <class Index>
 std::vector<int64_t> training_rows(int64_t n, int64_t nt, uint64_t seed)
@@ -785,10 +835,10 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     LEANN_HIP(hipSetDevice(ctx->device));
     const int dsub = d / m_sub;
     const int64_t nt = n < MAX_TRAIN ? n : MAX_TRAIN;
-    const std::vector<int64_t> train = n <= 0xffffffffll ? training_rows<uint32_t>(n, nt, seed) : training_rows<int64_t>(n, nt, seed);
     leann_pq *pq = nullptr;
     LEANN_TRY(alloc_pq(ctx, n, d, m_sub, true, &pq));
-    // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts | counts
+    // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts | counts; before that, from the
+    // copies on, the permutation's steps
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
@@ -799,6 +849,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     const size_t o_assign = carve((size_t)nt * m_sub), o_order = carve((size_t)nt * m_sub * sizeof(int32_t));
     const size_t o_first = carve((size_t)m_sub * (KSUB + 1) * sizeof(int32_t));
     const size_t o_counts = carve((size_t)m_sub * GROUP_RUNS * KSUB * sizeof(int32_t));
+    const size_t step_bytes = ((size_t)n * sizeof(uint32_t) + 255) & ~(size_t)255, with_steps = std::max(off, o_xt + 4 * step_bytes);
     auto fail = [&](int code) {
         leann_pq_free(pq);
         return code;
@@ -811,15 +862,28 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
             if (work.bytes > PQ_WORK_KEEP) work.release();
         }
     } give_back{ctx->pq_work};
-    if (ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
+    // The steps take 16 bytes per row, beside rows of at least 4: on the host where there are more of them than fit into what the context
+    // keeps, or where the device has no room.
+    const bool on_device = with_steps <= std::max(off, PQ_WORK_KEEP) && ctx->pq_work.reserve(with_steps) == LEANN_OK;
+    if (!on_device && ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
     unsigned char *scr = (unsigned char *)ctx->pq_work.p;
     int64_t *rows_dev = (int64_t *)(scr + o_rows);
     float *xt = (float *)(scr + o_xt);
     uint8_t *assign = scr + o_assign;
     int32_t *order = (int32_t *)(scr + o_order), *first = (int32_t *)(scr + o_first), *counts = (int32_t *)(scr + o_counts);
-    if (hipMemcpyAsync(rows_dev, train.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) !=
-        hipSuccess)
-        return fail(LEANN_EDEVICE);
+    std::vector<int64_t> train;  // read by the copy until the stream has been waited for
+    if (on_device) {
+        auto steps = [&](int k) { return (uint32_t *)(scr + o_xt + k * step_bytes); };
+        const Steps st = {steps(0), steps(1), steps(2), steps(3)};
+        const dim3 all((unsigned)((n + 255) / 256)), some((unsigned)((nt + 255) / 256));
+        hipLaunchKernelGGL(clear_steps_kernel, all, dim3(256), 0, ctx->stream, st, n);
+        hipLaunchKernelGGL(draw_steps_kernel, all, dim3(256), 0, ctx->stream, st, n, seed);
+        hipLaunchKernelGGL(training_rows_kernel, some, dim3(256), 0, ctx->stream, st, nt, rows_dev);
+    } else {
+        train = n <= 0xffffffffll ? training_rows<uint32_t>(n, nt, seed) : training_rows<int64_t>(n, nt, seed);
+        if (hipMemcpyAsync(rows_dev, train.data(), (size_t)nt * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
+            return fail(LEANN_EDEVICE);
+    }
     const bool by_four = (dsub & 3) == 0 && (reinterpret_cast<uintptr_t>(emb_dev) & 15) == 0;
     hipLaunchKernelGGL(by_four ? gather_rows_kernel<f32x4> : gather_rows_kernel<float>, dim3((unsigned)((nt + GATHER_ROWS - 1) / GATHER_ROWS)),
                        dim3(256), 0, ctx->stream, emb_dev, rows_dev, nt, d, dsub, xt);
