@@ -32,8 +32,8 @@ def codebook(L, ctx, x, iters, seed):
         L.leann_pq_free(pq)
 
 
-@pytest.mark.parametrize("n,seed", [(1, 0), (2, 1), (3, 1234567), (255, 9), (256, 2 ** 64 - 1), (257, 5), (1000, 42), (65535, 3), (65536, 7), (65537, 8),
-                                    (300001, 2 ** 63 + 11)])
+@pytest.mark.parametrize("n,seed", [(1, 0), (2, 1), (3, 1234567), (255, 9), (256, 2 ** 64 - 1), (257, 5), (1000, 42), (4096, 12), (4097, 13), (5001, 14),
+                                    (65535, 3), (65536, 7), (65537, 8), (300001, 2 ** 63 + 11)])
 def test_first_training_rows(L, orc, ctx, n, seed):
     """Without an iteration the codebook is the first 256 training rows, exactly."""
     say(f"training rows, n={n} seed={seed}")
