@@ -112,8 +112,9 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //  - x and c are centred on a common point u (differences to u instead of to the origin: what is left to round scales
 //    with the spread of the data), split into two bf16 each, and |c'|^2 - 2 x'.c' is accumulated in fp32 by three MFMAs
 //    per 16 elements (hi.hi, hi.lo, lo.hi), 32 centroids by 32 rows at a time; a lane owns a row and half the centroids.
-//  - the running minimum and second minimum are kept as floats with 7 bits of index in the low mantissa bits: one bit
-//    operation, one median and one minimum per value.
+//  - the running minimum and second minimum are kept as floats with 7 bits of index in the low mantissa bits.  Of the minimum and two
+//    values the smallest is the new minimum and the median the one that may be the new second: nine instructions for four values, a bit operation for
+//    each, two medians and three minima of three (138 us; one value after the other, twelve instructions, 144: 65536 rows, d = 768, 32 subspaces).
 //  - With X = |x'|, C = max |c'|, U = (X + C)^2 and bf16's rounding of 2^-8, a centroid's value is off by, in units of
 //    2^-16 U: the split 1 (each low part rounded by 2^-17 of its operand and low.low left out: 4 * 2^-17 of |2x'||c'| <= U / 2),
 //    the additions of the six MFMAs at most 0.75 (each of the 96 counted with 2^-23 U, a whole unit), |c'|^2 0.13, s(c) itself
@@ -254,16 +255,26 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *
             fetch(min(t + 1, KSUB / 32 - 1));
             asm volatile("" ::: "memory");  // here, not where they are used
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {  // register r: centroid 32t + 8(r/4) + 4 half + r%4
-                // The index in a scalar register, and the minimum by its instruction: three instructions per value.  Otherwise the
-                // compiler adds the index in two and quiets both operands of the minimum.
-                uint32_t index = t * 16 + r;
-                asm("" : "+s"(index));
+            for (int r = 0; r < 16; r += 4) {  // register r: centroid 32t + 8(r/4) + 4 half + r%4
+                // The index in a scalar register, and the minima by their instructions: otherwise the compiler adds the index in two and
+                // quiets the operands.
+                uint32_t index[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    index[i] = t * 16 + r + i;
+                    asm("" : "+s"(index[i]));
+                }
 #pragma unroll
                 for (int g = 0; g < 2; ++g) {
-                    const float v = __uint_as_float((__float_as_uint(acc[g][r]) & keep) | index);
-                    m2[g] = __builtin_amdgcn_fmed3f(m1[g], m2[g], v);
-                    asm("v_min_f32 %0, %1, %2" : "=v"(m1[g]) : "v"(m1[g]), "v"(v));
+                    float v[4], second[2];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = __uint_as_float((__float_as_uint(acc[g][r + i]) & keep) | index[i]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        second[i] = __builtin_amdgcn_fmed3f(m1[g], v[2 * i], v[2 * i + 1]);
+                        asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m1[g]) : "v"(m1[g]), "v"(v[2 * i]), "v"(v[2 * i + 1]));
+                    }
+                    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m2[g]) : "v"(m2[g]), "v"(second[0]), "v"(second[1]));
                 }
             }
         }
