@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void training_rows_kernel(Steps s, int64_t nt,
 // The training rows: rows[i] of x (fp32 [n][d]) -> xt[m][i][d / m_sub], a plane per subspace, so that kernels that work on one
 // subspace read nothing else: pieces of 96 bytes straddle 128-byte lines, and in rows the line's rest belongs to other subspaces.  A block
 // takes GATHER_ROWS rows: that many pieces of a plane lie together.  65536 x 768 from 100000: 73 us, copied row by row 98; a call's
-// assignments of such rows (and the last one, of rows as they are) 148 us on average, 151 with training rows as they are.
+// assignments of such rows (and the last one, of rows as they are) took 148 us on average, 151 with training rows as they are (135 now).
 constexpr int GATHER_ROWS = 16;
 
 template <class Piece>  // f32x4 where every sub-vector consists of such and begins at one
@@ -114,7 +114,7 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    per 16 elements (hi.hi, hi.lo, lo.hi), 32 centroids by 32 rows at a time; a lane owns a row and half the centroids.
 //  - the running minimum and second minimum are kept as floats with 7 bits of index in the low mantissa bits.  Of the minimum and two
 //    values the smallest is the new minimum and the median the one that may be the new second: nine instructions for four values, a bit operation for
-//    each, two medians and three minima of three (138 us; one value after the other, twelve instructions, 144: 65536 rows, d = 768, 32 subspaces).
+//    each, two medians and three minima of three (132 us; one value after the other, twelve instructions, 138: 65536 rows, d = 768, 32 subspaces).
 //  - With X = |x'|, C = max |c'|, U = (X + C)^2 and bf16's rounding of 2^-8, a centroid's value is off by, in units of
 //    2^-16 U: the split 1 (each low part rounded by 2^-17 of its operand and low.low left out: 4 * 2^-17 of |2x'||c'| <= U / 2),
 //    the additions of the six MFMAs at most 0.75 (each of the 96 counted with 2^-23 U, a whole unit), |c'|^2 0.13, s(c) itself
@@ -122,8 +122,11 @@ __global__ void first_centroids_kernel(const float *__restrict__ xt, int64_t nt,
 //    itself; p - 2^-16 |p| grows with p, so the second minimum's share covers all other centroids.  A gap of more than
 //    2^-16 (5.5 U + |minimum| + |second|) therefore leaves no doubt.  The other rows (few on embeddings; all of them where anything
 //    could overflow or is not a number, or where the nearest centroids are equal) get s(c) for all centroids by one wavefront.
-// So the result is s(c)'s for every input.  148 us on average at 65536 to 100000 rows, d = 768, 32 subspaces (some 185 with five
-// instructions per value and twice as many blocks).
+//    Such a row is read once, an element per lane, and eight elements' centroids are read together (an element after the other, each waited for: 132 us
+//    where it takes 124).
+// So the result is s(c)'s for every input.  65536 rows, d = 768, 32 subspaces: 124 us, of them 15 before the first row, 32 for the rows' way in and
+// their splitting, 10 for each of the eight tiles (5 of matrix instructions, 4 of the nine above) and some 8 for the rows in doubt.  No faster: the next
+// rows' lines asked for while the tiles run (131), a wavefront's priority raised for its matrix instructions or lowered (124).
 constexpr int ASSIGN_THREADS = 512;
 
 __host__ __device__ constexpr int assign_smem(int ks, int dsub)
@@ -299,8 +302,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS, 4) void assign_kernel(const float *
                 doubt &= doubt - 1;
                 const float *xr = x + (r0 + g * 32 + who) * x_row + m * x_sub;
                 float s[4] = {0.f, 0.f, 0.f, 0.f};
+                const int own = __float_as_int(xr[min(lane, dsub - 1)]);
+#pragma unroll 8
                 for (int j = 0; j < dsub; ++j) {
-                    const float xv = xr[j];
+                    const float xv = __int_as_float(__builtin_amdgcn_readlane(own, j));
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const float t = xv - cbf[(k * 64 + lane) * P + j];
@@ -708,8 +713,8 @@ __global__ __launch_bounds__(256) void adc_kernel(const float *__restrict__ lut,
 // Two blocks per CU, as many as stay there at once (four, one round after the other, pay the set-up twice: 173 us, not 162), each with a
 // multiple of what its wavefronts take at once.  A multiple of 8 runs of rows is aimed at
 // where there are rows enough, so that the XCDs get even shares (rounded down: up, 24 subspaces were 6 % slower); with fewer than
-// 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1100 us per launch,
-// 1000 rows of 192 subspaces of one 43; with the kernel of five instructions per value 1431 and 49, and 5358 and 129 where all
+// 8 runs the subspaces are spread over the XCDs instead.  65536 rows of 384 subspaces of 2 elements take 1004 us per launch,
+// 1000 rows of 192 subspaces of one 43; with a kernel of five instructions per value 1431 and 49, and 5358 and 129 where all
 // subspaces of a run were on one XCD however few the runs (two in both cases).
 void launch_assign(leann_ctx *ctx, const float *x, int64_t x_row, int64_t x_sub, int64_t n, int dsub, int m_sub, const float *codebook, uint8_t *out,
                    int64_t row_pitch, int64_t m_pitch)
