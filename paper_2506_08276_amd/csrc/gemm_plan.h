@@ -50,7 +50,7 @@ struct GemmChoice {
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
 // Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
-// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
+// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's, whose 256x256 tile gemm_large_kernel has replaced since):
 //                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
 //    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |   8.6
 //    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |  26.1
@@ -72,8 +72,10 @@ struct GemmChoice {
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
 // and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
 // gemm_kernel (128x128) and gemm_large_kernel (256x256, and 256x192 for what those leave of the chip or of the columns) walk over their tiles:
-// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 1.2 + 6.4 k (and 1 per launch),
-// 4.8 + 16 k, 4.1 + 13.2 k.  Microseconds per launch in a row of launches, all three measured (rows x N x K; "G": with GELU):
+// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 2 + 9.2 k (and 1 per launch),
+// 4.8 + 16 k, 4.1 + 13.2 k.  The first is what a 128x128 tile takes behind the kernels of a pass (19000 x 384 x 1536 42 us, 38000 x 384 x 384 26); in a row of
+// launches, A always the same, it is 1.2 + 6.4 k, while the others take the same in both.  Passes of the encoder of 384 columns, chosen by either:
+// 9500 tokens 1071 and 1005 us, 19000 1776 and 1620, 38000 3327 and 3063, 6900 792 and 811.  Microseconds per launch in a row of launches, all three measured (rows x N x K; "G": with GELU):
 //                        128x128 256x256 256x192 |                       128x128 256x256 256x192
 //   5000 x 2304 x  768      25.1    22.7    22.2 |  8000 x  384 x  384       6.7    12.3    10.4
 //  12000 x 2304 x  768      54.6    48.9    52.6 | 20000 x 1152 x  384      26.5    24.6    22.9
@@ -92,7 +94,7 @@ inline GemmChoice choose_gemm(int cus, int large_tile, int small_rows, int rows,
     };
     const double k = K / 768.0;
     GemmChoice best = {-1, 1, 128, 128};
-    double best_us = 1.0 + busiest(128, 128) * (1.2 + 6.4 * k);
+    double best_us = 1.0 + busiest(128, 128) * (2.0 + 9.2 * k);
     if (large_tile == 256 && K >= 8 * GEMM_BK) {
         const double us256 = busiest(256, 256) * (4.8 + 16.0 * k), us192 = busiest(256, 192) * (4.1 + 13.2 * k), us = std::min(us256, us192);
         if (us <= best_us) {
