@@ -72,7 +72,7 @@ struct GemmChoice {
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
 // and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
 // gemm_kernel (128x128) and gemm_large_kernel (256x256, and 256x192 for what those leave of the chip or of the columns) walk over their tiles:
-// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 2 + 9.2 k (and 1 per launch),
+// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 0.4 + 9.02 k (and 1 per launch),
 // 4.8 + 16 k, 4.1 + 13.2 k.  The first is what a 128x128 tile takes behind the kernels of a pass (19000 x 384 x 1536 42 us, 38000 x 384 x 384 26); in a row of
 // launches, A always the same, it is 1.2 + 6.4 k, while the others take the same in both.  Passes of the encoder of 384 columns, chosen by either:
 // 9500 tokens 1071 and 1005 us, 19000 1776 and 1620, 38000 3327 and 3063, 6900 792 and 811.  Microseconds per launch in a row of launches, all three measured (rows x N x K; "G": with GELU):
@@ -94,7 +94,7 @@ inline GemmChoice choose_gemm(int cus, int large_tile, int small_rows, int rows,
     };
     const double k = K / 768.0;
     GemmChoice best = {-1, 1, 128, 128};
-    double best_us = 1.0 + busiest(128, 128) * (2.0 + 9.2 * k);
+    double best_us = 1.0 + busiest(128, 128) * (0.4 + 9.02 * k);
     if (large_tile == 256 && K >= 8 * GEMM_BK) {
         const double us256 = busiest(256, 256) * (4.8 + 16.0 * k), us192 = busiest(256, 192) * (4.1 + 13.2 * k), us = std::min(us256, us192);
         if (us <= best_us) {
