@@ -2,6 +2,7 @@
 #pragma once
 #include "common.h"
 #include "gemm.h"
+#include "gemm_requests.h"
 
 namespace {
 
@@ -103,22 +104,20 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
     // Requests.  A: two of 16 rows per wavefront, the lanes' 16-byte chunks permuted so that chunk c of row r lands at c ^ ((r >> 2) & 3): 16 rows'
     // reads of one chunk reach all banks.  W: two for every 32 columns, 16 elements of K each, operand order in LDS too; from rows, 16
     // columns each, as A's.  The last column tile may reach past N: zeros.
-    const int chunk = ((lane & 3) ^ ((lane >> 4) & 3)) << 4, a_off = (lane >> 2) * 64 + chunk;
-    const int w_off = w_packed ? lane * 16 : (lane >> 2) * K * 2 + chunk, w_part = w_packed ? 1024 : 32 * K, w_slab = w_packed ? 2048 : 64;
+    const int a_off = weight_offset(lane, 0, BK, 0);  // a plane's rows are 32 elements long
     const int w_ct = BN == 256 || !second ? wave : 4 + ((wave - 4) >> 1), w_i = BN == 256 || !second ? 0 : wave & 1;  // 192 columns: the second group has one request
+    const int w_off[2] = {weight_offset(lane, w_i, K, w_packed), weight_offset(lane, 1, K, w_packed)};
     auto a_tile = [&](int tm) { return A + (size_t)tm * BM * PLANE; };
-    auto w_tile = [&](int tn) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(W + (size_t)tn * BN * K), 0, min(BN, N - tn * BN) * K * 2, 0x00020000);
-    };
-    auto request = [&](const bf16_t *a, __amdgpu_buffer_rsrc_t w, int slab, int stage) {
+    auto request = [&](const bf16_t *a, int tn, int slab, int stage) {
         const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a + (size_t)slab * plane), 0, BM * BK * 2, 0x00020000);
+        const WeightSlab ws = weight_slab(tn * BN + w_ct * 32, slab, N, K, w_packed);
+        const auto wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(W + ws.first), 0, ws.bytes, 0x00020000);
         unsigned char *to = smem + stage * Cfg::STAGE;
-        const int ws = w_ct * 64 * K + slab * w_slab + w_i * w_part;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_t *)(to + wave * 2048 + i * 1024), 16, a_off, wave * 2048 + i * 1024, 0, 0);
             if (i == 0 || BN == 256 || !second)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(w, (lds_t *)(to + Cfg::A_BYTES + w_ct * 2048 + (w_i + i) * 1024), 16, w_off, ws + i * w_part, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_t *)(to + Cfg::A_BYTES + w_ct * 2048 + (w_i + i) * 1024), 16, w_off[i], 0, 0, 0);
         }
     };
     unsigned char *own = smem + 4 * Cfg::STAGE + wave * 2048;
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
     auto request_bias = [&](int tn) {
 #pragma unroll
         for (int i = 0; i < TN * 32; i += 64)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(bias_rsrc, (lds_t *)(own + i * 4), 4, lane * 4, (tn * BN + wn * TN * 32 + i) * 4, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(bias_rsrc, (lds_t *)(own + i * 4), 4, (tn * BN + wn * TN * 32 + i + lane) * 4, 0, 0, 0);
     };
 
     int foff[2], wfoff[2];
@@ -192,11 +191,10 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
     };
 
     const bf16_t *a = a_tile(tile_m);
-    auto w = w_tile(tile_n);
     request_bias(tile_n);
-    request(a, w, 0, 0);
-    request(a, w, 1, 1);
-    request(a, w, 2, 2);
+    request(a, tile_n, 0, 0);
+    request(a, tile_n, 1, 1);
+    request(a, tile_n, 2, 2);
     wait_memory_and_lds<2 * Cfg::LOADS>();
     barrier();
     if (second) barrier();  // a phase behind
@@ -205,7 +203,6 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
         int next_m = tile_m, next_n = tile_n;
         const bool have_next = tile_at(step + 1, next_m, next_n);
         const bf16_t *a_next = a_tile(next_m);
-        const auto w_next = w_tile(next_n);
         {  // slab 0: the sums start at the bias
             f32x16 start[TN];
 #pragma unroll
@@ -217,7 +214,7 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
                     for (int i = 0; i < 4; ++i) start[ni][4 * g + i] = b[i];
                 }
             read(0);
-            request(a, w, 3, 3);
+            request(a, tile_n, 3, 3);
             write_out(0);
             wait_memory_and_lds<Cfg::in_flight(0)>();
             barrier();
@@ -231,17 +228,17 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
             barrier();
         }
         read(1);
-        request(a, w, 4, 0);
+        request(a, tile_n, 4, 0);
         write_out(1);
         wait_memory_and_lds<Cfg::in_flight(1)>();
         compute_phase();
         read(2);
-        request(a, w, 5, 1);
+        request(a, tile_n, 5, 1);
         if constexpr (TM > 2) write_out(2);
         wait_memory_and_lds<Cfg::in_flight(2)>();
         compute_phase();
         read(3);
-        request(a, w, 6, 2);
+        request(a, tile_n, 6, 2);
         if constexpr (TM > 2) write_out(3);
         wait_memory_and_lds<Cfg::in_flight(3)>();
         compute_phase();
@@ -249,7 +246,7 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 read(u);
-                request(a, w, s + u + 3, (u + 3) & 3);
+                request(a, tile_n, s + u + 3, (u + 3) & 3);
                 wait_memory_and_lds<2 * Cfg::LOADS>();
                 compute_phase();
             }
@@ -258,8 +255,8 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             read(u);
-            if (u == 0) request(a, w, KT - 1, 3);
-            else request(a_next, w_next, u - 1, u - 1);
+            if (u == 0) request(a, tile_n, KT - 1, 3);
+            else request(a_next, next_n, u - 1, u - 1);
             wait_memory_and_lds<2 * Cfg::LOADS>();
             compute_phase();
         }
@@ -280,7 +277,6 @@ __global__ __launch_bounds__(512, 1) void gemm_large_kernel(const bf16_t *__rest
         tile_m = next_m;
         tile_n = next_n;
         a = a_next;
-        w = w_next;
     }
     if (!second) barrier();
 #pragma unroll
