@@ -167,8 +167,8 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t *__restrict
 // the registers: mean, then the biased variance of the centred values.
 // A row's sum is defined on its 16-byte pieces p (8 elements, at most 128): 64 sums of the elements of the pieces l and l + 64 in order, then pairwise over
 // l ^ 32, 16, 8, 4, 2, 1.
-//  - Small passes (EARLY), which are nothing but this chain of latencies: a wave takes one row, lane l the pieces l and l + 64.  The first row is
-//    requested before the token count is there (the buffers reach past the last block's rows); with many rows per wavefront that
+//  - Small passes (EARLY, see ln_few_rows), which are nothing but this chain of latencies: a wave takes one row, lane l the pieces l and l + 64.  The
+//    first row is requested before the token count is there (the buffers reach past the last block's rows); with many rows per wavefront that
 //    order costs 3 % of the bandwidth.
 //  - Large ones: a wave takes a pair of rows, 2p and 2p + 1, whose pieces of a plane are one 128-byte line, eight lanes of 16 bytes; lane bit 2
 //    tells the row, and the lane's other bits, q, that it has the pieces q, q + 32, q + 64 and q + 96: the sums l = q and q + 32.  An odd
@@ -278,6 +278,14 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t *__restrict__ delt
             }
     }
 }
+
+// Whether a pass has its rows one per wave.  Twice as many waves with half as long a chain, until the chip has more rows than it hides; rows of up to 256
+// elements leave half of a wave idle that has one alone.  Whole passes of twelve layers, one row and a pair per wave, microseconds
+// (tokens: 2000, 3600, 5000, 6600, 8200):
+//     128 columns   +2    +5    +7    +6   +15  of 400 to 600         512 columns   -7    -9    -8    -2   +15  of 600 to 1500
+//     256           +4    +5   +10   +12   +12                        768          -10   -10   -11    -1    +5  of 800 to 2200
+//     384           -6   -11    -9    -7    -2  of 490 to 930        1024          -28   -13   -23    -7    +9
+bool ln_few_rows(int d, int rows) { return rows <= (d <= 256 ? 2048 : d <= 384 ? 7168 : 5120); }
 
 auto ln_kernel_for(int d, bool early)  // leann_create takes rows of up to 1024 elements
 {
@@ -769,7 +777,7 @@ int enc_forward(leann_ctx *ctx, const leann_chunks *chunks, const int64_t *ids_d
         }
         // as many blocks as are resident at once (measured: 10 % faster than a row per wave, and than twice as
         // many blocks); their waves go through several rows each
-        const bool few_rows = rows <= 2048;
+        const bool few_rows = ln_few_rows(d, rows);
         const int ln_grid = std::min((max_rows + (few_rows ? 3 : 7)) / (few_rows ? 4 : 8), ctx->num_cus * ctx->ln_blocks_per_cu);
         const auto ln = ln_kernel_for(d, few_rows);
         auto layer_norm = [&](const float *g, const float *b) {
