@@ -72,10 +72,24 @@ struct GemmChoice {
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
 // and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
 // gemm_kernel (128x128) and gemm_large_kernel (256x256, and 256x192 for what those leave of the chip or of the columns) walk over their tiles:
-// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes, by 768 elements of K: 0.4 + 9.02 k (and 1 per launch),
-// 4.8 + 16 k, 4.1 + 13.2 k.  The first is what a 128x128 tile takes behind the kernels of a pass (19000 x 384 x 1536 42 us, 38000 x 384 x 384 26); in a row of
-// launches, A always the same, it is 1.2 + 6.4 k, while the others take the same in both.  Passes of the encoder of 384 columns, chosen by either:
-// 9500 tokens 1071 and 1005 us, 19000 1776 and 1620, 38000 3327 and 3063, 6900 792 and 811.  Microseconds per launch in a row of launches, all three measured (rows x N x K; "G": with GELU):
+// what decides is how many the busiest CU gets, c = ceil(tiles / CUs), and what one takes.  By 768 elements of K, 256x256 takes 4.8 + 16 k, 256x192
+// 4.35 + 12.7 k and 128x128 7 k (3 more for each 768 beyond the first), with 2.45 per launch and, where c > 1, 0.135 per MB of A.  In a row of launches, whose A
+// never leaves the caches, 128x128 takes 1 + c (1.2 + 6.4 k); its figures are of launches behind the kernels of a pass, which read what those have just
+// written past the caches: least squares of 340 of them, on the scale of the stream tiles' figures, are 2.3 + c (0.6 + 6.6 k) + 0.13 per MB, and near
+// these the values were taken whose choices lose least, in the 340 and in whole passes of 384 and 768 columns with one product's tile exchanged.
+// Microseconds in a pass (chunks of 76 tokens, five eighths full; "s": the fastest stream tile):
+//                        128x128 256x256 256x192     s |                       128x128 256x256 256x192     s
+//   6900 x  384 x  128       5.9                   7.0 |  6900 x 1152 x  384      11.3    13.4    12.4  13.8
+//  13000 x  512 x  128 G     8.6                  12.3 | 13000 x 1536 x  384 G    25.7    32.4    28.3  31.5
+//   6900 x  768 x  256       8.5    10.4    10.2   8.6 | 19000 x  384 x  384      14.5    13.9    12.7  16.1
+//   6900 x 1024 x  256 G    10.5    16.0    14.5  12.9 | 38000 x  384 x  384      25.7    25.3    26.2
+//   9500 x  384 x 1536      23.0    29.4    28.0  17.8 | 38000 x  384 x 1536      79.7    66.8    62.4
+//  25500 x  768 x  256      16.8    19.7    22.5       | 13000 x  768 x  768      30.4    21.8    19.9  26.8
+// Over the 340 (K 128 to 4096, 1000 to 100 000 rows) the tile taken is 1.1 % slower than the fastest on average; with 1 + c (0.4 + 9.02 k) for 128x128 1.6 %;
+// with 1 + c (2 + 9.2 k), which two products of K = 384 and 1536 suggest, 2.5 %: it leaves 128x128 for stream tiles at K of 128 and 256.  Whole passes
+// with the first of these two and now: 384 columns, 6700 tokens 814 and 791 us, 11 600 1229 and 1148, 12 900 1266 and 1191; 256 columns, 20 200 tokens 1208 and 1079.
+// Slower than before by 1 to 2 %: 256 columns at 3000 tokens.
+// In a row of launches, all three measured (rows x N x K; "G": with GELU):
 //                        128x128 256x256 256x192 |                       128x128 256x256 256x192
 //   5000 x 2304 x  768      25.1    22.7    22.2 |  8000 x  384 x  384       6.7    12.3    10.4
 //  12000 x 2304 x  768      54.6    48.9    52.6 | 20000 x 1152 x  384      26.5    24.6    22.9
@@ -94,9 +108,10 @@ inline GemmChoice choose_gemm(int cus, int large_tile, int small_rows, int rows,
     };
     const double k = K / 768.0;
     GemmChoice best = {-1, 1, 128, 128};
-    double best_us = 1.0 + busiest(128, 128) * (0.4 + 9.02 * k);
+    const double c128 = busiest(128, 128);
+    double best_us = 2.45 + c128 * (7.03 * k + 3.0 * std::max(0.0, k - 1.0)) + (c128 > 1 ? 0.135e-6 * sizeof(uint16_t) * rows * K : 0.0);
     if (large_tile == 256 && K >= 8 * GEMM_BK) {
-        const double us256 = busiest(256, 256) * (4.8 + 16.0 * k), us192 = busiest(256, 192) * (4.1 + 13.2 * k), us = std::min(us256, us192);
+        const double us256 = busiest(256, 256) * (4.8 + 16.0 * k), us192 = busiest(256, 192) * (4.35 + 12.7 * k), us = std::min(us256, us192);
         if (us <= best_us) {
             best_us = us;
             best.large = 256;
