@@ -69,7 +69,7 @@ struct leann_ctx {
     int32_t gemm_small_rows = 2048;  // passes of at most this many rows may use tiles of 64x64 and smaller; 0: gemm_kernel only
     // encoder workspace
     DevBuf x, qkv, att, delta, hid, cu, len, meta, enc_ids;
-    // scratch of leann_build_pq (at most 65536 training rows, and 16 bytes per row of the table): allocating and freeing 220 MB took 0.1 to 0.5 ms per call.  Calls on several
+    // scratch of leann_build_pq (at most 65536 training rows): allocating and freeing 220 MB took 0.1 to 0.5 ms per call.  Calls on several
     // threads take turns with it (each waits for its stream before it leaves).  What is larger than PQ_WORK_KEEP is given back at the
     // end of the call, the rest when another allocation of the context finds no memory.
     DevBuf pq_work;

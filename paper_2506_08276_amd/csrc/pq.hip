@@ -854,7 +854,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     leann_pq *pq = nullptr;
     LEANN_TRY(alloc_pq(ctx, n, d, m_sub, true, &pq));
     // scratch: training rows | their copies | assignments | rows grouped by centroid | where each group starts | counts; before that, from the
-    // copies on, the permutation's steps
+    // copies on, the permutation's steps where they fit
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
@@ -865,7 +865,7 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     const size_t o_assign = carve((size_t)nt * m_sub), o_order = carve((size_t)nt * m_sub * sizeof(int32_t));
     const size_t o_first = carve((size_t)m_sub * (KSUB + 1) * sizeof(int32_t));
     const size_t o_counts = carve((size_t)m_sub * GROUP_RUNS * KSUB * sizeof(int32_t));
-    const size_t step_bytes = ((size_t)n * sizeof(uint32_t) + 255) & ~(size_t)255, with_steps = std::max(off, o_xt + 4 * step_bytes);
+    const size_t step_bytes = ((size_t)n * sizeof(uint32_t) + 255) & ~(size_t)255;
     auto fail = [&](int code) {
         leann_pq_free(pq);
         return code;
@@ -873,16 +873,19 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     std::lock_guard<std::mutex> turn(ctx->pq_work_mutex);
     struct GiveBack {
         DevBuf &work;
+        DevBuf steps;  // those that the scratch has no room for: nothing that grows with the table is kept
         ~GiveBack()
         {
+            steps.release();
             if (work.bytes > PQ_WORK_KEEP) work.release();
         }
-    } give_back{ctx->pq_work};
-    // The steps take 16 bytes per row, beside rows of at least 4: on the host where there are more of them than fit into what the context
-    // keeps, or where the device has no room; also where its loop is over before three more launches would be (whole calls of 384 dimensions,
+    } mem{ctx->pq_work, {}};
+    if (ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
+    // The steps take 16 bytes per row, beside rows of at least 4: on the host where that is more than a context ever keeps, or where the
+    // device has no room; also where its loop is over before three more launches would be (whole calls of 384 dimensions,
     // 32 subspaces and 2 iterations, host and device: 1000 rows 168 and 176 us, 4000 rows 197 and 196, 6000 rows 223 and 215, 40 000 rows 560 and 463).
-    const bool on_device = n > 4096 && with_steps <= std::max(off, PQ_WORK_KEEP) && ctx->pq_work.reserve(with_steps) == LEANN_OK;
-    if (!on_device && ctx->pq_work.reserve(off) != LEANN_OK) return fail(LEANN_ENOMEM);
+    const bool in_scratch = o_xt + 4 * step_bytes <= off;
+    const bool on_device = n > 4096 && 4 * step_bytes <= PQ_WORK_KEEP && (in_scratch || mem.steps.reserve(4 * step_bytes) == LEANN_OK);
     unsigned char *scr = (unsigned char *)ctx->pq_work.p;
     int64_t *rows_dev = (int64_t *)(scr + o_rows);
     float *xt = (float *)(scr + o_xt);
@@ -890,7 +893,8 @@ int leann_build_pq(leann_ctx *ctx, const float *emb_dev, int64_t n, int32_t d, i
     int32_t *order = (int32_t *)(scr + o_order), *first = (int32_t *)(scr + o_first), *counts = (int32_t *)(scr + o_counts);
     std::vector<int64_t> train;  // read by the copy until the stream has been waited for
     if (on_device) {
-        auto steps = [&](int k) { return (uint32_t *)(scr + o_xt + k * step_bytes); };
+        unsigned char *at = in_scratch ? scr + o_xt : (unsigned char *)mem.steps.p;
+        auto steps = [&](int k) { return (uint32_t *)(at + k * step_bytes); };
         const Steps st = {steps(0), steps(1), steps(2), steps(3)};
         const dim3 all((unsigned)((n + 255) / 256)), some((unsigned)((nt + 255) / 256));
         hipLaunchKernelGGL(clear_steps_kernel, all, dim3(256), 0, ctx->stream, st, n);

@@ -55,3 +55,64 @@ def test_all_training_rows(L, orc, ctx, n, seed):
     nearest = np.argmin(np.abs(train[:, None] - cent[None, :]), 1)
     want = np.array([train[nearest == c].mean() for c in range(256)])
     assert np.abs(codebook(L, ctx, x, 1, seed)[:, 0] - want).max() <= 2e-6 * n
+
+
+def numbered_rows(n):
+    """A row for every number, exact in fp32, on the device."""
+    import torch
+    i = torch.arange(n, dtype=torch.int32, device="cuda:0")
+    x = torch.empty((n, 2), dtype=torch.float32, device="cuda:0")
+    x[:, 0] = i & 4095
+    x[:, 1] = i >> 12
+    return x
+
+
+def first_rows(L, ctx, x, seed):
+    pq = L.leann_build_pq(ctx, x, 1, 0, seed)
+    try:
+        cb = np.empty((256, 2), np.float32)
+        import ctypes as C
+        L.load_library().leann_pq_export(ctx, pq, cb.ctypes.data_as(C.c_void_p), None)
+        return cb.astype(np.int64) @ [1, 4096]
+    finally:
+        L.leann_pq_free(pq)
+
+
+def test_a_large_table_leaves_no_more_behind_than_its_training(L, orc):
+    """The permutation's steps of a table of 6 000 000 rows are 96 MB, its training's scratch 2.4 MB."""
+    import torch
+    say("memory kept after a large table")
+    ctx = L.leann_create(li.TINY, to_dev(li.encoder_weights(li.TINY, 3)))
+    try:
+        n, seed = 6_000_000, 21
+        x = numbered_rows(n)
+        first_rows(L, ctx, x[:5000].contiguous(), seed)  # kernels loaded
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        assert np.array_equal(first_rows(L, ctx, x, seed), orc.permutation(n, seed)[:256])
+        assert torch.cuda.mem_get_info()[0] > free - (32 << 20)
+    finally:
+        L.leann_destroy(ctx)
+
+
+def test_the_host_runs_the_steps_of_the_largest_tables(L, orc, ctx):
+    """More than 2^26 rows: 16 bytes each are more than a context keeps."""
+    n, seed = (1 << 26) + 1001, 22
+    say(f"steps on the host, n={n}")
+    assert np.array_equal(first_rows(L, ctx, numbered_rows(n), seed), orc.permutation(n, seed)[:256])
+
+
+def test_the_host_runs_the_steps_where_the_device_has_no_room(L, orc, ctx):
+    """960 MB of steps beside other allocations that leave 300 MB (up to half a gigabyte more has been seen)."""
+    import torch
+    n, seed = 60_000_000, 23
+    say(f"steps on the host for want of memory, n={n}")
+    x = numbered_rows(n)
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (300 << 20), dtype=torch.uint8, device="cuda:0")
+    try:
+        got = first_rows(L, ctx, x, seed)
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    assert np.array_equal(got, orc.permutation(n, seed)[:256])
