@@ -14,10 +14,10 @@ SOURCE = """
 static const int sizes[][2] = {LEANN_STREAM_TILES(SIZE)};
 extern "C" int tiles() { return sizeof(sizes) / sizeof(sizes[0]); }
 extern "C" void tile_size(int tile, int *rows, int *cols) { *rows = sizes[tile][0], *cols = sizes[tile][1]; }
-extern "C" void choose(int cus, int large_tile, int small_rows, int rows, int N, int K, int *stream, int *xr, int *large)
+extern "C" void choose(int cus, int large_tile, int small_rows, int rows, int N, int K, int *stream, int *xr, int *large, int *cols)
 {
     const GemmChoice c = choose_gemm(cus, large_tile, small_rows, rows, N, K);
-    *stream = c.stream, *xr = c.xr, *large = c.large;
+    *stream = c.stream, *xr = c.xr, *large = c.large, *cols = c.cols;
 }
 extern "C" int pass_rows(int max_rows, int tokens) { return max_rows > ASK_ROWS ? tokens : guessed_rows(max_rows); }
 """
@@ -32,6 +32,9 @@ def library():
         return ctypes.CDLL(os.path.join(d, "plan.so"))
 
 
+LARGE_TILES = ["128x128", "256x256", "256x192"]
+
+
 def stream_tiles():
     """Names of the stream kernels' tiles."""
     out = []
@@ -44,9 +47,9 @@ def stream_tiles():
 
 def tile(rows, N, K, large_tile=256, small_rows=2048):
     """The tile of one product."""
-    stream, xr, large = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
-    library().choose(CUS, large_tile, small_rows, rows, N, K, ctypes.byref(stream), ctypes.byref(xr), ctypes.byref(large))
-    return stream_tiles()[stream.value] if stream.value >= 0 else f"{large.value}x{large.value}"
+    stream, xr, large, cols = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    library().choose(CUS, large_tile, small_rows, rows, N, K, ctypes.byref(stream), ctypes.byref(xr), ctypes.byref(large), ctypes.byref(cols))
+    return stream_tiles()[stream.value] if stream.value >= 0 else f"{large.value}x{cols.value}"
 
 
 def tiles_of_embed(cfg, lengths, seq, **setting):

@@ -154,7 +154,7 @@ def test_base_shape_sample_matches_oracle(L, orc):
     lengths[:5] = [1, 33, 64, 200, 256]
     ctx = L.leann_create(cfg, to_dev(w).to(torch.bfloat16))  # bf16 weight upload path
     try:
-        got = L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy()  # 5466 tokens: 256 x 256 and 128 x 192 tiles
+        got = L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy()  # 5466 tokens: tiles of 256 x 256, 256 x 192 and 128 x 192
         L.leann_set_gemm_tiles(ctx, 128, 0)  # the same pass through 128 x 128 tiles: the same bits
         assert np.array_equal(L.leann_embed(ctx, to_dev(tokens), to_dev(lengths), hidden=768).cpu().numpy(), got)
         with pytest.raises(L.LeannError):
@@ -257,7 +257,7 @@ def one_round_lengths():
 def test_every_gemm_tile_gives_the_same_bits(L, hidden, heads, ffn):
     """Passes from a handful of tokens to tens of thousands, one to 24 K-slabs, row counts that are no multiple of any tile: each
     chunk's embedding equals the one that the 128 x 128 tile alone gives.  Together with the passes of the next test these go through
-    every tile from 32 x 16 to 256 x 256, with and without GELU (test_gemm_plan.py counts them)."""
+    every tile from 32 x 16 to 256 x 192 and 256 x 256, with and without GELU (test_gemm_plan.py counts them)."""
     import torch
     cfg = dict(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=128, ln_eps=1e-12)
     say(f"all GEMM tiles, hidden {hidden}")
