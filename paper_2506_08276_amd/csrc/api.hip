@@ -196,7 +196,7 @@ int leann_create(leann_ctx **out, const leann_encoder_desc *desc, const void *we
         leann_destroy(ctx);
         return LEANN_ENOMEM;
     }
-    const bool pack = ctx->w_packed.reserve(packed_bytes) == LEANN_OK;  // without them small passes are slower, nothing else
+    const bool pack = ctx->w_packed.reserve(packed_bytes) == LEANN_OK;  // without them passes are slower (small ones go through gemm_kernel, large ones read W in rows), nothing else
     char *pb = (char *)ctx->w_bf16.p, *pf = (char *)ctx->w_f32.p;
     size_t so = 0;  // element offset in the packed source
     hipError_t copy_rc = hipSuccess;

@@ -50,24 +50,24 @@ struct GemmChoice {
 
 // Tile choice of one product.  All tiles add the K-slabs in the same order, so a row's result does not depend on it.
 // Measured per launch in a row of dependent launches, W of twelve layers in turn, in microseconds (rows x N x K; "16:" tiles of
-// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's, whose 256x256 tile gemm_large_kernel has replaced since):
-//                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128 256x256
-//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |   8.6
-//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |  26.1
+// gemm_stream16_kernel, then those of gemm_stream_kernel, behind the bar gemm_kernel's):
+//                   16: 32x16   32x32   32x48   32x64   64x64 |   32x96  32x128   64x96  64x128  64x192  64x256 128x192 128x256 | 128x128
+//    80 x  768 x  768     2.7     2.8     3.0     3.1     4.0 |     3.6     4.0     4.6     4.9                                 |    8.6
+//    80 x  768 x 3072     5.2     5.6     6.2     7.1     9.1 |     8.6    10.6    11.2    12.9                                 |   26.1
 //   244 x 2304 x  768                                     4.4 |     4.2     4.6     5.0     5.3     6.3     7.0                 |
 //   244 x  768 x 3072             5.8     6.6     7.2     9.2 |     8.8    10.7    11.3    13.0                                 |
-//   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |   9.8
+//   450 x 2304 x  768                                         |                     5.5     5.9     6.8     7.2                 |    9.8
 //   450 x  768 x 3072                     7.1     7.2     9.2 |     8.9    10.7    11.3    12.9                                 |
-//  1040 x  768 x  768                                     4.7 |             4.9     5.2     5.4     6.5                         |   9.1
+//  1040 x  768 x  768                                     4.7 |             4.9     5.2     5.4     6.5                         |    9.1
 //  1040 x  768 x 3072                                    10.1 |            12.0    11.9    13.4    17.2                         |
-//  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |  10.7
-//  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |  19.0    19.0
-//  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |   6.6    11.3
-//  3500 x 1152 x  384                                         |                                     9.4     9.9     8.1     8.6 |   6.9    11.2
-//  3500 x 3072 x  768                                         |                                                    23.6    25.1 |  28.3    21.6
-//  8000 x  768 x 3072                                         |                                    42.7    47.1    37.0    37.5 |  51.2    56.5
-// 10000 x  384 x 1536                                         |                                    21.5    23.9    17.5    18.5 |  18.9    30.4
-// 12000 x  768 x  768                                         |                                                    22.3    24.3 |  23.7    19.1
+//  1040 x 2304 x  768                                         |                                     7.4     7.9    10.7         |   10.7
+//  2000 x 3072 x  768                                         |                                    14.6    15.8    13.4    14.1 |   19.0
+//  2500 x 1152 x  384                                         |                                     5.7     5.9     7.8     8.2 |    6.6
+//  3500 x 1152 x  384                                         |                                     9.4     9.9     8.1     8.6 |    6.9
+//  3500 x 3072 x  768                                         |                                                    23.6    25.1 |   28.3
+//  8000 x  768 x 3072                                         |                                    42.7    47.1    37.0    37.5 |   51.2
+// 10000 x  384 x 1536                                         |                                    21.5    23.9    17.5    18.5 |   18.9
+// 12000 x  768 x  768                                         |                                                    22.3    24.3 |   23.7
 // The smallest stream tile that needs one round of blocks is the fastest (in a second round nothing hides the first operands' way).
 // Tiles of gemm_stream16_kernel with the columns of 32x96 and 32x128 were no faster than those (4.3 and 4.8 where these take 4.2
 // and 4.6).  32x128 is for K = 128: the FFN's first product at hidden 128, 1320 to 2000 x 512 x 128, takes 0.1 to 0.3 us longer through 64x64.
@@ -85,6 +85,10 @@ struct GemmChoice {
 //   6900 x 1024 x  256 G    10.5    16.0    14.5  12.9 | 38000 x  384 x  384      25.7    25.3    26.2
 //   9500 x  384 x 1536      23.0    29.4    28.0  17.8 | 38000 x  384 x 1536      79.7    66.8    62.4
 //  25500 x  768 x  256      16.8    19.7    22.5       | 13000 x  768 x  768      30.4    21.8    19.9  26.8
+//   3600 x  768 x 3072      40.5    56.0    51.6  22.4 |  3600 x 2304 x  768      21.9    19.8    18.2  20.4
+//   6900 x  768 x 3072      67.7    58.4    53.7  36.1 |  6900 x  768 x  768      19.9    18.9    17.0  14.2
+//   9500 x  768 x 3072      70.1    59.8    55.6  43.2 |  9500 x  768 x  768      21.1    20.0    18.2  17.2
+//  13000 x  768 x 3072     101.8    63.0    57.6  69.5 |  6900 x 3072 x  768 G    49.5    46.1    41.5  49.2
 // Over the 340 (K 128 to 4096, 1000 to 100 000 rows) the tile taken is 1.1 % slower than the fastest on average; with 1 + c (0.4 + 9.02 k) for 128x128 1.6 %;
 // with 1 + c (2 + 9.2 k), which two products of K = 384 and 1536 suggest, 2.5 %: it leaves 128x128 for stream tiles at K of 128 and 256.  Whole passes
 // with the first of these two and now: 384 columns, 6700 tokens 814 and 791 us, 11 600 1229 and 1148, 12 900 1266 and 1191; 256 columns, 20 200 tokens 1208 and 1079.
